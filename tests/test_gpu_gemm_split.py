@@ -164,3 +164,59 @@ def test_sliding_window_in_every_configuration(layer, tmp_path):
                     err = float((y.cpu().double() - ref).abs().max() / ref.abs().max())
                     assert err < tol, (names[v], split, err)
     m.cache_clear()
+
+
+@pytest.mark.parametrize("c", [9, 67, 260])
+@pytest.mark.parametrize("pointwise", [True, False])
+def test_non_finite_image_stays_in_its_image(c, pointwise, tmp_path):
+    """Channel counts that are no multiple of the groups of 8: the rows past the end of the reduction lie in the next image, whose infinities
+    and NaN must not reach this one.  Tiles on the fp32 instructions give the very bits they give without them; of the others a block that
+    holds a non-finite column is formed on the fp32 instructions as a whole."""
+    m = mnn()
+    k = 1 if pointwise else 3
+    layer = ConvLayer("nf", 3, c, 3, 5, 20, k, k, 1, 0 if pointwise else 1)
+    g = torch.Generator().manual_seed(c)
+    x = torch.rand(layer.n, c, layer.h, layer.w, generator=g) * 2 - 1
+    w = torch.randn(layer.c_out, c, k, k, generator=g)
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), padding=layer.pad)
+    bad = x.clone()
+    bad[1, :8, :, :] = torch.tensor([float("inf"), float("nan")] * 4)[:, None, None]
+    x, bad, w = x.cuda(), bad.cuda(), w.cuda()
+    opt = m.Options(force_kind=m.SCHEME_GEMM1X1 if pointwise else m.SCHEME_DIRECT)
+    names = m.gemm_variants()
+    failed = []
+    for v in range(1, len(names)):
+        for split in (1, 2):
+            m.cache_clear()
+            m.ConvPlan.for_layer(layer, options=opt).close()
+            rewrite_choices(m, tmp_path / "cache", m.GEMM_FP32, (v, split))
+            with m.ConvPlan.for_layer(layer, options=opt) as plan:
+                try:
+                    clean = plan.run(x, w, None).cpu()
+                    got = plan.run(bad, w, None).cpu()
+                except m.MnnError:          # the older tiles refuse a split with an empty slice
+                    assert split > 1 and not names[v].startswith(("x6_", "f32_")), names[v]
+                    continue
+            for i in (0, 2):
+                err = float((got[i].double() - ref[i]).abs().max() / ref.abs().max())
+                if not err < 2e-6 or (not names[v].startswith("x6_") and not torch.equal(got[i], clean[i])):
+                    failed.append((names[v], split, i, err))
+            assert torch.isnan(got[1, :, 0, 0]).all(), names[v]
+    m.cache_clear()
+    assert not failed, failed
+
+
+def test_few_columns_without_timing_keep_images_apart():
+    """Variant 0 at 16 columns and fewer: a fully connected layer on a few samples."""
+    m = mnn()
+    M, R, P = 40, 300, 7
+    g = torch.Generator().manual_seed(1)
+    A, B = torch.randn(R, M, generator=g), torch.randn(P, R, generator=g)
+    ref = (A.double().T @ B.double().T)
+    B[3, :6] = float("nan")
+    D = torch.zeros(P, M, device="cuda")
+    m.gemm_f32(A.cuda(), B.cuda(), D, M=M, ncols=P, R=R, L=1, strideB_img=R, strideB_row=1, strideD_img=M, strideD_row=1)
+    got = D.cpu().double().T
+    others = [i for i in range(P) if i != 3]
+    assert torch.isnan(got[:, 3]).all()
+    assert float((got[:, others] - ref[:, others]).abs().max() / ref.abs().max()) < 2e-6
