@@ -65,7 +65,10 @@ typedef enum {
 typedef enum {
     MNN_GEMM_FP32 = 0,        /* fp32 products: v_mfma_f32_32x32x2_f32, or (configurations "x6_...") each operand cut into
                                  three bf16 parts that hold all its 24 bits and six products of parts on the bf16 matrix
-                                 cores, with no larger an error; the planner times both                */
+                                 cores.  The three products left out come to 2^-24 of |a b| at the very most, one fp32
+                                 rounding, and the sums have fewer roundings: no larger an error.  Tiles that
+                                 meet an operand three parts do not hold (below 2^-109) or a sum that is not finite are
+                                 formed on the fp32 instructions, at up to 2.3 times the time.  The planner times both */
     MNN_GEMM_BF16 = 1,        /* operands rounded to bf16 (RNE), v_mfma_f32_32x32x16_bf16 */
     MNN_GEMM_BF16X3 = 2       /* each operand split into bf16 hi + lo, product = hi*hi + hi*lo + lo*hi on
                                  the bf16 matrix cores: about 16 mantissa bits, fp32-grade results    */

@@ -220,3 +220,57 @@ def test_few_columns_without_timing_keep_images_apart():
     others = [i for i in range(P) if i != 3]
     assert torch.isnan(got[:, 3]).all()
     assert float((got[:, others] - ref[:, others]).abs().max() / ref.abs().max()) < 2e-6
+
+
+def tiny_error(m, A, B, v, absolute=0.0):
+    """Largest error of an output in units of sum |a||b| (+ the spacing of the smallest fp32 values, where results come near it)."""
+    ref = A.double().transpose(1, 2) @ B.double()
+    scale = A.double().abs().transpose(1, 2) @ B.double().abs()
+    got = product(m, A.cuda(), B.cuda(), v).cpu().double()
+    return float((((got - ref).abs() - absolute).clamp_min(0) / scale.clamp_min(1e-300)).max())
+
+
+@pytest.mark.parametrize("exponent,factor", [(-118, 0), (-126, 0), (-126, 40), (-140, 0), (-140, 30), (-147, 60)])
+@pytest.mark.parametrize("where", ["column", "row", "column_of_all", "one_row_of_reduction"])
+def test_tiny_operands_beside_ordinary_ones(exponent, factor, where):
+    """One column (row) of tiny values in a tile of ordinary ones, and tiny values times large ones: each output keeps what the fp32
+    instructions give it.  Bound: R roundings of 2^-24 of sum |a||b|, and of the spacing 2^-149 where products fall below the normal range."""
+    m = mnn()
+    M, R, P = 68, 48, 132
+    g = torch.Generator().manual_seed(6)
+    A = torch.randn(1, R, M, generator=g)
+    B = torch.randn(1, R, P, generator=g)
+    t = 2.0 ** exponent
+    if where == "column":
+        B[:, :, 5] *= t
+        A *= 2.0 ** factor
+    elif where == "row":
+        A[:, :, 37] *= t
+        B *= 2.0 ** factor
+    elif where == "column_of_all":
+        B *= t
+        A *= 2.0 ** factor
+    else:                                     # outputs of column 9 see the tiny row of B only
+        B[:, 20] *= t
+        B[:, :20, 9] = 0
+        B[:, 21:, 9] = 0
+        A *= 2.0 ** factor
+    bound, absolute = R * 2.0 ** -24, R * 2.0 ** -149
+    fp32 = next(i for i, n in enumerate(m.gemm_variants()) if n == "64x64x16_w2x2")
+    assert tiny_error(m, A, B, fp32, absolute) <= bound
+    errs = {name: tiny_error(m, A, B, v, absolute) for v, name in x6_variants(m)}
+    assert all(e <= bound for e in errs.values()), errs
+
+
+def test_equal_parts_in_every_term():
+    """Operands whose lower parts are as large as they get and of one sign, so that the part products left out all add up: still no more than
+    the rounding of a product, 2^-24."""
+    m = mnn()
+    M, R, P = 64, 512, 64
+    x = 1.0 + 2.0 ** -8 - 2.0 ** -10 + 2.0 ** -17 - 2.0 ** -19
+    A, B = torch.full((1, R, M), x), torch.full((1, R, P), x)
+    ref = R * float(A[0, 0, 0].double()) ** 2
+    for v, name in x6_variants(m):
+        got = product(m, A.cuda(), B.cuda(), v).cpu().double()
+        # 2^-24 for the terms, 2^-24 for each of the R / 16 steps of the sum at the most
+        assert float((got - ref).abs().max()) / ref <= (1 + R / 16) * 2.0 ** -24, name

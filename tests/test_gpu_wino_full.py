@@ -125,3 +125,35 @@ def test_weights_past_its_addresses_take_another_arrangement():
             assert opt is None or p.scheme.variant != m.WINO_FUSED_ALL
         # both sides are sums of 28800 fp32 products: alpha <= 10 bound
         assert float((y - ref).abs().max() / ref.abs().max()) < 1e-3
+
+
+def per_output_error(y, x, w, pad):
+    """Largest error of an output in units of the sum of |x||w| over its whole tile's taps (what the transforms add and cancel)."""
+    k = w.shape[-1]
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), padding=pad)
+    # the largest |x| within reach of a tile, per image; the sum of |w| per output channel
+    scale = x.double().abs().amax((1, 2, 3))[:, None] * w.double().abs().sum((1, 2, 3))[None, :]
+    return float(((y.double() - ref).abs() / scale[:, :, None, None]).max())
+
+
+@pytest.mark.parametrize("exponent", [-112, -120, -126])
+@pytest.mark.parametrize("where", ["image", "large_weights"])
+def test_tiny_values_beside_ordinary_ones(exponent, where):
+    """A tiny image in a block of ordinary ones; tiny inputs with large weights."""
+    m = mnn()
+    shape = (3, 19, 6, 6, 40, 3, 1)
+    x, w, _ = tensors(shape, 12)
+    t = 2.0 ** exponent
+    if where == "image":
+        x[1] *= t
+        w *= 2.0 ** 8
+    else:
+        x *= t
+        w *= 2.0 ** 60
+    for n in (2, 3, 4):
+        err = {}
+        for variant in (m.WINO_UNFUSED, m.WINO_FUSED_ALL):
+            with plan(m, shape, n, variant) as p:
+                err[variant] = per_output_error(p.run(x.cuda(), w.cuda(), None).cpu(), x, w, 1)
+        # alpha <= 6: 3e-7 measured on ordinary values, and a lost part at these sizes is 1e-5 and more
+        assert all(e < 2e-6 for e in err.values()), (n, err)
