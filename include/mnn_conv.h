@@ -132,7 +132,8 @@ enum {
                                  element (xi, c, k) = (G w[k][c] G^T)[xi / alpha][xi % alpha];
                                  fused variants: [b][c/4][a][kg][c%4][k%16], xi = a*alpha + b (kg groups of 16
                                  output channels, channel groups padded to whole 16-channel chunks);
-                                 FUSED_ALL: bf16 parts in matrix-operand order (no float layout)    */
+                                 FUSED_ALL: bf16 parts in matrix-operand order (no float layout); values that three parts
+                                 do not hold are kept as their 32 bits                               */
     MNN_BUF_V = 1,            /* transformed input tiles, unfused: [alpha^2][C][ldp] (ldp = P rounded up to 4), or, when
                                  mnn_plan_info.tiled is set (layers with many tiles), [C][pb][alpha^2][64]: element
                                  (xi, c, p) at ((c*pb + p/64)*alpha^2 + xi)*64 + p%64, ldp = 64*pb;

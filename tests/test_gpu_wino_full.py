@@ -137,9 +137,9 @@ def per_output_error(y, x, w, pad):
 
 
 @pytest.mark.parametrize("exponent", [-112, -120, -126])
-@pytest.mark.parametrize("where", ["image", "large_weights"])
+@pytest.mark.parametrize("where", ["image", "output_channel", "large_weights", "all_weights"])
 def test_tiny_values_beside_ordinary_ones(exponent, where):
-    """A tiny image in a block of ordinary ones; tiny inputs with large weights."""
+    """A tiny image, or the tiny weights of one output channel, in a block of ordinary ones; tiny inputs with large weights; tiny weights."""
     m = mnn()
     shape = (3, 19, 6, 6, 40, 3, 1)
     x, w, _ = tensors(shape, 12)
@@ -147,9 +147,15 @@ def test_tiny_values_beside_ordinary_ones(exponent, where):
     if where == "image":
         x[1] *= t
         w *= 2.0 ** 8
-    else:
+    elif where == "output_channel":
+        w[33] *= t
+        x *= 2.0 ** 8
+    elif where == "large_weights":
         x *= t
         w *= 2.0 ** 60
+    else:
+        w *= t
+        x *= 2.0 ** 20
     for n in (2, 3, 4):
         err = {}
         for variant in (m.WINO_UNFUSED, m.WINO_FUSED_ALL):
@@ -157,3 +163,28 @@ def test_tiny_values_beside_ordinary_ones(exponent, where):
                 err[variant] = per_output_error(p.run(x.cuda(), w.cuda(), None).cpu(), x, w, 1)
         # alpha <= 6: 3e-7 measured on ordinary values, and a lost part at these sizes is 1e-5 and more
         assert all(e < 2e-6 for e in err.values()), (n, err)
+
+
+@pytest.mark.parametrize("value", [3.397e38, -3.4028e38, 1e-44, float("inf"), float("nan")])
+@pytest.mark.parametrize("n", [2, 4])
+def test_weights_that_three_parts_do_not_hold(value, n):
+    """Transformed weights that are finite but round to an infinite bf16, subnormal ones, infinities and NaN: what the separate kernels give."""
+    m = mnn()
+    shape = (1, 18, 10, 10, 40, 3, 1)
+    x, w, _ = tensors(shape, 13)
+    x *= 2.0 ** -10                                   # sums of products with the largest fp32 stay finite
+    G = m.get_transforms(n, 3, 0.5)[1]
+    w[21] = 0.0
+    w[21, 17, 0, 0] = value / float(max(abs(G[:, 0])) ** 2) if abs(value) > 1 else value       # its largest transformed value: `value`
+    out = []
+    for variant in (m.WINO_UNFUSED, m.WINO_FUSED_ALL):
+        with plan(m, shape, n, variant) as p:
+            out.append(p.run(x.cuda(), w.cuda(), None).cpu().double())
+    a, c = out
+    assert torch.equal(torch.isfinite(a), torch.isfinite(c))
+    for k in range(shape[4]):
+        if k == 21 and not abs(value) < 3.41e38:
+            assert not torch.isfinite(a[0, k]).any()
+        else:
+            assert torch.isfinite(a[0, k]).all()
+            assert float((a[0, k] - c[0, k]).abs().max()) <= 1e-5 * float(a[0, k].abs().max()), k
