@@ -24,11 +24,11 @@ def tensors(shape, seed):
 
 
 # (N, C, H, W, K, k, pad): channels around the chunk of 16, output channels around the blocks of 32 and 64, tiles around 32, planes of
-# one row, tiles wider than the image, padding beyond the kernel
+# one row, tiles wider than the image, padding beyond the kernel, planes smaller than a tile row with one or two channels past a chunk
 SHAPES = [
     (1, 1, 3, 3, 1, 3, 0), (1, 16, 8, 8, 32, 3, 1), (2, 17, 9, 7, 33, 3, 1), (1, 15, 31, 2, 64, 3, 1), (3, 32, 13, 29, 65, 3, 2),
     (1, 33, 1, 40, 31, 3, 1), (5, 48, 6, 6, 130, 3, 1), (2, 5, 4, 3, 7, 2, 1), (1, 20, 11, 10, 40, 5, 2), (2, 3, 7, 9, 16, 5, 4),
-    (1, 9, 16, 16, 12, 4, 2),
+    (1, 9, 16, 16, 12, 4, 2), (1, 17, 1, 1, 8, 3, 1), (1, 33, 1, 2, 8, 3, 1), (2, 18, 1, 1, 5, 3, 2), (1, 17, 2, 1, 4, 5, 3), (1, 34, 1, 1, 3, 2, 1),
 ]
 
 
