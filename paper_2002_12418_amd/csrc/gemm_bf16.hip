@@ -1,7 +1,7 @@
 // Batched GEMM with bf16 matrix-core operands and fp32 accumulation for gfx950
-// (v_mfma_f32_32x32x16_bf16) for operands of 2 GiB and more per batch (64-bit
-// addresses, one tile configuration; smaller operands: gemm_split.hip), fed from
-// the same fp32 tensors as the fp32 kernel:
+// (v_mfma_f32_32x32x16_bf16) with 64-bit addresses, for operands that the 32-bit
+// offsets of gemm_split.hip do not cover (per batch B of 2 GiB or A of 1 GiB, rows
+// of 2^18 weights), fed from the same fp32 tensors as the fp32 kernel:
 //
 //   D_b[m][col] = sum_r At_b[r][m] * B_b[r][col] (+ bias[m])
 //
@@ -301,13 +301,19 @@ hipError_t launch_cfg(const GemmProblem& p, bool vec, hipStream_t s)
     return launch_splitk_reduce(p, s);
 }
 
+// In the order of gemm_split.hip's table.
+hipError_t (*const kConfigs[])(const GemmProblem&, bool, hipStream_t) = {
+    launch_cfg<128, 128, 32, 2, 2>, launch_cfg<64, 128, 32, 1, 4>, launch_cfg<128, 64, 32, 2, 2>, launch_cfg<64, 64, 32, 2, 2>,
+    launch_cfg<128, 128, 16, 2, 2>, launch_cfg<64, 64, 64, 2, 2>, launch_cfg<256, 128, 32, 4, 2>,
+};
+
 }  // namespace
 
-hipError_t launch_gemm_bf16_wide(const GemmProblem& p, bool vec, hipStream_t s)
+hipError_t launch_gemm_bf16_wide(const GemmProblem& p, int config, bool vec, hipStream_t s)
 {
-    // split-K scratch was sized for the variant's own tile, and a tensor this large has tiles enough
-    if (p.splitk > 1) return hipErrorInvalidValue;
-    return launch_cfg<128, 128, 32, 2, 2>(p, vec, s);
+    constexpr int n = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
+    if (config < 0 || config >= n || gemm_bf16_variant_count() != n + 1) return hipErrorInvalidValue;
+    return kConfigs[config](p, vec, s);
 }
 
 }  // namespace mnnconv

@@ -140,7 +140,7 @@ constexpr int kShort16 = 0, kShort32 = 2, kShort64 = 4;
 int gemm_bf16_variant_count();
 const char* gemm_bf16_variant_name(int variant);
 hipError_t launch_gemm_bf16(const GemmProblem& p, hipStream_t s);
-hipError_t launch_gemm_bf16_wide(const GemmProblem& p, bool vec, hipStream_t s);
+hipError_t launch_gemm_bf16_wide(const GemmProblem& p, int config, bool vec, hipStream_t s);     // config: gemm_bf16_variant - 1
 bool gemm_bf16_variant_tile(int variant, int* bm, int* bn, int* bk);
 bool gemm_variant_tuned(const GemmProblem& p, int variant);     // whether the planner times it
 // variants of the table that serves precision `prec`

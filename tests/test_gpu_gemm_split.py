@@ -274,3 +274,39 @@ def test_equal_parts_in_every_term():
         got = product(m, A.cuda(), B.cuda(), v).cpu().double()
         # 2^-24 for the terms, 2^-24 for each of the R / 16 steps of the sum at the most
         assert float((got - ref).abs().max()) / ref <= (1 + R / 16) * 2.0 ** -24, name
+
+
+def test_bf16_operands_past_the_range_checked_loader(tmp_path):
+    """Rows of 2^18 weights, more than the 32-bit offsets of the range-checked loader are used for: every bf16 configuration and its split of
+    the reduction, plain and gathered."""
+    m = mnn()
+    K, c = 1 << 18, 8
+    g = torch.Generator().manual_seed(2)
+    layer = ConvLayer("wide", 1, c, 3, 2, K, 3, 3, 1, 1)
+    x = torch.rand(1, c, 3, 2, generator=g) * 2 - 1
+    w = torch.randn(K, c, 3, 3, generator=g)
+    ref = torch.nn.functional.conv2d(x.double(), w.double(), padding=1)
+    A, B = torch.randn(1, 70, 200, generator=g), torch.randn(1, 70, 36, generator=g)
+    pref = A.double().transpose(1, 2) @ B.double()
+    Aw = torch.zeros(70, K)
+    Aw[:, :200] = A[0]
+    x, w, Aw, B = x.cuda(), w.cuda(), Aw.cuda(), B.cuda()
+    for prec, tol in ((m.GEMM_BF16X3, 3e-5), (m.GEMM_BF16, 1e-2)):
+        opt = m.Options(force_kind=m.SCHEME_DIRECT, force_prec=prec)
+        names = m.gemm_variants(prec)
+        for v in range(1, len(names)):
+            for ncols in (36, 35):                              # 16-byte loads and single ones
+                D = torch.zeros(200, ncols, device="cuda")
+                m.gemm_f32(Aw, B[:, :, :ncols].contiguous(), D, M=200, ncols=ncols, R=70, lda=K, variant=v, prec=prec)
+                err = float((D.cpu().double() - pref[0, :, :ncols]).abs().max() / pref.abs().max())
+                assert err < tol, (names[v], ncols, err)
+            for split in (1, 2):
+                m.cache_clear()
+                m.ConvPlan.for_layer(layer, options=opt).close()
+                rewrite_choices(m, tmp_path / "cache", prec, (v, split))
+                with m.ConvPlan.for_layer(layer, options=opt) as plan:
+                    assert names[v] in plan.describe() and ("splitk=2" in plan.describe()) == (split == 2)
+                    y = plan.run(x, w, None)
+                    err = float((y.cpu().double() - ref).abs().max() / ref.abs().max())
+                    assert err < tol, (names[v], split, err)
+    m.cache_clear()
