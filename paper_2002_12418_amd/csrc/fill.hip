@@ -24,10 +24,10 @@ __device__ __forceinline__ unsigned mix32(unsigned v)
 
 __global__ __launch_bounds__(256) void fill_pattern_kernel(float* __restrict__ dst, size_t n, unsigned seed, float lo, float scale)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const unsigned h = mix32((unsigned)i * 0x9e3779b9u + (unsigned)(i >> 32) + seed);
-    dst[i] = lo + scale * (float)(h >> 8);          // 24 random bits
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
+        const unsigned h = mix32((unsigned)i * 0x9e3779b9u + (unsigned)(i >> 32) + seed);
+        dst[i] = lo + scale * (float)(h >> 8);          // 24 random bits
+    }
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float4* __restrict__ dst4, size_t n4, float* __restrict__ tail, int ntail)
@@ -43,8 +43,8 @@ hipError_t launch_fill_pattern(float* dst, size_t n_floats, unsigned seed, float
 {
     if (!dst || !(hi >= lo)) return hipErrorInvalidValue;
     if (n_floats == 0) return hipSuccess;
-    const size_t blocks = (n_floats + 255) / 256;
-    if (blocks >= (1ull << 31)) return hipErrorInvalidValue;
+    const size_t all = (n_floats + 255) / 256, most = (size_t)1 << 23;       // a launch holds fewer than 2^32 work-items
+    const size_t blocks = all < most ? all : most;
     fill_pattern_kernel<<<(unsigned)blocks, 256, 0, s>>>(dst, n_floats, seed, lo, (hi - lo) / 16777215.f);
     return hipGetLastError();
 }
@@ -56,7 +56,7 @@ hipError_t launch_fill_zero(float* dst, size_t n_floats, hipStream_t s)
     const size_t n4 = n_floats / 4;
     const int ntail = (int)(n_floats & 3);
     const size_t blocks = (n4 + 255) / 256 + (n4 == 0 ? 1 : 0);
-    if (blocks >= (1ull << 31)) return hipErrorInvalidValue;
+    if (!grid_fits((long long)blocks, 256)) return hipErrorInvalidValue;
     fill_zero_kernel<<<(unsigned)blocks, 256, 0, s>>>((float4*)dst, n4, dst + n4 * 4, ntail);
     return hipGetLastError();
 }

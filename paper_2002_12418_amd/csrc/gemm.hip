@@ -456,6 +456,7 @@ hipError_t launch_cfg(const GemmProblem& p, bool vec, hipStream_t s)
         if ((long long)(splitk - 1) * per_split >= all_chunks || !p.splitk_partial || total * splitk >= (1ll << 31))
             return hipErrorInvalidValue;
     }
+    if (!grid_fits(total * splitk, WM * WN * WK * 64)) return hipErrorInvalidValue;
     const Extents ex = operand_extents(p);
     if (BUF && !ex.narrow) return hipErrorNotSupported;       // the caller falls back to the 64-bit loader
     const dim3 grid((unsigned)(total * splitk)), block(WM * WN * WK * 64);
@@ -577,7 +578,7 @@ hipError_t launch_splitk_reduce(const GemmProblem& p, hipStream_t s)
     if (p.splitk < 2 || !p.splitk_partial || !p.D) return hipErrorInvalidValue;
     const int ldc = gemm_splitk_ldc(p);
     const long long groups = (long long)p.batch * p.M * (ldc / 4);
-    if (groups <= 0 || (groups + 255) / 256 >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!grid_fits((groups + 255) / 256, 256)) return hipErrorInvalidValue;
     GemmProblem q = p;
     q.splitk = 1;                                   // vectorisability of D itself, not of the scratch tensor
     const int vecD = result_rows_vectorisable(q);

@@ -279,6 +279,7 @@ hipError_t launch_cfg(const GemmProblem& p, bool vec, hipStream_t s)
         if ((long long)(splitk - 1) * per_split >= all_chunks || !p.splitk_partial || total * splitk >= (1ll << 31))
             return hipErrorInvalidValue;
     }
+    if (!grid_fits(total * splitk, WM * WN * 64)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(total * splitk)), block(WM * WN * 64);
     const bool split = p.prec == 2;
     const int vecD = result_rows_vectorisable(p);

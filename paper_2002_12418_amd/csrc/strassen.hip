@@ -104,7 +104,7 @@ hipError_t launch_strassen_expand(bool left, const StrassenView& v, const float*
 {
     if (!view_ok(v, src, cols_half) || !dst || rows_half <= 0 || nb <= 0 || (src_batch_stride & 3)) return hipErrorInvalidValue;
     const long long total = (long long)nb * rows_half * (cols_half / 4);
-    if ((total + 255) / 256 >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!grid_fits((total + 255) / 256, 256)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((total + 255) / 256));
     if (left)
         hipLaunchKernelGGL(strassen_expand_kernel<true>, grid, dim3(256), 0, s, v, src, src_batch_stride, rows_half, cols_half, nb, dst);
@@ -118,7 +118,7 @@ hipError_t launch_strassen_combine(const StrassenView& v, const float* src, int 
 {
     if (!view_ok(v, dst, cols_half) || !src || rows_half <= 0 || nb <= 0 || (dst_batch_stride & 3)) return hipErrorInvalidValue;
     const long long total = (long long)nb * rows_half * (cols_half / 4);
-    if ((total + 255) / 256 >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!grid_fits((total + 255) / 256, 256)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(strassen_combine_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, v, src, rows_half,
                        cols_half, nb, dst, dst_batch_stride, bias);
     return hipGetLastError();

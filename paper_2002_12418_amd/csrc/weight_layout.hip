@@ -23,6 +23,7 @@ hipError_t launch_weight_transpose(const float* w, float* Wt, int K, int R, int 
 {
     if (!w || !Wt || K <= 0 || R <= 0 || ldk < K) return hipErrorInvalidValue;
     const long long total = (long long)R * ldk;
+    if (!grid_fits((total + 255) / 256, 256)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(weight_transpose_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, w, Wt, K, R,
                        ldk);
     return hipGetLastError();

@@ -316,7 +316,7 @@ hipError_t launch_fused_t(const WinoGeom& g, const float* AT, const float* Ub, c
     const int count = r.count < 0 ? pblocks - r.first : r.count;
     if (r.first < 0 || count < 0 || r.first + count > pblocks) return hipErrorInvalidValue;
     if (count == 0) return hipSuccess;
-    if ((long long)kblocks * count >= (1ll << 31)) return hipErrorInvalidValue;
+    if (!grid_fits((long long)kblocks * count, WM * WN * 64)) return hipErrorInvalidValue;
     MatArg<NT_, A> m;
     for (int i = 0; i < NT_; ++i)
         for (int j = 0; j < A; ++j) m.v[i][j] = AT[i * A + j];

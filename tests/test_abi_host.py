@@ -107,6 +107,19 @@ def test_one_kernel_arrangement_is_offered_within_its_addresses(mnn):
     assert tiles(1, 16, 5793, 5793, 16) == set()
 
 
+def test_launches_of_2_to_the_32_work_items_are_refused(mnn):
+    """Such a launch would run, without an error, on what is left modulo 2^32: every configuration of every precision says no before it."""
+    import torch
+    t = torch.zeros(4)
+    for prec in (mnn.GEMM_FP32, mnn.GEMM_BF16X3, mnn.GEMM_BF16):
+        names = mnn.gemm_variants(prec)
+        for v in range(len(names)):
+            for lda in (4, 1 << 18):                             # the second takes the bf16 products past the 32-bit loader
+                with pytest.raises(mnn.MnnError) as e:
+                    mnn.gemm_f32(t, t, t, M=1, ncols=1, R=1, batch=1 << 25, lda=lda, variant=v, prec=prec)
+                assert e.value.code == -1, (names[v], lda, str(e.value))
+
+
 def test_enumeration_rules(mnn):
     # k = 1, stride 1, no padding -> one matrix multiplication
     c = mnn.enumerate_schemes(16, 32, 112, 112, 64, 1, 1)
