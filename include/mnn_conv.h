@@ -296,7 +296,8 @@ int mnn_conv_analytic_tile(int32_t k, int32_t i_c, int32_t o_c, int32_t o_h, int
  * mnn_conv_predict_ms: host only; the predicted milliseconds of `scheme` for the layer.
  */
 typedef struct {
-    double flops;             /* fp32 multiply-add rate of the matrix-multiplication stage, FLOP/s */
+    double flops;             /* rate of a product on the fp32 matrix instructions, FLOP/s; products that the "x6_..."
+                                 configurations form are priced at it too and take up to 1.6 times less         */
     double bytes_per_s;       /* sustained HBM rate of a streaming kernel, B/s                     */
     double t_schedule_ms;     /* fixed cost per kernel launch in a dependent chain, ms             */
 } mnn_device_model;

@@ -81,6 +81,7 @@ int wino_fused_launch_count(const WinoGeom& g, int config);      // kernels one 
 // The whole convolution in one kernel (alpha <= 6, x below 2 GiB): y = A^T [ sum_c U (.) B^T x B ] A + bias.  U: the prepared weights as
 // bf16 parts in matrix-operand order, wino_full_weight_bytes, written by launch_filter_full.
 bool wino_full_available(int n, int k);
+int wino_full_block_channels(int alpha);            // output channels per workgroup
 // Sizes the one-kernel arrangement takes: 32-bit byte offsets into the input (with room for the over-read of a tile row) and the weights,
 // a grid the hardware counts.  Reads N, C, H, W, K, n, k, alpha, th and tw.
 bool wino_full_covers(const WinoGeom& g);

@@ -107,6 +107,18 @@ def test_one_kernel_arrangement_is_offered_within_its_addresses(mnn):
     assert tiles(1, 16, 5793, 5793, 16) == set()
 
 
+def test_one_kernel_arrangement_is_priced_with_its_repeated_transforms(mnn):
+    """It transforms a tile again for every block of output channels and walks the channels in a workgroup: beside the separate kernels it
+    must not look cheap where it is measured to lose (256 channels, F(4,3): 60 us against 39; one image 22 against 15), nor dear where it wins
+    (64 channels, F(2,3) on 16 images of 112 x 112: 82 us against 126)."""
+    def ms(variant, n, N, C, H, K):
+        return mnn.predict_ms(N, C, H, H, K, 3, 3, mnn.Scheme(mnn.SCHEME_WINOGRAD, n, mnn.GEMM_FP32, variant, -1.0), pad=1)
+    for n, N, C, H, K, wins in ((4, 32, 256, 14, 256, False), (4, 1, 64, 56, 64, False), (2, 16, 64, 112, 64, True), (4, 8, 16, 128, 16, True)):
+        assert (ms(mnn.WINO_FUSED_ALL, n, N, C, H, K) < ms(mnn.WINO_UNFUSED, n, N, C, H, K)) == wins, (n, N, C, H, K)
+    # more blocks of output channels than CUs: another round of workgroups
+    assert ms(mnn.WINO_FUSED_ALL, 4, 32, 64, 28, 512) > 1.9 * ms(mnn.WINO_FUSED_ALL, 4, 32, 64, 28, 128)
+
+
 def test_launches_of_2_to_the_32_work_items_are_refused(mnn):
     """Such a launch would run, without an error, on what is left modulo 2^32: every configuration of every precision says no before it."""
     import torch
