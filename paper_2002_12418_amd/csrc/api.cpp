@@ -370,6 +370,24 @@ int mnn_conv_run(mnn_conv_plan_t plan, const float* input, const float* weight, 
     return MNN_OK;
 }
 
+namespace {
+// Whether the call that prepares its weights each time and cannot time anything takes the one-kernel arrangement.  Measured on both, 247
+// shapes (1 to 32 images, 2 to 256 channels, 4 to 150 pixels wide, alpha 3 to 6), whole calls in us: the separate kernels cost 2 more to begin
+// with, 0.25 per megabyte of V and M written and read, and 2 where padding has to be cleared first; the one kernel costs 1/8 per position
+// for each chunk of 16 channels that a workgroup walks, one workgroup per CU at a time.  F(2,3) one image 64 -> 64 56 x 56 17.3 separate,
+// 21.3 one; 112 x 112 30.0, 21.3; F(4,3) 16 images 32 -> 64 56 x 56 35.7, 27.8; one image 64 -> 64 20.2, 33.8.  Where it errs it loses 17 % or
+// less in all but two of the 247 (33 and 19 %, seven and eleven output channels), 0.5 % on average.
+bool one_kernel_sooner(const WinoGeom& g, bool clear)
+{
+    if (!wino_full_available(g.n, g.k)) return false;
+    const double a2 = (double)g.alpha * g.alpha, per_block = wino_full_block_channels(g.alpha);
+    const double wgs = std::ceil(g.K / per_block) * std::ceil(g.P / 32.0);
+    const double chunks = std::ceil(g.C / 16.0) * std::ceil(wgs / 256.0);
+    const double bytes = 4.0 * a2 * g.P * 2.0 * ((double)g.C + g.K);
+    return a2 * chunks / 8.0 < 2.0 + 0.25e-6 * bytes + (clear ? 2.0 : 0.0);
+}
+}  // namespace
+
 size_t mnn_conv_static_scratch_bytes(void) { return kStaticScratchBytes; }
 
 int mnn_conv_run_static(const mnn_conv_shape* shape, const mnn_conv_geom* geom, int32_t tile_n, const float* input,
@@ -396,12 +414,11 @@ int mnn_conv_run_static(const mnn_conv_shape* shape, const mnn_conv_geom* geom, 
         hipError_t e = static_scratch(&base);
         if (e != hipSuccess) return fail_hip(e, "static scratch buffer");
         hipStream_t s = (hipStream_t)stream;
-        // One kernel after the weights where it is the faster arrangement without timing: up to alpha = 4 and four chunks of channels its
-        // latency is below that of three launches, and with up to 64 output channels and tiles for every CU it saves the traffic of V and M
-        // (F(2,3), one image, 64 -> 64 56 x 56: 14.1 against 16.2 us; F(4,3), 32 images: 44 against 53, but one image 22 against 15).
+        // the buffer keeps the last call's contents: the padding of the prepared weights and of V must read as zero.  The other schemes,
+        // and the one-kernel arrangement, write their padding themselves.
+        const bool clear = sc.kind == MNN_SCHEME_WINOGRAD && (im.wg.ldk != L.s.c_out || im.wg.ldp != im.wg.P);
         Impl one;
-        if (sc.kind == MNN_SCHEME_WINOGRAD && !im.rect && wino_full_available(tile_n, L.s.kh) &&
-            ((im.wg.alpha <= 4 && L.s.c_in <= 64) || (L.s.c_out <= 64 && im.wg.P >= 32 * 256)) &&
+        if (sc.kind == MNN_SCHEME_WINOGRAD && !im.rect && one_kernel_sooner(im.wg, clear) &&
             one.prepare(L, make_scheme(MNN_SCHEME_WINOGRAD, tile_n, MNN_GEMM_FP32, MNN_WINO_FUSED_ALL), o, true, true) == MNN_OK &&
             one.external_bytes() <= kStaticScratchBytes) {
             one.bind_external(reinterpret_cast<char*>(base));
@@ -409,9 +426,8 @@ int mnn_conv_run_static(const mnn_conv_shape* shape, const mnn_conv_geom* geom, 
             return one.run_stage(MNN_STAGE_GEMM, input, weight, bias, output, s);
         }
         im.bind_external(reinterpret_cast<char*>(base));
-        // the buffer keeps the last call's contents: the padding of the prepared weights and of V must read as zero
-        // (by a kernel, not a memset: the call may be recorded into a graph).  The other schemes write their padding themselves.
-        if (sc.kind == MNN_SCHEME_WINOGRAD && (im.wg.ldk != L.s.c_out || im.wg.ldp != im.wg.P) &&
+        // (by a kernel, not a memset: the call may be recorded into a graph)
+        if (clear &&
             (e = launch_fill_zero(base, (Impl::align256(im.U_bytes) + Impl::align256(im.V_bytes)) / sizeof(float), s)) != hipSuccess)
             return fail_hip(e, "scratch clear");
         for (int st = MNN_STAGE_FILTER; st < MNN_STAGE_COUNT; ++st)

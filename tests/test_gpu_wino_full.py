@@ -188,3 +188,27 @@ def test_weights_that_three_parts_do_not_hold(value, n):
         else:
             assert torch.isfinite(a[0, k]).all()
             assert float((a[0, k] - c[0, k]).abs().max()) <= 1e-5 * float(a[0, k].abs().max()), k
+
+
+@pytest.mark.parametrize("shape,n,one", [
+    ((1, 64, 28, 28, 64, 3, 1), 2, False), ((1, 64, 112, 112, 64, 3, 1), 2, True), ((1, 128, 14, 14, 130, 3, 1), 2, False),
+    ((16, 32, 56, 56, 64, 3, 1), 4, True), ((1, 64, 56, 56, 64, 3, 1), 4, False), ((5, 3, 31, 33, 7, 3, 1), 2, True),
+    ((8, 17, 40, 41, 35, 3, 1), 3, True), ((2, 40, 9, 9, 33, 5, 2), 2, False),
+], ids=str)
+def test_allocation_free_call_takes_the_arrangement_its_rule_names(shape, n, one):
+    """Of the one-kernel and the separate arrangement the call without timing takes the one that was faster for such sizes; the scratch
+    array holds another layer's values before."""
+    from conv_workloads import ConvLayer
+    m = mnn()
+    N, C, H, W, K, k, pad = shape
+    layer = ConvLayer("s", N, C, H, W, K, k, k, 1, pad)
+    x, w, b = (t.cuda() for t in tensors(shape, 14))
+    dirty = ConvLayer("d", 4, 40, 40, 40, 64, 3, 3, 1, 1)
+    dx, dw, dy = torch.full((4, 40, 40, 40), 1e30, device="cuda"), torch.full((64, 40, 3, 3), 1e4, device="cuda"), torch.empty(4, 64, 40, 40, device="cuda")
+    m.conv_run_static(dirty, 4, dx, dw, None, dy)
+    y = m.conv_run_static(layer, n, x, w, b, torch.full((N, K, H, W), float("nan"), device="cuda")).cpu()
+    with plan(m, shape, n, m.WINO_FUSED_ALL) as p:
+        same = torch.equal(y, p.run(x, w, b).cpu())          # the separate kernels add in another order
+    ref = torch.nn.functional.conv2d(x.cpu().double(), w.cpu().double(), b.cpu().double(), padding=pad)
+    assert float((y.double() - ref).abs().max() / ref.abs().max()) < 1e-4
+    assert same == one
