@@ -374,9 +374,9 @@ namespace {
 // Whether the call that prepares its weights each time and cannot time anything takes the one-kernel arrangement.  Measured on both, 247
 // shapes (1 to 32 images, 2 to 256 channels, 4 to 150 pixels wide, alpha 3 to 6), whole calls in us: the separate kernels cost 2 more to begin
 // with, 0.25 per megabyte of V and M written and read, and 2 where padding has to be cleared first; the one kernel costs 1/8 per position
-// for each chunk of 16 channels that a workgroup walks, one workgroup per CU at a time.  F(2,3) one image 64 -> 64 56 x 56 17.3 separate,
-// 21.3 one; 112 x 112 30.0, 21.3; F(4,3) 16 images 32 -> 64 56 x 56 35.7, 27.8; one image 64 -> 64 20.2, 33.8.  Where it errs it loses 17 % or
-// less in all but two of the 247 (33 and 19 %, seven and eleven output channels), 0.5 % on average.
+// for each chunk of 16 channels that a workgroup walks, one workgroup per CU at a time, and 0.5 per tap beyond 3 (its weights).  F(2,3) one image 64 -> 64 56 x 56 17.3 separate,
+// 21.3 one; 112 x 112 30.0, 21.3; F(4,3) 16 images 32 -> 64 56 x 56 35.7, 27.8; one image 64 -> 64 20.2, 33.8.  Where it errs it loses 10 % or
+// less in all but two of the 247 (33 and 19 %, eleven and seven output channels), 0.4 % on average.
 bool one_kernel_sooner(const WinoGeom& g, bool clear)
 {
     if (!wino_full_available(g.n, g.k)) return false;
@@ -384,7 +384,7 @@ bool one_kernel_sooner(const WinoGeom& g, bool clear)
     const double wgs = std::ceil(g.K / per_block) * std::ceil(g.P / 32.0);
     const double chunks = std::ceil(g.C / 16.0) * std::ceil(wgs / 256.0);
     const double bytes = 4.0 * a2 * g.P * 2.0 * ((double)g.C + g.K);
-    return a2 * chunks / 8.0 < 2.0 + 0.25e-6 * bytes + (clear ? 2.0 : 0.0);
+    return a2 * chunks / 8.0 + 0.5 * (g.k - 3) < 2.0 + 0.25e-6 * bytes + (clear ? 2.0 : 0.0);
 }
 }  // namespace
 

@@ -591,12 +591,14 @@ namespace {
 // A reduction of one short chunk keeps the fp32 tiles.  Otherwise the staged tiles once 64 x 64 tiles fill the chip twice, and below that
 // the short-grid tiles where the reduction is long enough to divide (R = 64: 9.0 us staged, 8.9 to 9.0 divided; R = 512, 1024 x 784: 20.3
 // staged, 12.7 divided; 16 columns: 17.3 staged, 10.1 divided).
-int auto_variant(const GemmProblem& p)
+// Columns that need 4-byte loads (`vec` 0, no gather) spread them over all wavefronts in the 64 x 64 tile only (347 x 629 x 9073: 49.7 us against
+// 71 in the 128-wide one, 1024 x 1024 x 2049 51 against 106, 64 x 64 x 200705 25.5 against 28).
+int auto_variant(const GemmProblem& p, bool vec)
 {
     const int split6 = kNumVariants, staged64 = split6 + kStaged64, shorts = split6 + gemm_split6_variant_count();
     if (p.R < 64) return p.M <= 64 ? 2 : 1;
     const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64) * p.batch;
-    if (tiles64 >= 512) return p.M <= 64 ? split6 + kStaged64x128 : split6 + kStaged128;
+    if (tiles64 >= 512) return !vec && !p.gather ? staged64 : p.M <= 64 ? split6 + kStaged64x128 : split6 + kStaged128;
     if (p.R < 256) return staged64;
     if (p.Ncols <= 16) return shorts + kShort16;
     return tiles64 >= 160 ? shorts + kShort64 : shorts + kShort32;
@@ -618,7 +620,7 @@ hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s)
     const bool vec = aligned16(p.B) && (p.L % 4 == 0) && (p.Ncols % 4 == 0) && (p.strideB_batch % 4 == 0) &&
                      (p.strideB_img % 4 == 0) && (p.strideB_row % 4 == 0);
     int v = p.variant;
-    if (v == 0) v = auto_variant(p);
+    if (v == 0) v = auto_variant(p, vec);
     const hipError_t e = v < kNumVariants ? kVariants[v].fn(p, vec, s) : x6_variant(v - kNumVariants).fn(p, vec, s);
     if (e != hipErrorNotSupported) return e;
     // an operand of 2 GiB or more per batch: one tile configuration with 64-bit addressing serves all variants

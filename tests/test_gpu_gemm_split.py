@@ -310,3 +310,29 @@ def test_bf16_operands_past_the_range_checked_loader(tmp_path):
                     err = float((y.cpu().double() - ref).abs().max() / ref.abs().max())
                     assert err < tol, (names[v], split, err)
     m.cache_clear()
+
+
+@pytest.mark.parametrize("shape", [(103, 130, 326, 1), (64, 64, 32768, 1), (64, 64, 32704, 1), (130, 70, 260, 72), (130, 70, 257, 72), (33, 9, 3, 36)])
+def test_products_without_a_named_configuration(shape):
+    """Variant 0 on both sides of the number of tiles, and of the alignment, at which it takes another one: the bits of the configuration it
+    stands for."""
+    m = mnn()
+    M, R, P, batch = shape
+    lda = (M + 3) // 4 * 4
+    g = torch.Generator().manual_seed(sum(shape))
+    A, B = torch.randn(batch, R, lda, generator=g), torch.randn(batch, R, P, generator=g)
+    ref = A[:, :, :M].double().transpose(1, 2) @ B.double()
+    A, B = A.cuda(), B.cuda()
+    few = -(-M // 64) * -(-P // 64) * batch < 512 or P % 4 != 0
+    stands_for = "bf16_64x64x64_w2x2" if few else "bf16_64x128x32_w1x4" if M <= 64 else "bf16_128x128x32_w2x2"
+    many = "x6_64x64x64_w2x2" if P % 4 else "x6_64x128x32_w1x4" if M <= 64 else "x6_128x128x32_w2x2"
+    for prec, name, tol in ((m.GEMM_BF16X3, stands_for, 3e-5), (m.GEMM_BF16, stands_for, 1e-2), (m.GEMM_FP32, many, 2e-6)):
+        if prec == m.GEMM_FP32 and (R < 64 or -(-M // 64) * -(-P // 64) * batch < 512):
+            continue                                     # the rule for fewer tiles: other tests
+        out = []
+        for v in (0, m.gemm_variants(prec).index(name)):
+            D = torch.zeros(batch, M, P, device="cuda")
+            m.gemm_f32(A, B, D, M=M, ncols=P, R=R, batch=batch, lda=lda, variant=v, prec=prec, strideA_batch=R * lda, strideB_batch=R * P, strideD_batch=M * P)
+            out.append(D.cpu())
+        assert torch.equal(*out)
+        assert float((out[0].double() - ref).abs().max() / ref.abs().max()) < tol
