@@ -542,7 +542,8 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 
 // Configurations the planner times.  Of the fp32 tiles only those that still win somewhere: 64 x 64 x 16, 64 x 128 x 16 and 128 x 64 x 16 where the
 // reduction is one short chunk (64 x 32 x 200704: 17.4 us against 18.4), 64 x 32 k2 where a gather has fewer channels than a group of eight
-// (7 x 7 stride 2, 3 -> 64 on 224 x 224: 10.4 against 15).  The others are there for callers that name them and for choices saved
+// (7 x 7 stride 2, 3 -> 64 on 224 x 224: 10.4 against 15), and 32 x 64 k2 for few output channels and a long reduction (16 of 10 x 969 x 9452: 113
+// against 129; 25 of 8 x 1818 x 1896 64 against 71).  The others are there for callers that name them and for choices saved
 // earlier; they lose to the x6 tiles wherever they were the best (100 products 256 x 256 x 4096: 446 against 305 us; 36 of
 // 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).
 bool gemm_variant_tuned(const GemmProblem& p, int v)
@@ -552,7 +553,7 @@ bool gemm_variant_tuned(const GemmProblem& p, int v)
     static const char* const kept[] = {"64x64x16_w2x2", "64x128x16_w1x4", "128x64x16_w2x2", "64x32x32_w2x1k2_pf2"};
     for (const char* k : kept)
         if (std::strcmp(kVariants[v].name, k) == 0) return true;
-    return false;
+    return p.M <= 32 && std::strcmp(kVariants[v].name, "32x64x32_w1x2k2_pf2") == 0;
 }
 
 bool gemm_variant_tile(int prec, int variant, int* bm, int* bn, int* bk)
@@ -591,14 +592,19 @@ namespace {
 // A reduction of one short chunk keeps the fp32 tiles.  Otherwise the staged tiles once 64 x 64 tiles fill the chip twice, and below that
 // the short-grid tiles where the reduction is long enough to divide (R = 64: 9.0 us staged, 8.9 to 9.0 divided; R = 512, 1024 x 784: 20.3
 // staged, 12.7 divided; 16 columns: 17.3 staged, 10.1 divided).
-// Columns that need 4-byte loads (`vec` 0, no gather) spread them over all wavefronts in the 64 x 64 tile only (347 x 629 x 9073: 49.7 us against
-// 71 in the 128-wide one, 1024 x 1024 x 2049 51 against 106, 64 x 64 x 200705 25.5 against 28).
+// Columns that need 4-byte loads (`vec` 0, no gather) spread them over all wavefronts in the 64 x 64 x 64 tile (347 x 629 x 9073: 49.7 us against
+// 71 in the 128-wide one, 1024 x 1024 x 2049 51 against 106, 64 x 64 x 200705 25.5 against 28) where the reduction fills its chunks to
+// four fifths; else over half of them in 128 x 64 or 64 x 128 (96 x 96 x 30001 12.1 against 15.6; 64 of 43 x 77 x 19301 152 against 203).
 int auto_variant(const GemmProblem& p, bool vec)
 {
     const int split6 = kNumVariants, staged64 = split6 + kStaged64, shorts = split6 + gemm_split6_variant_count();
     if (p.R < 64) return p.M <= 64 ? 2 : 1;
     const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64) * p.batch;
-    if (tiles64 >= 512) return !vec && !p.gather ? staged64 : p.M <= 64 ? split6 + kStaged64x128 : split6 + kStaged128;
+    if (tiles64 >= 512) {
+        const bool loads4 = !vec && !p.gather;
+        if (loads4 && (p.R + 63) / 64 * 64 * 4ll <= p.R * 5ll) return staged64;
+        return split6 + (p.M <= 64 ? kStaged64x128 : loads4 ? kStaged128x64 : kStaged128);
+    }
     if (p.R < 256) return staged64;
     if (p.Ncols <= 16) return shorts + kShort16;
     return tiles64 >= 160 ? shorts + kShort64 : shorts + kShort32;

@@ -1,7 +1,8 @@
 // Batched GEMM with bf16 matrix-core operands and fp32 accumulation for gfx950
 // (v_mfma_f32_32x32x16_bf16) with 64-bit addresses, for operands that the 32-bit
 // offsets of gemm_split.hip do not cover (per batch B of 2 GiB or A of 1 GiB, rows
-// of 2^18 weights), fed from the same fp32 tensors as the fp32 kernel:
+// of 2^18 weights) and for sliding windows over 1 to 3 channels, fed from the same
+// fp32 tensors as the fp32 kernel:
 //
 //   D_b[m][col] = sum_r At_b[r][m] * B_b[r][col] (+ bias[m])
 //
@@ -25,30 +26,12 @@
 #include "kernels.hpp"
 #include "xcd_remap.hpp"
 #include "gemm_epilogue.hpp"
+#include "bf16_parts.hpp"
 
 namespace mnnconv {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-
-// round-to-nearest-even bf16 of x, as the upper 16 bits of a float pattern (inputs are finite)
-__device__ __forceinline__ unsigned bf16_bits(float x)
-{
-    const unsigned u = __float_as_uint(x);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-
-// packs rows (r, r+1) of one column: low half = row r.  *lo gets the packed residuals.
-__device__ __forceinline__ void split_pair(float x0, float x1, unsigned* hi, unsigned* lo)
-{
-    const unsigned h0 = bf16_bits(x0), h1 = bf16_bits(x1);
-    *hi = h0 | (h1 << 16);
-    const float r0 = x0 - __uint_as_float(h0 << 16);
-    const float r1 = x1 - __uint_as_float(h1 << 16);
-    *lo = bf16_bits(r0) | (bf16_bits(r1) << 16);
-}
 
 // MODE 0: B element by element through (col / L, col % L); 1: 16-byte loads; 2: im2col gather.
 template <int BM, int BN, int BK, int WM, int WN, int MODE, bool SPLIT>
@@ -174,11 +157,18 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmProblem p, 
             for (int h = 0; h < 2; ++h) rb[j][h] = load_b_row(j, r0 + 2 * b_rp[j] + h);
     };
     auto pack = [&](const float4& x0, const float4& x1, uintx4* hi, uintx4* lo) {
-        unsigned h[4], l[4];
-        split_pair(x0.x, x1.x, &h[0], &l[0]);
-        split_pair(x0.y, x1.y, &h[1], &l[1]);
-        split_pair(x0.z, x1.z, &h[2], &l[2]);
-        split_pair(x0.w, x1.w, &h[3], &l[3]);
+        constexpr int NP = SPLIT ? 2 : 1;
+        unsigned h[4], l[4], none = 0;
+        auto cut = [&](int i, float r0, float r1) {
+            unsigned part[NP];
+            split_pair<NP>(r0, r1, part, none);
+            h[i] = part[0];
+            l[i] = part[NP - 1];
+        };
+        cut(0, x0.x, x1.x);
+        cut(1, x0.y, x1.y);
+        cut(2, x0.z, x1.z);
+        cut(3, x0.w, x1.w);
         *hi = uintx4{h[0], h[1], h[2], h[3]};
         *lo = uintx4{l[0], l[1], l[2], l[3]};
     };
@@ -210,7 +200,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmProblem p, 
     const int all_chunks = (p.R + BK - 1) / BK;
     const int per_split = (all_chunks + splitk - 1) / splitk;
     const int ch0 = split * per_split;
-    const int nchunks = (all_chunks - ch0 < per_split ? all_chunks - ch0 : per_split);   // launcher guarantees >= 1
+    const int nchunks = (all_chunks - ch0 < per_split ? all_chunks - ch0 : per_split);   // <= 0: an empty slice, zeros
     load_global(ch0 * BK);
     store_lds(0);
     __syncthreads();
@@ -272,13 +262,8 @@ hipError_t launch_cfg(const GemmProblem& p, bool vec, hipStream_t s)
     const long long total = (long long)tilesM * tilesN * p.batch;
     if (total <= 0 || total >= (1ll << 31)) return hipErrorInvalidValue;
     const int splitk = p.splitk > 1 ? p.splitk : 1;
-    if (splitk > 1) {
-        // every slice needs at least one chunk, and the scratch buffers must be there
-        const int all_chunks = (p.R + BK - 1) / BK;
-        const int per_split = (all_chunks + splitk - 1) / splitk;
-        if ((long long)(splitk - 1) * per_split >= all_chunks || !p.splitk_partial || total * splitk >= (1ll << 31))
-            return hipErrorInvalidValue;
-    }
+    // a slice past the end of the reduction (a split remembered from a kernel with another chunk count) adds zeros
+    if (splitk > 1 && !p.splitk_partial) return hipErrorInvalidValue;
     if (!grid_fits(total * splitk, WM * WN * 64)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(total * splitk)), block(WM * WN * 64);
     const bool split = p.prec == 2;

@@ -132,7 +132,7 @@ bool gemm_operand_extents(const GemmProblem& p, unsigned* a_bytes, unsigned* b_b
 struct GemmVariant { const char* name; hipError_t (*fn)(const GemmProblem&, bool, hipStream_t); int bm, bn, bk; };
 int gemm_split6_variant_count();
 const GemmVariant& gemm_split6_variant(int i);
-constexpr int kStaged128 = 0, kStaged64x128 = 2, kStaged64 = 3;        // its tiles of that size
+constexpr int kStaged128 = 0, kStaged128x64 = 1, kStaged64x128 = 2, kStaged64 = 3;        // its tiles of that size
 // the same for grids too short to fill the chip (gemm_short.hip); these follow
 int gemm_short_variant_count();
 const GemmVariant& gemm_short_variant(int i);

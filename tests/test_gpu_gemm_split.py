@@ -312,7 +312,7 @@ def test_bf16_operands_past_the_range_checked_loader(tmp_path):
     m.cache_clear()
 
 
-@pytest.mark.parametrize("shape", [(103, 130, 326, 1), (64, 64, 32768, 1), (64, 64, 32704, 1), (130, 70, 260, 72), (130, 70, 257, 72), (33, 9, 3, 36)])
+@pytest.mark.parametrize("shape", [(103, 130, 326, 1), (64, 64, 32768, 1), (64, 64, 32704, 1), (130, 70, 260, 72), (130, 70, 257, 72), (130, 128, 257, 72), (33, 9, 3, 36)])
 def test_products_without_a_named_configuration(shape):
     """Variant 0 on both sides of the number of tiles, and of the alignment, at which it takes another one: the bits of the configuration it
     stands for."""
@@ -323,11 +323,14 @@ def test_products_without_a_named_configuration(shape):
     A, B = torch.randn(batch, R, lda, generator=g), torch.randn(batch, R, P, generator=g)
     ref = A[:, :, :M].double().transpose(1, 2) @ B.double()
     A, B = A.cuda(), B.cuda()
-    few = -(-M // 64) * -(-P // 64) * batch < 512 or P % 4 != 0
+    tiles = -(-M // 64) * -(-P // 64) * batch
+    few = R > 32 and (tiles < 512 or P % 4 != 0)
     stands_for = "bf16_64x64x64_w2x2" if few else "bf16_64x128x32_w1x4" if M <= 64 else "bf16_128x128x32_w2x2"
-    many = "x6_64x64x64_w2x2" if P % 4 else "x6_64x128x32_w1x4" if M <= 64 else "x6_128x128x32_w2x2"
+    fills = -(-R // 64) * 64 * 4 <= R * 5
+    many = ("x6_64x64x64_w2x2" if P % 4 and fills else "x6_64x128x32_w1x4" if M <= 64
+            else "x6_128x64x32_w2x2" if P % 4 else "x6_128x128x32_w2x2")
     for prec, name, tol in ((m.GEMM_BF16X3, stands_for, 3e-5), (m.GEMM_BF16, stands_for, 1e-2), (m.GEMM_FP32, many, 2e-6)):
-        if prec == m.GEMM_FP32 and (R < 64 or -(-M // 64) * -(-P // 64) * batch < 512):
+        if prec == m.GEMM_FP32 and (R < 64 or tiles < 512):
             continue                                     # the rule for fewer tiles: other tests
         out = []
         for v in (0, m.gemm_variants(prec).index(name)):
