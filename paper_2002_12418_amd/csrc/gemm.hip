@@ -543,7 +543,8 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 // Configurations the planner times.  Of the fp32 tiles only those that still win somewhere: 64 x 64 x 16, 64 x 128 x 16 and 128 x 64 x 16 where the
 // reduction is one short chunk (64 x 32 x 200704: 17.4 us against 18.4), 64 x 32 k2 where a gather has fewer channels than a group of eight
 // (7 x 7 stride 2, 3 -> 64 on 224 x 224: 10.4 against 15), and 32 x 64 k2 for few output channels and a long reduction (16 of 10 x 969 x 9452: 113
-// against 129; 25 of 8 x 1818 x 1896 64 against 71).  The others are there for callers that name them and for choices saved
+// against 129; 25 of 8 x 1818 x 1896 64 against 71), and 128 x 128 pf2 where groups of eight channels are not full (7 x 7, 4 -> 234 on 16 x 34 x 30 25.8
+// against 27.6).  The others are there for callers that name them and for choices saved
 // earlier; they lose to the x6 tiles wherever they were the best (100 products 256 x 256 x 4096: 446 against 305 us; 36 of
 // 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).
 bool gemm_variant_tuned(const GemmProblem& p, int v)
@@ -553,7 +554,8 @@ bool gemm_variant_tuned(const GemmProblem& p, int v)
     static const char* const kept[] = {"64x64x16_w2x2", "64x128x16_w1x4", "128x64x16_w2x2", "64x32x32_w2x1k2_pf2"};
     for (const char* k : kept)
         if (std::strcmp(kVariants[v].name, k) == 0) return true;
-    return p.M <= 32 && std::strcmp(kVariants[v].name, "32x64x32_w1x2k2_pf2") == 0;
+    if (p.M <= 32 && std::strcmp(kVariants[v].name, "32x64x32_w1x2k2_pf2") == 0) return true;
+    return p.gather && p.cv_C % 8 != 0 && p.cv_C < 16 && p.M > 64 && std::strcmp(kVariants[v].name, "128x128x16_w4x2_pf2") == 0;
 }
 
 bool gemm_variant_tile(int prec, int variant, int* bm, int* bn, int* bk)
@@ -588,21 +590,29 @@ hipError_t launch_splitk_reduce(const GemmProblem& p, hipStream_t s)
 }
 
 namespace {
-// Configuration from the shape alone, for callers that cannot time (code under capture, chains planned without scratch memory).
-// A reduction of one short chunk keeps the fp32 tiles.  Otherwise the staged tiles once 64 x 64 tiles fill the chip twice, and below that
-// the short-grid tiles where the reduction is long enough to divide (R = 64: 9.0 us staged, 8.9 to 9.0 divided; R = 512, 1024 x 784: 20.3
-// staged, 12.7 divided; 16 columns: 17.3 staged, 10.1 divided).
-// Columns that need 4-byte loads (`vec` 0, no gather) spread them over all wavefronts in the 64 x 64 x 64 tile (347 x 629 x 9073: 49.7 us against
-// 71 in the 128-wide one, 1024 x 1024 x 2049 51 against 106, 64 x 64 x 200705 25.5 against 28) where the reduction fills its chunks to
-// four fifths; else over half of them in 128 x 64 or 64 x 128 (96 x 96 x 30001 12.1 against 15.6; 64 of 43 x 77 x 19301 152 against 203).
+// Configuration from the shape alone, for callers that cannot time (code under capture, chains planned without scratch memory).  Whole calls
+// or products, us:
+// - A reduction of one short chunk keeps the fp32 tiles, and so does a gather of 1 to 3 channels, most of whose groups of 8 would be empty
+//   (allocation-free call, 7 x 7 stride 2, 3 -> 64 on 8 x 224 x 224 44 against 54, 5 x 5 3 -> 128 on 4 x 64 x 64 18 against 26), but for
+//   short grids of more than 64 output channels (5 x 5 3 -> 128 on one 28 x 28 image 17.5 against 14.3).  In large grids of more than 64 also one
+//   of 4 or 9 channels (7 x 7 -> 234 on 16 x 34 x 30 34 against 44, 60 against 74; on 16 x 34 x 34 47 against 50, 87 against 86).
+// - The short-grid tiles where 64 x 64 tiles do not fill the chip twice and the reduction is long enough to divide (R = 64: 9.0 staged, 8.9 to 9.0
+//   divided; R = 512, 1024 x 784: 20.3 staged, 12.7 divided; 16 columns: 17.3 staged, 10.1 divided).
+// - The 64 x 64 x 64 staged tile up to three such tiles per CU (128 x 256 x 16384 12.1 against 19.1 in 128 x 128, whose 128 workgroups leave half the
+//   chip idle; 512 x 256 x 6272, 784 tiles, 19.3 both), and for columns that need 4-byte loads (`vec` 0, no gather), which it alone spreads
+//   over all wavefronts (347 x 629 x 9073 49.7 against 71, 1024 x 1024 x 2049 51 against 106), if the reduction fills its chunks to four fifths;
+//   else over half of them in 128 x 64 or 64 x 128 (96 x 96 x 30001 12.1 against 15.6; 64 of 43 x 77 x 19301 152 against 203).
 int auto_variant(const GemmProblem& p, bool vec)
 {
     const int split6 = kNumVariants, staged64 = split6 + kStaged64, shorts = split6 + gemm_split6_variant_count();
-    if (p.R < 64) return p.M <= 64 ? 2 : 1;
+    const int fp32 = p.M <= 64 ? 2 : 1;
     const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64) * p.batch;
+    const int groups8 = (p.cv_C + 7) / 8 * 8;
+    if (p.R < 64 || (p.gather && p.cv_C <= 3 && (p.M <= 64 || tiles64 >= 512))) return fp32;
+    if (p.gather && groups8 * 4 >= p.cv_C * 7 && p.M > 64 && tiles64 >= 768) return fp32;
     if (tiles64 >= 512) {
         const bool loads4 = !vec && !p.gather;
-        if (loads4 && (p.R + 63) / 64 * 64 * 4ll <= p.R * 5ll) return staged64;
+        if (loads4 ? (p.R + 63) / 64 * 64 * 4ll <= p.R * 5ll : tiles64 < 768) return staged64;
         return split6 + (p.M <= 64 ? kStaged64x128 : loads4 ? kStaged128x64 : kStaged128);
     }
     if (p.R < 256) return staged64;

@@ -312,7 +312,7 @@ def test_bf16_operands_past_the_range_checked_loader(tmp_path):
     m.cache_clear()
 
 
-@pytest.mark.parametrize("shape", [(103, 130, 326, 1), (64, 64, 32768, 1), (64, 64, 32704, 1), (130, 70, 260, 72), (130, 70, 257, 72), (130, 128, 257, 72), (33, 9, 3, 36)])
+@pytest.mark.parametrize("shape", [(103, 130, 326, 1), (64, 64, 32768, 1), (64, 64, 32704, 1), (64, 64, 49152, 1), (130, 70, 260, 72), (130, 70, 257, 72), (130, 128, 257, 72), (33, 9, 3, 36)])
 def test_products_without_a_named_configuration(shape):
     """Variant 0 on both sides of the number of tiles, and of the alignment, at which it takes another one: the bits of the configuration it
     stands for."""
@@ -327,7 +327,7 @@ def test_products_without_a_named_configuration(shape):
     few = R > 32 and (tiles < 512 or P % 4 != 0)
     stands_for = "bf16_64x64x64_w2x2" if few else "bf16_64x128x32_w1x4" if M <= 64 else "bf16_128x128x32_w2x2"
     fills = -(-R // 64) * 64 * 4 <= R * 5
-    many = ("x6_64x64x64_w2x2" if P % 4 and fills else "x6_64x128x32_w1x4" if M <= 64
+    many = ("x6_64x64x64_w2x2" if (fills if P % 4 else tiles < 768) else "x6_64x128x32_w1x4" if M <= 64
             else "x6_128x64x32_w2x2" if P % 4 else "x6_128x128x32_w2x2")
     for prec, name, tol in ((m.GEMM_BF16X3, stands_for, 3e-5), (m.GEMM_BF16, stands_for, 1e-2), (m.GEMM_FP32, many, 2e-6)):
         if prec == m.GEMM_FP32 and (R < 64 or tiles < 512):
@@ -339,3 +339,25 @@ def test_products_without_a_named_configuration(shape):
             out.append(D.cpu())
         assert torch.equal(*out)
         assert float((out[0].double() - ref).abs().max() / ref.abs().max()) < tol
+
+
+@pytest.mark.parametrize("c", [1, 3, 4, 9])
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3", "bf16"])
+def test_sliding_windows_over_few_channels(c, prec):
+    """1 to 3 channels take other kernels than 4 do (in large grids 4 and 9, others than 5): planned in every precision, and the call without
+    timing, at 64 and 65 output channels."""
+    m = mnn()
+    p = {"fp32": m.GEMM_FP32, "bf16x3": m.GEMM_BF16X3, "bf16": m.GEMM_BF16}[prec]
+    tol = {"fp32": 2e-6, "bf16x3": 3e-5, "bf16": 1e-2}[prec]
+    g = torch.Generator().manual_seed(c)
+    for k_out, n, h in ((64, 1, 27), (65, 1, 27), (65, 9, 63), (65, 8, 120)):
+        layer = ConvLayer("few", n, c, h, h + 1, k_out, 7, 7, 2, 3)
+        x, w = torch.rand(n, c, h, h + 1, generator=g) * 2 - 1, torch.randn(k_out, c, 7, 7, generator=g)
+        ref = torch.nn.functional.conv2d(x.double(), w.double(), stride=2, padding=3)
+        x, w = x.cuda(), w.cuda()
+        with m.ConvPlan.for_layer(layer, options=m.Options(force_kind=m.SCHEME_DIRECT, force_prec=p)) as plan:
+            got = [plan.run(x, w, None)]
+        if prec == "fp32":
+            got.append(m.conv_run_static(layer, 0, x, w, None, torch.full(ref.shape, float("nan"), device="cuda")))
+        for y in got:
+            assert float((y.cpu().double() - ref).abs().max() / ref.abs().max()) < tol, (k_out, n)
