@@ -6,7 +6,7 @@ namespace mnnconv {
 
 // Division of a value below 2^31 by a constant the host knows: q = mulhi(n, m) >> sh with m = ceil(2^(31+L) / d),
 // L = ceil(log2 d), sh = L - 1 (exact for every n < 2^31).  A run-time division costs some thirty vector instructions,
-// and this kernel's instruction count is part of its time.
+// and the instruction count of the kernels that use this is part of their time.
 struct FastDiv { unsigned m, sh, d; };
 inline FastDiv make_fastdiv(unsigned d)
 {

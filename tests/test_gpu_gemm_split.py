@@ -64,8 +64,8 @@ def test_operands_of_any_magnitude():
 
 @pytest.mark.parametrize("exponent", [-80, -112, -118, -124])
 def test_tiny_operands_as_accurate_as_the_fp32_kernel(exponent):
-    """Below 2^-109 a bf16 has no room for the last parts; blocks of tiny sums come from the fp32 instructions.  Either operand, and a
-    matrix whose other half is zero."""
+    """Below 2^-109 a bf16 has no room for the last parts; tiles that hold such operands come from the fp32 instructions.  Either operand, and
+    a matrix whose other half is zero."""
     m = mnn()
     M, R, P = 132, 96, 136
     g = torch.Generator().manual_seed(5)
@@ -260,6 +260,19 @@ def test_tiny_operands_beside_ordinary_ones(exponent, factor, where):
     assert tiny_error(m, A, B, fp32, absolute) <= bound
     errs = {name: tiny_error(m, A, B, v, absolute) for v, name in x6_variants(m)}
     assert all(e <= bound for e in errs.values()), errs
+
+
+@pytest.mark.parametrize("exponents", [(-60, -50), (-60, -66), (-60, -70), (-70, -72), (-80, -72)])
+def test_products_at_the_end_of_the_range(exponents):
+    """Operands that three parts hold, products that are subnormal or below: the matrix cores keep subnormal values, so every configuration is
+    as far off as the fp32 tile, R spacings of 2^-149 at the most beside its R roundings."""
+    m = mnn()
+    M, R, P = 68, 48, 132
+    g = torch.Generator().manual_seed(7)
+    A = torch.randn(1, R, M, generator=g) * 2.0 ** exponents[0]
+    B = torch.randn(1, R, P, generator=g) * 2.0 ** exponents[1]
+    for v, name in x6_variants(m):
+        assert tiny_error(m, A, B, v, R * 2.0 ** -149) <= R * 2.0 ** -24, name
 
 
 def test_equal_parts_in_every_term():
