@@ -543,7 +543,7 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 // Configurations the planner times.  Of the fp32 tiles only those that still win somewhere: 64 x 64 x 16, 64 x 128 x 16 and 128 x 64 x 16 where the
 // reduction is one short chunk (64 x 32 x 200704: 17.4 us against 18.4), 64 x 32 k2 where a gather has fewer channels than a group of eight
 // (7 x 7 stride 2, 3 -> 64 on 224 x 224: 10.4 against 15), and 32 x 64 k2 for few output channels and a long reduction (16 of 10 x 969 x 9452: 113
-// against 129; 25 of 8 x 1818 x 1896 64 against 71), and 128 x 128 pf2 where groups of eight channels are not full (7 x 7, 4 -> 234 on 16 x 34 x 30 25.8
+// against 129; 25 of 8 x 1818 x 1896 64 against 71) and 32 x 32 k4 for gathers among them (7 x 7, 4 -> 9 on 8 x 94 x 54 15.0 against 16.5), and 128 x 128 pf2 where groups of eight channels are not full (7 x 7, 4 -> 234 on 16 x 34 x 30 25.8
 // against 27.6).  The others are there for callers that name them and for choices saved
 // earlier; they lose to the x6 tiles wherever they were the best (100 products 256 x 256 x 4096: 446 against 305 us; 36 of
 // 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).
@@ -554,7 +554,7 @@ bool gemm_variant_tuned(const GemmProblem& p, int v)
     static const char* const kept[] = {"64x64x16_w2x2", "64x128x16_w1x4", "128x64x16_w2x2", "64x32x32_w2x1k2_pf2"};
     for (const char* k : kept)
         if (std::strcmp(kVariants[v].name, k) == 0) return true;
-    if (p.M <= 32 && std::strcmp(kVariants[v].name, "32x64x32_w1x2k2_pf2") == 0) return true;
+    if (p.M <= 32 && (std::strcmp(kVariants[v].name, "32x64x32_w1x2k2_pf2") == 0 || std::strcmp(kVariants[v].name, "32x32x32_k4") == 0)) return true;
     return p.gather && p.cv_C % 8 != 0 && p.cv_C < 16 && p.M > 64 && std::strcmp(kVariants[v].name, "128x128x16_w4x2_pf2") == 0;
 }
 
