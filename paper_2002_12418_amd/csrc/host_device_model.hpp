@@ -27,7 +27,7 @@ std::vector<KernelWork> scheme_kernels(const Layer& L, const mnn_scheme& s)
             // A workgroup per CU owns 32 tiles and 32 (alpha <= 4: 64) output channels, transforms its tiles anew and walks the channels
             // 16 at a time: what bounds it is instruction issue and latency per chunk, not the multiplications.  In floating-point operations
             // at the rate of the model: 52 thousand per position and chunk, 1.6 million for the two ends (us measured / predicted: F(2,3)
-            // 16 x 64 x 112 x 112 82 / 82, 32 x 64 x 56 x 56 49 / 49, 32 x 128 x 28 x 28 40 / 42, 32 x 256 x 14 x 14 38 / 38; F(4,3) 32 x 64 x 56 x 56
+            // 16 x 64 x 112 x 112 88 / 82, 32 x 64 x 56 x 56 49 / 49, 32 x 128 x 28 x 28 40 / 42, 32 x 256 x 14 x 14 38 / 38; F(4,3) 32 x 64 x 56 x 56
             // 43 / 46, 32 x 128 x 28 x 28 43 / 42, 32 x 256 x 14 x 14 60 / 75, one image 64 x 56 x 56 22 / 25).
             const double cus = 256.0, wgs = std::ceil(K / wino_full_block_channels((int)ah)) * std::ceil(P / 32.0);
             const double each = std::ceil(C / 16.0) * a2 * 52e3 + 1.6e6;

@@ -110,7 +110,7 @@ def test_one_kernel_arrangement_is_offered_within_its_addresses(mnn):
 def test_one_kernel_arrangement_is_priced_with_its_repeated_transforms(mnn):
     """It transforms a tile again for every block of output channels and walks the channels in a workgroup: beside the separate kernels it
     must not look cheap where it is measured to lose (256 channels, F(4,3): 60 us against 39; one image 22 against 15), nor dear where it wins
-    (64 channels, F(2,3) on 16 images of 112 x 112: 82 us against 126)."""
+    (64 channels, F(2,3) on 16 images of 112 x 112: 88 us against 126)."""
     def ms(variant, n, N, C, H, K):
         return mnn.predict_ms(N, C, H, H, K, 3, 3, mnn.Scheme(mnn.SCHEME_WINOGRAD, n, mnn.GEMM_FP32, variant, -1.0), pad=1)
     for n, N, C, H, K, wins in ((4, 32, 256, 14, 256, False), (4, 1, 64, 56, 64, False), (2, 16, 64, 112, 64, True), (4, 8, 16, 128, 16, True)):
