@@ -39,6 +39,17 @@ __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const Tile
     const int lrow = lane >> 5, lcol = lane & 31;
     if (vec) {
         const int rrow = lane >> 3, rc4 = (lane & 7) * 4;
+        // all bias values at once: behind the bounds check of its row each load would be a trip of its own
+        float bias[TM][4];
+        if (d.bias) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int ps = 0; ps < 4; ++ps) {
+                    const int m = mw0 + i * 32 + ps * 8 + rrow;
+                    bias[i][ps] = d.bias[m < M ? m : M - 1];
+                }
+        }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int col = nw0 + j * 32 + rc4;
@@ -56,7 +67,7 @@ __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const Tile
                     float4 v = *reinterpret_cast<const float4*>(&stage[row * kStageStride + rc4]);
                     if (cok && m < M) {
                         if (d.bias) {
-                            const float bv = d.bias[m];
+                            const float bv = bias[i][ps];
                             v.x += bv; v.y += bv; v.z += bv; v.w += bv;
                         }
                         *reinterpret_cast<float4*>(d.base + coff + (long long)m * d.sRow) = v;
@@ -65,6 +76,16 @@ __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const Tile
             }
         }
         return;
+    }
+    float bias[TM][16];
+    if (d.bias) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = mw0 + i * 32 + 4 * lrow + 8 * (r / 4) + (r % 4);
+                bias[i][r] = d.bias[m < M ? m : M - 1];
+            }
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
@@ -79,7 +100,7 @@ __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const Tile
                 const int m = mbase + 8 * (r / 4) + (r % 4);
                 if (m < M) {
                     float v = acc[i][j][r];
-                    if (d.bias) v += d.bias[m];
+                    if (d.bias) v += bias[i][r];
                     d.base[coff + (long long)m * d.sRow] = v;
                 }
             }
