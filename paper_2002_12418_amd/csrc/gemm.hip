@@ -517,11 +517,16 @@ constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 // the variants after the fp32 ones
 const GemmVariant& x6_variant(int i)
 {
-    return i < gemm_split6_variant_count() ? gemm_split6_variant(i) : gemm_short_variant(i - gemm_split6_variant_count());
+    const int shorts = gemm_split6_variant_count(), patches = shorts + gemm_short_variant_count();
+    return i < shorts ? gemm_split6_variant(i) : i < patches ? gemm_short_variant(i - shorts) : conv_patch_variant(i - patches);
 }
 
+static int first_patch_variant() { return kNumVariants + gemm_split6_variant_count() + gemm_short_variant_count(); }
+
+bool gemm_variant_is_patch(int prec, int v) { return prec == 0 && v >= first_patch_variant() && v < gemm_f32_variant_count(); }
+
 // Variant ids: 0 = choose from the shape, 1 .. kNumVariants-1 = the tile configurations above.
-int gemm_f32_variant_count() { return kNumVariants + gemm_split6_variant_count() + gemm_short_variant_count(); }
+int gemm_f32_variant_count() { return first_patch_variant() + conv_patch_variant_count(); }
 const char* gemm_f32_variant_name(int v)
 {
     if (v < 0 || v >= gemm_f32_variant_count()) return nullptr;
@@ -530,7 +535,7 @@ const char* gemm_f32_variant_name(int v)
 
 bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 {
-    if (v < 1 || v >= gemm_f32_variant_count()) return false;
+    if (v < 1 || v >= first_patch_variant()) return false;          // the patch kernels do not split the reduction
     if (v >= kNumVariants) {
         const GemmVariant& sv = x6_variant(v - kNumVariants);
         *bm = sv.bm; *bn = sv.bn; *bk = sv.bk;
@@ -546,10 +551,12 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 // against 129; 25 of 8 x 1818 x 1896 64 against 71) and 32 x 32 k4 for gathers among them (7 x 7, 4 -> 9 on 8 x 94 x 54 15.0 against 16.5), and 128 x 128 pf2 where groups of eight channels are not full (7 x 7, 4 -> 234 on 16 x 34 x 30 25.8
 // against 27.6).  The others are there for callers that name them and for choices saved
 // earlier; they lose to the x6 tiles wherever they were the best (100 products 256 x 256 x 4096: 446 against 305 us; 36 of
-// 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).
+// 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).  The patch kernels from 8 channels on: their
+// chunks of 16 would be more than half empty.
 bool gemm_variant_tuned(const GemmProblem& p, int v)
 {
     if (v < 1 || v >= gemm_variant_count(p.prec)) return false;
+    if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && p.cv_C >= 8 && p.cv_kh * p.cv_kw > 1;
     if (p.prec != 0 || v >= kNumVariants) return true;
     static const char* const kept[] = {"64x64x16_w2x2", "64x128x16_w1x4", "128x64x16_w2x2", "64x32x32_w2x1k2_pf2"};
     for (const char* k : kept)
@@ -636,6 +643,7 @@ hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s)
     const bool vec = aligned16(p.B) && (p.L % 4 == 0) && (p.Ncols % 4 == 0) && (p.strideB_batch % 4 == 0) &&
                      (p.strideB_img % 4 == 0) && (p.strideB_row % 4 == 0);
     int v = p.variant;
+    if (gemm_variant_is_patch(0, v) && !p.a_parts) v = 0;           // weights in the common form
     if (v == 0) v = auto_variant(p, vec);
     const hipError_t e = v < kNumVariants ? kVariants[v].fn(p, vec, s) : x6_variant(v - kNumVariants).fn(p, vec, s);
     if (e != hipErrorNotSupported) return e;

@@ -25,6 +25,7 @@ struct Impl {
     int gemm_variant = 0;      // tile configuration of the GEMM stage (0 = shape heuristic)
     int gemm_splitk = 1;       // workgroups per tile along the reduction
     float* sk_partial = nullptr; size_t sk_partial_bytes = 0;
+    bool patch_room = false;   // sliding window: U has room for the weights in the patch kernels' form
     // V, M and the split-K partials hold nothing between two runs.  A plan on its own allocates them;
     // a chain of layers binds them to a region of its arena instead (bind_transient).
     bool transient_external = false;
@@ -192,6 +193,9 @@ struct Impl {
             if ((long long)sh.n * L.Ho * L.Wo >= (1ll << 31) || (long long)sh.n * sh.c_in * sh.h * sh.w >= (1ll << 31))
                 return fail(MNN_E_UNSUPPORTED, "tensor too large for the sliding-window kernel");
             U_bytes = (size_t)sh.c_in * sh.kh * sh.kw * ldk * sizeof(float);
+            // room for the form that the patch kernels read, whichever is chosen in the end (not where fixed scratch bounds it)
+            patch_room = !persistent_external && conv_patch_covers(direct_gemm_problem(nullptr, nullptr, nullptr));
+            if (patch_room) U_bytes = std::max(U_bytes, conv_patch_weight_bytes(sh.c_out, sh.c_in, sh.kh * sh.kw));
             int rcd = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
             if (rcd) return rcd;
             return MNN_OK;
@@ -243,6 +247,9 @@ struct Impl {
         return p;
     }
 
+    // whether the prepared weights have the form that the patch kernels read
+    bool patch_weights() const { return patch_room && gemm_variant_is_patch(scheme.prec, gemm_variant); }
+
     GemmProblem direct_gemm_problem(const float* x, const float* b, float* y) const
     {
         const mnn_conv_shape& sh = L.s;
@@ -253,6 +260,7 @@ struct Impl {
         p.lda = ldk; p.L = HoWo;
         p.strideD_img = (long long)sh.c_out * HoWo; p.strideD_row = HoWo;
         set_gemm_choice(&p);
+        p.a_parts = patch_room ? U : nullptr;
         p.gather = 1;
         p.cv_C = sh.c_in; p.cv_H = sh.h; p.cv_W = sh.w; p.cv_kh = sh.kh; p.cv_kw = sh.kw;
         p.cv_sh = L.g.stride_h; p.cv_sw = L.g.stride_w; p.cv_ph = L.g.pad_h; p.cv_pw = L.g.pad_w;
@@ -501,7 +509,8 @@ struct Impl {
             }
         } else {
             if (st == MNN_STAGE_FILTER)
-                e = launch_weight_transpose(w, U, sh.c_out, sh.c_in * sh.kh * sh.kw, ldk, s);
+                e = patch_weights() ? launch_patch_weights(w, U, sh.c_out, sh.c_in, sh.kh * sh.kw, s)
+                                    : launch_weight_transpose(w, U, sh.c_out, sh.c_in * sh.kh * sh.kw, ldk, s);
             else
                 e = launch_gemm_f32(direct_gemm_problem(x, b, y), s);
         }

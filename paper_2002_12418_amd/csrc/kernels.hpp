@@ -111,6 +111,7 @@ struct GemmProblem {
     // aligned); a second kernel adds them up in slice order.  0 or 1 = off.
     int splitk;
     float* splitk_partial;
+    const void* a_parts;        // the patch kernels' weights (launch_patch_weights); At is then unused
     // Implicit-GEMM gather for the sliding-window scheme (gather != 0): B is the input tensor x[N][C][H][W],
     // row r = (c, kr, ks), column = (img, oy, ox), element = x[img][c][oy*sh - ph + kr*dh][ox*sw - pw + ks*dw] or 0.
     // L must be H_o*W_o; the strideB_* fields are ignored.
@@ -137,6 +138,13 @@ constexpr int kStaged128 = 0, kStaged128x64 = 1, kStaged64x128 = 2, kStaged64 = 
 int gemm_short_variant_count();
 const GemmVariant& gemm_short_variant(int i);
 constexpr int kShort16 = 0, kShort32 = 2, kShort64 = 4;
+// and the sliding window on staged patches (conv_patch.hip), with weights of a form of their own; these come last
+int conv_patch_variant_count();
+const GemmVariant& conv_patch_variant(int i);
+bool conv_patch_covers(const GemmProblem& p);       // whether the patch kernels take this product
+size_t conv_patch_weight_bytes(int K, int C, int taps);
+hipError_t launch_patch_weights(const float* w, void* Wp, int K, int C, int taps, hipStream_t s);
+bool gemm_variant_is_patch(int prec, int variant);
 // bf16 / bf16x3 operands (gemm_split.hip; operands of 2 GiB and more: gemm_bf16.hip); launch_gemm_f32 forwards to them when prec != 0
 int gemm_bf16_variant_count();
 const char* gemm_bf16_variant_name(int variant);
