@@ -92,7 +92,10 @@ enum {
                                  (where the registers of two wavefronts per SIMD allow it)         */
     MNN_WINO_FUSED_ALL = 3,   /* one kernel from input to output: neither the transformed input nor the products are
                                  stored (n + k - 1 <= 6, input below 2 GiB)                        */
-    MNN_WINO_VARIANTS = 4
+    MNN_WINO_BY_AXIS = 4,     /* transforms along the image width, and what couples to them along its height inside the
+                                 multiplying kernel: alpha n instead of alpha^2 values per tile and channel pass through
+                                 memory (n + k - 1 from 7, kernels of 5 taps and more, input below 2 GiB)      */
+    MNN_WINO_VARIANTS = 5
 };
 
 typedef struct {
@@ -133,12 +136,14 @@ enum {
                                  fused variants: [b][c/4][a][kg][c%4][k%16], xi = a*alpha + b (kg groups of 16
                                  output channels, channel groups padded to whole 16-channel chunks);
                                  FUSED_ALL: bf16 parts in matrix-operand order (no float layout); values that three parts
-                                 do not hold are kept as their 32 bits                               */
+                                 do not hold are kept as their 32 bits; BY_AXIS: the same, [b][k/32][c/16][a] */
     MNN_BUF_V = 1,            /* transformed input tiles, unfused: [alpha^2][C][ldp] (ldp = P rounded up to 4), or, when
                                  mnn_plan_info.tiled is set (layers with many tiles), [C][pb][alpha^2][64]: element
                                  (xi, c, p) at ((c*pb + p/64)*alpha^2 + xi)*64 + p%64, ldp = 64*pb;
-                                 fused variants: [b][c/4][a][pg][c%4][p%16]                          */
-    MNN_BUF_M = 2             /* products [alpha^2][c_out][ldp], or [c_out][pb][alpha^2][64] when tiled (unfused variant only) */
+                                 fused variants: [b][c/4][a][pg][c%4][p%16];
+                                 BY_AXIS: rows of the input, [b][c][n][h][tiles_w]                   */
+    MNN_BUF_M = 2             /* products [alpha^2][c_out][ldp], or [c_out][pb][alpha^2][64] when tiled (unfused variant);
+                                 BY_AXIS: the sums after A^T along the height, in accumulator order  */
 };
 
 typedef struct {

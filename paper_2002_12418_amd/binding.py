@@ -21,7 +21,7 @@ SCHEME_AUTO, SCHEME_DIRECT, SCHEME_WINOGRAD, SCHEME_GEMM1X1 = 0, 1, 2, 3
 GEMM_FP32, GEMM_BF16, GEMM_BF16X3 = 0, 1, 2
 STAGE_FILTER, STAGE_INPUT, STAGE_GEMM, STAGE_OUTPUT, STAGE_COUNT = 0, 1, 2, 3, 4
 BUF_U, BUF_V, BUF_M = 0, 1, 2
-WINO_UNFUSED, WINO_FUSED_OUT_32, WINO_FUSED_OUT_64, WINO_FUSED_ALL = 0, 1, 2, 3
+WINO_UNFUSED, WINO_FUSED_OUT_32, WINO_FUSED_OUT_64, WINO_FUSED_ALL, WINO_BY_AXIS = 0, 1, 2, 3, 4
 _KIND_NAMES = {SCHEME_AUTO: "auto", SCHEME_DIRECT: "direct", SCHEME_WINOGRAD: "winograd", SCHEME_GEMM1X1: "gemm1x1"}
 
 
@@ -180,7 +180,7 @@ class Scheme:
     def label(self, k: Optional[int] = None) -> str:
         p = {GEMM_FP32: "", GEMM_BF16: "/bf16", GEMM_BF16X3: "/bf16x3"}.get(self.prec, f"/p{self.prec}")
         if self.kind == SCHEME_WINOGRAD:
-            v = {WINO_UNFUSED: "", WINO_FUSED_OUT_32: "+fo32", WINO_FUSED_OUT_64: "+fo64", WINO_FUSED_ALL: "+fall"}.get(self.variant, f"+v{self.variant}")
+            v = {WINO_UNFUSED: "", WINO_FUSED_OUT_32: "+fo32", WINO_FUSED_OUT_64: "+fo64", WINO_FUSED_ALL: "+fall", WINO_BY_AXIS: "+axis"}.get(self.variant, f"+v{self.variant}")
             return f"F({self.tile_n},{k if k is not None else 'k'}){v}{p}"
         st = f"+strassen{self.variant}" if (self.kind == SCHEME_GEMM1X1 and self.variant > 0) else ""
         return _KIND_NAMES.get(self.kind, str(self.kind)) + st + p

@@ -94,8 +94,8 @@ struct mnn_chain_s {
                 if (im->has_stage(st))
                     k += (st == MNN_STAGE_GEMM && im->strassen) ? im->strassen->launches()
                          : (st == MNN_STAGE_GEMM && im->gemm_splitk > 1) ? 2                    // + the slice reduction
-                         : (st == MNN_STAGE_GEMM && im->scheme.kind == MNN_SCHEME_WINOGRAD && im->scheme.variant != MNN_WINO_UNFUSED &&
-                            im->scheme.variant != MNN_WINO_FUSED_ALL)
+                         : (st == MNN_STAGE_GEMM && im->scheme.kind == MNN_SCHEME_WINOGRAD && (im->scheme.variant == MNN_WINO_FUSED_OUT_32 ||
+                            im->scheme.variant == MNN_WINO_FUSED_OUT_64))
                                ? wino_fused_launch_count(im->wg, im->scheme.variant - 1) : 1;
         return k;
     }

@@ -69,6 +69,15 @@ struct Impl {
         return alloc_zero(p, bytes, what);
     }
 
+    // for tensors that every pass writes as a whole
+    int alloc_unset(float** p, size_t bytes, const char* what)
+    {
+        if (transient_external) { *p = nullptr; return MNN_OK; }
+        const hipError_t e = hipMalloc((void**)p, bytes);
+        if (e != hipSuccess) { *p = nullptr; return fail_hip(e, what); }
+        return MNN_OK;
+    }
+
     int alloc_persistent(float** p, size_t bytes, const char* what)
     {
         if (persistent_external) { *p = nullptr; return MNN_OK; }
@@ -154,6 +163,16 @@ struct Impl {
                     return fail(MNN_E_UNSUPPORTED, "the one-kernel Winograd arrangement takes inputs and prepared weights below 2 GiB");
                 U_bytes = wino_full_weight_bytes(wg);
                 return alloc_persistent(&U, U_bytes, "hipMalloc U");
+            }
+            if (s.variant == MNN_WINO_BY_AXIS) {
+                if (!wino_cols_covers(wg))
+                    return fail(MNN_E_UNSUPPORTED, "the Winograd arrangement by axes takes inputs, their row transforms and prepared weights below 2 GiB");
+                U_bytes = wino_cols_weight_bytes(wg);
+                V_bytes = wino_cols_input_bytes(wg);
+                M_bytes = wino_cols_sum_bytes(wg);
+                if ((rc = alloc_persistent(&U, U_bytes, "hipMalloc U"))) return rc;
+                if ((rc = alloc_unset(&V, V_bytes, "hipMalloc T"))) return rc;
+                return alloc_unset(&M, M_bytes, "hipMalloc S");
             }
             if (s.variant != MNN_WINO_UNFUSED) {
                 // blocked operands, padded so that whole 128-wide blocks can be copied unchecked
@@ -288,7 +307,8 @@ struct Impl {
     // exceeds what the cap moves.)
     int tune_input_cap(hipStream_t s)
     {
-        if (scheme.kind != MNN_SCHEME_WINOGRAD || rect || scheme.variant == MNN_WINO_FUSED_ALL) return MNN_OK;
+        if (scheme.kind != MNN_SCHEME_WINOGRAD || rect || scheme.variant == MNN_WINO_FUSED_ALL || scheme.variant == MNN_WINO_BY_AXIS)
+            return MNN_OK;
         int dev = 0;
         (void)hipGetDevice(&dev);
         const InputCapKey key(dev, std::vector<int>{wg.N, wg.C, wg.H, wg.W, wg.K, wg.n, wg.k, wg.pad_h, wg.pad_w, wg.blocked, wg.tiled,
@@ -455,7 +475,7 @@ struct Impl {
         switch (scheme.kind) {
             case MNN_SCHEME_WINOGRAD:
                 if (scheme.variant == MNN_WINO_FUSED_ALL) return st == MNN_STAGE_FILTER || st == MNN_STAGE_GEMM;
-                return scheme.variant == MNN_WINO_UNFUSED || st != MNN_STAGE_OUTPUT;
+                return scheme.variant == MNN_WINO_UNFUSED || scheme.variant == MNN_WINO_BY_AXIS || st != MNN_STAGE_OUTPUT;
             case MNN_SCHEME_GEMM1X1: return st == MNN_STAGE_FILTER || st == MNN_STAGE_GEMM;
             default: return st == MNN_STAGE_FILTER || st == MNN_STAGE_GEMM;
         }
@@ -466,7 +486,14 @@ struct Impl {
         if (!has_stage(st)) return MNN_OK;
         hipError_t e = hipSuccess;
         const mnn_conv_shape& sh = L.s;
-        if (scheme.kind == MNN_SCHEME_WINOGRAD) {
+        if (scheme.kind == MNN_SCHEME_WINOGRAD && scheme.variant == MNN_WINO_BY_AXIS) {
+            switch (st) {
+                case MNN_STAGE_FILTER: e = launch_cols_filter(wg, mats.G.data(), w, U, s); break;
+                case MNN_STAGE_INPUT: e = launch_cols_rows_in(wg, mats.BT.data(), x, V, s); break;
+                case MNN_STAGE_GEMM: e = launch_cols(wg, mats.BT.data(), mats.AT.data(), V, U, M, s); break;
+                case MNN_STAGE_OUTPUT: e = launch_cols_rows_out(wg, mats.AT.data(), M, b, y, s); break;
+            }
+        } else if (scheme.kind == MNN_SCHEME_WINOGRAD) {
             switch (st) {
                 case MNN_STAGE_FILTER:
                     e = scheme.variant == MNN_WINO_FUSED_ALL ? launch_filter_full(wg, mats.G.data(), w, U, s)
@@ -542,6 +569,8 @@ void describe_impl(const Impl& im, char* buf, size_t cap)
                 std::snprintf(buf, cap, "F(%d,%d) unfused gemm=%s%s", im.wg.n, im.wg.k, gv, tail.c_str());
             else if (im.scheme.variant == MNN_WINO_FUSED_ALL)
                 std::snprintf(buf, cap, "F(%d,%d) one kernel", im.wg.n, im.wg.k);
+            else if (im.scheme.variant == MNN_WINO_BY_AXIS)
+                std::snprintf(buf, cap, "F(%d,%d) by axes", im.wg.n, im.wg.k);
             else
                 std::snprintf(buf, cap, "F(%d,%d) fused-output %s%s", im.wg.n, im.wg.k,
                               im.scheme.variant == MNN_WINO_FUSED_OUT_32 ? "32x32" : "64x64", tail.c_str());

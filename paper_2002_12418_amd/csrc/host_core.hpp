@@ -137,23 +137,26 @@ bool wino_variant_available(int n, int k, int variant)
         case MNN_WINO_FUSED_OUT_32: return wino_fused_available(n, k);
         case MNN_WINO_FUSED_OUT_64: return wino_fused_has_big_block(n, k);
         case MNN_WINO_FUSED_ALL: return wino_full_available(n, k);
+        case MNN_WINO_BY_AXIS: return wino_cols_available(n, k);
         default: return false;
     }
 }
 
-bool one_kernel_covers(const Layer& L, int n)
+// whether the sizes of the layer fit the arrangements that have limits of their own
+bool wino_variant_covers(const Layer& L, int n, int variant)
 {
+    if (variant != MNN_WINO_FUSED_ALL && variant != MNN_WINO_BY_AXIS) return true;
     WinoGeom g{};
     g.N = L.s.n; g.C = L.s.c_in; g.H = L.s.h; g.W = L.s.w; g.K = L.s.c_out;
     g.n = n; g.k = L.s.kh; g.alpha = n + L.s.kh - 1;
     g.th = (L.Ho + n - 1) / n; g.tw = (L.Wo + n - 1) / n;
-    return wino_full_covers(g);
+    return variant == MNN_WINO_FUSED_ALL ? wino_full_covers(g) : wino_cols_covers(g);
 }
 
 void push_wino_variants(std::vector<mnn_scheme>* out, const Layer& L, int n, int k, int prec)
 {
     for (int v = 0; v < MNN_WINO_VARIANTS; ++v)
-        if (wino_variant_available(n, k, v) && (v != MNN_WINO_FUSED_ALL || one_kernel_covers(L, n))) out->push_back(make_scheme(MNN_SCHEME_WINOGRAD, n, prec, v));
+        if (wino_variant_available(n, k, v) && wino_variant_covers(L, n, v)) out->push_back(make_scheme(MNN_SCHEME_WINOGRAD, n, prec, v));
 }
 
 // Recursion rule of Section 3.3.2 for [n,k] x [k,m]: go one level down while the multiplications saved exceed

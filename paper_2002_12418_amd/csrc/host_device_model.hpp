@@ -34,6 +34,13 @@ std::vector<KernelWork> scheme_kernels(const Layer& L, const mnn_scheme& s)
             v.push_back(KernelWork{std::ceil(wgs / cus) * cus * each, in_b + 6.0 * a2 * K * C + out_b});
             return v;
         }
+        if (s.variant == MNN_WINO_BY_AXIS) {
+            const double rows = N * L.s.h * std::ceil(Wo / nw);
+            v.push_back(KernelWork{2.0 * aw * aw * C * rows, in_b + 4.0 * aw * C * rows});
+            v.push_back(KernelWork{2.0 * a2 * K * C * P, 4.0 * aw * C * rows + 6.0 * a2 * K * C + 4.0 * aw * nh * K * P});
+            v.push_back(KernelWork{2.0 * nh * aw * nw * K * P, 4.0 * aw * nh * K * P + out_b});
+            return v;
+        }
         v.push_back(KernelWork{2.0 * (ah * ah * aw + ah * aw * aw) * C * P, in_b + 4.0 * a2 * C * P});
         if (s.variant == MNN_WINO_UNFUSED) {
             v.push_back(KernelWork{2.0 * a2 * K * C * P, 4.0 * a2 * (K * C + C * P + K * P)});

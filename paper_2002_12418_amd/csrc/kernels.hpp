@@ -90,6 +90,19 @@ hipError_t launch_filter_full(const WinoGeom& g, const float* G /*host*/, const 
 hipError_t launch_wino_full(const WinoGeom& g, const float* BT /*host*/, const float* AT /*host*/, const float* x, const void* U,
                             const float* bias, float* y, hipStream_t s);
 
+// One axis at a time (alpha 7 to 10, x and its row transform below 2 GiB): T[b] = x B by rows, then for each column b of the positions the
+// transform along the image height, the channel sums and A^T along the height in one kernel (S), then A^T along the rows.  U: bf16 parts in
+// matrix-operand order.  T, U and S have the sizes below.
+bool wino_cols_available(int n, int k);
+bool wino_cols_covers(const WinoGeom& g);           // reads N, C, H, W, K, n, k, alpha, th and tw
+size_t wino_cols_weight_bytes(const WinoGeom& g);
+size_t wino_cols_input_bytes(const WinoGeom& g);
+size_t wino_cols_sum_bytes(const WinoGeom& g);
+hipError_t launch_cols_filter(const WinoGeom& g, const float* G /*host*/, const float* w, void* U, hipStream_t s);
+hipError_t launch_cols_rows_in(const WinoGeom& g, const float* BT /*host*/, const float* x, float* T, hipStream_t s);
+hipError_t launch_cols(const WinoGeom& g, const float* BT /*host*/, const float* AT /*host*/, const float* T, const void* U, float* S, hipStream_t s);
+hipError_t launch_cols_rows_out(const WinoGeom& g, const float* AT /*host*/, const float* S, const float* bias, float* y, hipStream_t s);
+
 // Batched GEMM  D_b[m][col] = sum_r At_b[r][m] * B_b[r][col] (+ bias[m]).
 //   At: [batch][R][lda]  (A stored transposed, m contiguous; lda % 4 == 0, 16-byte aligned)
 //   B : element (r, col) at  B + b*strideB_batch + (col / L)*strideB_img + r*strideB_row + (col % L)
