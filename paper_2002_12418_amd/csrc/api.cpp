@@ -129,8 +129,9 @@ struct Scratch {
 };
 
 // Times one candidate: `warmup` untimed and `iters` timed passes of the
-// per-inference stages, bracketed by HIP events on `s`.
-int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, const Scratch& sc, hipStream_t s)
+// per-inference stages, bracketed by HIP events on `s`.  A candidate whose last warm-up pass takes 1.3 times `best_ms` (< 0: none yet) or more is not
+// going to win and keeps that time: passes of one candidate differ by a few per cent.
+int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, const Scratch& sc, float best_ms, hipStream_t s)
 {
     Impl impl;
     int rc = impl.prepare(L, *cand, o);
@@ -144,8 +145,6 @@ int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, 
         }
         return MNN_OK;
     };
-    for (int i = 0; i < o.plan_warmup; ++i)
-        if ((rc = pass())) return rc;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e;
     if ((e = hipEventCreate(&e0)) != hipSuccess) return fail_hip(e, "hipEventCreate");
@@ -153,17 +152,27 @@ int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, 
     float ms = -1.f;
     rc = MNN_OK;
     do {
-        if ((e = hipEventRecord(e0, s)) != hipSuccess) { rc = fail_hip(e, "hipEventRecord"); break; }
-        for (int i = 0; i < o.plan_iters && !rc; ++i) rc = pass();
-        if (rc) break;
-        if ((e = hipEventRecord(e1, s)) != hipSuccess) { rc = fail_hip(e, "hipEventRecord"); break; }
-        if ((e = hipEventSynchronize(e1)) != hipSuccess) { rc = fail_hip(e, "hipEventSynchronize"); break; }
-        if ((e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) { rc = fail_hip(e, "hipEventElapsedTime"); break; }
+        auto timed = [&](int passes) -> int {
+            if ((e = hipEventRecord(e0, s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
+            for (int i = 0; i < passes; ++i) {
+                const int r = pass();
+                if (r) return r;
+            }
+            if ((e = hipEventRecord(e1, s)) != hipSuccess) return fail_hip(e, "hipEventRecord");
+            if ((e = hipEventSynchronize(e1)) != hipSuccess) return fail_hip(e, "hipEventSynchronize");
+            if ((e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) return fail_hip(e, "hipEventElapsedTime");
+            ms /= (float)passes;
+            return MNN_OK;
+        };
+        for (int i = 0; i + 1 < o.plan_warmup && !rc; ++i) rc = pass();
+        if (!rc && o.plan_warmup > 0) rc = timed(1);
+        if (rc || (o.plan_warmup > 1 && best_ms >= 0.f && ms >= 1.3f * best_ms)) break;
+        rc = timed(o.plan_iters);
     } while (false);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    cand->est_ms = ms / (float)o.plan_iters;
+    cand->est_ms = ms;
     return MNN_OK;
 }
 
@@ -249,13 +258,19 @@ int plan_impl(const mnn_conv_shape* shape, const mnn_conv_geom* geom, const mnn_
                 }
                 double best_pred = -1.0;
                 int last_skip = MNN_E_OOM;
-                for (const auto& c : plan->cands) {
-                    const double pm = predict_ms(L, c);
+                float best_ms = -1.f;
+                std::vector<std::pair<double, size_t>> order;                // the most promising first
+                for (size_t i = 0; i < plan->cands.size(); ++i) {
+                    const double pm = predict_ms(L, plan->cands[i]);
                     if (best_pred < 0.0 || pm < best_pred) best_pred = pm;
+                    order.emplace_back(pm, i);
                 }
-                for (auto& c : plan->cands) {
-                    if (o.prune_ratio > 1.f && predict_ms(L, c) > (double)o.prune_ratio * best_pred) { c.est_ms = -1.f; continue; }
-                    rc = time_candidate(L, o, &c, sc, s);
+                std::sort(order.begin(), order.end());
+                for (const auto& turn : order) {
+                    mnn_scheme& c = plan->cands[turn.second];
+                    if (o.prune_ratio > 1.f && turn.first > (double)o.prune_ratio * best_pred) { c.est_ms = -1.f; continue; }
+                    rc = time_candidate(L, o, &c, sc, best_ms, s);
+                    if (!rc && (best_ms < 0.f || c.est_ms < best_ms)) best_ms = c.est_ms;
                     // a scheme that does not fit in memory or that the kernels do not cover for this shape is not a
                     // candidate; the cheapest of those that apply is selected (Section 3.2 (1))
                     if (rc == MNN_E_OOM || rc == MNN_E_UNSUPPORTED) { c.est_ms = -1.f; (void)hipGetLastError(); last_skip = rc; continue; }
