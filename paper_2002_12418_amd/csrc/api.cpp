@@ -130,7 +130,7 @@ struct Scratch {
 
 // Times one candidate: `warmup` untimed and `iters` timed passes of the
 // per-inference stages, bracketed by HIP events on `s`.  A candidate whose last warm-up pass takes 1.3 times `best_ms` (< 0: none yet) or more is not
-// going to win and keeps that time: passes of one candidate differ by a few per cent.
+// going to win and keeps that time: passes of one candidate differ by a few per cent.  (Below 0.05 ms the wait for that pass costs what it saves.)
 int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, const Scratch& sc, float best_ms, hipStream_t s)
 {
     Impl impl;
@@ -164,9 +164,10 @@ int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, 
             ms /= (float)passes;
             return MNN_OK;
         };
-        for (int i = 0; i + 1 < o.plan_warmup && !rc; ++i) rc = pass();
-        if (!rc && o.plan_warmup > 0) rc = timed(1);
-        if (rc || (o.plan_warmup > 1 && best_ms >= 0.f && ms >= 1.3f * best_ms)) break;
+        const bool look = o.plan_warmup > 1 && best_ms >= 0.05f;
+        for (int i = 0; i < o.plan_warmup - (look ? 1 : 0) && !rc; ++i) rc = pass();
+        if (!rc && look) rc = timed(1);
+        if (rc || (look && ms >= 1.3f * best_ms)) break;
         rc = timed(o.plan_iters);
     } while (false);
     (void)hipEventDestroy(e0);
