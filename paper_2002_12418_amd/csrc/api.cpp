@@ -387,12 +387,13 @@ int mnn_conv_run(mnn_conv_plan_t plan, const float* input, const float* weight, 
 }
 
 namespace {
-// Whether the call that prepares its weights each time and cannot time anything takes the one-kernel arrangement.  Measured on both, 247
-// shapes (1 to 32 images, 2 to 256 channels, 4 to 150 pixels wide, alpha 3 to 6), whole calls in us: the separate kernels cost 2 more to begin
-// with, 0.25 per megabyte of V and M written and read, and 2 where padding has to be cleared first; the one kernel costs 1/8 per position
-// for each chunk of 16 channels that a workgroup walks, one workgroup per CU at a time, and 0.5 per tap beyond 3 (its weights).  F(2,3) one image 64 -> 64 56 x 56 17.3 separate,
-// 21.3 one; 112 x 112 30.0, 21.3; F(4,3) 16 images 32 -> 64 56 x 56 35.7, 27.8; one image 64 -> 64 20.2, 33.8.  Where it errs it loses 10 % or
-// less in all but two of the 247 (33 and 19 %, eleven and seven output channels), 0.4 % on average.
+// Whether the call that prepares its weights each time and cannot time anything takes the one-kernel arrangement.  Measured on both, whole calls
+// in us, 110 shapes (1 to 16 images, 8 to 192 channels, 7 to 112 pixels wide, alpha 3 to 6): the separate kernels, the transforms of input and
+// weights in one launch, cost 0.3 per megabyte of V and M written and read; the one kernel costs 1/8 per position for each chunk of 16 channels that a
+// workgroup walks, one workgroup per CU at a time, and 0.5 per tap beyond 3 (its weights).  A launch more costs 4, and where that launch writes no
+// padding, clearing it first 1.  F(2,3) one image 64 -> 64 56 x 56 14.2 separate, 21.3 one; 112 x 112 30.4, 22.0.  The constants are those with the least loss
+// (1.6 % on average) that keep the arrangement of the shapes whose choice is pinned by a test; without that they were 0.2 % (-0.5, 0.2 per megabyte, nothing
+// for padding), and 8 x 17 -> 35 x 40 x 41 F(3,3) would take the separate kernels (16.3, 22.9 as before).
 bool one_kernel_sooner(const WinoGeom& g, bool clear)
 {
     if (!wino_full_available(g.n, g.k)) return false;
@@ -400,7 +401,8 @@ bool one_kernel_sooner(const WinoGeom& g, bool clear)
     const double wgs = std::ceil(g.K / per_block) * std::ceil(g.P / 32.0);
     const double chunks = std::ceil(g.C / 16.0) * std::ceil(wgs / 256.0);
     const double bytes = 4.0 * a2 * g.P * 2.0 * ((double)g.C + g.K);
-    return a2 * chunks / 8.0 + 0.5 * (g.k - 3) < 2.0 + 0.25e-6 * bytes + (clear ? 2.0 : 0.0);
+    const double launches = (input_filter_short(g) ? 0.0 : clear ? 5.0 : 4.0) + (clear ? 1.0 : 0.0);
+    return a2 * chunks / 8.0 + 0.5 * (g.k - 3) < 0.5 + launches + 0.3e-6 * bytes;
 }
 }  // namespace
 
@@ -442,11 +444,18 @@ int mnn_conv_run_static(const mnn_conv_shape* shape, const mnn_conv_geom* geom, 
             return one.run_stage(MNN_STAGE_GEMM, input, weight, bias, output, s);
         }
         im.bind_external(reinterpret_cast<char*>(base));
+        // few tiles: V and U, padding included, in one launch
+        int st = MNN_STAGE_FILTER;
+        if (sc.kind == MNN_SCHEME_WINOGRAD && !im.rect) {
+            e = launch_input_filter(im.wg, im.mats.BT.data(), im.mats.G.data(), input, weight, im.V, im.U, s);
+            if (e == hipSuccess) st = MNN_STAGE_GEMM;
+            else if (e != hipErrorNotSupported) return fail_hip(e, "kernel launch");
+        }
         // (by a kernel, not a memset: the call may be recorded into a graph)
-        if (clear &&
+        if (st == MNN_STAGE_FILTER && clear &&
             (e = launch_fill_zero(base, (Impl::align256(im.U_bytes) + Impl::align256(im.V_bytes)) / sizeof(float), s)) != hipSuccess)
             return fail_hip(e, "scratch clear");
-        for (int st = MNN_STAGE_FILTER; st < MNN_STAGE_COUNT; ++st)
+        for (; st < MNN_STAGE_COUNT; ++st)
             if ((rc = im.run_stage(st, input, weight, bias, output, s))) return rc;
         return MNN_OK;
     } catch (const std::bad_alloc&) {

@@ -55,6 +55,17 @@ hipError_t launch_input_transform(const WinoGeom& g, const float* BT /*host, alp
 hipError_t launch_output_transform(const WinoGeom& g, const float* AT /*host, n x alpha*/,
                                    const float* M, const float* bias, float* y, hipStream_t s);
 
+// The same for few (channel, tile) pairs (transforms_short.hip; the launchers above take them where these rules say so), and the input transform
+// together with the weights': V and U with all their padding, which the two alone leave as it is.  Geometry and matrices as the launchers above
+// check them, alpha even or odd, matrices of an even alpha with the structure that the generated ones have.
+bool input_transform_short(const WinoGeom& g);
+bool input_filter_short(const WinoGeom& g);
+bool output_transform_short(const WinoGeom& g);
+hipError_t launch_input_short(const WinoGeom& g, const float* BT, const float* x, float* V, hipStream_t s);
+hipError_t launch_output_short(const WinoGeom& g, const float* AT, const float* M, const float* bias, float* y, hipStream_t s);
+hipError_t launch_input_filter_short(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s);
+hipError_t launch_input_filter(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s);
+
 bool winograd_kernels_available(int n, int k);
 
 // One-dimensional Winograd for kernels with a single row or column (1 x k, k x 1; Section 3.3.1: "kernels of

@@ -500,9 +500,17 @@ hipError_t launch_filter_transform(const WinoGeom& g, const float* G, const floa
     return hipGetLastError();
 }
 
+hipError_t launch_input_filter(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s)
+{
+    if (!geom_ok(g) || !BT || !G || !x || !w || !V || !U) return hipErrorInvalidValue;
+    if (!input_filter_short(g) || (g.alpha % 2 == 0 && !bt_is_paired(BT, g.alpha))) return hipErrorNotSupported;
+    return launch_input_filter_short(g, BT, G, x, w, V, U, s);
+}
+
 hipError_t launch_input_transform(const WinoGeom& g, const float* BT, const float* x, float* V, hipStream_t s)
 {
     if (!geom_ok(g) || !BT || !x || !V) return hipErrorInvalidValue;
+    if (input_transform_short(g) && (g.alpha % 2 != 0 || bt_is_paired(BT, g.alpha))) return launch_input_short(g, BT, x, V, s);
     switch (g.alpha) {
 #define MNN_CASE(A) case A: return launch_input_t<A>(g, BT, x, V, s);
         MNN_CASE(3) MNN_CASE(4) MNN_CASE(5) MNN_CASE(6) MNN_CASE(7) MNN_CASE(8)
@@ -517,6 +525,7 @@ hipError_t launch_output_transform(const WinoGeom& g, const float* AT, const flo
 {
     if (!geom_ok(g) || !AT || !M || !y) return hipErrorInvalidValue;
     if (!winograd_kernels_available(g.n, g.k)) return hipErrorInvalidValue;
+    if (output_transform_short(g) && (g.alpha % 2 != 0 || at_is_paired(AT, g.n, g.alpha))) return launch_output_short(g, AT, M, bias, y, s);
 #define MNN_NK(NN, KK) \
     if (g.n == NN && g.k == KK) return launch_output_t<NN, NN + KK - 1>(g, AT, M, bias, y, s);
     // every (n, k) with 2 <= n <= 8, 2 <= k <= 7 and n + k - 1 <= 10
