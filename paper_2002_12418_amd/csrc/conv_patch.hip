@@ -11,10 +11,10 @@
 // does not overlap with them, because the 448 workgroups are one round in step: launch and first patch 7 us, LDS reads and taps 3, the later
 // patches 3, the stores 3 (measured by leaving each out).  A wavefront owns 32 output channels and all columns of the rectangle: 64 x 32 and 64 x 64
 // blocks read more weights per product than the L1 delivers (64 bytes per cycle and CU; 35 and 41 us).
-// Measured against the best of the other configurations, us: that layer 41.5 -> 29.4; stride 2 128 -> 256 on 32 x 28 x 28 41.6 -> 35; stride 1 64 -> 64 on
-// 16 x 56 x 56 39.4 -> 29, 2 x 2 24.4 -> 20.  Short grids stay with gemm_short.hip (5 x 5 128 -> 128 on 8 x 28 x 28: 43.9 there, 45.1 here; stride 2
-// 256 -> 512 on 32 x 14 x 14: 41, 50): the planner times both.  Relative error of the first layer 1.4e-7 -> 1.3e-7 (one sum for all six products
-// would give 3.6e-7).
+// Measured against the best of the other configurations, us: that layer 41.5 -> 29.4; stride 2 128 -> 256 on 32 x 28 x 28 41.6 -> 30; stride 1 64 -> 64 on
+// 16 x 56 x 56 39.4 -> 29, 2 x 2 24.4 -> 20.  Short grids stay with gemm_short.hip (3 x 3 128 -> 128 on 4 x 28 x 28: 13.8 there, 19.3 here): the
+// planner times both.  Relative error of the first layer 1.4e-7 -> 1.0e-7, 5 x 5 128 -> 128 on 8 x 28 x 28
+// 3.0e-7 -> 2.2e-7 (one sum for all six products would give 3.6e-7 and 8.5e-7).
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "kernels.hpp"
@@ -63,14 +63,18 @@ __global__ __launch_bounds__(256) void patch_weights_kernel(const float* __restr
     }
 }
 
-// LDS: nbuf patches [part][8-channel group][slot][8 bf16]
-template <int BM, int BN, int WM, int WN, int ITEMS>
-__global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p, PatchArgs g)
+// LDS: nbuf patches [part][8-channel group][slot][8 bf16].  WM x WN wavefronts multiply.  NS = 0: they stage, too.  NS > 0: that many more stage.  Loads
+// of one wavefront return in order, and weights that follow pixels wait for those, a trip to memory in every chunk: it pays where chunks
+// are many and workgroups few (stride 2 128 -> 256 on 32 x 28 x 28 35 -> 30 us, 256 -> 512 on 32 x 14 x 14 50 -> 40), not where more workgroups
+// per CU hide it (64 -> 128 on 32 x 56 x 56 30 -> 32, stride 1 64 -> 64 on 16 x 56 x 56 29 -> 31).
+template <int BM, int BN, int WM, int WN, int ITEMS, int NS>
+__global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patch_kernel(GemmProblem p, PatchArgs g)
 {
-    constexpr int NW = WM * WN, LANES = NW * 64;
+    constexpr int NW = WM * WN;
+    constexpr int SW = NS > 0 ? NS : NW, S0 = NS > 0 ? NW : 0, LANES = SW * 64;          // wavefronts that stage, the first of them
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ int wave_lost[NW];
+    __shared__ int wave_lost[SW];
     unsigned lost = 0;
 
     const int tid = threadIdx.x;
@@ -101,7 +105,7 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
     int bgrp[ITEMS];
 #pragma unroll
     for (int t = 0; t < ITEMS; ++t) {
-        const int id = t * LANES + tid;
+        const int id = t * LANES + tid - S0 * 64;
         const int grp = id >= g.ppr ? 1 : 0, q = id - grp * g.ppr;
         const int r1 = (int)fast_div((unsigned)q, g.by_pw), px = q - r1 * g.pw;
         const int i = (int)fast_div((unsigned)r1, g.by_ph), py = r1 - i * g.ph;
@@ -149,6 +153,30 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
 
+    auto flag_lost = [&]() {                            // read behind a barrier
+        const bool l = parts_lost(lost);
+        if (lane == 0) wave_lost[wave - S0] = l ? 1 : 0;
+    };
+
+    if (NS > 0 && wave >= NW) {
+        // patch ch + 1 is staged while the taps of chunk ch are multiplied, from pixels loaded during the chunk before
+        load_b(0);
+        store_b(0);
+        if (g.nch > 1) load_b(1);
+        barrier();
+#pragma unroll 1
+        for (int ch = 0; ch < g.nch; ++ch) {
+            if (g.nbuf == 1) barrier();                  // the taps of this chunk have been read
+            if (ch + 1 < g.nch) {
+                store_b(g.nbuf == 2 ? (ch + 1) & 1 : 0);
+                load_b(ch + 2 < g.nch ? ch + 2 : ch + 1);
+            }
+            if (ch + 1 == g.nch) flag_lost();
+            barrier();
+        }
+        return;
+    }
+
     // ---- this lane's columns
     struct Col { int y, x, img; bool ok; };
     auto column = [&](int c) -> Col {
@@ -166,22 +194,25 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
         b_slot[j] = (lrow * g.pp + (c.ok ? (c.img * g.ph + c.y * p.cv_sh) * (p.cv_sw * g.pws) + c.x : 0)) * 16;
     }
 
-    // The products of the leading parts have sums of their own: those round once per tap, the small products round where it does not show.
-    floatx16 acc[TM][TN], small[TM][TN];
+    // The products of the leading parts have sums of their own, one for every other tap: those round once per two taps, the small products round where
+    // it does not show.
+    floatx16 acc[TM][TN], odd[TM][TN], small[TM][TN];
     auto clear = [&]() {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = odd[i][j][r] = small[i][j][r] = 0.f;
     };
     clear();
 
-    // Operands of one tap, read while the tap before it is multiplied.  Weights: tap `u` of the whole reduction (chunk by chunk).
+    // Operands: the patch's one tap ahead, the weights' too, or three where a tap has few products (a trip to the L2 is longer) and the registers
+    // hold them.  Weights: tap `u` of the whole reduction (chunk by chunk).
+    constexpr int RING = NS == 0 || TM * TN > 1 ? 2 : 4;
     const int all_taps = g.nch * taps;
     const int mb0 = (m0 + wm * (BM / WM)) / 32;
-    uintx4 av[2][TM][3];
+    uintx4 av[RING][TM][3];
     bf16x8 bv[2][TN][3];
     auto read_a = [&](int u, uintx4 (&a)[TM][3]) __attribute__((always_inline)) {
 #pragma unroll
@@ -197,7 +228,7 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
 #pragma unroll
             for (int q = 0; q < 3; ++q) b[j][q] = *reinterpret_cast<const bf16x8*>(b0 + q * 2 * g.pp * 16 + b_slot[j]);
     };
-    auto multiply = [&](const uintx4 (&a)[TM][3], const bf16x8 (&b)[TN][3]) __attribute__((always_inline)) {
+    auto multiply = [&](const uintx4 (&a)[TM][3], const bf16x8 (&b)[TN][3], floatx16 (&lead)[TM][TN]) __attribute__((always_inline)) {
         constexpr int pa[6] = {0, 1, 1, 0, 2, 0}, pb[6] = {0, 1, 0, 1, 0, 2};
 #pragma unroll
         for (int t = 0; t < 6; ++t)
@@ -205,7 +236,7 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    floatx16& sum = t == 0 ? acc[i][j] : small[i][j];
+                    floatx16& sum = t == 0 ? lead[i][j] : small[i][j];
                     sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][pa[t]]), b[j][pb[t]], sum, 0, 0, 0);
                 }
     };
@@ -217,49 +248,67 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
         return ((ky * p.cv_dh * p.cv_sw + xr) * g.pws + xq) * 16;
     };
 
-    // The patch of the next chunk is loaded while the taps of a chunk are multiplied.
-    load_b(0);
-    read_a(0, av[0]);
-    store_b(0);
-    int u = 0;
+    if (NS == 0) load_b(0);
+#pragma unroll
+    for (int r = 0; r < RING - 1; ++r) read_a(r < all_taps ? r : 0, av[r]);
+    if (NS == 0) store_b(0);
+    int u = RING - 2;                                   // the last tap whose weights were loaded
 #pragma unroll 1
     for (int ch = 0; ch < g.nch; ++ch) {
         const char* patch = smem + (g.nbuf == 2 ? (ch & 1) * PBUF : 0);
-        const bool more = ch + 1 < g.nch;
+        const bool more = NS == 0 && ch + 1 < g.nch;
         barrier();
         if (more) load_b(ch + 1);
         read_b(patch, bv[0]);
-        auto tap = [&](auto even) __attribute__((always_inline)) {
-            constexpr int E = decltype(even)::value;
+        auto tap = [&](auto slot) __attribute__((always_inline)) {
+            constexpr int I = decltype(slot)::value;
             ++u;
-            read_a(u < all_taps ? u : 0, av[1 - E]);
-            read_b(patch + next_tap(), bv[1 - E]);
+            read_a(u < all_taps ? u : 0, av[(I + RING - 1) % RING]);
+            read_b(patch + next_tap(), bv[(I + 1) % 2]);
             __builtin_amdgcn_sched_barrier(0);          // or the reads move down to their use
-            multiply(av[E], bv[E]);
+            multiply(av[I], bv[I % 2], I % 2 == 0 ? acc : odd);
         };
+        // the slots behind an incomplete round start the next chunk
+        auto rotate = [&](auto by) __attribute__((always_inline)) {
+            uintx4 t[RING][TM][3];
+#pragma unroll
+            for (int r = 0; r < RING; ++r)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) t[r][i][q] = av[(r + decltype(by)::value) % RING][i][q];
+#pragma unroll
+            for (int r = 0; r < RING - 1; ++r)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) av[r][i][q] = t[r][i][q];
+        };
+        using I0 = std::integral_constant<int, 0>;
+        using I1 = std::integral_constant<int, 1>;
+        using I2 = std::integral_constant<int, 2>;
+        using I3 = std::integral_constant<int, 3>;
         int t = 0;
 #pragma unroll 1
-        for (; t + 1 < taps; t += 2) {
-            tap(std::integral_constant<int, 0>{});
-            tap(std::integral_constant<int, 1>{});
+        for (; t + RING <= taps; t += RING) {
+            tap(I0{});
+            tap(I1{});
+            if constexpr (RING == 4) { tap(I2{}); tap(I3{}); }
         }
-        if (t < taps) {                                 // an odd number of taps
-            tap(std::integral_constant<int, 0>{});
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int q = 0; q < 3; ++q) av[0][i][q] = av[1][i][q];
+        const int rest = taps - t;
+        if (rest == 1) { tap(I0{}); rotate(I1{}); }
+        if constexpr (RING == 4) {
+            if (rest == 2) { tap(I0{}); tap(I1{}); rotate(I2{}); }
+            if (rest == 3) { tap(I0{}); tap(I1{}); tap(I2{}); rotate(I3{}); }
         }
+        if (NS > 0 && g.nbuf == 1) barrier();
         if (more) {
             if (g.nbuf == 1) barrier();
             store_b(g.nbuf == 2 ? (ch + 1) & 1 : 0);
         }
     }
-    {
-        const bool l = parts_lost(lost);
-        if (lane == 0) wave_lost[wave] = l ? 1 : 0;
-        barrier();
-    }
+    if (NS == 0) flag_lost();
+    barrier();
 
     // A wavefront with sums that are not finite, and every wavefront of a workgroup that staged a value its parts do not hold, repeats its
     // block on the fp32 matrix instructions, inputs straight from memory (as in gemm_split.hip; the weights come out of their stored form with
@@ -271,12 +320,12 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                acc[i][j][r] += small[i][j][r];
+                acc[i][j][r] += odd[i][j][r] + small[i][j][r];
                 check.add(acc[i][j][r]);
             }
     int any_lost = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) any_lost |= wave_lost[w];
+    for (int w = 0; w < SW; ++w) any_lost |= wave_lost[w];
     if (check.failed() || __builtin_amdgcn_readfirstlane(any_lost) != 0) {
         clear();
         Col cs[TN];
@@ -313,8 +362,8 @@ __global__ __launch_bounds__(WM * WN * 64) void conv_patch_kernel(GemmProblem p,
 
     // accumulator layout of v_mfma_f32_32x32x*: lane l holds column l % 32, rows 8 * (r / 4) + 4 * (l / 32) + r % 4
     if (g.vecD) {
-        // four columns are four floats in a row: through a wavefront's own 32 x 32 tile in LDS, 16 bytes per lane and store (gemm_epilogue.hpp)
-        barrier();                                       // the patch is no longer needed
+        // four columns are four floats in a row: through a wavefront's own 32 x 32 tile in LDS, where the patch was, 16 bytes per lane and store
+        // (gemm_epilogue.hpp)
         float* stage = reinterpret_cast<float*>(smem) + wave * kStageFloats;
         const int rrow = lane >> 3, rc4 = (lane & 7) * 4;
         float bias[TM][4];                                 // all at once: behind the bounds check of a row each would be a trip of its own
@@ -411,10 +460,10 @@ bool choose_rectangle(const GemmProblem& p, int bn, PatchArgs* out)
     return found;
 }
 
-template <int BM, int BN, int WM, int WN, int ITEMS>
+template <int BM, int BN, int WM, int WN, int ITEMS, int NS>
 hipError_t launch_patch_cfg(const GemmProblem& p, bool, hipStream_t s)
 {
-    constexpr int LANES = WM * WN * 64;
+    constexpr int LANES = (NS > 0 ? NS : WM * WN) * 64, THREADS = (WM * WN + NS) * 64;
     static_assert(ITEMS * LANES / 2 >= kPatchPixels * BN / 128, "staging items for the largest patch");
     PatchArgs g{};
     unsigned plain = 0;
@@ -424,7 +473,7 @@ hipError_t launch_patch_cfg(const GemmProblem& p, bool, hipStream_t s)
     g.N = p.Ncols / p.L;
     g.Ho = p.L / p.cv_Wo;
     const long long total = (long long)g.tilesM * g.tilesX * g.tilesY * ((g.N + g.ni - 1) / g.ni);
-    if (!grid_fits(total, LANES)) return hipErrorInvalidValue;
+    if (!grid_fits(total, THREADS)) return hipErrorInvalidValue;
     g.total = (int)total;
     g.nch = (p.cv_C + kPatchChannels - 1) / kPatchChannels;
     // a second patch buffer while two workgroups still fit a CU, or if one alone does
@@ -439,14 +488,16 @@ hipError_t launch_patch_cfg(const GemmProblem& p, bool, hipStream_t s)
     g.by_tm = make_fastdiv((unsigned)g.tilesM);
     g.by_tiles_x = make_fastdiv((unsigned)g.tilesX);
     g.by_tiles_y = make_fastdiv((unsigned)g.tilesY);
-    hipLaunchKernelGGL((conv_patch_kernel<BM, BN, WM, WN, ITEMS>), dim3((unsigned)total), dim3(LANES), (size_t)(g.nbuf * one > stage ? g.nbuf * one : stage), s, p, g);
+    hipLaunchKernelGGL((conv_patch_kernel<BM, BN, WM, WN, ITEMS, NS>), dim3((unsigned)total), dim3(THREADS), (size_t)(g.nbuf * one > stage ? g.nbuf * one : stage), s, p, g);
     return hipGetLastError();
 }
 
 const GemmVariant kPatch[] = {
-    {"x6_patch_128x64_w4x1", launch_patch_cfg<128, 64, 4, 1, 3>, 128, 64, 16},
-    {"x6_patch_64x128_w2x2", launch_patch_cfg<64, 128, 2, 2, 6>, 64, 128, 16},
-    {"x6_patch_64x64_w2x2", launch_patch_cfg<64, 64, 2, 2, 3>, 64, 64, 16},
+    {"x6_patch_128x64_w4x1", launch_patch_cfg<128, 64, 4, 1, 3, 0>, 128, 64, 16},
+    {"x6_patch_64x128_w2x2", launch_patch_cfg<64, 128, 2, 2, 6, 0>, 64, 128, 16},
+    {"x6_patch_64x64_w2x2", launch_patch_cfg<64, 64, 2, 2, 3, 0>, 64, 64, 16},
+    {"x6_patch_128x64_w4x1s4", launch_patch_cfg<128, 64, 4, 1, 3, 4>, 128, 64, 16},
+    {"x6_patch_64x64_w2x2s4", launch_patch_cfg<64, 64, 2, 2, 3, 4>, 64, 64, 16},
 };
 
 }  // namespace
