@@ -383,20 +383,32 @@ def cache_load(path: str) -> None:
     _check(lib.mnn_conv_cache_load(os.fsencode(path)))
 
 
-_torch = None            # the module, once a GPU was seen: asking for one costs more than the rest of a small call
+_current_stream = None   # () -> handle of the current stream, once a GPU was seen: asking for one costs more than the rest of a small call
+_float32 = None
+
+
+def _find_current_stream():
+    """Looks the current stream up by the shortest way this torch has; None on a machine without a GPU."""
+    global _current_stream, _float32
+    import torch
+    if not torch.cuda.is_available():
+        return None
+    torch.cuda.init()
+    _float32 = torch.float32
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        _current_stream = lambda: raw(device())          # 0.2 us; through torch.cuda.current_stream 1.4
+    else:
+        cuda = torch.cuda
+        _current_stream = lambda: cuda.current_stream(cuda.current_device()).cuda_stream
+    return _current_stream
 
 
 def _stream_handle(stream) -> int:
-    global _torch
-    if _torch is None:
-        import torch
-        if not torch.cuda.is_available():
-            return 0 if stream is None else int(stream.cuda_stream)          # the library itself reports MNN_E_NO_DEVICE
-        _torch = torch
-    if stream is None:
-        cuda = _torch.cuda
-        stream = cuda.current_stream(cuda.current_device())     # without the index torch looks it up by a much longer way
-    return stream.cuda_stream
+    if stream is not None:
+        return int(stream.cuda_stream)
+    find = _current_stream or _find_current_stream()
+    return find() if find else 0          # 0: the library itself reports MNN_E_NO_DEVICE
 
 
 class ConvPlan:
@@ -414,6 +426,8 @@ class ConvPlan:
         self.info = {f: int(getattr(info, f)) for f, _ in _Info._fields_}
         self.out_shape = (n, c_out, self.info["h_out"], self.info["w_out"])
         self._in_shape, self._w_shape, self._b_shape = (n, c_in, h, w), (c_out, c_in, kh, kw), (c_out,)
+        if _float32 is None:
+            _find_current_stream()   # a plan made with a stream of the caller's has not asked for one
         self._w_seen = None          # (address, torch version counter) of the weight tensor last handed to the library
 
     @classmethod
@@ -444,14 +458,14 @@ class ConvPlan:
         return int(lib.mnn_conv_workspace_bytes(self._h))
 
     def _check_tensors(self, x, w, b, y):
-        import torch
-        f32 = torch.float32
+        f32 = _float32
         # one expression for the case that nothing is wrong: on a small layer these checks cost as much as the launch
         if (x.shape == self._in_shape and w.shape == self._w_shape and y.shape == self.out_shape
                 and x.dtype is f32 and w.dtype is f32 and y.dtype is f32 and x.is_cuda and w.is_cuda and y.is_cuda
                 and x.is_contiguous() and w.is_contiguous() and y.is_contiguous()
                 and (b is None or (b.shape == self._b_shape and b.dtype is f32 and b.is_cuda and b.is_contiguous()))):
             return
+        import torch
         for t, shp, name in ((x, self._in_shape, "input"), (w, self._w_shape, "weight"), (y, self.out_shape, "output")):
             if tuple(t.shape) != tuple(shp) or t.dtype != torch.float32 or not t.is_contiguous() or not t.is_cuda:
                 raise ValueError(f"{name}: expected contiguous float32 device tensor of shape {shp}, got {tuple(t.shape)} {t.dtype}")
