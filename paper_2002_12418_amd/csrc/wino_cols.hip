@@ -9,10 +9,10 @@
 // F(4,7) on 16 x 64 x 112 x 112 moves 514 MB this way where separate transforms move 1.39 GB, for more vector instructions: a block of output channels
 // transforms its tiles anew.  So it pays for few outputs per tile and many taps: kernels of 5 taps and more (F(6,3) on 16 x 128 x 64 x 64: 69 us against 72
 // for separate kernels, F(8,3) 83 against 68).
-// Measured against the best of the other arrangements, us: F(4,5) 16 x 128 x 64 x 64 125 -> 100, 8 x 256 x 56 x 56 139 -> 126; F(4,7) 16 x 64 x 112 x 112 222 -> 187;
+// Measured against the best of the other arrangements, us: F(4,5) 16 x 128 x 64 x 64 125 -> 100, 8 x 256 x 56 x 56 139 -> 126; F(4,7) 16 x 64 x 112 x 112 222 -> 180;
 // F(2,7) there 458 -> 357, 96 -> 192 channels on 8 x 80 x 80 367 -> 325.  Behind them where tiles are few (F(4,7) 4 x 128 x 28 x 28 39, 32) and where
 // channels are (F(4,5) 16 x 32 x 112 x 112 95, 60): the planner times all.
-// Of the 187: rows in 29 and rows out 35 at 5 to 6 TB/s, columns 120, where the matrix cores are busy 23 % and the vector units 50 % of the cycles
+// Of the 180: rows in 28 and rows out 36 at 5 to 6 TB/s, columns 115, where the matrix cores are busy 23 % and the vector units 50 % of the cycles
 // (F(4,5): 61 of 100, matrix cores 55 %).  Tried for that kernel: four wavefronts that stage and four that multiply, walking over blocks (F(4,7) 115,
 // F(4,5) 85: one wavefront of a SIMD issues a vector instruction every 8 cycles where each needs the one before); the same walk with all
 // eight doing both (registers spill); matrix and vector instructions interleaved by the compiler (F(4,5) 71); one buffer and two workgroups of
@@ -29,6 +29,7 @@ namespace mnnconv {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int kColsChunk = 16;               // channels per chunk
 constexpr int kColsTiles = 64;               // tiles per workgroup
 
@@ -434,7 +435,9 @@ struct RowsOutArgs {
 };
 
 // One workgroup per (32 channels, row i of the tiles, 32 tiles); a lane holds four channels of one tile, as the accumulators left them.
-template <int NT, int A>
+// STREAM: S is too large to stay in the last-level cache, and this, its last read, goes past the caches instead of evicting what comes next
+// (F(4,7) 16 x 64 x 112 x 112, 128 MB: whole call 188 -> 180 us; 67 MB: no difference).
+template <int NT, int A, bool STREAM>
 __global__ __launch_bounds__(256) void cols_rows_out_kernel(RowsOutArgs g, MatArg<NT, A> at, const float* __restrict__ S,
                                                             const float* __restrict__ bias, float* __restrict__ y)
 {
@@ -447,8 +450,10 @@ __global__ __launch_bounds__(256) void cols_rows_out_kernel(RowsOutArgs g, MatAr
     float in[4][A];
 #pragma unroll
     for (int b = 0; b < A; ++b) {
-        const float4 v = *reinterpret_cast<const float4*>(src + b * step);
-        in[0][b] = v.x; in[1][b] = v.y; in[2][b] = v.z; in[3][b] = v.w;
+        const floatx4* q = reinterpret_cast<const floatx4*>(src + b * step);
+        const floatx4 v = STREAM ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) in[e][b] = v[e];
     }
     const int p = pp * 32 + (lane & 31), k0 = mb * 32 + 8 * r4 + 4 * (lane >> 5);
     const int r1 = (int)fast_div((unsigned)p, g.by_tw), tx = p - r1 * g.tw;
@@ -599,8 +604,11 @@ hipError_t launch_rows_out_t(const WinoGeom& g, const float* AT, const float* S,
             : (NT % 2 == 0 && g.Wo % 2 == 0 && (reinterpret_cast<uintptr_t>(y) & 7u) == 0) ? 1 : 0;
     a.by_pairs = make_fastdiv((unsigned)a.pairs); a.by_n = make_fastdiv((unsigned)NT);
     a.by_tw = make_fastdiv((unsigned)g.tw); a.by_th = make_fastdiv((unsigned)g.th);
-    hipLaunchKernelGGL((cols_rows_out_kernel<NT, A>), dim3((unsigned)((long long)a.mblocks * a.pairs * NT)), dim3(256), 0, s, a, at_arg<NT, A>(AT),
-                       S, bias, y);
+    const dim3 grid((unsigned)((long long)a.mblocks * a.pairs * NT));
+    if (wino_cols_sum_bytes(g) > 100000000)
+        hipLaunchKernelGGL((cols_rows_out_kernel<NT, A, true>), grid, dim3(256), 0, s, a, at_arg<NT, A>(AT), S, bias, y);
+    else
+        hipLaunchKernelGGL((cols_rows_out_kernel<NT, A, false>), grid, dim3(256), 0, s, a, at_arg<NT, A>(AT), S, bias, y);
     return hipGetLastError();
 }
 
