@@ -32,7 +32,7 @@ STAGE_NAMES = ["filter_transform", "input_transform", "gemm", "output_transform"
 def matrix_peak(desc):
     """(peak of the instructions that kernel multiplies with, in TFLOP/s of its own products; its multiple of the fp32
     instructions' rate).  The x6 configurations and the one-kernel Winograd arrangement take six bf16 products per fp32-grade one."""
-    if "gemm=x6_" in desc or desc.endswith("one kernel"):
+    if "gemm=x6_" in desc or desc.endswith(("one kernel", "by axes")):
         return PEAK_BF16_MFMA_TFLOPS / 6, 16.0 / 6
     return PEAK_FP32_MFMA_TFLOPS, 1.0
 
@@ -51,6 +51,11 @@ def stage_work(layer, scheme, info, mnn):
         out["output_transform"] = (2.0 * (n * a * aw + n * nw * aw) * K * P, 4.0 * (a2 * K * P + N * K * Ho * Wo))
         if scheme.variant == mnn.WINO_FUSED_ALL:           # V and M never leave the CU; the weights are three bf16 parts
             out["gemm"] = (2.0 * a2 * K * C * P, 4.0 * (N * C * layer.h * layer.w + N * K * Ho * Wo) + 6.0 * a2 * K * C)
+        if scheme.variant == mnn.WINO_BY_AXIS:             # transforms along the width, and what couples to them inside the product
+            rows = N * layer.h * -(-Wo // nw)
+            out["input_transform"] = (2.0 * aw * aw * C * rows, 4.0 * (N * C * layer.h * layer.w + aw * C * rows))
+            out["gemm"] = (2.0 * a2 * K * C * P, 4.0 * aw * (C * rows + n * K * P) + 6.0 * a2 * K * C)
+            out["output_transform"] = (2.0 * n * aw * nw * K * P, 4.0 * (aw * n * K * P + N * K * Ho * Wo))
     elif scheme.kind == mnn.SCHEME_GEMM1X1:
         HW = layer.h * layer.w
         out["gemm"] = (2.0 * N * K * C * HW, 4.0 * (N * C * HW + N * K * HW + K * C))
