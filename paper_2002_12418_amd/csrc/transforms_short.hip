@@ -255,8 +255,12 @@ bool input_transform_short(const WinoGeom& g)
 }
 
 // Many weights: a lane per row of G w G^T reads them alpha times over (allocation-free F(4,3) 32 x 512 -> 512 x 7 x 7 54 us in two launches, 73 in one;
-// 256 -> 256 x 14 x 14 49 both).
-bool input_filter_short(const WinoGeom& g) { return input_transform_short(g) && (long long)g.K * g.C <= 65536; }
+// 256 -> 256 x 14 x 14 49 both), and each is a run of k^2 values of its own, so that the line lies sooner for larger kernels (one image of 14 x 14, F(4,5)
+// 160 -> 160 channels 31 and 28, 192 33.7 and 33.8, 224 37 and 41, 254 46 and 63; F(2,6) 128 26.2 and 24.5, 160 28.4 and 31.6).
+bool input_filter_short(const WinoGeom& g)
+{
+    return input_transform_short(g) && (long long)g.K * g.C <= 65536 && (long long)g.K * g.C * g.k * g.k <= 800000;
+}
 
 bool output_transform_short(const WinoGeom& g)
 {
