@@ -133,3 +133,33 @@ def test_gemm_rejects_bad_descriptors():
         m.gemm_f32(a, a, a, M=8, ncols=8, R=8, lda=8, variant=999)
     with pytest.raises(m.MnnError):
         m.gemm_f32(a, a, a, M=0, ncols=8, R=8, lda=8)
+
+
+@pytest.mark.parametrize("M", [1, 8, 9, 25, 31, 33, 72])
+@pytest.mark.parametrize("hw", [7, 49])
+def test_rows_stored_element_by_element(M, hw):
+    """Columns that are no multiple of four, row counts around the groups of eight rows that a tile stores; nothing past the result is written.
+    Bound: R roundings of the sum, the largest left-out products 2^-24 each, below 2^-19 of sum |a||b| for R = 19."""
+    m = mnn()
+    N, R = 3, 19
+    rng = np.random.default_rng(100 * M + hw)
+    x = rng.uniform(-1, 1, (N, R, hw)).astype(np.float32)
+    w = rng.normal(0, 1, (M, R)).astype(np.float32)
+    b = rng.uniform(-1, 1, (M,)).astype(np.float32)
+    ld = (M + 3) // 4 * 4
+    Wt = np.zeros((R, ld), np.float32)
+    Wt[:, :M] = w.T
+    xd, Wtd, bd = (torch.from_numpy(a).cuda() for a in (x, Wt, b))
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    for bias in (None, bd):
+        add = 0.0 if bias is None else b.astype(np.float64)[None, :, None]
+        ref = np.matmul(w64, x64) + add
+        bound = 2.0 ** -19 * (np.matmul(np.abs(w64), np.abs(x64)) + np.abs(add))
+        for v, name in enumerate(m.gemm_variants()):
+            y = torch.full((N * M * hw + 64,), float("nan"), device="cuda")
+            m.gemm_f32(Wtd, xd, y, bias, M=M, ncols=N * hw, R=R, batch=1, lda=ld, L=hw, variant=v,
+                       strideB_img=R * hw, strideB_row=hw, strideD_img=M * hw, strideD_row=hw)
+            torch.cuda.synchronize()
+            got = y.cpu().numpy().astype(np.float64)
+            assert np.isnan(got[N * M * hw:]).all(), name
+            assert (np.abs(got[:N * M * hw].reshape(N, M, hw) - ref) <= bound).all(), name
