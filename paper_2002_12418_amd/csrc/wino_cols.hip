@@ -22,6 +22,7 @@
 #include "kernels.hpp"
 #include "xcd_remap.hpp"
 #include "wino_paired.hpp"
+#include "row_shares.hpp"
 #include "bf16_parts.hpp"
 #include "fast_div.hpp"
 
@@ -242,9 +243,9 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[q][j][r] = 0.f;
     };
-    // rows a0 .. a0 + mine - 1: the first A % Q shares have one more
-    constexpr int LESS = A / Q, MORE = A % Q;
-    const int mine = MORE == 0 || grp < MORE ? A0 : LESS, a0 = grp * LESS + (grp < MORE ? grp : MORE);
+    // rows a0 .. a0 + mine - 1
+    constexpr int MORE = A % Q;
+    const int mine = row_share(A, Q, grp).rows, a0 = row_share(A, Q, grp).first;
     const unsigned u0 = (unsigned)(mb * g.nch * A + a0) * 3072u;
     uintx4 u[2][3];
     auto load_u = [&](int ch, int q, uintx4 (&v)[3]) __attribute__((always_inline)) {
@@ -271,11 +272,12 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
                 continue;
             }
             // operands one product ahead: weights a row, V a tile block
-            load_u(final ? next : ch, final ? 0 : MORE != 0 && q + 2 == A0 && q + 1 >= mine ? q : q + 1, u[(q + 1) & 1]);
+            const int ahead = row_of_step(A, Q, grp, q + 1);
+            load_u(final ? next : ch, final ? 0 : ahead, u[(q + 1) & 1]);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 if (j == 0) load_v(q, 1);
-                else if (!final) load_v(q + 1, 0);                  // past a smaller share: read, in bounds, and not used
+                else if (!final) load_v(ahead, 0);
                 __builtin_amdgcn_sched_barrier(0);                  // or the reads move down to their use
                 constexpr int pa[6] = {1, 2, 0, 1, 0, 0}, pv[6] = {1, 0, 2, 0, 1, 0};     // small products first
 #pragma unroll
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
 #pragma unroll
                     for (int h = 1; h < Q; ++h) {
                         constexpr int kLast = A - 1;
-                        const int a = q + h * LESS + (h < MORE ? h : MORE);
+                        const int a = q + row_share(A, Q, h).first;
                         if (grp == h) vv = v[a < A ? a : kLast];
                     }
                     if (j == 0) acc[q][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, vv, acc[q][0], 0, 0, 0);
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
     const int pairs = 2 * g.pblocks;
     auto fold = [&](auto h) __attribute__((always_inline)) {
         constexpr int H = decltype(h)::value;
-        constexpr int FIRST = H * LESS + (H < MORE ? H : MORE), COUNT = H < MORE ? LESS + 1 : LESS;
+        constexpr int FIRST = row_share(A, Q, H).first, COUNT = row_share(A, Q, H).rows;
         constexpr int RI = Q / 2, MERGE = LDS / XSLOT;                  // rows of S per exchange slot, slots per pair of barriers
         auto sum = [&](int i, int j, int r) __attribute__((always_inline)) {
             float s = 0.f;
