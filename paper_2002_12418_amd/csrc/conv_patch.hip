@@ -510,6 +510,9 @@ size_t conv_patch_weight_bytes(int K, int C, int taps)
     return (size_t)((K + 127) / 128 * 4) * ((C + kPatchChannels - 1) / kPatchChannels) * taps * 3072;      // whole blocks of 128 channels
 }
 
+// Fewer channels would leave a chunk of 16 more than half empty; one tap reads each value of a patch once.
+bool conv_patch_offered(const GemmProblem& p) { return p.gather && p.prec == 0 && p.cv_C >= 8 && p.cv_kh * p.cv_kw > 1; }
+
 bool conv_patch_covers(const GemmProblem& p)
 {
     if (!p.gather || p.batch != 1 || p.prec != 0 || p.splitk > 1 || p.M <= 0 || p.L <= 0 || p.cv_Wo <= 0 || p.Ncols % p.L != 0) return false;

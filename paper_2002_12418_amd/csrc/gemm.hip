@@ -551,12 +551,12 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 // against 129; 25 of 8 x 1818 x 1896 64 against 71) and 32 x 32 k4 for gathers among them (7 x 7, 4 -> 9 on 8 x 94 x 54 15.0 against 16.5), and 128 x 128 pf2 where groups of eight channels are not full (7 x 7, 4 -> 234 on 16 x 34 x 30 25.8
 // against 27.6).  The others are there for callers that name them and for choices saved
 // earlier; they lose to the x6 tiles wherever they were the best (100 products 256 x 256 x 4096: 446 against 305 us; 36 of
-// 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).  The patch kernels from 8 channels on: their
-// chunks of 16 would be more than half empty.
+// 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).  The patch kernels: where
+// conv_patch_offered says so.
 bool gemm_variant_tuned(const GemmProblem& p, int v)
 {
     if (v < 1 || v >= gemm_variant_count(p.prec)) return false;
-    if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && p.cv_C >= 8 && p.cv_kh * p.cv_kw > 1;
+    if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && conv_patch_offered(p);
     if (p.prec != 0 || v >= kNumVariants) return true;
     static const char* const kept[] = {"64x64x16_w2x2", "64x128x16_w1x4", "128x64x16_w2x2", "64x32x32_w2x1k2_pf2"};
     for (const char* k : kept)

@@ -25,7 +25,7 @@ struct Impl {
     int gemm_variant = 0;      // tile configuration of the GEMM stage (0 = shape heuristic)
     int gemm_splitk = 1;       // workgroups per tile along the reduction
     float* sk_partial = nullptr; size_t sk_partial_bytes = 0;
-    bool patch_room = false;   // sliding window: U has room for the weights in the patch kernels' form
+    bool patch_offered = false;   // sliding window: the patch kernels, whose weights have a form of their own, may be chosen
     // V, M and the split-K partials hold nothing between two runs.  A plan on its own allocates them;
     // a chain of layers binds them to a region of its arena instead (bind_transient).
     bool transient_external = false;
@@ -212,9 +212,9 @@ struct Impl {
             if ((long long)sh.n * L.Ho * L.Wo >= (1ll << 31) || (long long)sh.n * sh.c_in * sh.h * sh.w >= (1ll << 31))
                 return fail(MNN_E_UNSUPPORTED, "tensor too large for the sliding-window kernel");
             U_bytes = (size_t)sh.c_in * sh.kh * sh.kw * ldk * sizeof(float);
-            // room for the form that the patch kernels read, whichever is chosen in the end (not where fixed scratch bounds it)
-            patch_room = !persistent_external && conv_patch_covers(direct_gemm_problem(nullptr, nullptr, nullptr));
-            if (patch_room) U_bytes = std::max(U_bytes, conv_patch_weight_bytes(sh.c_out, sh.c_in, sh.kh * sh.kw));
+            // (not where fixed scratch bounds U; the tuner sizes U anew when it takes one of them)
+            const GemmProblem p = direct_gemm_problem(nullptr, nullptr, nullptr);
+            patch_offered = !persistent_external && conv_patch_offered(p) && conv_patch_covers(p);
             int rcd = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
             if (rcd) return rcd;
             return MNN_OK;
@@ -267,7 +267,8 @@ struct Impl {
     }
 
     // whether the prepared weights have the form that the patch kernels read
-    bool patch_weights() const { return patch_room && gemm_variant_is_patch(scheme.prec, gemm_variant); }
+    bool patch_weights() const { return patch_offered && gemm_variant_is_patch(scheme.prec, gemm_variant); }
+    size_t patch_weight_bytes() const { return conv_patch_weight_bytes(L.s.c_out, L.s.c_in, L.s.kh * L.s.kw); }
 
     GemmProblem direct_gemm_problem(const float* x, const float* b, float* y) const
     {
@@ -279,7 +280,7 @@ struct Impl {
         p.lda = ldk; p.L = HoWo;
         p.strideD_img = (long long)sh.c_out * HoWo; p.strideD_row = HoWo;
         set_gemm_choice(&p);
-        p.a_parts = patch_room ? U : nullptr;
+        p.a_parts = patch_weights() ? U : nullptr;
         p.gather = 1;
         p.cv_C = sh.c_in; p.cv_H = sh.h; p.cv_W = sh.w; p.cv_kh = sh.kh; p.cv_kw = sh.kw;
         p.cv_sh = L.g.stride_h; p.cv_sw = L.g.stride_w; p.cv_ph = L.g.pad_h; p.cv_pw = L.g.pad_w;
@@ -298,6 +299,17 @@ struct Impl {
         if (!gemm_variant_tile(p.prec, gemm_variant, &bm, &bn, &bk)) { gemm_splitk = 1; return MNN_OK; }
         sk_partial_bytes = (size_t)gemm_splitk_workspace(p, gemm_splitk) * sizeof(float);
         return alloc_transient(&sk_partial, sk_partial_bytes, "hipMalloc split-K partials");
+    }
+
+    // the same for the sliding window, where U then takes the size of the form that the chosen kernel reads
+    int adopt_direct(const GemmProblem& p, const GemmChoice& c)
+    {
+        const bool elsewhere = gemm_variant_is_patch(p.prec, c.variant) && !patch_offered;      // a saved choice that does not apply
+        const int rc = adopt(p, elsewhere ? GemmChoice{0, 1} : c);
+        if (rc || !patch_weights()) return rc;
+        (void)hipFree(U);
+        U_bytes = patch_weight_bytes();
+        return alloc_persistent(&U, U_bytes, "hipMalloc Wp");
     }
 
     // Resident wavefronts per CU of the input transform (WinoGeom::itx_waves), remembered per geometry.  What is timed is the
@@ -445,14 +457,15 @@ struct Impl {
             const mnn_conv_shape& sh = L.s;
             const size_t xb = (size_t)sh.n * sh.c_in * sh.h * sh.w * sizeof(float);
             const size_t yb = (size_t)sh.n * sh.c_out * L.Ho * L.Wo * sizeof(float);
-            float *tx = nullptr, *ty = nullptr, *tb = nullptr;
+            float *tx = nullptr, *ty = nullptr, *tb = nullptr, *tp = nullptr;
             hipError_t e;
             int rc = MNN_OK;
+            const bool direct = scheme.kind == MNN_SCHEME_DIRECT;
+            auto take = [&](const GemmProblem& p) { return direct ? adopt_direct(p, c) : adopt(p, c); };
             {
                 // a shape tuned before needs no scratch tensors (the key holds no addresses)
-                const GemmProblem q = scheme.kind == MNN_SCHEME_DIRECT ? direct_gemm_problem(nullptr, &dummy_bias, nullptr)
-                                                                       : pointwise_gemm_problem(nullptr, &dummy_bias, nullptr);
-                if (cached_gemm_choice(q, &c)) return adopt(q, c);
+                const GemmProblem q = direct ? direct_gemm_problem(nullptr, &dummy_bias, nullptr) : pointwise_gemm_problem(nullptr, &dummy_bias, nullptr);
+                if (cached_gemm_choice(q, &c)) return take(q);
             }
             if ((e = hipMalloc((void**)&tx, xb)) != hipSuccess || (e = hipMalloc((void**)&ty, yb)) != hipSuccess ||
                 (e = hipMalloc((void**)&tb, (size_t)sh.c_out * sizeof(float))) != hipSuccess)
@@ -460,12 +473,19 @@ struct Impl {
             if (!rc && ((e = launch_fill_pattern(tx, xb / sizeof(float), 0x57u, -1.f, 1.f, s)) != hipSuccess ||
                         (e = launch_fill_pattern(tb, (size_t)sh.c_out, 0x58u, -0.1f, 0.1f, s)) != hipSuccess))
                 rc = fail_hip(e, "tuning scratch fill");
-            GemmProblem p = scheme.kind == MNN_SCHEME_DIRECT ? direct_gemm_problem(tx, tb, ty) : pointwise_gemm_problem(tx, tb, ty);
+            GemmProblem p = direct ? direct_gemm_problem(tx, tb, ty) : pointwise_gemm_problem(tx, tb, ty);
+            if (!rc && direct && patch_offered) {
+                // the weights once more in the patch kernels' form; without room for them those kernels are not candidates
+                if (hipMalloc((void**)&tp, patch_weight_bytes()) != hipSuccess) { tp = nullptr; (void)hipGetLastError(); }
+                else if ((e = launch_patch_weights(U, tp, sh.c_out, sh.c_in, sh.kh * sh.kw, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
+                p.a_parts = tp;
+            }
             if (!rc) rc = tune_gemm(p, s, &c);
             if (tx) (void)hipFree(tx);
             if (ty) (void)hipFree(ty);
             if (tb) (void)hipFree(tb);
-            return rc ? rc : adopt(p, c);
+            if (tp) (void)hipFree(tp);
+            return rc ? rc : take(p);
         }
         return MNN_OK;
     }

@@ -166,6 +166,7 @@ constexpr int kShort16 = 0, kShort32 = 2, kShort64 = 4;
 int conv_patch_variant_count();
 const GemmVariant& conv_patch_variant(int i);
 bool conv_patch_covers(const GemmProblem& p);       // whether the patch kernels take this product
+bool conv_patch_offered(const GemmProblem& p);      // whether the planner times them
 size_t conv_patch_weight_bytes(int K, int C, int taps);
 hipError_t launch_patch_weights(const float* w, void* Wp, int K, int C, int taps, hipStream_t s);
 bool gemm_variant_is_patch(int prec, int variant);

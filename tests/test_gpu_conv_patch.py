@@ -21,7 +21,7 @@ LAYERS = [
     ConvLayer("row_kernel", 2, 32, 17, 17, 48, 1, 7, 1, (0, 3)),
     ConvLayer("two_taps", 2, 17, 12, 12, 130, 2, 1, 1, 0),
     ConvLayer("mostly_padding", 1, 16, 4, 4, 64, 5, 5, 1, 4),
-    ConvLayer("wide_dilation", 1, 16, 30, 30, 16, 3, 3, 1, 9, 9),            # patches of the 64-column tiles too large: the largest that fit
+    ConvLayer("wide_dilation", 1, 16, 30, 30, 16, 3, 3, 1, 6, 6),            # patches of 64 columns too large: the most columns that fit
 ]
 
 
@@ -129,3 +129,26 @@ def test_first_pass_and_new_weights(mnn, tmp_path):
         assert name in chain.describe(0)
         chain.set_weights(0, w, b)
         assert torch.equal(chain.run(x), first)
+
+
+@pytest.mark.parametrize("layer", [
+    ConvLayer("rgb", 2, 3, 40, 40, 64, 7, 7, 2, 3),                          # too few channels for the patch kernels
+    ConvLayer("one_tap", 2, 16, 20, 20, 16, 1, 1, 2, 0),
+    ConvLayer("wider_dilation", 1, 16, 30, 30, 16, 3, 3, 1, 9, 9),           # no patch fits
+    ConvLayer("either", 2, 16, 20, 20, 16, 3, 3, 1, 1),
+], ids=lambda l: l.name)
+def test_weights_take_the_room_of_their_form(mnn, layer, tmp_path):
+    """A plan owns the prepared weights in the form that its kernel reads, and no more."""
+    x, w, b = (t.cuda() for t in inputs(layer, 3))
+    taps = layer.kh * layer.kw
+    plain = layer.c_in * taps * -(-layer.c_out // 4) * 4 * 4
+    parts = -(-layer.c_out // 128) * 128 * -(-layer.c_in // 16) * 16 * taps * 6
+    names = mnn.gemm_variants()
+    for v in [names.index("64x64x16_w2x2")] + [v for v, _ in patch_variants(mnn)]:
+        patch = names[v].startswith("x6_patch_") and layer.name == "either"
+        with planned(mnn, layer, v, tmp_path / "cache") as plan:
+            assert ("x6_patch_" in plan.describe()) == patch
+            assert plan.workspace_bytes == (parts if patch else plain), names[v]
+            y = plan.run(x, w, b)
+            ref = conv64(layer, x.cpu(), w.cpu(), b.cpu())
+            assert float((y.cpu().double() - ref).abs().max() / ref.abs().max()) < 2e-6, names[v]
