@@ -470,8 +470,10 @@ struct Impl {
             if ((e = hipMalloc((void**)&tx, xb)) != hipSuccess || (e = hipMalloc((void**)&ty, yb)) != hipSuccess ||
                 (e = hipMalloc((void**)&tb, (size_t)sh.c_out * sizeof(float))) != hipSuccess)
                 rc = fail_hip(e, "hipMalloc tuning scratch");
+            // seeded operands for the reason above, the weights among them
             if (!rc && ((e = launch_fill_pattern(tx, xb / sizeof(float), 0x57u, -1.f, 1.f, s)) != hipSuccess ||
-                        (e = launch_fill_pattern(tb, (size_t)sh.c_out, 0x58u, -0.1f, 0.1f, s)) != hipSuccess))
+                        (e = launch_fill_pattern(tb, (size_t)sh.c_out, 0x58u, -0.1f, 0.1f, s)) != hipSuccess ||
+                        (e = launch_fill_pattern(U, U_bytes / sizeof(float), 0x61u, -0.5f, 0.5f, s)) != hipSuccess))
                 rc = fail_hip(e, "tuning scratch fill");
             GemmProblem p = direct ? direct_gemm_problem(tx, tb, ty) : pointwise_gemm_problem(tx, tb, ty);
             if (!rc && direct && patch_offered) {
@@ -481,6 +483,8 @@ struct Impl {
                 p.a_parts = tp;
             }
             if (!rc) rc = tune_gemm(p, s, &c);
+            if (!rc && ((e = hipMemsetAsync(U, 0, U_bytes, s)) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess))
+                rc = fail_hip(e, "tuning operand reset");
             if (tx) (void)hipFree(tx);
             if (ty) (void)hipFree(ty);
             if (tb) (void)hipFree(tb);
