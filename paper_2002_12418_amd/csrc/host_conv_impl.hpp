@@ -321,6 +321,7 @@ struct Impl {
     {
         if (scheme.kind != MNN_SCHEME_WINOGRAD || rect || scheme.variant == MNN_WINO_FUSED_ALL || scheme.variant == MNN_WINO_BY_AXIS)
             return MNN_OK;
+        if (!input_transform_capped(wg, mats.BT.data())) return MNN_OK;
         int dev = 0;
         (void)hipGetDevice(&dev);
         const InputCapKey key(dev, std::vector<int>{wg.N, wg.C, wg.H, wg.W, wg.K, wg.n, wg.k, wg.pad_h, wg.pad_w, wg.blocked, wg.tiled,

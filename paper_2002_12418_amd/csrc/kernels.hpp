@@ -66,6 +66,8 @@ hipError_t launch_output_short(const WinoGeom& g, const float* AT, const float* 
 hipError_t launch_input_filter_short(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s);
 hipError_t launch_input_filter(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s);
 
+bool input_transform_capped(const WinoGeom& g, const float* BT);       // whether the kernel that itx_waves limits is launched
+
 bool winograd_kernels_available(int n, int k);
 
 // One-dimensional Winograd for kernels with a single row or column (1 x k, k x 1; Section 3.3.1: "kernels of

@@ -507,10 +507,15 @@ hipError_t launch_input_filter(const WinoGeom& g, const float* BT, const float* 
     return launch_input_filter_short(g, BT, G, x, w, V, U, s);
 }
 
+bool input_transform_capped(const WinoGeom& g, const float* BT)
+{
+    return !(input_transform_short(g) && (g.alpha % 2 != 0 || bt_is_paired(BT, g.alpha)));
+}
+
 hipError_t launch_input_transform(const WinoGeom& g, const float* BT, const float* x, float* V, hipStream_t s)
 {
     if (!geom_ok(g) || !BT || !x || !V) return hipErrorInvalidValue;
-    if (input_transform_short(g) && (g.alpha % 2 != 0 || bt_is_paired(BT, g.alpha))) return launch_input_short(g, BT, x, V, s);
+    if (!input_transform_capped(g, BT)) return launch_input_short(g, BT, x, V, s);
     switch (g.alpha) {
 #define MNN_CASE(A) case A: return launch_input_t<A>(g, BT, x, V, s);
         MNN_CASE(3) MNN_CASE(4) MNN_CASE(5) MNN_CASE(6) MNN_CASE(7) MNN_CASE(8)

@@ -64,6 +64,23 @@ def test_planned_and_allocation_free(nk):
         assert torch.equal(s1, s2) and error(s1, ref) < bound(n, k)
 
 
+def test_no_cap_on_wavefronts_where_the_short_kernel_runs(tmp_path):
+    """The cap on resident wavefronts is one of the other kernel: on a grid long enough for it, none is timed, kept or described."""
+    m = mnn()
+    options = m.Options(force_kind=m.SCHEME_WINOGRAD, force_tile_n=4, force_variant=m.WINO_UNFUSED)
+    short = ConvLayer("short", 16, 128, 64, 64, 32, 5, 5, 1, 2)             # 524288 pairs of channel and tile, 33.6 million values
+    fewer = ConvLayer("fewer", 16, 128, 64, 64, 32, 3, 3, 1, 1)             # as many pairs, 18.9 million
+    long = ConvLayer("long", 40, 128, 64, 64, 32, 3, 3, 1, 1)               # 47 million: a lane per tile
+    for layer, capped in ((short, False), (fewer, False), (long, True)):
+        with m.ConvChain([layer], options=options) as chain:                # has nothing to time on and takes a fixed cap
+            assert ("input-waves/cu" in chain.describe(0)) == capped, layer.name
+    with m.ConvPlan.for_layer(short, options=options) as p:
+        assert "input-waves/cu" not in p.describe()
+    m.cache_save(str(tmp_path / "cache"))
+    sizes = ["16", "128", "64", "64", "32", "4", "5"]
+    assert not [l for l in (tmp_path / "cache").read_text().splitlines() if l.startswith("I ") and l.split()[3:10] == sizes]
+
+
 @pytest.mark.parametrize("nk,shape", [
     ((2, 3), (4, 64, 32, 32, 64)), ((2, 3), (4, 64, 33, 32, 65)),            # C P and K P at 65536, and past it
     ((6, 3), (20, 64, 66, 66, 70)), ((4, 3), (9, 96, 60, 61, 100)),          # longer chains on larger grids: input alone (alpha 6), both (8)
