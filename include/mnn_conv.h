@@ -345,7 +345,8 @@ int mnn_conv_select(const mnn_scheme* cands, int32_t count, int32_t k, int32_t* 
  * D element (m, col) at        D + b*strideD_batch + (col / L)*strideD_img + m*strideD_row + col % L
  * (L = run of columns that is contiguous in memory; strides in elements).
  * prec is a mnn_gemm_prec.  variant 0 picks the tile configuration from the shape;
- * 1..mnn_gemm_variant_count(prec)-1 force one.
+ * 1..mnn_gemm_variant_count(prec)-1 force one.  (mnn_gemm_variant_name knows more: the kernels of the sliding window that keep a
+ * patch of the image, which planned layers describe and remember by these numbers and no product takes.)
  */
 typedef struct {
     int32_t M, ncols, R, batch, lda, L, variant, prec;

@@ -269,7 +269,13 @@ def select_scheme(cands: Sequence[Scheme], k: int) -> int:
     return int(out.value)
 
 
+def gemm_variant_name(variant: int, prec: int = GEMM_FP32) -> Optional[str]:
+    name = lib.mnn_gemm_variant_name(prec, variant)
+    return name.decode() if name else None
+
+
 def gemm_variants(prec: int = GEMM_FP32) -> List[str]:
+    """Tile configurations that gemm_f32 takes; planned layers may run others (gemm_variant_name)."""
     return [lib.mnn_gemm_variant_name(prec, i).decode() for i in range(lib.mnn_gemm_variant_count(prec))]
 
 

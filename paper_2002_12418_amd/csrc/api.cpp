@@ -631,6 +631,7 @@ int mnn_gemm_f32(const mnn_gemm_desc* d, const float* At, const float* B, const 
     p.variant = d->variant;
     p.prec = d->prec;
     if (p.prec < MNN_GEMM_FP32 || p.prec > MNN_GEMM_BF16X3) return fail(MNN_E_INVALID_ARG, "unknown precision %d", p.prec);
+    if (p.variant >= gemm_product_variant_count(p.prec)) return fail(MNN_E_INVALID_ARG, "no tile configuration %d for products", p.variant);
     p.strideA_batch = d->strideA_batch;
     p.strideB_batch = d->strideB_batch; p.strideB_img = d->strideB_img; p.strideB_row = d->strideB_row;
     p.strideD_batch = d->strideD_batch; p.strideD_img = d->strideD_img; p.strideD_row = d->strideD_row;
@@ -705,7 +706,7 @@ void mnn_strassen_destroy(mnn_strassen_t h) { delete h; }
 
 int mnn_gemm_variant_count(int32_t prec)
 {
-    return (prec < MNN_GEMM_FP32 || prec > MNN_GEMM_BF16X3) ? 0 : gemm_variant_count(prec);
+    return (prec < MNN_GEMM_FP32 || prec > MNN_GEMM_BF16X3) ? 0 : gemm_product_variant_count(prec);
 }
 
 const char* mnn_gemm_variant_name(int32_t prec, int32_t variant)

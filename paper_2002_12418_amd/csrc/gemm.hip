@@ -525,6 +525,8 @@ static int first_patch_variant() { return kNumVariants + gemm_split6_variant_cou
 
 bool gemm_variant_is_patch(int prec, int v) { return prec == 0 && v >= first_patch_variant() && v < gemm_f32_variant_count(); }
 
+int gemm_product_variant_count(int prec) { return prec == 0 ? first_patch_variant() : gemm_variant_count(prec); }
+
 // Variant ids: 0 = choose from the shape, 1 .. kNumVariants-1 = the tile configurations above.
 int gemm_f32_variant_count() { return first_patch_variant() + conv_patch_variant_count(); }
 const char* gemm_f32_variant_name(int v)

@@ -181,6 +181,7 @@ bool gemm_bf16_variant_tile(int variant, int* bm, int* bn, int* bk);
 bool gemm_variant_tuned(const GemmProblem& p, int variant);     // whether the planner times it
 // variants of the table that serves precision `prec`
 inline int gemm_variant_count(int prec) { return prec == 0 ? gemm_f32_variant_count() : gemm_bf16_variant_count(); }
+int gemm_product_variant_count(int prec);       // of these, the ones that take any product: all but the patch kernels
 inline const char* gemm_variant_name(int prec, int v) { return prec == 0 ? gemm_f32_variant_name(v) : gemm_bf16_variant_name(v); }
 
 // Strassen's algorithm (Section 3.3.2), one level = expand both operands, one batched GEMM, combine.

@@ -249,6 +249,21 @@ def test_gemm_variant_table(mnn):
     assert mnn.gemm_variants(7) == []
 
 
+def test_configurations_that_take_no_product_are_refused(mnn):
+    """The patch kernels of the sliding window read weights of a form of their own: named for a product they are an error, not another kernel."""
+    import torch
+    t = torch.zeros(64)
+    for prec in (mnn.GEMM_FP32, mnn.GEMM_BF16X3, mnn.GEMM_BF16):
+        count = len(mnn.gemm_variants(prec))
+        assert not any("patch" in n for n in mnn.gemm_variants(prec))
+        for v in range(count, count + 8):
+            with pytest.raises(mnn.MnnError) as e:
+                mnn.gemm_f32(t, t, t, M=4, ncols=4, R=4, lda=4, variant=v, prec=prec)
+            assert e.value.code == -1, (v, str(e.value))
+    first = len(mnn.gemm_variants())
+    assert mnn.gemm_variant_name(first) == "x6_patch_128x64_w4x1" and mnn.gemm_variant_name(first + 5) is None
+
+
 def test_enumeration_with_bf16_allowed(mnn):
     c = mnn.enumerate_schemes(1, 64, 56, 56, 64, 3, 3, pad=1, options=mnn.Options(allow_bf16=1))
     x3 = [s for s in c if s.prec == mnn.GEMM_BF16X3]

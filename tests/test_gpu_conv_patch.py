@@ -33,7 +33,13 @@ def mnn():
 
 
 def patch_variants(m):
-    return [(i, n) for i, n in enumerate(m.gemm_variants()) if n.startswith("x6_patch_")]
+    """(number, name): what planned layers take beyond the configurations of products."""
+    out, v = [], len(m.gemm_variants())
+    while m.gemm_variant_name(v):
+        out.append((v, m.gemm_variant_name(v)))
+        v += 1
+    assert len(out) == 5 and all(n.startswith("x6_patch_") for _, n in out)
+    return out
 
 
 def planned(m, layer, variant, path):
@@ -143,12 +149,12 @@ def test_weights_take_the_room_of_their_form(mnn, layer, tmp_path):
     taps = layer.kh * layer.kw
     plain = layer.c_in * taps * -(-layer.c_out // 4) * 4 * 4
     parts = -(-layer.c_out // 128) * 128 * -(-layer.c_in // 16) * 16 * taps * 6
-    names = mnn.gemm_variants()
-    for v in [names.index("64x64x16_w2x2")] + [v for v, _ in patch_variants(mnn)]:
-        patch = names[v].startswith("x6_patch_") and layer.name == "either"
+    plain_tile = (mnn.gemm_variants().index("64x64x16_w2x2"), "64x64x16_w2x2")
+    for v, name in [plain_tile] + patch_variants(mnn):
+        patch = name.startswith("x6_patch_") and layer.name == "either"
         with planned(mnn, layer, v, tmp_path / "cache") as plan:
             assert ("x6_patch_" in plan.describe()) == patch
-            assert plan.workspace_bytes == (parts if patch else plain), names[v]
+            assert plan.workspace_bytes == (parts if patch else plain), name
             y = plan.run(x, w, b)
             ref = conv64(layer, x.cpu(), w.cpu(), b.cpu())
-            assert float((y.cpu().double() - ref).abs().max() / ref.abs().max()) < 2e-6, names[v]
+            assert float((y.cpu().double() - ref).abs().max() / ref.abs().max()) < 2e-6, name
