@@ -388,21 +388,20 @@ int mnn_conv_run(mnn_conv_plan_t plan, const float* input, const float* weight, 
 
 namespace {
 // Whether the call that prepares its weights each time and cannot time anything takes the one-kernel arrangement.  Measured on both, whole calls
-// in us, 110 shapes (1 to 16 images, 8 to 192 channels, 7 to 112 pixels wide, alpha 3 to 6): the separate kernels, the transforms of input and
-// weights in one launch, cost 0.3 per megabyte of V and M written and read; the one kernel costs 1/8 per position for each chunk of 16 channels that a
-// workgroup walks, one workgroup per CU at a time, and 0.5 per tap beyond 3 (its weights).  A launch more costs 4, and where that launch writes no
-// padding, clearing it first 1.  F(2,3) one image 64 -> 64 56 x 56 14.2 separate, 21.3 one; 112 x 112 30.4, 22.0.  The constants are those with the least loss
-// (1.6 % on average) that keep the arrangement of the shapes whose choice is pinned by a test; without that they were 0.2 % (-0.5, 0.2 per megabyte, nothing
-// for padding), and 8 x 17 -> 35 x 40 x 41 F(3,3) would take the separate kernels (16.3, 22.9 as before).
-bool one_kernel_sooner(const WinoGeom& g, bool clear)
+// in us, 415 shapes (1 to 32 images, 3 to 256 channels, 6 to 147 pixels wide, alpha 3 to 6): the separate kernels, the transforms of input and
+// weights in one launch, cost 0.25 per megabyte of V and M written and read; the one kernel costs 1.5 and 1/8 per position for each chunk of 16 channels that
+// a workgroup walks, one workgroup per CU at a time, and 0.5 per tap beyond 3 (its weights).  Where the two transforms take a launch each, the separate
+// kernels cost 7 more.  F(2,3) one image 64 -> 64 56 x 56 14.0 separate, 21.3 one; 112 x 112 30.9, 21.8; F(3,3) 8 x 17 -> 35 40 x 41 16.1, 22.6;
+// F(2,3) 5 x 3 -> 7 31 x 33 12.9, 13.2.  The rule loses 0.8 % on average against the better of the two, 27 % at most (F(3,4) 32 x 62 -> 179 16 x 13 42.3, 34.8).
+bool one_kernel_sooner(const WinoGeom& g)
 {
     if (!wino_full_available(g.n, g.k)) return false;
     const double a2 = (double)g.alpha * g.alpha, per_block = wino_full_block_channels(g.alpha);
     const double wgs = std::ceil(g.K / per_block) * std::ceil(g.P / 32.0);
     const double chunks = std::ceil(g.C / 16.0) * std::ceil(wgs / 256.0);
     const double bytes = 4.0 * a2 * g.P * 2.0 * ((double)g.C + g.K);
-    const double launches = (input_filter_short(g) ? 0.0 : clear ? 5.0 : 4.0) + (clear ? 1.0 : 0.0);
-    return a2 * chunks / 8.0 + 0.5 * (g.k - 3) < 0.5 + launches + 0.3e-6 * bytes;
+    const double launches = input_filter_short(g) ? 0.0 : 7.0;
+    return 1.5 + a2 * chunks / 8.0 + 0.5 * (g.k - 3) < launches + 0.25e-6 * bytes;
 }
 }  // namespace
 
@@ -436,7 +435,7 @@ int mnn_conv_run_static(const mnn_conv_shape* shape, const mnn_conv_geom* geom, 
         // and the one-kernel arrangement, write their padding themselves.
         const bool clear = sc.kind == MNN_SCHEME_WINOGRAD && (im.wg.ldk != L.s.c_out || im.wg.ldp != im.wg.P);
         Impl one;
-        if (sc.kind == MNN_SCHEME_WINOGRAD && !im.rect && one_kernel_sooner(im.wg, clear) &&
+        if (sc.kind == MNN_SCHEME_WINOGRAD && !im.rect && one_kernel_sooner(im.wg) &&
             one.prepare(L, make_scheme(MNN_SCHEME_WINOGRAD, tile_n, MNN_GEMM_FP32, MNN_WINO_FUSED_ALL), o, true, true) == MNN_OK &&
             one.external_bytes() <= kStaticScratchBytes) {
             one.bind_external(reinterpret_cast<char*>(base));
