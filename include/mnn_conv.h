@@ -79,7 +79,9 @@ typedef struct {
     int32_t tile_n;           /* n of F(n,k); 0 unless kind == MNN_SCHEME_WINOGRAD        */
     int32_t prec;             /* mnn_gemm_prec                                            */
     int32_t variant;          /* kernel arrangement of the scheme, see MNN_WINO_*; 0 otherwise */
-    float   est_ms;           /* time measured by the planner; < 0 when it was not timed  */
+    float   est_ms;           /* time measured by the planner: mean of plan_iters passes, or, of a candidate that was at least
+                                 1.3 times the best one's time in two single passes before, the shorter of those;
+                                 < 0 when it was not timed  */
 } mnn_scheme;
 
 /* Kernel arrangements of a Winograd scheme (all compute the same F(n,k)).  For MNN_SCHEME_GEMM1X1 the variant
@@ -111,8 +113,9 @@ typedef struct {
     float   point_scale_f;    /* f of the Winograd generator (Section 3.3.1).  0 (default): the paper's 0.5 up to
                                  alpha = 8 and 0.425 for alpha = 9 and 10, where 0.5 no longer gives the least fp32
                                  error; > 0: that f for every tile */
-    int32_t plan_warmup;      /* untimed launches per candidate (default 2)               */
-    int32_t plan_iters;       /* timed launches per candidate (default 10)                */
+    int32_t plan_warmup;      /* passes per candidate before the timed ones (default 2); above 1, and where the best candidate
+                                 takes 0.05 ms or more, the last of them tells a candidate that cannot win (est_ms) */
+    int32_t plan_iters;       /* timed passes per candidate (default 10)                  */
     int32_t use_cache;        /* 1 (default): consult / fill the process-wide choice cache */
     float   prune_ratio;      /* > 1: candidates whose predicted time (mnn_conv_predict_ms) exceeds prune_ratio times
                                  the best predicted one are not timed; 0 (default): time every candidate */

@@ -129,8 +129,9 @@ struct Scratch {
 };
 
 // Times one candidate: `warmup` untimed and `iters` timed passes of the
-// per-inference stages, bracketed by HIP events on `s`.  A candidate whose last warm-up pass takes 1.3 times `best_ms` (< 0: none yet) or more is not
-// going to win and keeps that time: passes of one candidate differ by a few per cent.  (Below 0.05 ms the wait for that pass costs what it saves.)
+// per-inference stages, bracketed by HIP events on `s`.  A candidate whose last warm-up pass takes 1.3 times `best_ms` (< 0: none yet) or more, and
+// so does another pass, is not going to win and keeps the shorter of the two: single passes hold the gaps between their launches and now and then
+// a hiccup, but seldom two.  (Below 0.05 ms the waits for these passes cost what they save.)
 int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, const Scratch& sc, float best_ms, hipStream_t s)
 {
     Impl impl;
@@ -166,8 +167,14 @@ int time_candidate(const Layer& L, const mnn_conv_options& o, mnn_scheme* cand, 
         };
         const bool look = o.plan_warmup > 1 && best_ms >= 0.05f;
         for (int i = 0; i < o.plan_warmup - (look ? 1 : 0) && !rc; ++i) rc = pass();
-        if (!rc && look) rc = timed(1);
-        if (rc || (look && ms >= 1.3f * best_ms)) break;
+        float least = -1.f;
+        for (int i = 0; look && i < 2 && !rc; ++i) {
+            if ((rc = timed(1))) break;
+            if (least < 0.f || ms < least) least = ms;
+            if (least < 1.3f * best_ms) break;
+        }
+        if (!rc && look && least >= 1.3f * best_ms) ms = least;
+        if (rc || (look && least >= 1.3f * best_ms)) break;
         rc = timed(o.plan_iters);
     } while (false);
     (void)hipEventDestroy(e0);
