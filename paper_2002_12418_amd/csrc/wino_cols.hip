@@ -45,24 +45,43 @@ inline int cols_chunks(int C) { return (C + kColsChunk - 1) / kColsChunk; }
 // Channels past K and C hold zeros.
 struct ColsFilterMat { float g[kMaxAlphaT][7]; };
 
-// One workgroup per 32 output channels x 16 input channels (as filter_full_kernel)
+// One workgroup per 32 output channels x 16 input channels and share of the rows of G w G^T: rows grp, grp + groups, ... of `groups` shares, one
+// for each `row_waves` wavefronts, which take turns at its columns.  Few blocks are a handful of workgroups, bound by the trips to memory for
+// their weights: many loads at once, and a share per row.  us, a workgroup per block and a load at a time -> here: F(4,7) 64 -> 64 36 -> 12 (8 blocks, ten
+// shares), F(4,5) 128 -> 128 18 -> 8, 256 -> 256 23 -> 13; F(4,7) 512 -> 512 99 -> 57 (one share; 157 MB of parts).
 template <int KT>
 __global__ __launch_bounds__(256) void cols_filter_kernel(int K, int C, int alpha, int mblocks, ColsFilterMat gm, const float* __restrict__ w,
-                                                          uintx4* __restrict__ U, int nch)
+                                                          uintx4* __restrict__ U, int nch, int groups, int row_waves)
 {
-    constexpr int RUN = kColsChunk * KT * KT, LD = RUN + 1;
+    constexpr int RUN = kColsChunk * KT * KT, LD = RUN + 1, LOADS = 32 * RUN / 256;
     __shared__ float ws[32 * LD];
-    const int kb = blockIdx.x / nch, ch = blockIdx.x % nch;
+    const int block = (int)blockIdx.x / groups, grp = (int)blockIdx.x - block * groups;
+    const int kb = block / nch, ch = block % nch;
     const int c_run = (C - ch * kColsChunk < kColsChunk ? C - ch * kColsChunk : kColsChunk) * KT * KT;
-    for (int i = threadIdx.x; i < 32 * RUN; i += 256) {
-        const int k = i / RUN, j = i % RUN;
-        ws[k * LD + j] = kb * 32 + k < K && j < c_run ? w[((long long)(kb * 32 + k) * C + ch * kColsChunk) * KT * KT + j] : 0.f;
+    constexpr int STEP = LOADS % 14 == 0 ? 14 : LOADS % 12 == 0 ? 12 : 10;
+    static_assert(32 * RUN % 256 == 0 && LOADS % STEP == 0, "whole rounds of loads");
+#pragma unroll 1
+    for (int r = 0; r < LOADS; r += STEP) {
+        float v[STEP];
+#pragma unroll
+        for (int t = 0; t < STEP; ++t) {
+            const int i = (r + t) * 256 + (int)threadIdx.x, k = i / RUN, j = i % RUN;
+            const bool ok = kb * 32 + k < K && j < c_run;
+            v[t] = w[((long long)(ok ? kb * 32 + k : 0) * C + ch * kColsChunk) * KT * KT + (ok ? j : 0)];
+            v[t] = ok ? v[t] : 0.f;
+        }
+#pragma unroll
+        for (int t = 0; t < STEP; ++t) {
+            const int i = (r + t) * 256 + (int)threadIdx.x;
+            ws[i / RUN * LD + i % RUN] = v[t];
+        }
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wrow = wave % row_waves, wcol = wave / row_waves, col_waves = 4 / row_waves;
     const float* wp = ws + (lane & 31) * LD + (lane >> 5) * 8 * KT * KT;
 #pragma unroll 1
-    for (int i = wave; i < alpha; i += 4) {
+    for (int i = grp + groups * wrow; i < alpha; i += groups * row_waves) {
         float row[8][KT];                                     // row i of G w, 8 channels
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -74,7 +93,7 @@ __global__ __launch_bounds__(256) void cols_filter_kernel(int K, int C, int alph
                 row[e][s] = acc;
             }
 #pragma unroll 1
-        for (int j = 0; j < alpha; ++j) {
+        for (int j = wcol; j < alpha; j += col_waves) {
             unsigned part[4][3];
             float v[8];
 #pragma unroll
@@ -543,9 +562,12 @@ hipError_t launch_cols_filter(const WinoGeom& g, const float* G, const float* w,
     for (int i = 0; i < kMaxAlphaT; ++i)
         for (int j = 0; j < 7; ++j) m.g[i][j] = (i < g.alpha && j < g.k) ? G[i * g.k + j] : 0.f;
     const int mb = cols_mblocks(g.K, g.alpha), nch = cols_chunks(g.C);
-    const dim3 grid((unsigned)((long long)mb * nch));
+    const int blocks = mb * nch;                          // K C < 2^27: fewer than 2^19
+    const int groups = blocks >= 256 ? 1 : 256 / blocks < g.alpha ? 256 / blocks : g.alpha;
+    const int rows = (g.alpha + groups - 1) / groups, row_waves = rows >= 4 ? 4 : rows >= 2 ? 2 : 1;
+    const dim3 grid((unsigned)(blocks * groups));
     switch (g.k) {
-#define MNN_FILTER(KT_) case KT_: hipLaunchKernelGGL(cols_filter_kernel<KT_>, grid, dim3(256), 0, s, g.K, g.C, g.alpha, mb, m, w, (uintx4*)U, nch); break;
+#define MNN_FILTER(KT_) case KT_: hipLaunchKernelGGL(cols_filter_kernel<KT_>, grid, dim3(256), 0, s, g.K, g.C, g.alpha, mb, m, w, (uintx4*)U, nch, groups, row_waves); break;
         MNN_FILTER(5) MNN_FILTER(6) MNN_FILTER(7)
 #undef MNN_FILTER
         default: return hipErrorInvalidValue;
