@@ -244,28 +244,42 @@ hipError_t launch_input_filter_t(const WinoGeom& g, const ShortInArgs& a, const 
 
 }  // namespace
 
-// Where the lane's chain is what counts: a wavefront of whole tiles per SIMD or fewer, and for the long chains of a large alpha as long as the tensor
-// does not pass by the caches anyway (us, a lane per tile / per row: input, F(2,3) 16 x 64 x 56 x 56 12.1 / 12.6, F(4,3) 32 x 64 x 56 x 56 15.0 / 13.9, F(3,3) 8 x 64 x 112 x 112
-// 17.7 / 19.2, F(4,5) 16 x 128 x 64 x 64 29.1 / 26.1, F(6,5) 16 x 64 x 112 x 112 34.8 / 30.0, F(4,7) there 80 / 91; output, F(4,3) 32 x 256 x 14 x 14 6.3 / 7.6, F(6,3) 20 x 93 x 39 x 39
-// 12.2 / 10.3, F(6,5) 32.7 / 29.7, F(6,3) 16 x 128 x 128 x 128 66 / 78).
+// Where the lane's chain is what counts.  Whole planned calls of the separate kernels, a lane per tile against a lane per row of one, 473 + 349 shapes of
+// 16 to 1024 channels: up to 65536 pairs of channel and tile, a wavefront of whole tiles per SIMD or fewer, 1.00 (alpha 3) to 1.12 (9 and 10) times the
+// speed.  Beyond, for the long chains of a large alpha: alpha 6 and 7 up to 150000 pairs 1.00 to 1.15, but F(2,5) 4 x 602 -> 445 21 x 21 (291368 pairs) 82.9 us
+// a lane per tile and 85.0 here, and F(2,5) one image 400 -> 512 40 x 40 (160000) 59.5 and 60.5: the products read V a little slower afterwards,
+// which few output channels do not show (-> 64 28.2 and 25.4).  Alpha 8, two paired transforms, up to 600000 pairs 1.03 on average and 0.98 at worst; 10 up to
+// 200000 1.05, at 390000 0.95 to 1.04; 9, whose matrices have no pairs, 0.96 on average from 100000 on, and 0.89 at 480000.
 bool input_transform_short(const WinoGeom& g)
 {
-    const long long lanes = (long long)g.C * g.P;
-    return !g.blocked && (long long)g.N * g.C * g.H * g.W < (1ll << 29) - 1024 && (lanes <= 65536 || (g.alpha >= 6 && lanes * g.alpha * g.alpha <= 40000000));
+    const long long pairs = (long long)g.C * g.P;
+    if (g.blocked || (long long)g.N * g.C * g.H * g.W >= (1ll << 29) - 1024) return false;
+    if (pairs <= 65536) return true;
+    switch (g.alpha) {
+        case 6: case 7: return pairs <= 150000 || (pairs <= 200000 && g.K <= 256);
+        case 8: return pairs <= 625000;
+        case 10: return pairs <= 250000;
+        default: return false;
+    }
 }
 
+// The call that prepares its weights saves a launch as well, and its scratch array bounds the grid.
 // Many weights: a lane per row of G w G^T reads them alpha times over (allocation-free F(4,3) 32 x 512 -> 512 x 7 x 7 54 us in two launches, 73 in one;
 // 256 -> 256 x 14 x 14 49 both), and each is a run of k^2 values of its own, so that the line lies sooner for larger kernels (one image of 14 x 14, F(4,5)
 // 160 -> 160 channels 31 and 28, 192 33.7 and 33.8, 224 37 and 41, 254 46 and 63; F(2,6) 128 26.2 and 24.5, 160 28.4 and 31.6).
 bool input_filter_short(const WinoGeom& g)
 {
-    return input_transform_short(g) && (long long)g.K * g.C <= 65536 && (long long)g.K * g.C * g.k * g.k <= 800000;
+    const long long pairs = (long long)g.C * g.P;
+    if (g.blocked || (long long)g.N * g.C * g.H * g.W >= (1ll << 29) - 1024) return false;
+    if (pairs > 65536 && (g.alpha < 6 || pairs * g.alpha * g.alpha > 40000000)) return false;
+    return (long long)g.K * g.C <= 65536 && (long long)g.K * g.C * g.k * g.k <= 800000;
 }
 
+// Of the same calls: up to 65536 pairs 1.00 (alpha 8) to 1.01 (9 and 10), up to 200000 1.01 to 1.02 from alpha 8 on, beyond 0.95 to 1.04, 1.00 on average.
 bool output_transform_short(const WinoGeom& g)
 {
-    const long long lanes = (long long)g.K * g.P;
-    return lanes <= 65536 || (g.alpha >= 8 && lanes * g.alpha * g.alpha <= 40000000);
+    const long long pairs = (long long)g.K * g.P;
+    return pairs <= 65536 || (g.alpha >= 8 && pairs <= 200000);
 }
 
 hipError_t launch_input_short(const WinoGeom& g, const float* BT, const float* x, float* V, hipStream_t s)

@@ -68,23 +68,25 @@ def test_no_cap_on_wavefronts_where_the_short_kernel_runs(tmp_path):
     """The cap on resident wavefronts is one of the other kernel: on a grid long enough for it, none is timed, kept or described."""
     m = mnn()
     options = m.Options(force_kind=m.SCHEME_WINOGRAD, force_tile_n=4, force_variant=m.WINO_UNFUSED)
-    short = ConvLayer("short", 16, 128, 64, 64, 32, 5, 5, 1, 2)             # 524288 pairs of channel and tile, 33.6 million values
-    fewer = ConvLayer("fewer", 16, 128, 64, 64, 32, 3, 3, 1, 1)             # as many pairs, 18.9 million
-    long = ConvLayer("long", 40, 128, 64, 64, 32, 3, 3, 1, 1)               # 47 million: a lane per tile
-    for layer, capped in ((short, False), (fewer, False), (long, True)):
-        with m.ConvChain([layer], options=options) as chain:                # has nothing to time on and takes a fixed cap
-            assert ("input-waves/cu" in chain.describe(0)) == capped, layer.name
-    with m.ConvPlan.for_layer(short, options=options) as p:
-        assert "input-waves/cu" not in p.describe()
-    m.cache_save(str(tmp_path / "cache"))
-    sizes = ["16", "128", "64", "64", "32", "4", "5"]
-    assert not [l for l in (tmp_path / "cache").read_text().splitlines() if l.startswith("I ") and l.split()[3:10] == sizes]
+    # 622592 pairs of channel and tile; alpha 8: a lane per row of a tile, alpha 6: a lane per tile
+    for k, capped in ((5, False), (3, True)):
+        layer = ConvLayer("cap", 19, 128, 64, 64, 32, k, k, 1, k // 2)
+        with m.ConvPlan.for_layer(layer, options=options) as p:
+            assert capped or "input-waves/cu" not in p.describe()
+        m.cache_save(str(tmp_path / "cache"))
+        sizes = ["19", "128", "64", "64", "32", "4", str(k)]
+        kept = [l for l in (tmp_path / "cache").read_text().splitlines() if l.startswith("I ") and l.split()[3:10] == sizes]
+        assert len(kept) == capped
 
 
 @pytest.mark.parametrize("nk,shape", [
     ((2, 3), (4, 64, 32, 32, 64)), ((2, 3), (4, 64, 33, 32, 65)),            # C P and K P at 65536, and past it
-    ((6, 3), (20, 64, 66, 66, 70)), ((4, 3), (9, 96, 60, 61, 100)),          # longer chains on larger grids: input alone (alpha 6), both (8)
-    ((8, 3), (4, 64, 128, 128, 40)), ((4, 7), (6, 64, 112, 113, 66)),        # at 40 million values, and past it
+    ((4, 3), (9, 74, 60, 60, 20)), ((4, 3), (9, 75, 60, 60, 20)),            # alpha 6: 149850 and 151875 pairs
+    ((4, 3), (9, 98, 60, 60, 256)), ((4, 3), (9, 98, 60, 60, 257)), ((3, 5), (9, 98, 45, 45, 20)),      # up to 200000 with few output channels
+    ((6, 3), (21, 64, 126, 126, 9)), ((4, 5), (24, 64, 80, 82, 20)),         # alpha 8: 592704 pairs and 645120
+    ((6, 3), (3, 9, 120, 120, 166)), ((6, 3), (3, 9, 120, 120, 167)),        # its output: 199200 and 200400
+    ((5, 5), (4, 64, 80, 80, 64)), ((5, 5), (4, 65, 80, 81, 65)),            # alpha 9: 65536, and past it
+    ((8, 3), (4, 244, 128, 128, 40)), ((8, 3), (4, 245, 128, 128, 40)),      # alpha 10: 249856 and 250880
 ])
 def test_both_sides_of_the_rules(nk, shape):
     m = mnn()
