@@ -377,8 +377,9 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmProblem
 
     // ---- results (or this slice's partial results) to memory
     const TileDest dest = tile_dest(p, b, split, splitk, ldc);
-    store_tiles<TM, TN>(acc, dest, p.M, p.Ncols, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane,
-                        smem + wmn * kStageFloats, vecD);
+    const int mw0 = m0 + wm * (BM / WM), nw0 = n0 + wn * (BN / WN);
+    if constexpr (MODE == 1) store_tiles_lean<TM, TN>(acc, dest, p.M, p.Ncols, mw0, nw0, lane, smem + wmn * kStageFloats, vecD);
+    else store_tiles<TM, TN, false>(acc, dest, p.M, p.Ncols, mw0, nw0, lane, smem + wmn * kStageFloats, vecD);
 }
 
 // Adds the split-K slices P[split][batch][M][ldc] in slice order, applies the bias and writes D.

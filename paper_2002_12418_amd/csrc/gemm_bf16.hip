@@ -250,7 +250,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmProblem p, 
     }
 
     const TileDest dest = tile_dest(p, b, split, splitk, ldc);
-    store_tiles<TM, TN>(acc, dest, p.M, p.Ncols, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane,
+    store_tiles<TM, TN, true>(acc, dest, p.M, p.Ncols, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane,
                         reinterpret_cast<float*>(smem) + wave * kStageFloats, vecD);
 }
 

@@ -9,6 +9,7 @@
 // workgroup wait for an L2 write-back on this multi-die part and costs more than the second launch.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <type_traits>
 #include "kernels.hpp"
 
 namespace mnnconv {
@@ -32,49 +33,56 @@ __device__ __forceinline__ TileDest tile_dest(const GemmProblem& p, int b, int s
 // tile, so that a lane stores 4 consecutive columns of one row and one store instruction covers 8 rows x
 // 128 bytes instead of 2 rows x 128 bytes in 4-byte pieces.  LDS accesses of one wavefront execute in
 // order, so the staging needs no barrier (the caller's LDS must be free: after its last barrier).
-template <int TM, int TN, typename Acc>
+// TWO: with and without a bias, a code path each.  A branch around the bias in one path costs products without one 1 to 3 % (64 x 64 tiles,
+// 16 x 8 x 51 x 32256 41.1 -> 42.1 us); the second path costs the fp32 kernels registers that they have no use for otherwise.
+template <int TM, int TN, bool TWO, typename Acc>
 __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const TileDest& d, int M, int Ncols, int mw0,
                                             int nw0, int lane, float* stage, int vec)
 {
     const int lrow = lane >> 5, lcol = lane & 31;
     if (vec) {
         const int rrow = lane >> 3, rc4 = (lane & 7) * 4;
-        // all bias values at once: behind the bounds check of its row each load would be a trip of its own
-        float bias[TM][4];
-        if (d.bias) {
+        auto store = [&](auto known) __attribute__((always_inline)) {
+            const bool has_bias = TWO ? decltype(known)::value : d.bias != nullptr;
+            // all bias values at once: behind the bounds check of its row each load would be a trip of its own
+            float bias[TM][4];
+            if (has_bias) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int ps = 0; ps < 4; ++ps) {
-                    const int m = mw0 + i * 32 + ps * 8 + rrow;
-                    bias[i][ps] = d.bias[m < M ? m : M - 1];
-                }
-        }
+                    for (int ps = 0; ps < 4; ++ps) {
+                        const int m = mw0 + i * 32 + ps * 8 + rrow;
+                        bias[i][ps] = d.bias[m < M ? m : M - 1];
+                    }
+            }
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = nw0 + j * 32 + rc4;
-            const bool cok = col < Ncols;                     // 4 | Ncols: all four columns or none
-            const long long coff = (long long)(col / d.L) * d.sImg + (col % d.L);
+            for (int j = 0; j < TN; ++j) {
+                const int col = nw0 + j * 32 + rc4;
+                const bool cok = col < Ncols;                     // 4 | Ncols: all four columns or none
+                const long long coff = (long long)(col / d.L) * d.sImg + (col % d.L);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
+                for (int i = 0; i < TM; ++i) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    stage[(8 * (r / 4) + 4 * lrow + (r % 4)) * kStageStride + lcol] = acc[i][j][r];
+                    for (int r = 0; r < 16; ++r)
+                        stage[(8 * (r / 4) + 4 * lrow + (r % 4)) * kStageStride + lcol] = acc[i][j][r];
 #pragma unroll
-                for (int ps = 0; ps < 4; ++ps) {
-                    const int row = ps * 8 + rrow;
-                    const int m = mw0 + i * 32 + row;
-                    float4 v = *reinterpret_cast<const float4*>(&stage[row * kStageStride + rc4]);
-                    if (cok && m < M) {
-                        if (d.bias) {
-                            const float bv = bias[i][ps];
-                            v.x += bv; v.y += bv; v.z += bv; v.w += bv;
+                    for (int ps = 0; ps < 4; ++ps) {
+                        const int row = ps * 8 + rrow;
+                        const int m = mw0 + i * 32 + row;
+                        float4 v = *reinterpret_cast<const float4*>(&stage[row * kStageStride + rc4]);
+                        if (cok && m < M) {
+                            if (has_bias) {
+                                const float bv = bias[i][ps];
+                                v.x += bv; v.y += bv; v.z += bv; v.w += bv;
+                            }
+                            *reinterpret_cast<float4*>(d.base + coff + (long long)m * d.sRow) = v;
                         }
-                        *reinterpret_cast<float4*>(d.base + coff + (long long)m * d.sRow) = v;
                     }
                 }
             }
-        }
+        };
+        if (!TWO || d.bias) store(std::true_type{});
+        else store(std::false_type{});
         return;
     }
     // Row by row: what counts is that nothing but the row's own check stands between two stores.  Bias loads, their branch and the column's divisions are done before,
@@ -114,6 +122,64 @@ __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const Tile
                 for (int e = 0; e < 4; ++e) {
                     if (m + 4 * lrow + e < M) *dst = acc[i][j][q * 4 + e] + bias[i][q * 4 + e];
                     dst += d.sRow;
+                }
+            }
+        }
+    }
+}
+
+// The same with few registers, bias values loaded where they are added: for the fp32 kernels whose operands come in 16-byte loads, and whose results
+// nearly always take 16-byte stores.  With store_tiles they had room for a wavefront per SIMD less: without a bias 81 x 13 x 41 x 10000 in 64 x 128
+// 34.7 -> 37.5 us, 16 x 8 x 51 x 32256 22.3 -> 24.0, 36 x 128 x 128 x 6272 in 64 x 256 81.5 -> 88.2.
+template <int TM, int TN, typename Acc>
+__device__ __forceinline__ void store_tiles_lean(const Acc (&acc)[TM][TN], const TileDest& d, int M, int Ncols, int mw0,
+                                                 int nw0, int lane, float* stage, int vec)
+{
+    const int lrow = lane >> 5, lcol = lane & 31;
+    if (vec) {
+        const int rrow = lane >> 3, rc4 = (lane & 7) * 4;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = nw0 + j * 32 + rc4;
+            const bool cok = col < Ncols;                     // 4 | Ncols: all four columns or none
+            const long long coff = (long long)(col / d.L) * d.sImg + (col % d.L);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    stage[(8 * (r / 4) + 4 * lrow + (r % 4)) * kStageStride + lcol] = acc[i][j][r];
+#pragma unroll
+                for (int ps = 0; ps < 4; ++ps) {
+                    const int row = ps * 8 + rrow;
+                    const int m = mw0 + i * 32 + row;
+                    float4 v = *reinterpret_cast<const float4*>(&stage[row * kStageStride + rc4]);
+                    if (cok && m < M) {
+                        if (d.bias) {
+                            const float bv = d.bias[m];
+                            v.x += bv; v.y += bv; v.z += bv; v.w += bv;
+                        }
+                        *reinterpret_cast<float4*>(d.base + coff + (long long)m * d.sRow) = v;
+                    }
+                }
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int col = nw0 + j * 32 + lcol;
+        if (col >= Ncols) continue;
+        const long long coff = (long long)(col / d.L) * d.sImg + (col % d.L);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mbase = mw0 + i * 32 + 4 * lrow;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = mbase + 8 * (r / 4) + (r % 4);
+                if (m < M) {
+                    float v = acc[i][j][r];
+                    if (d.bias) v += d.bias[m];
+                    d.base[coff + (long long)m * d.sRow] = v;
                 }
             }
         }
