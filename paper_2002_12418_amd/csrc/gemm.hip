@@ -51,7 +51,7 @@ typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 // four SIMDs of a CU, so that a problem with few output elements and a long reduction (batch-1 layers) spreads
 // over four times as many workgroups without a second kernel.
 template <int BM, int BN, int BK, int WM, int WN, int MODE, int PF = 1, bool BUF = true, int WK = 1>
-__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmProblem p, int tilesM, int tilesN, int total,
+__global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmArgs p, int tilesM, int tilesN, int total,
                                                                 unsigned a_bytes, unsigned b_bytes, int vecD, int ldc)
 {
     static_assert(PF == 1 || PF % 2 == 0, "the LDS buffer index is derived from the stage index");
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmProblem
 }
 
 // Adds the split-K slices P[split][batch][M][ldc] in slice order, applies the bias and writes D.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmProblem p, int ldc, int vecD)
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs p, int ldc, int vecD)
 {
     const int q = ldc >> 2;
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;

@@ -35,7 +35,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // MODE 0: B element by element through (col / L, col % L); 1: 16-byte loads; 2: im2col gather.
 template <int BM, int BN, int BK, int WM, int WN, int MODE, bool SPLIT>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmProblem p, int tilesM, int tilesN, int total,
+__global__ __launch_bounds__(WM * WN * 64) void gemm_bf16_kernel(GemmArgs p, int tilesM, int tilesN, int total,
                                                                  int vecD, int ldc)
 {
     constexpr int NT = WM * WN * 64;

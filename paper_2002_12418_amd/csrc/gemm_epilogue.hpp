@@ -20,7 +20,7 @@ constexpr int kStageFloats = 32 * kStageStride;
 // element (m, col) of the destination lives at base + (col / L) * sImg + m * sRow + col % L
 struct TileDest { float* base; long long sImg, sRow; int L; const float* bias; };
 
-__device__ __forceinline__ TileDest tile_dest(const GemmProblem& p, int b, int split, int splitk, int ldc)
+__device__ __forceinline__ TileDest tile_dest(const GemmArgs& p, int b, int split, int splitk, int ldc)
 {
     if (splitk > 1)
         return TileDest{p.splitk_partial + ((long long)split * p.batch + b) * p.M * ldc, 0, ldc, ldc, nullptr};

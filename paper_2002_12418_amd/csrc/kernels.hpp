@@ -122,7 +122,7 @@ hipError_t launch_cols_rows_out(const WinoGeom& g, const float* AT /*host*/, con
 //   D : element (m, col) at  D + b*strideD_batch + (col / L)*strideD_img + m*strideD_row + (col % L)
 // L is the number of consecutive columns that are contiguous in memory (the whole
 // row for the Winograd-domain product, H*W for the 1x1 convolution of one image).
-struct GemmProblem {
+struct GemmArgs {
     const float* At; const float* B; float* D; const float* bias;
     int M, Ncols, R, batch;
     int lda;
@@ -137,12 +137,15 @@ struct GemmProblem {
     // aligned); a second kernel adds them up in slice order.  0 or 1 = off.
     int splitk;
     float* splitk_partial;
-    const void* a_parts;        // the patch kernels' weights (launch_patch_weights); At is then unused
     // Implicit-GEMM gather for the sliding-window scheme (gather != 0): B is the input tensor x[N][C][H][W],
     // row r = (c, kr, ks), column = (img, oy, ox), element = x[img][c][oy*sh - ph + kr*dh][ox*sw - pw + ks*dw] or 0.
     // L must be H_o*W_o; the strideB_* fields are ignored.
     int gather;
     int cv_C, cv_H, cv_W, cv_kh, cv_kw, cv_sh, cv_sw, cv_ph, cv_pw, cv_dh, cv_dw, cv_Wo;
+};
+// What the product kernels do not read stays out of their arguments (gemm_split.hip says why it matters).
+struct GemmProblem : GemmArgs {
+    const void* a_parts;        // the patch kernels' weights (launch_patch_weights); At is then unused
 };
 hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s);
 int gemm_f32_variant_count();
