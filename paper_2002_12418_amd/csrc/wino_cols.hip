@@ -456,8 +456,9 @@ struct RowsOutArgs {
 };
 
 // One workgroup per (32 channels, row i of the tiles, 32 tiles); a lane holds four channels of one tile, as the accumulators left them.
-// STREAM: S is too large to stay in the last-level cache, and this, its last read, goes past the caches instead of evicting what comes next
-// (F(4,7) 16 x 64 x 112 x 112, 128 MB: whole call 188 -> 180 us; 67 MB: no difference).
+// STREAM: S is too large to stay in the last-level cache, and this, its last read, goes past the caches instead of evicting what comes next.  Whole
+// calls, us, through the caches and past them: S of 67 MB (F(4,5) 16 x 128 x 64 x 64) 94.9 and 95.9, 101 MB (24 images) 142 and 146, 113 MB (F(4,7)
+// 14 x 64 x 112 x 112) 154 and 158, 128 MB (16) 187 and 179, 134 MB 203 and 196, 154 MB (F(2,7), 12) 270 and 259, 179 MB (F(6,5) 16 x 64 -> 128) 238 and 217.
 template <int NT, int A, bool STREAM>
 __global__ __launch_bounds__(256) void cols_rows_out_kernel(RowsOutArgs g, MatArg<NT, A> at, const float* __restrict__ S,
                                                             const float* __restrict__ bias, float* __restrict__ y)
@@ -629,7 +630,7 @@ hipError_t launch_rows_out_t(const WinoGeom& g, const float* AT, const float* S,
     a.by_pairs = make_fastdiv((unsigned)a.pairs); a.by_n = make_fastdiv((unsigned)NT);
     a.by_tw = make_fastdiv((unsigned)g.tw); a.by_th = make_fastdiv((unsigned)g.th);
     const dim3 grid((unsigned)((long long)a.mblocks * a.pairs * NT));
-    if (wino_cols_sum_bytes(g) > 100000000)
+    if (wino_cols_sum_bytes(g) > 120000000)
         hipLaunchKernelGGL((cols_rows_out_kernel<NT, A, true>), grid, dim3(256), 0, s, a, at_arg<NT, A>(AT), S, bias, y);
     else
         hipLaunchKernelGGL((cols_rows_out_kernel<NT, A, false>), grid, dim3(256), 0, s, a, at_arg<NT, A>(AT), S, bias, y);
