@@ -142,21 +142,21 @@ bool wino_variant_available(int n, int k, int variant)
     }
 }
 
-// whether the sizes of the layer fit the arrangements that have limits of their own
-bool wino_variant_covers(const Layer& L, int n, int variant)
+// whether the sizes of the layer fit the arrangements that have limits of their own, and an arrangement can win there at all
+bool wino_variant_offered(const Layer& L, int n, int variant)
 {
     if (variant != MNN_WINO_FUSED_ALL && variant != MNN_WINO_BY_AXIS) return true;
     WinoGeom g{};
     g.N = L.s.n; g.C = L.s.c_in; g.H = L.s.h; g.W = L.s.w; g.K = L.s.c_out;
     g.n = n; g.k = L.s.kh; g.alpha = n + L.s.kh - 1;
     g.th = (L.Ho + n - 1) / n; g.tw = (L.Wo + n - 1) / n;
-    return variant == MNN_WINO_FUSED_ALL ? wino_full_covers(g) : wino_cols_covers(g);
+    return variant == MNN_WINO_FUSED_ALL ? wino_full_covers(g) : wino_cols_covers(g) && wino_cols_offered(g);
 }
 
 void push_wino_variants(std::vector<mnn_scheme>* out, const Layer& L, int n, int k, int prec)
 {
     for (int v = 0; v < MNN_WINO_VARIANTS; ++v)
-        if (wino_variant_available(n, k, v) && wino_variant_covers(L, n, v)) out->push_back(make_scheme(MNN_SCHEME_WINOGRAD, n, prec, v));
+        if (wino_variant_available(n, k, v) && wino_variant_offered(L, n, v)) out->push_back(make_scheme(MNN_SCHEME_WINOGRAD, n, prec, v));
 }
 
 // Recursion rule of Section 3.3.2 for [n,k] x [k,m]: go one level down while the multiplications saved exceed

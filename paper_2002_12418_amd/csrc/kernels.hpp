@@ -108,6 +108,7 @@ hipError_t launch_wino_full(const WinoGeom& g, const float* BT /*host*/, const f
 // matrix-operand order.  T, U and S have the sizes below.
 bool wino_cols_available(int n, int k);
 bool wino_cols_covers(const WinoGeom& g);           // reads N, C, H, W, K, n, k, alpha, th and tw
+bool wino_cols_offered(const WinoGeom& g);          // whether the planner times it where it covers; reads the same
 size_t wino_cols_weight_bytes(const WinoGeom& g);
 size_t wino_cols_input_bytes(const WinoGeom& g);
 size_t wino_cols_sum_bytes(const WinoGeom& g);

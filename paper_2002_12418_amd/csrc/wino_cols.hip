@@ -10,7 +10,7 @@
 // transforms its tiles anew.  So it pays for few outputs per tile and many taps: kernels of 5 taps and more (F(6,3) on 16 x 128 x 64 x 64: 69 us against 72
 // for separate kernels, F(8,3) 83 against 68).
 // Measured against the best of the other arrangements, us: F(4,5) 16 x 128 x 64 x 64 125 -> 100, 8 x 256 x 56 x 56 139 -> 126; F(4,7) 16 x 64 x 112 x 112 222 -> 180;
-// F(2,7) there 458 -> 357, 96 -> 192 channels on 8 x 80 x 80 367 -> 325.  Behind them where tiles are few (F(4,7) 4 x 128 x 28 x 28 39, 32) and where
+// F(2,7) there 458 -> 357, 96 -> 192 channels on 8 x 80 x 80 367 -> 325.  Behind them where tiles are few (F(4,7) 4 x 128 x 28 x 28 39, 32; wino_cols_offered) and where
 // channels are (F(4,5) 16 x 32 x 112 x 112 95, 60): the planner times all.
 // Of the 180: rows in 28 and rows out 36 at 5 to 6 TB/s, columns 115, where the matrix cores are busy 23 % and the vector units 50 % of the cycles
 // (F(4,5): 61 of 100, matrix cores 55 %).  Tried for that kernel: four wavefronts that stage and four that multiply, walking over blocks (F(4,7) 115,
@@ -550,6 +550,15 @@ bool wino_cols_covers(const WinoGeom& g)
     const long long mb = cols_mblocks(g.K, g.alpha), pb = cols_pblocks((int)P), kb = mb / cols_kw(g.K, g.alpha);
     if (!grid_fits((rows * g.C + 255) / 256, 256) || !grid_fits(kb * pb * g.alpha, 512)) return false;
     return pb < (1ll << 24) && mb < (1ll << 20) && mb * pb < (1ll << 28) && grid_fits(mb * 2 * pb * g.n, 256);
+}
+
+// Few workgroups of the columns kernel walk all channels each while the others' products fill the chip: of 75 layers with fewer than 32 it won none (0.83 of
+// the speed at best), of 50 with 32 to 63 two (1.14), of 62 with 64 to 255 twelve (1.50).  Timing it took as long as the other arrangements together
+// (planning F(6,5) 2 x 85 -> 175 9 x 11 4.4 ms, 2.8 without it).
+bool wino_cols_offered(const WinoGeom& g)
+{
+    const long long P = (long long)g.N * g.th * g.tw;
+    return (P + kColsTiles - 1) / kColsTiles * (cols_mblocks(g.K, g.alpha) / cols_kw(g.K, g.alpha)) * g.alpha >= 32;
 }
 
 size_t wino_cols_weight_bytes(const WinoGeom& g) { return cols_column_bytes(g) * g.alpha; }

@@ -119,6 +119,18 @@ def test_one_kernel_arrangement_is_priced_with_its_repeated_transforms(mnn):
     assert ms(mnn.WINO_FUSED_ALL, 4, 32, 64, 28, 512) > 1.9 * ms(mnn.WINO_FUSED_ALL, 4, 32, 64, 28, 128)
 
 
+def test_by_axes_is_timed_where_it_can_win(mnn):
+    """The planner does not time Winograd by axes for a handful of workgroups (alpha per 64 tiles and 64 or 128 output channels): it never won below 32."""
+    def offered(n, *shape):
+        return any(s.variant == mnn.WINO_BY_AXIS and s.tile_n == n for s in mnn.enumerate_schemes(*shape, 5, 5, pad=2, options=mnn.Options(alpha_max=10)))
+    assert not offered(4, 1, 16, 32, 32, 128)               # 64 tiles, one block of 128 output channels at alpha 8: 8 workgroups
+    assert not offered(4, 1, 16, 32, 32, 384)               # 24
+    assert offered(4, 1, 16, 32, 32, 385)                   # 32
+    assert offered(4, 4, 16, 32, 32, 128) and not offered(4, 3, 16, 32, 32, 128)
+    assert offered(6, 1, 16, 48, 48, 256) and not offered(6, 1, 16, 48, 48, 192)      # alpha 10: blocks of 64, 40 and 30
+    assert offered(4, 16, 128, 64, 64, 128)
+
+
 def test_launches_of_2_to_the_32_work_items_are_refused(mnn):
     """Such a launch would run, without an error, on what is left modulo 2^32: every configuration of every precision says no before it."""
     import torch
