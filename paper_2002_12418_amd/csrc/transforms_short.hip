@@ -12,7 +12,7 @@
 #include "kernels.hpp"
 #include "xcd_remap.hpp"
 #include "wino_paired.hpp"
-#include "bf16_parts.hpp"
+#include "tile_row.hpp"
 #include "fast_div.hpp"
 
 namespace mnnconv {
@@ -44,34 +44,8 @@ __device__ __forceinline__ void input_short(const WinoGeom& g, const ShortInArgs
         const int y = ty * g.n - g.pad_h + i, x0 = tx * g.n - g.pad_w;
         const bool ok = row_ok && p < g.P && (unsigned)y < (unsigned)g.H;
         const int first = ((img * g.C + c) * g.H + y) * g.W + x0;        // elements; the tensor has fewer than 2^29
-        const bool leaves = ok && (first < 0 || first + A > (int)(sa.x_bytes / 4u));
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, (int)sa.x_bytes, 0x00020000);
-        const unsigned off = ok && !leaves ? (unsigned)first * 4u : kOutsideBytes;
         float d[A];
-        int j = 0;
-#pragma unroll
-        for (; j + 4 <= A; j += 4) {
-            const uintx4 v = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 4 * j), 0, 0));
-            d[j] = __uint_as_float(v.x); d[j + 1] = __uint_as_float(v.y);
-            d[j + 2] = __uint_as_float(v.z); d[j + 3] = __uint_as_float(v.w);
-        }
-        if (j + 2 <= A) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(off + 4 * j), 0, 0);
-            d[j] = __uint_as_float(v[0]); d[j + 1] = __uint_as_float(v[1]);
-            j += 2;
-        }
-        if (j < A) d[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off + 4 * j), 0, 0));
-        if (__builtin_amdgcn_ballot_w64(leaves) != 0) {                  // a row whose loads would leave the tensor: element by element
-#pragma unroll
-            for (int e = 0; e < A; ++e) {
-                const unsigned oe = leaves && (unsigned)(x0 + e) < (unsigned)g.W ? (unsigned)(first + e) * 4u : kOutsideBytes;
-                const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)oe, 0, 0));
-                d[e] = leaves ? v : d[e];
-            }
-        }
-        // columns left or right of the image were read from the neighbouring row
-#pragma unroll
-        for (int e = 0; e < A; ++e) d[e] = (unsigned)(x0 + e) < (unsigned)g.W ? d[e] : 0.f;
+        load_tile_row<A>(x, sa.x_bytes, first, x0, g.W, ok, d);
         if (row_ok) {
 #pragma unroll
             for (int e = 0; e < A; ++e) lds[(e * A + i) * kShortTiles + t] = d[e];

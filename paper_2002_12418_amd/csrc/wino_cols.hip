@@ -23,6 +23,7 @@
 #include "xcd_remap.hpp"
 #include "wino_paired.hpp"
 #include "row_shares.hpp"
+#include "tile_row.hpp"
 #include "bf16_parts.hpp"
 #include "fast_div.hpp"
 
@@ -129,34 +130,8 @@ __global__ __launch_bounds__(256) void cols_rows_in_kernel(RowsArgs g, MatArg<A,
     const int c = (int)fast_div((unsigned)r2, g.by_n), img = r2 - c * g.N;
     const int x0 = tx * g.n - g.pad_w;
     const int first = ((img * g.C + c) * g.H + y) * g.W + x0;            // elements; the tensor has fewer than 2^29
-    const bool leaves = live && (first < 0 || first + A > (int)(g.x_bytes / 4u));
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, (int)g.x_bytes, 0x00020000);
-    const unsigned off = live && !leaves ? (unsigned)first * 4u : kOutsideBytes;
     float d[A];
-    int j = 0;
-#pragma unroll
-    for (; j + 4 <= A; j += 4) {
-        const uintx4 v = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(off + 4 * j), 0, 0));
-        d[j] = __uint_as_float(v.x); d[j + 1] = __uint_as_float(v.y);
-        d[j + 2] = __uint_as_float(v.z); d[j + 3] = __uint_as_float(v.w);
-    }
-    if (j + 2 <= A) {
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(off + 4 * j), 0, 0);
-        d[j] = __uint_as_float(v[0]); d[j + 1] = __uint_as_float(v[1]);
-        j += 2;
-    }
-    if (j < A) d[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(off + 4 * j), 0, 0));
-    if (__builtin_amdgcn_ballot_w64(leaves) != 0) {       // a row whose loads would leave the tensor: element by element
-#pragma unroll
-        for (int i = 0; i < A; ++i) {
-            const unsigned o = leaves && (unsigned)(x0 + i) < (unsigned)g.W ? (unsigned)(first + i) * 4u : kOutsideBytes;
-            const float v = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)o, 0, 0));
-            d[i] = leaves ? v : d[i];
-        }
-    }
-    // columns left or right of the image were read from the neighbouring row
-#pragma unroll
-    for (int i = 0; i < A; ++i) d[i] = (unsigned)(x0 + i) < (unsigned)g.W ? d[i] : 0.f;
+    load_tile_row<A>(x, g.x_bytes, first, x0, g.W, live, d);
     float out[A];
     bt_apply<A>(bt, d, out);
     if (!live) return;
