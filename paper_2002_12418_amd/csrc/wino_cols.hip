@@ -9,10 +9,10 @@
 // F(4,7) on 16 x 64 x 112 x 112 moves 514 MB this way where separate transforms move 1.39 GB, for more vector instructions: a block of output channels
 // transforms its tiles anew.  So it pays for few outputs per tile and many taps: kernels of 5 taps and more (F(6,3) on 16 x 128 x 64 x 64: 69 us against 72
 // for separate kernels, F(8,3) 83 against 68).
-// Measured against the best of the other arrangements, us: F(4,5) 16 x 128 x 64 x 64 125 -> 100, 8 x 256 x 56 x 56 139 -> 126; F(4,7) 16 x 64 x 112 x 112 222 -> 180;
+// Measured against the best of the other arrangements, us: F(4,5) 16 x 128 x 64 x 64 125 -> 100, 8 x 256 x 56 x 56 139 -> 126; F(4,7) 16 x 64 x 112 x 112 222 -> 188;
 // F(2,7) there 458 -> 357, 96 -> 192 channels on 8 x 80 x 80 367 -> 325.  Behind them where tiles are few (F(4,7) 4 x 128 x 28 x 28 39, 32; wino_cols_offered) and where
 // channels are (F(4,5) 16 x 32 x 112 x 112 95, 60): the planner times all.
-// Of the 180: rows in 28 and rows out 36 at 5 to 6 TB/s, columns 115, where the matrix cores are busy 23 % and the vector units 50 % of the cycles
+// Of the 188: rows in 30 and rows out 35 at 5 to 6 TB/s, columns 112 to 134, where the matrix cores are busy 23 % and the vector units 50 % of the cycles
 // (F(4,5): 61 of 100, matrix cores 55 %).  Tried for that kernel: four wavefronts that stage and four that multiply, walking over blocks (F(4,7) 115,
 // F(4,5) 85: one wavefront of a SIMD issues a vector instruction every 8 cycles where each needs the one before); the same walk with all
 // eight doing both (registers spill); matrix and vector instructions interleaved by the compiler (F(4,5) 71); one buffer and two workgroups of
