@@ -163,3 +163,36 @@ def test_rows_stored_element_by_element(M, hw):
             got = y.cpu().numpy().astype(np.float64)
             assert np.isnan(got[N * M * hw:]).all(), name
             assert (np.abs(got[:N * M * hw].reshape(N, M, hw) - ref) <= bound).all(), name
+
+
+@pytest.mark.parametrize("M", [4, 25, 33, 72, 130])
+def test_stores_of_products_loaded_in_16_bytes(M):
+    """Operands that every kernel loads 16 bytes at a time, results that can be stored so and results that lie 4 bytes off, with and without a bias.
+    Bound as above, R = 21."""
+    m = mnn()
+    N, R, hw = 3, 21, 36
+    rng = np.random.default_rng(M)
+    x = rng.uniform(-1, 1, (N, R, hw)).astype(np.float32)
+    w = rng.normal(0, 1, (M, R)).astype(np.float32)
+    b = rng.uniform(-1, 1, (M,)).astype(np.float32)
+    ld = (M + 3) // 4 * 4
+    Wt = np.zeros((R, ld), np.float32)
+    Wt[:, :M] = w.T
+    xd, Wtd, bd = (torch.from_numpy(a).cuda() for a in (x, Wt, b))
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    for bias in (None, bd):
+        add = 0.0 if bias is None else b.astype(np.float64)[None, :, None]
+        ref = np.matmul(w64, x64) + add
+        bound = 2.0 ** -19 * (np.matmul(np.abs(w64), np.abs(x64)) + np.abs(add))
+        for v, name in enumerate(m.gemm_variants()):
+            both = []
+            for off in (0, 1):
+                y = torch.full((off + N * M * hw + 64,), float("nan"), device="cuda")[off:]
+                m.gemm_f32(Wtd, xd, y, bias, M=M, ncols=N * hw, R=R, batch=1, lda=ld, L=hw, variant=v,
+                           strideB_img=R * hw, strideB_row=hw, strideD_img=M * hw, strideD_row=hw)
+                torch.cuda.synchronize()
+                got = y.cpu().numpy()
+                assert np.isnan(got[N * M * hw:]).all(), (name, off)
+                both.append(got[:N * M * hw].reshape(N, M, hw))
+            assert np.array_equal(both[0], both[1]), name
+            assert (np.abs(both[0].astype(np.float64) - ref) <= bound).all(), name
