@@ -395,20 +395,21 @@ int mnn_conv_run(mnn_conv_plan_t plan, const float* input, const float* weight, 
 
 namespace {
 // Whether the call that prepares its weights each time and cannot time anything takes the one-kernel arrangement.  Measured on both, whole calls
-// in us, 415 shapes (1 to 32 images, 3 to 256 channels, 6 to 147 pixels wide, alpha 3 to 6): the separate kernels, the transforms of input and
-// weights in one launch, cost 0.25 per megabyte of V and M written and read; the one kernel costs 1.5 and 1/8 per position for each chunk of 16 channels that
-// a workgroup walks, one workgroup per CU at a time, and 0.5 per tap beyond 3 (its weights).  Where the two transforms take a launch each, the separate
-// kernels cost 7 more.  F(2,3) one image 64 -> 64 56 x 56 14.0 separate, 21.3 one; 112 x 112 30.9, 21.8; F(3,3) 8 x 17 -> 35 40 x 41 16.1, 22.6;
-// F(2,3) 5 x 3 -> 7 31 x 33 12.9, 13.2.  The rule loses 0.8 % on average against the better of the two, 27 % at most (F(3,4) 32 x 62 -> 179 16 x 13 42.3, 34.8).
+// in us, 712 shapes (1 to 32 images, 3 to 256 channels, 6 to 147 pixels wide, alpha 3 to 6).  The separate kernels cost 5.2 more to begin with, 0.25 per megabyte of V and M
+// written and read, 2.8 per GFLOP of their products, and 8.7 where the transforms of input and weights take a launch each.  The one kernel costs,
+// one workgroup per CU at a time, 0.29 per position, and 0.07 per position and 0.58 for each chunk of 16 channels that it walks; 1.5 more per megabyte
+// of transformed weights, which it cuts into parts, and 0.5 per tap.  F(2,3) one image 64 -> 64 56 x 56 14.0 separate, 21.3 one; 112 x 112 30.9, 21.8; F(3,3)
+// 8 x 17 -> 35 40 x 41 16.1, 22.6; 80 x 81 40.5, 34.1; F(4,2) 8 x 176 -> 31 74 x 69 55.9, 48.0.  Fitted to 415 of the shapes the rule loses 0.4 % on average against
+// the better of the two there, on the other 297 0.5 %, 29 % at most (F(2,3) one image 53 -> 287 39 x 71 28.9, 22.4).
 bool one_kernel_sooner(const WinoGeom& g)
 {
     if (!wino_full_available(g.n, g.k)) return false;
     const double a2 = (double)g.alpha * g.alpha, per_block = wino_full_block_channels(g.alpha);
-    const double wgs = std::ceil(g.K / per_block) * std::ceil(g.P / 32.0);
-    const double chunks = std::ceil(g.C / 16.0) * std::ceil(wgs / 256.0);
-    const double bytes = 4.0 * a2 * g.P * 2.0 * ((double)g.C + g.K);
-    const double launches = input_filter_short(g) ? 0.0 : 7.0;
-    return 1.5 + a2 * chunks / 8.0 + 0.5 * (g.k - 3) < launches + 0.25e-6 * bytes;
+    const double rounds = std::ceil(std::ceil(g.K / per_block) * std::ceil(g.P / 32.0) / 256.0), chunks = std::ceil(g.C / 16.0);
+    const double vm_bytes = 4.0 * a2 * g.P * 2.0 * ((double)g.C + g.K), u_bytes = 4.0 * a2 * g.K * g.C, flops = 2.0 * a2 * g.P * g.C * g.K;
+    const double launches = input_filter_short(g) ? 0.0 : 8.7;
+    return 0.29 * a2 * rounds + 0.07 * a2 * rounds * chunks + 0.58 * chunks + 1.5e-6 * u_bytes + 0.5 * g.k <
+           5.2 + 0.25e-6 * vm_bytes + 2.8e-9 * flops + launches;
 }
 }  // namespace
 

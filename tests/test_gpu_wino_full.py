@@ -193,7 +193,7 @@ def test_weights_that_three_parts_do_not_hold(value, n):
 @pytest.mark.parametrize("shape,n,one", [
     ((1, 64, 28, 28, 64, 3, 1), 2, False), ((1, 64, 112, 112, 64, 3, 1), 2, True), ((1, 128, 14, 14, 130, 3, 1), 2, False),
     ((16, 32, 56, 56, 64, 3, 1), 4, True), ((1, 64, 56, 56, 64, 3, 1), 4, False), ((5, 3, 31, 33, 7, 3, 1), 2, False),
-    ((8, 17, 40, 41, 35, 3, 1), 3, False), ((8, 17, 80, 81, 35, 3, 1), 3, True), ((2, 40, 9, 9, 33, 5, 2), 2, False),
+    ((8, 17, 40, 41, 35, 3, 1), 3, False), ((8, 17, 80, 81, 35, 3, 1), 3, True), ((1, 248, 104, 102, 46, 3, 1), 2, True), ((2, 40, 9, 9, 33, 5, 2), 2, False),
 ], ids=str)
 def test_allocation_free_call_takes_the_arrangement_its_rule_names(shape, n, one):
     """Of the one-kernel and the separate arrangement the call without timing takes the one that was faster for such sizes; the scratch
