@@ -50,7 +50,8 @@ typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 // order) before the store.  A 32 x 32 output tile is one MFMA tile: with WK = 4 its reduction still runs on all
 // four SIMDs of a CU, so that a problem with few output elements and a long reduction (batch-1 layers) spreads
 // over four times as many workgroups without a second kernel.
-template <int BM, int BN, int BK, int WM, int WN, int MODE, int PF = 1, bool BUF = true, int WK = 1>
+// LEAN: results stored by store_tiles_lean (gemm_epilogue.hpp).
+template <int BM, int BN, int BK, int WM, int WN, int MODE, int PF = 1, bool BUF = true, int WK = 1, bool LEAN = false>
 __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmArgs p, int tilesM, int tilesN, int total,
                                                                 unsigned a_bytes, unsigned b_bytes, int vecD, int ldc)
 {
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void gemm_f32_kernel(GemmArgs p,
     // ---- results (or this slice's partial results) to memory
     const TileDest dest = tile_dest(p, b, split, splitk, ldc);
     const int mw0 = m0 + wm * (BM / WM), nw0 = n0 + wn * (BN / WN);
-    if constexpr (MODE == 1) store_tiles_lean<TM, TN>(acc, dest, p.M, p.Ncols, mw0, nw0, lane, smem + wmn * kStageFloats, vecD);
+    if constexpr (LEAN) store_tiles_lean<TM, TN>(acc, dest, p.M, p.Ncols, mw0, nw0, lane, smem + wmn * kStageFloats, vecD);
     else store_tiles<TM, TN, false>(acc, dest, p.M, p.Ncols, mw0, nw0, lane, smem + wmn * kStageFloats, vecD);
 }
 
@@ -466,8 +467,11 @@ hipError_t launch_cfg(const GemmProblem& p, bool vec, hipStream_t s)
     if (p.gather)
         hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, 2, PF, BUF, WK>), grid, block, 0, s, p, tilesM, tilesN,
                            (int)total, ex.a_bytes, ex.b_bytes, vecD, ldc);
-    else if (vec)
+    else if (vec && p.bias && p.batch == 1 && splitk == 1)
         hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, 1, PF, BUF, WK>), grid, block, 0, s, p, tilesM, tilesN,
+                           (int)total, ex.a_bytes, ex.b_bytes, vecD, ldc);
+    else if (vec)
+        hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, 1, PF, BUF, WK, true>), grid, block, 0, s, p, tilesM, tilesN,
                            (int)total, ex.a_bytes, ex.b_bytes, vecD, ldc);
     else
         hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, 0, PF, BUF, WK>), grid, block, 0, s, p, tilesM, tilesN,

@@ -130,7 +130,8 @@ __device__ __forceinline__ void store_tiles(const Acc (&acc)[TM][TN], const Tile
 
 // The same with few registers, bias values loaded where they are added: for the fp32 kernels whose operands come in 16-byte loads, and whose results
 // nearly always take 16-byte stores.  With store_tiles they had room for a wavefront per SIMD less: without a bias 81 x 13 x 41 x 10000 in 64 x 128
-// 34.7 -> 37.5 us, 16 x 8 x 51 x 32256 22.3 -> 24.0, 36 x 128 x 128 x 6272 in 64 x 256 81.5 -> 88.2.
+// 34.7 -> 37.5 us, 16 x 8 x 51 x 32256 22.3 -> 24.0, 36 x 128 x 128 x 6272 in 64 x 256 81.5 -> 88.2.  One product with a bias, a pointwise layer, is better off
+// with store_tiles all the same: 25 -> 226 on 8 x 8 x 57 12.1 -> 10.5, 64 x 64 x 12544 in 64 x 128 7.8 -> 7.1; batches with one are not (81 x 13 x 41 x 10000 57.7, 60.8).
 template <int TM, int TN, typename Acc>
 __device__ __forceinline__ void store_tiles_lean(const Acc (&acc)[TM][TN], const TileDest& d, int M, int Ncols, int mw0,
                                                  int nw0, int lane, float* stage, int vec)
