@@ -9,6 +9,8 @@ using InputCapKey = std::tuple<int, std::vector<int>>;
 std::mutex g_input_cap_mu;
 std::map<InputCapKey, int> g_input_cap;
 
+const float kSomeBias = 0.f;      // only "is there a bias" enters the key of a remembered choice
+
 // ------------------------------------------------------------------ one realised scheme
 struct Impl {
     mnn_scheme scheme{};
@@ -211,10 +213,12 @@ struct Impl {
             // implicit GEMM on the matrix cores: weights transposed to [C*kh*kw][ldk]
             if ((long long)sh.n * L.Ho * L.Wo >= (1ll << 31) || (long long)sh.n * sh.c_in * sh.h * sh.w >= (1ll << 31))
                 return fail(MNN_E_UNSUPPORTED, "tensor too large for the sliding-window kernel");
-            U_bytes = (size_t)sh.c_in * sh.kh * sh.kw * ldk * sizeof(float);
-            // (not where fixed scratch bounds U; the tuner sizes U anew when it takes one of them)
-            const GemmProblem p = direct_gemm_problem(nullptr, nullptr, nullptr);
+            // (not where fixed scratch bounds U; U takes the form of a remembered choice, or is sized anew when the tuner takes the other)
+            const GemmProblem p = direct_gemm_problem(nullptr, &kSomeBias, nullptr);
             patch_offered = !persistent_external && conv_patch_offered(p) && conv_patch_covers(p);
+            GemmChoice known{0, 1};
+            const bool patch = patch_offered && cached_gemm_choice(p, &known) && gemm_variant_is_patch(s.prec, known.variant);
+            U_bytes = patch ? patch_weight_bytes() : plain_weight_bytes();
             int rcd = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
             if (rcd) return rcd;
             return MNN_OK;
@@ -268,6 +272,7 @@ struct Impl {
 
     // whether the prepared weights have the form that the patch kernels read
     bool patch_weights() const { return patch_offered && gemm_variant_is_patch(scheme.prec, gemm_variant); }
+    size_t plain_weight_bytes() const { return (size_t)L.s.c_in * L.s.kh * L.s.kw * ldk * sizeof(float); }
     size_t patch_weight_bytes() const { return conv_patch_weight_bytes(L.s.c_out, L.s.c_in, L.s.kh * L.s.kw); }
 
     GemmProblem direct_gemm_problem(const float* x, const float* b, float* y) const
@@ -306,10 +311,11 @@ struct Impl {
     {
         const bool elsewhere = gemm_variant_is_patch(p.prec, c.variant) && !patch_offered;      // a saved choice that does not apply
         const int rc = adopt(p, elsewhere ? GemmChoice{0, 1} : c);
-        if (rc || !patch_weights()) return rc;
+        const size_t bytes = patch_weights() ? patch_weight_bytes() : plain_weight_bytes();
+        if (rc || persistent_external || U_bytes == bytes) return rc;
         (void)hipFree(U);
-        U_bytes = patch_weight_bytes();
-        return alloc_persistent(&U, U_bytes, "hipMalloc Wp");
+        U_bytes = bytes;
+        return alloc_persistent(&U, U_bytes, "hipMalloc Wt");
     }
 
     // Resident wavefronts per CU of the input transform (WinoGeom::itx_waves), remembered per geometry.  What is timed is the
@@ -425,7 +431,6 @@ struct Impl {
     int tune_gemm_stage(hipStream_t s)
     {
         GemmChoice c{0, 1};
-        static const float dummy_bias = 0.f;      // only "is there a bias" enters the cache key
         if (scheme.kind == MNN_SCHEME_WINOGRAD && scheme.variant == MNN_WINO_UNFUSED) {
             const GemmProblem p = wino_gemm_problem();
             if (transient_external) {
@@ -465,7 +470,7 @@ struct Impl {
             auto take = [&](const GemmProblem& p) { return direct ? adopt_direct(p, c) : adopt(p, c); };
             {
                 // a shape tuned before needs no scratch tensors (the key holds no addresses)
-                const GemmProblem q = direct ? direct_gemm_problem(nullptr, &dummy_bias, nullptr) : pointwise_gemm_problem(nullptr, &dummy_bias, nullptr);
+                const GemmProblem q = direct ? direct_gemm_problem(nullptr, &kSomeBias, nullptr) : pointwise_gemm_problem(nullptr, &kSomeBias, nullptr);
                 if (cached_gemm_choice(q, &c)) return take(q);
             }
             if ((e = hipMalloc((void**)&tx, xb)) != hipSuccess || (e = hipMalloc((void**)&ty, yb)) != hipSuccess ||
