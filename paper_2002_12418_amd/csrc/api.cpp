@@ -718,7 +718,8 @@ int mnn_gemm_variant_count(int32_t prec)
 
 const char* mnn_gemm_variant_name(int32_t prec, int32_t variant)
 {
-    return (prec < MNN_GEMM_FP32 || prec > MNN_GEMM_BF16X3) ? nullptr : gemm_variant_name(prec, variant);
+    if (prec < MNN_GEMM_FP32 || prec > MNN_GEMM_BF16X3 || variant >= gemm_named_variant_count(prec)) return nullptr;
+    return gemm_variant_name(prec, variant);
 }
 
 int mnn_conv_get_device_model(mnn_device_model* out)

@@ -22,6 +22,7 @@
 #include "gemm_epilogue.hpp"
 #include "bf16_parts.hpp"
 #include "fast_div.hpp"
+#include "patch_rect.hpp"
 
 namespace mnnconv {
 namespace {
@@ -29,15 +30,10 @@ namespace {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kPatchChannels = 16;           // channels per chunk: the depth of one matrix instruction
 
-struct PatchArgs {
-    int ni, ty, tx;              // output rectangle of a workgroup
-    int ph, pw;                  // its patch, per image
-    int pws;                     // a patch row is stored as stride_w runs of pws pixels, so that a run holds what consecutive columns read
-    int pp, ppr;                 // slots and pixels of the patch, all images
-    int tilesM, tilesX, tilesY, total;
+struct PatchArgs : PatchRect {
+    int tilesM, total;
     int nch;                     // chunks of channels
     int nbuf;                    // patch buffers: 2 where they fit
-    int vecD;                    // four columns from a multiple of four on are four floats in a row, 16-byte aligned
     int N, Ho;
     unsigned a_bytes, b_bytes;
     FastDiv by_pw, by_ph, by_tx, by_ty, by_sw, by_tm, by_tiles_x, by_tiles_y;
@@ -421,43 +417,9 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patc
 constexpr int kPatchLds = 160 * 1024 - 1024;
 constexpr int kPatchPixels = 768;            // of a patch that 128 columns see
 
-// The rectangle of output pixels of one workgroup: as few workgroups as `bn` columns allow, then 16-byte stores, then the smallest patch.  False where no patch fits.
-bool choose_rectangle(const GemmProblem& p, int bn, PatchArgs* out)
+bool choose_rectangle(const GemmProblem& p, int bn, PatchRect* out)
 {
-    const int max_px = kPatchPixels * bn / 128, lds = kPatchLds;
-    const int Ho = p.L / p.cv_Wo, Wo = p.cv_Wo, N = p.Ncols / p.L;
-    bool found = false;
-    long long best = 0;
-    auto consider = [&](int ni, int ty, int tx) {
-        PatchArgs a{};
-        a.ni = ni; a.ty = ty; a.tx = tx;
-        const long long ph = (long long)(ty - 1) * p.cv_sh + (long long)(p.cv_kh - 1) * p.cv_dh + 1;
-        const long long pw = (long long)(tx - 1) * p.cv_sw + (long long)(p.cv_kw - 1) * p.cv_dw + 1;
-        if (ph > max_px || pw > max_px || ni * ph * pw > max_px) return;
-        a.ph = (int)ph; a.pw = (int)pw;
-        a.pws = (a.pw + p.cv_sw - 1) / p.cv_sw;
-        a.ppr = ni * a.ph * a.pw;
-        a.pp = ni * a.ph * a.pws * p.cv_sw;
-        if ((long long)a.pp * 96 > lds) return;
-        a.tilesX = (Wo + tx - 1) / tx;
-        a.tilesY = (Ho + ty - 1) / ty;
-        const long long tiles = (long long)a.tilesX * a.tilesY * ((N + ni - 1) / ni);
-        // runs of columns, a row of the rectangle or all its rows where they span the plane, that 16-byte stores can take
-        a.vecD = (tx == Wo ? ty * tx % 4 == 0 && p.L % 4 == 0 : tx % 4 == 0 && Wo % 4 == 0) ? 1 : 0;
-        if (found && (tiles > best || (tiles == best && (a.vecD < out->vecD || (a.vecD == out->vecD && a.pp >= out->pp))))) return;
-        found = true;
-        best = tiles;
-        *out = a;
-    };
-    auto level = [](int size, int most) { const int parts = (size + most - 1) / most; return (size + parts - 1) / parts; };
-    if ((long long)Ho * Wo <= bn) consider(level(N, bn / (Ho * Wo)), Ho, Wo);
-    const int least = (Wo + bn - 1) / bn;                 // columns of rectangles
-    for (int parts = least; parts < least + 12; ++parts) {
-        const int tx = (Wo + parts - 1) / parts;
-        consider(1, level(Ho, bn / tx), tx);
-        if (tx <= 4) break;
-    }
-    return found;
+    return choose_patch_rect(p, bn, kPatchPixels * bn / 128, kPatchLds / 96, true, out);
 }
 
 template <int BM, int BN, int WM, int WN, int ITEMS, int NS>

@@ -20,4 +20,15 @@ inline FastDiv make_fastdiv(unsigned d)
 }
 __device__ __forceinline__ unsigned fast_div(unsigned n, const FastDiv& f) { return f.d <= 1 ? n : (__umulhi(n, f.m) >> f.sh); }
 
+// The same without a branch for d = 1: q = n * m >> (31 + L).
+struct ConstDiv { unsigned m, L, d; };
+inline ConstDiv make_constdiv(unsigned d)
+{
+    ConstDiv f{0u, 0u, d < 1 ? 1 : d};
+    while ((1u << f.L) < f.d) ++f.L;
+    f.m = (unsigned)((((unsigned long long)1 << (31 + f.L)) + f.d - 1) / f.d);
+    return f;
+}
+__device__ __forceinline__ unsigned const_div(unsigned n, const ConstDiv& f) { return __umulhi(n + n, f.m) >> f.L; }
+
 }  // namespace mnnconv

@@ -522,18 +522,26 @@ constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 // the variants after the fp32 ones
 const GemmVariant& x6_variant(int i)
 {
-    const int shorts = gemm_split6_variant_count(), patches = shorts + gemm_short_variant_count();
-    return i < shorts ? gemm_split6_variant(i) : i < patches ? gemm_short_variant(i - shorts) : conv_patch_variant(i - patches);
+    const int shorts = gemm_split6_variant_count(), patches = shorts + gemm_short_variant_count(), short_patches = patches + conv_patch_variant_count();
+    return i < shorts ? gemm_split6_variant(i) : i < patches ? gemm_short_variant(i - shorts)
+           : i < short_patches ? conv_patch_variant(i - patches) : conv_short_variant(i - short_patches);
 }
 
 static int first_patch_variant() { return kNumVariants + gemm_split6_variant_count() + gemm_short_variant_count(); }
 
-bool gemm_variant_is_patch(int prec, int v) { return prec == 0 && v >= first_patch_variant() && v < gemm_f32_variant_count(); }
+int gemm_named_variant_count(int prec) { return prec == 0 ? first_patch_variant() + conv_patch_variant_count() : gemm_variant_count(prec); }
+
+WeightForm gemm_variant_weights(int prec, int v)
+{
+    if (prec != 0 || v < first_patch_variant() || v >= gemm_f32_variant_count()) return WeightForm::Rows;
+    const int i = v - gemm_named_variant_count(0);
+    return i >= 0 && conv_short_takes_octets(i) ? WeightForm::Octets : WeightForm::Parts;
+}
 
 int gemm_product_variant_count(int prec) { return prec == 0 ? first_patch_variant() : gemm_variant_count(prec); }
 
 // Variant ids: 0 = choose from the shape, 1 .. kNumVariants-1 = the tile configurations above.
-int gemm_f32_variant_count() { return first_patch_variant() + conv_patch_variant_count(); }
+int gemm_f32_variant_count() { return first_patch_variant() + conv_patch_variant_count() + conv_short_variant_count(); }
 const char* gemm_f32_variant_name(int v)
 {
     if (v < 0 || v >= gemm_f32_variant_count()) return nullptr;
@@ -563,7 +571,8 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 bool gemm_variant_tuned(const GemmProblem& p, int v)
 {
     if (v < 1 || v >= gemm_variant_count(p.prec)) return false;
-    if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && conv_patch_offered(p);
+    if (p.prec == 0 && v >= gemm_named_variant_count(0)) return conv_short_offered(p, v - gemm_named_variant_count(0));
+    if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && conv_patch_offered(p) && conv_patch_covers(p);
     if (p.prec != 0 || v >= kNumVariants) return true;
     static const char* const kept[] = {"64x64x16_w2x2", "64x128x16_w1x4", "128x64x16_w2x2", "64x32x32_w2x1k2_pf2"};
     for (const char* k : kept)
@@ -650,7 +659,8 @@ hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s)
     const bool vec = aligned16(p.B) && (p.L % 4 == 0) && (p.Ncols % 4 == 0) && (p.strideB_batch % 4 == 0) &&
                      (p.strideB_img % 4 == 0) && (p.strideB_row % 4 == 0);
     int v = p.variant;
-    if (gemm_variant_is_patch(0, v) && !p.a_parts) v = 0;           // weights in the common form
+    const WeightForm form = gemm_variant_weights(0, v);
+    if ((form == WeightForm::Parts && !p.a_parts) || (form == WeightForm::Octets && !p.a_octets)) v = 0;           // weights in the common form
     if (v == 0) v = auto_variant(p, vec);
     const hipError_t e = v < kNumVariants ? kVariants[v].fn(p, vec, s) : x6_variant(v - kNumVariants).fn(p, vec, s);
     if (e != hipErrorNotSupported) return e;

@@ -27,7 +27,8 @@ struct Impl {
     int gemm_variant = 0;      // tile configuration of the GEMM stage (0 = shape heuristic)
     int gemm_splitk = 1;       // workgroups per tile along the reduction
     float* sk_partial = nullptr; size_t sk_partial_bytes = 0;
-    bool patch_offered = false;   // sliding window: the patch kernels, whose weights have a form of their own, may be chosen
+    // sliding window: the kernels on staged patches (conv_patch.hip, conv_short.hip), whose weights have a form of their own, may be chosen
+    bool patch_offered = false, short_offered = false;
     // V, M and the split-K partials hold nothing between two runs.  A plan on its own allocates them;
     // a chain of layers binds them to a region of its arena instead (bind_transient).
     bool transient_external = false;
@@ -216,9 +217,10 @@ struct Impl {
             // (not where fixed scratch bounds U; U takes the form of a remembered choice, or is sized anew when the tuner takes the other)
             const GemmProblem p = direct_gemm_problem(nullptr, &kSomeBias, nullptr);
             patch_offered = !persistent_external && conv_patch_offered(p) && conv_patch_covers(p);
+            short_offered = !persistent_external && conv_short_covers(p);
             GemmChoice known{0, 1};
-            const bool patch = patch_offered && cached_gemm_choice(p, &known) && gemm_variant_is_patch(s.prec, known.variant);
-            U_bytes = patch ? patch_weight_bytes() : plain_weight_bytes();
+            (void)cached_gemm_choice(p, &known);
+            U_bytes = weight_bytes(weight_form(known.variant));
             int rcd = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
             if (rcd) return rcd;
             return MNN_OK;
@@ -270,10 +272,31 @@ struct Impl {
         return p;
     }
 
-    // whether the prepared weights have the form that the patch kernels read
-    bool patch_weights() const { return patch_offered && gemm_variant_is_patch(scheme.prec, gemm_variant); }
-    size_t plain_weight_bytes() const { return (size_t)L.s.c_in * L.s.kh * L.s.kw * ldk * sizeof(float); }
-    size_t patch_weight_bytes() const { return conv_patch_weight_bytes(L.s.c_out, L.s.c_in, L.s.kh * L.s.kw); }
+    // the form of the sliding window's prepared weights that a configuration reads
+    WeightForm weight_form(int variant) const
+    {
+        const bool offered = variant < gemm_named_variant_count(scheme.prec) ? patch_offered : short_offered;
+        return offered ? gemm_variant_weights(scheme.prec, variant) : WeightForm::Rows;
+    }
+    WeightForm weight_form() const { return weight_form(gemm_variant); }
+    size_t weight_bytes(WeightForm f) const
+    {
+        const int taps = L.s.kh * L.s.kw;
+        switch (f) {
+            case WeightForm::Parts: return conv_patch_weight_bytes(L.s.c_out, L.s.c_in, taps);
+            case WeightForm::Octets: return octet_weight_bytes(L.s.c_out, L.s.c_in, taps);
+            default: return (size_t)L.s.c_in * taps * ldk * sizeof(float);
+        }
+    }
+    hipError_t prepare_weights(WeightForm f, const float* w, void* to, hipStream_t s) const
+    {
+        const int taps = L.s.kh * L.s.kw;
+        switch (f) {
+            case WeightForm::Parts: return launch_patch_weights(w, to, L.s.c_out, L.s.c_in, taps, s);
+            case WeightForm::Octets: return launch_octet_weights(w, to, L.s.c_out, L.s.c_in, taps, s);
+            default: return launch_weight_transpose(w, (float*)to, L.s.c_out, L.s.c_in * taps, ldk, s);
+        }
+    }
 
     GemmProblem direct_gemm_problem(const float* x, const float* b, float* y) const
     {
@@ -285,7 +308,8 @@ struct Impl {
         p.lda = ldk; p.L = HoWo;
         p.strideD_img = (long long)sh.c_out * HoWo; p.strideD_row = HoWo;
         set_gemm_choice(&p);
-        p.a_parts = patch_weights() ? U : nullptr;
+        p.a_parts = weight_form() == WeightForm::Parts ? U : nullptr;
+        p.a_octets = weight_form() == WeightForm::Octets ? U : nullptr;
         p.gather = 1;
         p.cv_C = sh.c_in; p.cv_H = sh.h; p.cv_W = sh.w; p.cv_kh = sh.kh; p.cv_kw = sh.kw;
         p.cv_sh = L.g.stride_h; p.cv_sw = L.g.stride_w; p.cv_ph = L.g.pad_h; p.cv_pw = L.g.pad_w;
@@ -309,9 +333,9 @@ struct Impl {
     // the same for the sliding window, where U then takes the size of the form that the chosen kernel reads
     int adopt_direct(const GemmProblem& p, const GemmChoice& c)
     {
-        const bool elsewhere = gemm_variant_is_patch(p.prec, c.variant) && !patch_offered;      // a saved choice that does not apply
+        const bool elsewhere = gemm_variant_weights(p.prec, c.variant) != weight_form(c.variant);      // a saved choice that does not apply
         const int rc = adopt(p, elsewhere ? GemmChoice{0, 1} : c);
-        const size_t bytes = patch_weights() ? patch_weight_bytes() : plain_weight_bytes();
+        const size_t bytes = weight_bytes(weight_form());
         if (rc || persistent_external || U_bytes == bytes) return rc;
         (void)hipFree(U);
         U_bytes = bytes;
@@ -463,7 +487,7 @@ struct Impl {
             const mnn_conv_shape& sh = L.s;
             const size_t xb = (size_t)sh.n * sh.c_in * sh.h * sh.w * sizeof(float);
             const size_t yb = (size_t)sh.n * sh.c_out * L.Ho * L.Wo * sizeof(float);
-            float *tx = nullptr, *ty = nullptr, *tb = nullptr, *tp = nullptr;
+            float *tx = nullptr, *ty = nullptr, *tb = nullptr, *tp = nullptr, *to = nullptr;
             hipError_t e;
             int rc = MNN_OK;
             const bool direct = scheme.kind == MNN_SCHEME_DIRECT;
@@ -482,12 +506,15 @@ struct Impl {
                         (e = launch_fill_pattern(U, U_bytes / sizeof(float), 0x61u, -0.5f, 0.5f, s)) != hipSuccess))
                 rc = fail_hip(e, "tuning scratch fill");
             GemmProblem p = direct ? direct_gemm_problem(tx, tb, ty) : pointwise_gemm_problem(tx, tb, ty);
-            if (!rc && direct && patch_offered) {
-                // the weights once more in the patch kernels' form; without room for them those kernels are not candidates
-                if (hipMalloc((void**)&tp, patch_weight_bytes()) != hipSuccess) { tp = nullptr; (void)hipGetLastError(); }
-                else if ((e = launch_patch_weights(U, tp, sh.c_out, sh.c_in, sh.kh * sh.kw, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
-                p.a_parts = tp;
-            }
+            // the weights once more in the other forms; without room for them their kernels are not candidates
+            auto other_form = [&](WeightForm f, float** t) {
+                if (hipMalloc((void**)t, weight_bytes(f)) != hipSuccess) { *t = nullptr; (void)hipGetLastError(); }
+                else if ((e = prepare_weights(f, U, *t, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
+            };
+            if (!rc && direct && (patch_offered || short_offered)) other_form(WeightForm::Parts, &tp);
+            if (!rc && direct && short_offered) other_form(WeightForm::Octets, &to);
+            p.a_parts = tp;
+            p.a_octets = to;
             if (!rc) rc = tune_gemm(p, s, &c);
             if (!rc && ((e = hipMemsetAsync(U, 0, U_bytes, s)) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess))
                 rc = fail_hip(e, "tuning operand reset");
@@ -495,6 +522,7 @@ struct Impl {
             if (ty) (void)hipFree(ty);
             if (tb) (void)hipFree(tb);
             if (tp) (void)hipFree(tp);
+            if (to) (void)hipFree(to);
             return rc ? rc : take(p);
         }
         return MNN_OK;
@@ -566,8 +594,7 @@ struct Impl {
             }
         } else {
             if (st == MNN_STAGE_FILTER)
-                e = patch_weights() ? launch_patch_weights(w, U, sh.c_out, sh.c_in, sh.kh * sh.kw, s)
-                                    : launch_weight_transpose(w, U, sh.c_out, sh.c_in * sh.kh * sh.kw, ldk, s);
+                e = prepare_weights(weight_form(), w, U, s);
             else
                 e = launch_gemm_f32(direct_gemm_problem(x, b, y), s);
         }

@@ -72,9 +72,9 @@ int tune_gemm(GemmProblem p, hipStream_t s, GemmChoice* out)
     int rc = MNN_OK;
     const bool tune_log = std::getenv("MNNCONV_TUNE_LOG") != nullptr;    // one line per timed configuration on stderr
     for (int v = 1; v < gemm_variant_count(p.prec) && !rc; ++v) {
-        if (!gemm_variant_tuned(p, v)) continue;
         p.variant = v;
         p.splitk = 1; p.splitk_partial = nullptr;
+        if (!gemm_variant_tuned(p, v)) continue;
         float ms = -1.f;
         if ((rc = time_gemm(p, s, e0, e1, iters, &ms))) break;
         if (ms >= 0.f && (best_ms < 0.f || ms < best_ms)) { best_ms = ms; best = GemmChoice{v, 1}; }

@@ -147,6 +147,7 @@ struct GemmArgs {
 // What the product kernels do not read stays out of their arguments (gemm_split.hip says why it matters).
 struct GemmProblem : GemmArgs {
     const void* a_parts;        // the patch kernels' weights (launch_patch_weights); At is then unused
+    const void* a_octets;       // the same for those of them that read fp32 (launch_octet_weights)
 };
 hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s);
 int gemm_f32_variant_count();
@@ -175,7 +176,17 @@ bool conv_patch_covers(const GemmProblem& p);       // whether the patch kernels
 bool conv_patch_offered(const GemmProblem& p);      // whether the planner times them
 size_t conv_patch_weight_bytes(int K, int C, int taps);
 hipError_t launch_patch_weights(const float* w, void* Wp, int K, int C, int taps, hipStream_t s);
-bool gemm_variant_is_patch(int prec, int variant);
+// the same for short grids (conv_short.hip), which have numbers after theirs and no public names
+int conv_short_variant_count();
+const GemmVariant& conv_short_variant(int i);
+bool conv_short_takes_octets(int i);
+bool conv_short_covers(const GemmProblem& p);
+bool conv_short_offered(const GemmProblem& p, int i);      // whether the planner times it
+size_t octet_weight_bytes(int K, int C, int taps);
+hipError_t launch_octet_weights(const float* w, void* Wq, int K, int C, int taps, hipStream_t s);
+// what a variant reads the weights of a sliding window from: At, a_parts or a_octets
+enum class WeightForm { Rows, Parts, Octets };
+WeightForm gemm_variant_weights(int prec, int variant);
 // bf16 / bf16x3 operands (gemm_split.hip; operands of 2 GiB and more: gemm_bf16.hip); launch_gemm_f32 forwards to them when prec != 0
 int gemm_bf16_variant_count();
 const char* gemm_bf16_variant_name(int variant);
@@ -185,6 +196,7 @@ bool gemm_bf16_variant_tile(int variant, int* bm, int* bn, int* bk);
 bool gemm_variant_tuned(const GemmProblem& p, int variant);     // whether the planner times it
 // variants of the table that serves precision `prec`
 inline int gemm_variant_count(int prec) { return prec == 0 ? gemm_f32_variant_count() : gemm_bf16_variant_count(); }
+int gemm_named_variant_count(int prec);         // of these, the ones with a public name
 int gemm_product_variant_count(int prec);       // of these, the ones that take any product: all but the patch kernels
 inline const char* gemm_variant_name(int prec, int v) { return prec == 0 ? gemm_f32_variant_name(v) : gemm_bf16_variant_name(v); }
 
