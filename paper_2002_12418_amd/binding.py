@@ -7,6 +7,7 @@ There is no CPU fallback: if libmnnconv.so is missing the import fails loudly.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 from ctypes import POINTER, byref, c_char_p, c_double, c_float, c_int32, c_size_t, c_void_p
 from dataclasses import dataclass
@@ -391,16 +392,28 @@ def cache_load(path: str) -> None:
 
 _current_stream = None   # () -> handle of the current stream, once a GPU was seen: asking for one costs more than the rest of a small call
 _float32 = None
+_fast_call = None        # the short way into mnn_conv_run and mnn_conv_run_static, once a GPU was seen
+_address = {}            # of the library's functions that it calls
 
 
 def _find_current_stream():
     """Looks the current stream up by the shortest way this torch has; None on a machine without a GPU."""
-    global _current_stream, _float32
+    global _current_stream, _float32, _fast_call
     import torch
     if not torch.cuda.is_available():
         return None
     torch.cuda.init()
     _float32 = torch.float32
+    if _fast_call is None:
+        try:
+            fast = importlib.import_module("._fast_call", __package__)
+        except ImportError:
+            from .build import build_fast_call
+            build_fast_call()
+            fast = importlib.import_module("._fast_call", __package__)
+        for f in ("mnn_conv_run", "mnn_conv_run_static"):
+            _address[f] = ctypes.cast(getattr(lib, f), c_void_p).value
+        _fast_call = fast
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is not None and device is not None:
         _current_stream = lambda: raw(device())          # 0.2 us; through torch.cuda.current_stream 1.4
@@ -422,7 +435,7 @@ class ConvPlan:
 
     def __init__(self, n, c_in, h, w, c_out, kh, kw, stride=1, pad=0, dil=1,
                  options: Optional[Options] = None, stream=None):
-        self._h = c_void_p()
+        self._h, self._fast = c_void_p(), None
         self.shape = (n, c_in, h, w, c_out, kh, kw)
         s, g = _shape_geom(n, c_in, h, w, c_out, kh, kw, stride, pad, dil)
         o = options._c() if options else None
@@ -435,6 +448,8 @@ class ConvPlan:
         if _float32 is None:
             _find_current_stream()   # a plan made with a stream of the caller's has not asked for one
         self._w_seen = None          # (address, torch version counter) of the weight tensor last handed to the library
+        # takes the usual call: the weight tensor that _w_seen names, nothing out of the ordinary
+        self._fast = _fast_call.Runner(_address["mnn_conv_run"], self._h.value, self._in_shape, self._w_shape, self._b_shape, self.out_shape)
 
     @classmethod
     def for_layer(cls, layer, options: Optional[Options] = None, stream=None) -> "ConvPlan":
@@ -481,6 +496,12 @@ class ConvPlan:
         if y is None:
             import torch
             y = torch.empty(self.out_shape, dtype=torch.float32, device=x.device)
+        if stream is None:
+            rc = self._fast(x, w, b, y)
+            if rc == 0:
+                return y
+            if rc is not None:
+                _check(rc)
         self._check_tensors(x, w, b, y)
         ptr = w.data_ptr()
         self._note_weight(w, ptr)
@@ -497,6 +518,7 @@ class ConvPlan:
         if self._w_seen is not None and self._w_seen[0][0] == seen[0] and self._w_seen[0] != seen:
             _check(lib.mnn_conv_invalidate_weights(self._h))
         self._w_seen = (seen, w)
+        self._fast.remember(w)
 
     def set_weights(self, w, stream=None):
         """mnn_conv_set_weights: prepare the weights now (after new values were written behind the same pointer by
@@ -507,6 +529,7 @@ class ConvPlan:
             raise ValueError("weight: expected contiguous float32 device tensor of shape (c_out, c_in, kh, kw)")
         _check(lib.mnn_conv_set_weights(self._h, w.data_ptr(), _stream_handle(stream)))
         self._w_seen = ((w.data_ptr(), w._version, id(w)), w)
+        self._fast.remember(w)
 
     def run_stage(self, stage: int, x, w, b, y, stream=None):
         self._check_tensors(x, w, b, y)
@@ -539,6 +562,8 @@ class ConvPlan:
 
     def close(self):
         if getattr(self, "_h", None) is not None and self._h.value:
+            if self._fast is not None:
+                self._fast.close()
             lib.mnn_conv_plan_destroy(self._h)
             self._h = c_void_p()
         self._w_seen = None
@@ -562,6 +587,12 @@ def static_scratch_bytes() -> int:
 
 def conv_run_static(layer, tile_n: int, x, w, b, y, stream=None):
     """mnn_conv_run_static: one convolution with no device allocation (scratch in the library's fixed array)."""
+    if stream is None and (_fast_call or (_find_current_stream() and _fast_call)):
+        rc = _fast_call.run_static(_address["mnn_conv_run_static"], layer, tile_n, x, w, b, y)
+        if rc == 0:
+            return y
+        if rc is not None:
+            _check(rc)
     s, g = _shape_geom(layer.n, layer.c_in, layer.h, layer.w, layer.c_out, layer.kh, layer.kw, layer.stride, layer.pad, layer.dil)
     _check(lib.mnn_conv_run_static(byref(s), byref(g), tile_n, x.data_ptr(), w.data_ptr(),
                                    b.data_ptr() if b is not None else None, y.data_ptr(), _stream_handle(stream)))

@@ -4,10 +4,12 @@
 """
 from __future__ import annotations
 
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +17,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG), "include")
 OBJ_DIR = os.path.join(PKG, "_build")
 LIB_PATH = os.path.join(PKG, "libmnnconv.so")
+FAST_CALL_PATH = os.path.join(PKG, "_fast_call.so")
 
 SOURCES = ["api.cpp", "transforms.hip", "transforms_rect.hip", "transforms_short.hip", "gemm.hip", "gemm_split.hip", "gemm_short.hip", "conv_patch.hip", "conv_short.hip", "weight_layout.hip", "fill.hip", "static_scratch.hip", "wino_fused.hip", "wino_full.hip", "wino_cols.hip", "gemm_bf16.hip", "strassen.hip", "microbench.hip"]
 
@@ -44,6 +47,20 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_fast_call() -> None:
+    """The short way from Python into the library (fast_call.cpp), against the headers of the torch that is installed."""
+    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    tmp = FAST_CALL_PATH + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", INCLUDE,
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(torch_dir, "include"), "-I", "/opt/rocm/include",
+           os.path.join(CSRC, "fast_call.cpp"), "-o", tmp, "-L", os.path.join(torch_dir, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on fast_call.cpp:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, FAST_CALL_PATH)
+
+
 def build_library(verbose: bool = True) -> str:
     """Compile every source for gfx950 and link paper_2002_12418_amd/libmnnconv.so."""
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -52,7 +69,9 @@ def build_library(verbose: bool = True) -> str:
         if stale.endswith(".o") and stale not in wanted:
             os.remove(os.path.join(OBJ_DIR, stale))
     with ThreadPoolExecutor(max_workers=min(6, len(SOURCES))) as ex:
+        fast = ex.submit(build_fast_call)
         objs = list(ex.map(_compile, SOURCES))
+        fast.result()
     tmp = LIB_PATH + ".tmp"
     cmd = [_hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
