@@ -7,12 +7,12 @@
 // A tap is then one more offset into the patch, the same for all lanes.  The weights are prepared as parts in operand order and go from the L2
 // straight to registers, one tap ahead.
 //
-// What bounds it (3 x 3 stride 2, 64 -> 128 on 32 x 56 x 56, 128 x 64 tiles, 30 us): 15 us of matrix instructions, which the power holds at 1.5 to 1.7 GHz; the rest
-// does not overlap with them, because the 448 workgroups are one round in step: launch and first patch 7 us, LDS reads and taps 3, the later
+// What bounds it (3 x 3 stride 2, 64 -> 128 on 32 x 56 x 56, 128 x 64 tiles, 29 us): 15 us of matrix instructions, which the power holds at 1.5 to 1.7 GHz; the rest
+// does not overlap with them, because the 448 workgroups are one round in step: launch and first patch 6 us, LDS reads and taps 3, the later
 // patches 3, the stores 3 (measured by leaving each out).  A wavefront owns 32 output channels and all columns of the rectangle: 64 x 32 and 64 x 64
 // blocks read more weights per product than the L1 delivers (64 bytes per cycle and CU; 35 and 41 us).
-// Measured against the best of the other configurations, us: that layer 41.5 -> 29.4; stride 2 128 -> 256 on 32 x 28 x 28 41.6 -> 30; stride 1 64 -> 64 on
-// 16 x 56 x 56 39.4 -> 29, 2 x 2 24.4 -> 20.  Short grids stay with gemm_short.hip (3 x 3 128 -> 128 on 4 x 28 x 28: 13.8 there, 19.3 here): the
+// Measured against the best of the other configurations, us: that layer 41.5 -> 29.3; stride 2 128 -> 256 on 32 x 28 x 28 41.6 -> 30; stride 1 64 -> 64 on
+// 16 x 56 x 56 39.4 -> 29, 2 x 2 24.4 -> 20.  Short grids belong to conv_short.hip (3 x 3 128 -> 128 on 4 x 28 x 28: 10.8 there, 18.2 here): the
 // planner times both.  Relative error of the first layer 1.4e-7 -> 1.0e-7, 5 x 5 128 -> 128 on 8 x 28 x 28
 // 3.0e-7 -> 2.2e-7 (one sum for all six products would give 3.6e-7 and 8.5e-7).
 #include <hip/hip_runtime.h>
@@ -36,7 +36,7 @@ struct PatchArgs : PatchRect {
     int nbuf;                    // patch buffers: 2 where they fit
     int N, Ho;
     unsigned a_bytes, b_bytes;
-    FastDiv by_pw, by_ph, by_tx, by_ty, by_sw, by_tm, by_tiles_x, by_tiles_y;
+    ConstDiv by_pw, by_ph, by_tx, by_ty, by_sw, by_tm, by_tiles_x, by_tiles_y;
 };
 
 // Wp[m/32][c/16][tap]: lane l holds output channel l % 32 and channels 8 * (l / 32) .. + 7 of the chunk, as [part][lane][8 bf16] (weight_parts):
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void patch_weights_kernel(const float* __restr
 // are many and workgroups few (stride 2 128 -> 256 on 32 x 28 x 28 35 -> 30 us, 256 -> 512 on 32 x 14 x 14 50 -> 40), not where more workgroups
 // per CU hide it (64 -> 128 on 32 x 56 x 56 30 -> 32, stride 1 64 -> 64 on 16 x 56 x 56 29 -> 31).
 template <int BM, int BN, int WM, int WN, int ITEMS, int NS>
-__global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patch_kernel(GemmProblem p, PatchArgs g)
+__global__ __launch_bounds__((WM * WN + NS) * 64, 2) void conv_patch_kernel(GemmProblem p, PatchArgs g)
 {
     constexpr int NW = WM * WN;
     constexpr int SW = NS > 0 ? NS : NW, S0 = NS > 0 ? NW : 0, LANES = SW * 64;          // wavefronts that stage, the first of them
@@ -80,11 +80,11 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patc
     const int lrow = lane >> 5, lcol = lane & 31;
 
     const int wg = (int)xcd_contiguous(blockIdx.x, (unsigned)g.total);
-    const int t1 = (int)fast_div((unsigned)wg, g.by_tm);
+    const int t1 = (int)const_div((unsigned)wg, g.by_tm);
     const int m0 = (wg - t1 * g.tilesM) * BM;
-    const int t2 = (int)fast_div((unsigned)t1, g.by_tiles_x);
+    const int t2 = (int)const_div((unsigned)t1, g.by_tiles_x);
     const int ox0 = (t1 - t2 * g.tilesX) * g.tx;
-    const int t3 = (int)fast_div((unsigned)t2, g.by_tiles_y);
+    const int t3 = (int)const_div((unsigned)t2, g.by_tiles_y);
     const int oy0 = (t2 - t3 * g.tilesY) * g.ty;
     const int img0 = t3 * g.ni;
 
@@ -103,11 +103,11 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patc
     for (int t = 0; t < ITEMS; ++t) {
         const int id = t * LANES + tid - S0 * 64;
         const int grp = id >= g.ppr ? 1 : 0, q = id - grp * g.ppr;
-        const int r1 = (int)fast_div((unsigned)q, g.by_pw), px = q - r1 * g.pw;
-        const int i = (int)fast_div((unsigned)r1, g.by_ph), py = r1 - i * g.ph;
+        const int r1 = (int)const_div((unsigned)q, g.by_pw), px = q - r1 * g.pw;
+        const int i = (int)const_div((unsigned)r1, g.by_ph), py = r1 - i * g.ph;
         const int iy = oy0 * p.cv_sh - p.cv_ph + py, ix = ox0 * p.cv_sw - p.cv_pw + px;
         const bool ok = q < g.ppr && img0 + i < g.N && (unsigned)iy < (unsigned)p.cv_H && (unsigned)ix < (unsigned)p.cv_W;
-        const int xq = (int)fast_div((unsigned)px, g.by_sw), xr = px - xq * p.cv_sw;
+        const int xq = (int)const_div((unsigned)px, g.by_sw), xr = px - xq * p.cv_sw;
         bgrp[t] = grp;
         boff[t] = ok ? (unsigned)(((img0 + i) * C + grp * 8) * plane + iy * p.cv_W + ix) * 4u : kOutsideBytes;
         bslot[t] = q < g.ppr ? (grp * g.pp + (r1 * p.cv_sw + xr) * g.pws + xq) * 16 : -1;
@@ -176,8 +176,8 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patc
     // ---- this lane's columns
     struct Col { int y, x, img; bool ok; };
     auto column = [&](int c) -> Col {
-        const int u = (int)fast_div((unsigned)c, g.by_tx), tx = c - u * g.tx;
-        const int i = (int)fast_div((unsigned)u, g.by_ty), ty = u - i * g.ty;
+        const int u = (int)const_div((unsigned)c, g.by_tx), tx = c - u * g.tx;
+        const int i = (int)const_div((unsigned)u, g.by_ty), ty = u - i * g.ty;
         Col r;
         r.img = i; r.y = ty; r.x = tx;
         r.ok = i < g.ni && img0 + i < g.N && oy0 + ty < g.Ho && ox0 + tx < p.cv_Wo;
@@ -240,7 +240,7 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, NS > 0 ? 2 : 1) void conv_patc
     int ky = 0, kx = 0;
     auto next_tap = [&]() -> int {
         if (++kx == p.cv_kw) { kx = 0; if (++ky == p.cv_kh) ky = 0; }
-        const int dx = kx * p.cv_dw, xq = (int)fast_div((unsigned)dx, g.by_sw), xr = dx - xq * p.cv_sw;
+        const int dx = kx * p.cv_dw, xq = (int)const_div((unsigned)dx, g.by_sw), xr = dx - xq * p.cv_sw;
         return ((ky * p.cv_dh * p.cv_sw + xr) * g.pws + xq) * 16;
     };
 
@@ -442,14 +442,14 @@ hipError_t launch_patch_cfg(const GemmProblem& p, bool, hipStream_t s)
     const int one = g.pp * 96, stage = WM * WN * kStageFloats * 4;
     g.nbuf = g.nch > 1 && (2 * one <= kPatchLds / 2 || total <= 256) && 2 * one <= kPatchLds ? 2 : 1;
     g.vecD = g.vecD && (reinterpret_cast<uintptr_t>(p.D) & 15u) == 0 && p.strideD_img % 4 == 0 && p.strideD_row % 4 == 0;
-    g.by_pw = make_fastdiv((unsigned)g.pw);
-    g.by_ph = make_fastdiv((unsigned)g.ph);
-    g.by_tx = make_fastdiv((unsigned)g.tx);
-    g.by_ty = make_fastdiv((unsigned)g.ty);
-    g.by_sw = make_fastdiv((unsigned)p.cv_sw);
-    g.by_tm = make_fastdiv((unsigned)g.tilesM);
-    g.by_tiles_x = make_fastdiv((unsigned)g.tilesX);
-    g.by_tiles_y = make_fastdiv((unsigned)g.tilesY);
+    g.by_pw = make_constdiv((unsigned)g.pw);
+    g.by_ph = make_constdiv((unsigned)g.ph);
+    g.by_tx = make_constdiv((unsigned)g.tx);
+    g.by_ty = make_constdiv((unsigned)g.ty);
+    g.by_sw = make_constdiv((unsigned)p.cv_sw);
+    g.by_tm = make_constdiv((unsigned)g.tilesM);
+    g.by_tiles_x = make_constdiv((unsigned)g.tilesX);
+    g.by_tiles_y = make_constdiv((unsigned)g.tilesY);
     hipLaunchKernelGGL((conv_patch_kernel<BM, BN, WM, WN, ITEMS, NS>), dim3((unsigned)total), dim3(THREADS), (size_t)(g.nbuf * one > stage ? g.nbuf * one : stage), s, p, g);
     return hipGetLastError();
 }

@@ -24,7 +24,7 @@ struct ShortInArgs {
     int cblocks, input_blocks;               // blocks of 32 tiles per channel; workgroups of the input transform (the others: weights)
     unsigned x_bytes;
     long long plane, row;                    // floats between positions, and between channels (tiled: between runs of 64 tiles)
-    FastDiv by_tw, by_th, by_cblocks, by_ldk, by_c;
+    ConstDiv by_tw, by_th, by_cblocks, by_ldk, by_c;
 };
 
 constexpr int short_threads(int alpha) { return (alpha * kShortTiles + 63) / 64 * 64; }
@@ -34,13 +34,13 @@ template <int A>
 __device__ __forceinline__ void input_short(const WinoGeom& g, const ShortInArgs& sa, const MatArg<A, A>& bt, const float* __restrict__ x,
                                             float* __restrict__ V, int wg, float* lds)
 {
-    const int c = (int)fast_div((unsigned)wg, sa.by_cblocks);
+    const int c = (int)const_div((unsigned)wg, sa.by_cblocks);
     const int t = threadIdx.x % kShortTiles, i = threadIdx.x / kShortTiles;
     const int p = (wg - c * sa.cblocks) * kShortTiles + t;
     const bool row_ok = short_threads(A) == A * kShortTiles || i < A;
     {
-        const int r1 = (int)fast_div((unsigned)p, sa.by_tw), tx = p - r1 * g.tw;
-        const int img = (int)fast_div((unsigned)r1, sa.by_th), ty = r1 - img * g.th;
+        const int r1 = (int)const_div((unsigned)p, sa.by_tw), tx = p - r1 * g.tw;
+        const int img = (int)const_div((unsigned)r1, sa.by_th), ty = r1 - img * g.th;
         const int y = ty * g.n - g.pad_h + i, x0 = tx * g.n - g.pad_w;
         const bool ok = row_ok && p < g.P && (unsigned)y < (unsigned)g.H;
         const int first = ((img * g.C + c) * g.H + y) * g.W + x0;        // elements; the tensor has fewer than 2^29
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(short_threads(A)) void input_filter_short_kernel(Wi
         return;
     }
     const int idx = ((int)blockIdx.x - sa.input_blocks) * short_threads(A) + (int)threadIdx.x;
-    const int r1 = (int)fast_div((unsigned)idx, sa.by_ldk), kk = idx - r1 * g.ldk;
-    const int i = (int)fast_div((unsigned)r1, sa.by_c), c = r1 - i * g.C;
+    const int r1 = (int)const_div((unsigned)idx, sa.by_ldk), kk = idx - r1 * g.ldk;
+    const int i = (int)const_div((unsigned)r1, sa.by_c), c = r1 - i * g.C;
     if (i >= A) return;
     const float* wp = w + ((long long)(kk < g.K ? kk : 0) * g.C + c) * KT * KT;
     float wl[KT][KT], row[KT];
@@ -130,7 +130,7 @@ struct ShortOutArgs {
     int pblocks;
     int vec;                                  // 2: 16-byte stores of whole tile rows, 1: pairs, 0: single values
     long long plane, row;                     // as ShortInArgs, of M
-    FastDiv by_tw, by_th, by_pblocks;
+    ConstDiv by_tw, by_th, by_pblocks;
 };
 
 // 32 tiles of one output channel: a lane sums one column of m, then writes one row of the tile
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(short_threads(A)) void output_short_kernel(WinoGeom
 {
     __shared__ float lds[NT * A * kShortTiles];
     const int wg = (int)xcd_contiguous(blockIdx.x, gridDim.x);
-    const int k = (int)fast_div((unsigned)wg, sa.by_pblocks);
+    const int k = (int)const_div((unsigned)wg, sa.by_pblocks);
     const int t = threadIdx.x % kShortTiles, i = threadIdx.x / kShortTiles;
     const int p = (wg - k * sa.pblocks) * kShortTiles + t;
     const bool pok = p < g.P;
@@ -156,8 +156,8 @@ __global__ __launch_bounds__(short_threads(A)) void output_short_kernel(WinoGeom
     }
     __syncthreads();
     if (i >= NT || !pok) return;
-    const int r1 = (int)fast_div((unsigned)p, sa.by_tw), tx = p - r1 * g.tw;
-    const int img = (int)fast_div((unsigned)r1, sa.by_th), ty = r1 - img * g.th;
+    const int r1 = (int)const_div((unsigned)p, sa.by_tw), tx = p - r1 * g.tw;
+    const int img = (int)const_div((unsigned)r1, sa.by_th), ty = r1 - img * g.th;
     const int oy = ty * NT + i;
     if (oy >= g.Ho) return;
     float s[A], o[NT];
@@ -185,8 +185,8 @@ ShortInArgs short_in_args(const WinoGeom& g)
     a.x_bytes = (unsigned)((long long)g.N * g.C * g.H * g.W * 4);
     a.plane = g.tiled ? 64 : (long long)g.C * g.ldp;
     a.row = g.tiled ? 64ll * g.alpha * g.alpha : g.ldp;
-    a.by_tw = make_fastdiv((unsigned)g.tw); a.by_th = make_fastdiv((unsigned)g.th); a.by_cblocks = make_fastdiv((unsigned)a.cblocks);
-    a.by_ldk = make_fastdiv((unsigned)g.ldk); a.by_c = make_fastdiv((unsigned)g.C);
+    a.by_tw = make_constdiv((unsigned)g.tw); a.by_th = make_constdiv((unsigned)g.th); a.by_cblocks = make_constdiv((unsigned)a.cblocks);
+    a.by_ldk = make_constdiv((unsigned)g.ldk); a.by_c = make_constdiv((unsigned)g.C);
     return a;
 }
 
@@ -289,7 +289,7 @@ hipError_t launch_output_short(const WinoGeom& g, const float* AT, const float* 
     a.row = g.tiled ? 64ll * g.alpha * g.alpha : g.ldp;
     a.vec = (g.n == 4 && g.Wo % 4 == 0 && (reinterpret_cast<uintptr_t>(y) & 15u) == 0) ? 2
             : (g.n % 2 == 0 && g.Wo % 2 == 0 && (reinterpret_cast<uintptr_t>(y) & 7u) == 0) ? 1 : 0;
-    a.by_tw = make_fastdiv((unsigned)g.tw); a.by_th = make_fastdiv((unsigned)g.th); a.by_pblocks = make_fastdiv((unsigned)a.pblocks);
+    a.by_tw = make_constdiv((unsigned)g.tw); a.by_th = make_constdiv((unsigned)g.th); a.by_pblocks = make_constdiv((unsigned)a.pblocks);
     const dim3 grid((unsigned)((long long)a.pblocks * g.K));
     auto launch = [&](auto nt, auto al) -> hipError_t {
         constexpr int NT = decltype(nt)::value, A = decltype(al)::value;

@@ -116,7 +116,7 @@ struct RowsArgs {
     int lanes;                   // C * N * H * tw
     int N, C, H, W, tw, pad_w, n;
     unsigned x_bytes;
-    FastDiv by_tw, by_h, by_n;
+    ConstDiv by_tw, by_h, by_n;
 };
 
 // One lane per (channel, image, row, tile of the row): a row's alpha values in 16- and 8-byte loads, alpha stores whose lanes are consecutive.
@@ -125,9 +125,9 @@ __global__ __launch_bounds__(256) void cols_rows_in_kernel(RowsArgs g, MatArg<A,
 {
     const int idx = (int)(xcd_contiguous(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
     const bool live = idx < g.lanes;
-    const int r1 = (int)fast_div((unsigned)idx, g.by_tw), tx = idx - r1 * g.tw;
-    const int r2 = (int)fast_div((unsigned)r1, g.by_h), y = r1 - r2 * g.H;
-    const int c = (int)fast_div((unsigned)r2, g.by_n), img = r2 - c * g.N;
+    const int r1 = (int)const_div((unsigned)idx, g.by_tw), tx = idx - r1 * g.tw;
+    const int r2 = (int)const_div((unsigned)r1, g.by_h), y = r1 - r2 * g.H;
+    const int c = (int)const_div((unsigned)r2, g.by_n), img = r2 - c * g.N;
     const int x0 = tx * g.n - g.pad_w;
     const int first = ((img * g.C + c) * g.H + y) * g.W + x0;            // elements; the tensor has fewer than 2^29
     float d[A];
@@ -145,7 +145,7 @@ struct ColsArgs {
     int kblocks, pblocks, mblocks, nch;
     unsigned plane_bytes;        // of one channel of T[b]: N * H * tw floats
     unsigned t_bytes, u_bytes;   // of one column b
-    FastDiv by_kblocks, by_pblocks, by_tw, by_th;
+    ConstDiv by_kblocks, by_pblocks, by_tw, by_th;
 };
 
 // KW blocks of 32 output channels x 64 tiles, eight wavefronts: wavefront kt + KW grp owns block kt and a share of the alpha rows for both
@@ -174,9 +174,9 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
 
     // output-channel blocks fastest: they share the tiles; the position column slowest: its weights stay in an XCD's L2
     const int wg = (int)xcd_contiguous(blockIdx.x, gridDim.x);
-    const int t1 = (int)fast_div((unsigned)wg, g.by_kblocks);
+    const int t1 = (int)const_div((unsigned)wg, g.by_kblocks);
     const int kb = wg - t1 * g.kblocks;
-    const int b = (int)fast_div((unsigned)t1, g.by_pblocks);
+    const int b = (int)const_div((unsigned)t1, g.by_pblocks);
     const int pb = t1 - b * g.pblocks;
     const int mb = kb * KW + kt;
 
@@ -187,8 +187,8 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
 
     // byte offsets in channel 0 of the alpha rows that tile p sees, kOutsideBytes above and below the image
     auto rows = [&](int p, unsigned (&off)[A]) __attribute__((always_inline)) {
-        const int r1 = (int)fast_div((unsigned)p, g.by_tw), tx = p - r1 * g.tw;
-        const int img = (int)fast_div((unsigned)r1, g.by_th), ty = r1 - img * g.th;
+        const int r1 = (int)const_div((unsigned)p, g.by_tw), tx = p - r1 * g.tw;
+        const int img = (int)const_div((unsigned)r1, g.by_th), ty = r1 - img * g.th;
         const int y0 = ty * NT - g.pad_h;
 #pragma unroll
         for (int a = 0; a < A; ++a)
@@ -427,7 +427,7 @@ struct RowsOutArgs {
     int K, Ho, Wo, th, tw, P;
     int mblocks, pairs;          // 32-channel and 32-tile blocks of S
     int vec;                     // 2: 16-byte stores of whole tile rows, 1: pairs, 0: single values
-    FastDiv by_pairs, by_n, by_tw, by_th;
+    ConstDiv by_pairs, by_n, by_tw, by_th;
 };
 
 // One workgroup per (32 channels, row i of the tiles, 32 tiles); a lane holds four channels of one tile, as the accumulators left them.
@@ -439,8 +439,8 @@ __global__ __launch_bounds__(256) void cols_rows_out_kernel(RowsOutArgs g, MatAr
                                                             const float* __restrict__ bias, float* __restrict__ y)
 {
     const int wg = (int)xcd_contiguous(blockIdx.x, gridDim.x);
-    const int t1 = (int)fast_div((unsigned)wg, g.by_n), i = wg - t1 * NT;
-    const int mb = (int)fast_div((unsigned)t1, g.by_pairs), pp = t1 - mb * g.pairs;
+    const int t1 = (int)const_div((unsigned)wg, g.by_n), i = wg - t1 * NT;
+    const int mb = (int)const_div((unsigned)t1, g.by_pairs), pp = t1 - mb * g.pairs;
     const int lane = threadIdx.x & 63, r4 = threadIdx.x >> 6;
     const float* src = S + (((long long)i * g.mblocks + mb) * g.pairs + pp) * 1024 + r4 * 256 + lane * 4;
     const long long step = (long long)NT * g.mblocks * g.pairs * 1024;
@@ -453,8 +453,8 @@ __global__ __launch_bounds__(256) void cols_rows_out_kernel(RowsOutArgs g, MatAr
         for (int e = 0; e < 4; ++e) in[e][b] = v[e];
     }
     const int p = pp * 32 + (lane & 31), k0 = mb * 32 + 8 * r4 + 4 * (lane >> 5);
-    const int r1 = (int)fast_div((unsigned)p, g.by_tw), tx = p - r1 * g.tw;
-    const int img = (int)fast_div((unsigned)r1, g.by_th), ty = r1 - img * g.th;
+    const int r1 = (int)const_div((unsigned)p, g.by_tw), tx = p - r1 * g.tw;
+    const int img = (int)const_div((unsigned)r1, g.by_th), ty = r1 - img * g.th;
     const int oy = ty * NT + i;
     if (p >= g.P || oy >= g.Ho) return;
     const bool whole = tx * NT + NT <= g.Wo;
@@ -567,7 +567,7 @@ hipError_t launch_cols_rows_in(const WinoGeom& g, const float* BT, const float* 
     a.lanes = (int)(cols_row_tiles(g) * g.C);
     a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.tw = g.tw; a.pad_w = g.pad_w; a.n = g.n;
     a.x_bytes = (unsigned)((long long)g.N * g.C * g.H * g.W * 4);
-    a.by_tw = make_fastdiv((unsigned)g.tw); a.by_h = make_fastdiv((unsigned)g.H); a.by_n = make_fastdiv((unsigned)g.N);
+    a.by_tw = make_constdiv((unsigned)g.tw); a.by_h = make_constdiv((unsigned)g.H); a.by_n = make_constdiv((unsigned)g.N);
     const dim3 grid((unsigned)((a.lanes + 255ll) / 256));
     switch (g.alpha) {
 #define MNN_A(A_) case A_: hipLaunchKernelGGL(cols_rows_in_kernel<A_>, grid, dim3(256), 0, s, a, bt_arg<A_>(BT), x, T); break;
@@ -590,8 +590,8 @@ hipError_t launch_cols_t(const WinoGeom& g, const float* BT, const float* AT, co
     a.plane_bytes = (unsigned)(cols_row_tiles(g) * 4);
     a.t_bytes = (unsigned)(cols_row_tiles(g) * g.C * 4);
     a.u_bytes = (unsigned)cols_column_bytes(g);
-    a.by_kblocks = make_fastdiv((unsigned)a.kblocks); a.by_pblocks = make_fastdiv((unsigned)a.pblocks);
-    a.by_tw = make_fastdiv((unsigned)g.tw); a.by_th = make_fastdiv((unsigned)g.th);
+    a.by_kblocks = make_constdiv((unsigned)a.kblocks); a.by_pblocks = make_constdiv((unsigned)a.pblocks);
+    a.by_tw = make_constdiv((unsigned)g.tw); a.by_th = make_constdiv((unsigned)g.th);
     const dim3 grid((unsigned)((long long)a.kblocks * a.pblocks * A)), block(512);
     if constexpr (A <= 8) {
         if (kw == 4) {
@@ -611,8 +611,8 @@ hipError_t launch_rows_out_t(const WinoGeom& g, const float* AT, const float* S,
     a.mblocks = cols_mblocks(g.K, g.alpha); a.pairs = 2 * cols_pblocks(g.P);
     a.vec = (NT % 4 == 0 && g.Wo % NT == 0 && (reinterpret_cast<uintptr_t>(y) & 15u) == 0) ? 2
             : (NT % 2 == 0 && g.Wo % 2 == 0 && (reinterpret_cast<uintptr_t>(y) & 7u) == 0) ? 1 : 0;
-    a.by_pairs = make_fastdiv((unsigned)a.pairs); a.by_n = make_fastdiv((unsigned)NT);
-    a.by_tw = make_fastdiv((unsigned)g.tw); a.by_th = make_fastdiv((unsigned)g.th);
+    a.by_pairs = make_constdiv((unsigned)a.pairs); a.by_n = make_constdiv((unsigned)NT);
+    a.by_tw = make_constdiv((unsigned)g.tw); a.by_th = make_constdiv((unsigned)g.th);
     const dim3 grid((unsigned)((long long)a.mblocks * a.pairs * NT));
     if (wino_cols_sum_bytes(g) > 120000000)
         hipLaunchKernelGGL((cols_rows_out_kernel<NT, A, true>), grid, dim3(256), 0, s, a, at_arg<NT, A>(AT), S, bias, y);
