@@ -455,8 +455,15 @@ int mnn_conv_run_static(const mnn_conv_shape* shape, const mnn_conv_geom* geom, 
         int st = MNN_STAGE_FILTER;
         if (sc.kind == MNN_SCHEME_WINOGRAD && !im.rect) {
             e = launch_input_filter(im.wg, im.mats.BT.data(), im.mats.G.data(), input, weight, im.V, im.U, s);
-            if (e == hipSuccess) st = MNN_STAGE_GEMM;
-            else if (e != hipErrorNotSupported) return fail_hip(e, "kernel launch");
+            if (e == hipSuccess) {
+                // and their products and inverse transform in another
+                if (products_output_short(im.wg)) {
+                    e = launch_products_output(im.wg, im.mats.AT.data(), im.U, im.V, bias, output, s);
+                    if (e == hipSuccess) return MNN_OK;
+                    if (e != hipErrorNotSupported) return fail_hip(e, "kernel launch");
+                }
+                st = MNN_STAGE_GEMM;
+            } else if (e != hipErrorNotSupported) return fail_hip(e, "kernel launch");
         }
         // (by a kernel, not a memset: the call may be recorded into a graph)
         if (st == MNN_STAGE_FILTER && clear &&

@@ -66,6 +66,10 @@ hipError_t launch_output_short(const WinoGeom& g, const float* AT, const float* 
 hipError_t launch_input_filter_short(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s);
 hipError_t launch_input_filter(const WinoGeom& g, const float* BT, const float* G, const float* x, const float* w, float* V, float* U, hipStream_t s);
 
+// Products and inverse transform of few tiles in one launch, U and V in the row layouts (products_short.hip): M is never stored.
+bool products_output_short(const WinoGeom& g);
+hipError_t launch_products_output(const WinoGeom& g, const float* AT, const float* U, const float* V, const float* bias, float* y, hipStream_t s);
+
 bool input_transform_capped(const WinoGeom& g, const float* BT);       // whether the kernel that itx_waves limits is launched
 
 bool winograd_kernels_available(int n, int k);
