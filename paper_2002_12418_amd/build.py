@@ -19,7 +19,7 @@ OBJ_DIR = os.path.join(PKG, "_build")
 LIB_PATH = os.path.join(PKG, "libmnnconv.so")
 FAST_CALL_PATH = os.path.join(PKG, "_fast_call.so")
 
-SOURCES = ["api.cpp", "transforms.hip", "transforms_rect.hip", "transforms_short.hip", "products_short.hip", "gemm.hip", "gemm_split.hip", "gemm_short.hip", "conv_patch.hip", "conv_short.hip", "weight_layout.hip", "fill.hip", "static_scratch.hip", "wino_fused.hip", "wino_full.hip", "wino_cols.hip", "gemm_bf16.hip", "strassen.hip", "microbench.hip"]
+SOURCES = ["api.cpp", "transforms.hip", "transforms_rect.hip", "transforms_short.hip", "products_short.hip", "gemm.hip", "gemm_split.hip", "gemm_short.hip", "conv_patch.hip", "conv_short.hip", "gemm_prepared.hip", "weight_layout.hip", "fill.hip", "static_scratch.hip", "wino_fused.hip", "wino_full.hip", "wino_cols.hip", "gemm_bf16.hip", "strassen.hip", "microbench.hip"]
 
 # -packed-fp32-ops is switched off: hand-checked scalar fp32 code only.
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-I", INCLUDE, "-I", CSRC,

@@ -523,8 +523,10 @@ constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 const GemmVariant& x6_variant(int i)
 {
     const int shorts = gemm_split6_variant_count(), patches = shorts + gemm_short_variant_count(), short_patches = patches + conv_patch_variant_count();
+    const int prepared = short_patches + conv_short_variant_count();
     return i < shorts ? gemm_split6_variant(i) : i < patches ? gemm_short_variant(i - shorts)
-           : i < short_patches ? conv_patch_variant(i - patches) : conv_short_variant(i - short_patches);
+           : i < short_patches ? conv_patch_variant(i - patches) : i < prepared ? conv_short_variant(i - short_patches)
+           : gemm_prepared_variant(i - prepared);
 }
 
 static int first_patch_variant() { return kNumVariants + gemm_split6_variant_count() + gemm_short_variant_count(); }
@@ -535,13 +537,14 @@ WeightForm gemm_variant_weights(int prec, int v)
 {
     if (prec != 0 || v < first_patch_variant() || v >= gemm_f32_variant_count()) return WeightForm::Rows;
     const int i = v - gemm_named_variant_count(0);
-    return i >= 0 && conv_short_takes_octets(i) ? WeightForm::Octets : WeightForm::Parts;
+    return i >= 0 && i < conv_short_variant_count() && conv_short_takes_octets(i) ? WeightForm::Octets : WeightForm::Parts;
 }
 
 int gemm_product_variant_count(int prec) { return prec == 0 ? first_patch_variant() : gemm_variant_count(prec); }
 
 // Variant ids: 0 = choose from the shape, 1 .. kNumVariants-1 = the tile configurations above.
-int gemm_f32_variant_count() { return first_patch_variant() + conv_patch_variant_count() + conv_short_variant_count(); }
+int gemm_first_prepared_variant() { return first_patch_variant() + conv_patch_variant_count() + conv_short_variant_count(); }
+int gemm_f32_variant_count() { return gemm_first_prepared_variant() + gemm_prepared_variant_count(); }
 const char* gemm_f32_variant_name(int v)
 {
     if (v < 0 || v >= gemm_f32_variant_count()) return nullptr;
@@ -566,11 +569,12 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 // against 129; 25 of 8 x 1818 x 1896 64 against 71) and 32 x 32 k4 for gathers among them (7 x 7, 4 -> 9 on 8 x 94 x 54 15.0 against 16.5), and 128 x 128 pf2 where groups of eight channels are not full (7 x 7, 4 -> 234 on 16 x 34 x 30 25.8
 // against 27.6).  The others are there for callers that name them and for choices saved
 // earlier; they lose to the x6 tiles wherever they were the best (100 products 256 x 256 x 4096: 446 against 305 us; 36 of
-// 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).  The patch kernels: where
-// conv_patch_offered says so.
+// 128 x 128 x 1568: 23.1 against 17.0; 2048 x 2048 x 4096: 278 against 181; batch-1 layers: gemm_short.hip).  The patch kernels and those with
+// prepared weights: where their own rules say so.
 bool gemm_variant_tuned(const GemmProblem& p, int v)
 {
     if (v < 1 || v >= gemm_variant_count(p.prec)) return false;
+    if (p.prec == 0 && v >= gemm_first_prepared_variant()) return p.a_parts && gemm_prepared_offered(p, v - gemm_first_prepared_variant());
     if (p.prec == 0 && v >= gemm_named_variant_count(0)) return conv_short_offered(p, v - gemm_named_variant_count(0));
     if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && conv_patch_offered(p) && conv_patch_covers(p);
     if (p.prec != 0 || v >= kNumVariants) return true;

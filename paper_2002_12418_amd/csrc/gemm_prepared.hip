@@ -1,0 +1,460 @@
+// Pointwise layers with weights prepared as bf16 parts in operand order (parts and terms as in gemm_split.hip).
+//
+// gemm_split.hip and gemm_short.hip cut both operands into parts anew for every tile, the weights among them, which never change: half of their vector
+// instructions, and in the staged tiles half of what goes through LDS.  Here the weights go from the L2 straight to the registers that the matrix instruction
+// reads, 16 bytes per lane and load, one step ahead; only the columns are cut.  What bounds it then: 64 x 64 and 128 x 64 tiles the bytes of
+// both operands that a CU takes from the L2 (some 30 per clock), large ones the matrix cores.
+// Measured against the best of those two, us (images x plane, channels): 16 x 28 x 28 512 -> 256 31.6 -> 25.4, 32 x 14 x 15 1024 -> 512 57.7 -> 46.3,
+// 4 x 27 x 28 1024 -> 1024 48.3 -> 43.6, one of 56 x 56 512 -> 512 18.7 -> 16.6, 16 x 28 x 28 256 -> 256 19.3 -> 15.4, 8 x 28 x 28 128 -> 256 7.6 -> 7.0,
+// 16 x 13 x 13 1024 -> 195 17.3 -> 15.8; divided, 8 x 27 x 29 96 -> 130 6.5 -> 5.4, 16 x 7 x 7 512 -> 1024 12.4 -> 11.8.
+#include <hip/hip_runtime.h>
+#include <type_traits>
+#include "kernels.hpp"
+#include "xcd_remap.hpp"
+#include "gemm_epilogue.hpp"
+#include "bf16_parts.hpp"
+#include "fast_div.hpp"
+
+namespace mnnconv {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+// Weights: blocks of 32 rows and 16 reduction rows, as conv_patch.hip prepares them for one tap
+struct PreparedArgs {
+    int tilesM, tilesN, total;
+    unsigned a_bytes, b_bytes;
+    int blocks, steps;           // 32-row blocks of the weights; steps of 16 reduction rows
+    int vecD;
+    ConstDiv by_l, by_tm;
+};
+
+// LDS slot of a column: a lane holds two of them and writes one at a time, a matrix operand is 32 in a row; both spread over all banks
+template <int BN>
+__device__ __forceinline__ int column_slot(int col) { return (col & 1) * (BN / 2) + ((col >> 1) ^ ((col & 1) << 3)); }
+
+// Columns staged in LDS, two buffers, one barrier per chunk: planes of an even size (pairs of columns, aligned to 4 bytes).  RAGGED: a reduction that is no multiple of 8.
+template <int BM, int BN, int WM, int WN, bool RAGGED>
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProblem p, PreparedArgs g)
+{
+    constexpr int NW = WM * WN, THREADS = NW * 64;
+    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+    constexpr int NP = 3;
+    constexpr int KG = THREADS * 2 / BN, BK = KG * 8, KS = BK / 16;      // a lane stages eight rows of two columns
+    constexpr int GROUP = BN * 16, BUF = NP * KG * GROUP;
+    constexpr int EPI = NW * kStageFloats * 4;
+    __shared__ __attribute__((aligned(16))) char smem[2 * BUF > EPI ? 2 * BUF : EPI];
+    __shared__ int wave_lost[NW];
+    unsigned lost = 0;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int lrow = lane >> 5, lcol = lane & 31;
+
+    const int wg = (int)xcd_contiguous(blockIdx.x, (unsigned)g.total);
+    const int tn = (int)const_div((unsigned)wg, g.by_tm), tm = wg - tn * g.tilesM;
+    const int m0 = tm * BM, n0 = tn * BN;
+
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.a_parts), 0, (int)g.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.B), 0, (int)g.b_bytes, 0x00020000);
+
+    auto column = [&](int col) -> unsigned {             // byte offset in row 0, or kOutsideBytes
+        const int img = (int)const_div((unsigned)col, g.by_l), rest = col - img * p.L;
+        return col < p.Ncols ? (unsigned)(img * (int)p.strideB_img + rest) * 4u : kOutsideBytes;
+    };
+
+    // ---- staging
+    const unsigned row_bytes = (unsigned)p.strideB_row * 4u;
+    const int pair = tid % (BN / 2), grp = tid / (BN / 2);
+    const unsigned base = column(n0 + 2 * pair);
+    float st[16];
+    auto load_b = [&](int ch) __attribute__((always_inline)) {
+        const int r = (ch * KG + grp) * 8;
+        const unsigned o = r < p.R && base != kOutsideBytes ? base + (unsigned)r * row_bytes : kOutsideBytes;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uintx2 v = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(rsB, (int)(!RAGGED || r + i < p.R ? o : kOutsideBytes), (int)(i * row_bytes), 0));
+            st[2 * i] = __uint_as_float(v.x);
+            st[2 * i + 1] = __uint_as_float(v.y);
+        }
+    };
+    auto store_b = [&](int buf) __attribute__((always_inline)) {
+        char* d0 = smem + buf * BUF + grp * GROUP;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            unsigned part[4][NP];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) split_pair<NP>(st[4 * h + j], st[4 * h + 2 + j], part[h], lost);
+            const int slot = column_slot<BN>(2 * pair + j);
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                *reinterpret_cast<uintx4*>(d0 + q * (KG * GROUP) + slot * 16) = uintx4{part[0][q], part[1][q], part[2][q], part[3][q]};
+        }
+    };
+    // LDS writes of this wavefront done, then all wavefronts: loads from global memory stay in flight
+    auto barrier = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+
+    floatx16 acc[TM][TN];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    clear();
+
+    const int block0 = m0 / 32 + wm * TM;
+    uintx4 av[2][TM][NP];
+    auto read_a = [&](int step, uintx4 (&a)[TM][NP]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const bool in = block0 + i < g.blocks && step < g.steps;     // uniform
+            const unsigned from = in ? (unsigned)((block0 + i) * g.steps + step) * (NP * 1024u) : 0u;
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                a[i][q] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rsA, in ? lane * 16 + q * 1024 : (int)kOutsideBytes, (int)from, 0));
+        }
+    };
+    int b_slot[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b_slot[j] = column_slot<BN>(wn * (BN / WN) + j * 32 + lcol) * 16 + lrow * GROUP;
+    // A chunk has sums of its own, which start from nothing and are added to the others': 64 steps in one chain have an error of 4.8e-7 (2-norm,
+    // 1024 channels), in chunks of four 1.4e-7, and the time is the same.
+    floatx16 part[TM][TN];
+    auto multiply = [&](const char* s0, const uintx4 (&a)[TM][NP], bool begin) __attribute__((always_inline)) {
+        bf16x8 bv[TN][NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) bv[j][q] = *reinterpret_cast<const bf16x8*>(s0 + q * (KG * GROUP) + b_slot[j]);
+        // the product of the leading parts last; every accumulator is touched once per round of tiles
+        constexpr int pa[6] = {1, 1, 0, 2, 0, 0}, pb[6] = {1, 0, 1, 0, 2, 0};
+#pragma unroll
+        for (int t = 0; t < 6; ++t) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    part[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][pa[t]]), bv[j][pb[t]], begin && t == 0 ? floatx16{} : part[i][j], 0, 0, 0);
+        }
+    };
+
+    const int nchunks = (p.R + BK - 1) / BK;
+    load_b(0);
+    read_a(0, av[0]);
+    store_b(0);
+    if (nchunks > 1) load_b(1);
+#pragma unroll 1
+    for (int c = 0; c < nchunks; ++c) {
+        const char* s0 = smem + (c & 1) * BUF;
+        barrier();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            read_a(c * KS + ks + 1, av[(ks + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(s0 + 2 * ks * GROUP, av[ks & 1], ks == 0);
+        }
+        if (c + 1 < nchunks) {
+            store_b((c + 1) & 1);
+            if (c + 2 < nchunks) load_b(c + 2);
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] += part[i][j];
+    }
+    {
+        const bool l = parts_lost(lost);
+        if (lane == 0) wave_lost[wave] = l ? 1 : 0;
+    }
+    barrier();
+
+    // A wavefront with sums that are not finite, and every wavefront of a workgroup that staged a value its parts do not hold, repeats its
+    // block on the fp32 matrix instructions, columns straight from memory (as in conv_patch.hip)
+    FiniteCheck check;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
+    int any_lost = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) any_lost |= wave_lost[w];
+    if (check.failed() || __builtin_amdgcn_readfirstlane(any_lost) != 0) {
+        clear();
+        unsigned bc[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) bc[j] = column(n0 + wn * (BN / WN) + j * 32 + lcol);
+#pragma unroll 1
+        for (int step = 0; step < g.steps; ++step) {
+            read_a(step, av[0]);
+            const int r0 = step * 16 + 8 * lrow;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float x[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        rsB, (int)(r0 + e < p.R && bc[j] != kOutsideBytes ? bc[j] + (unsigned)(r0 + e) * row_bytes : kOutsideBytes), 0, 0));
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const float wv = weight_value(av[0][i], e);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x[j], acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    }
+
+    const TileDest dest = tile_dest(p, 0, 0, 1, 0);
+    store_tiles<TM, TN, true>(acc, dest, p.M, p.Ncols, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane,
+                              reinterpret_cast<float*>(smem) + wave * kStageFloats, g.vecD);
+}
+
+// Few columns and a long reduction (as gemm_short.hip): the WK wavefronts divide the reduction, each loads its columns straight into registers, and
+// their sums are added through LDS in wavefront order.
+template <int TM, int TN, int WK, bool RAGGED>
+__global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProblem p, PreparedArgs g)
+{
+    constexpr int THREADS = WK * 64;
+    __shared__ __attribute__((aligned(16))) float red[WK * TM * TN * 1024];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ls = lane & 31, lg = lane >> 5;
+
+    const int wg = (int)xcd_contiguous(blockIdx.x, (unsigned)g.total);
+    const int tn = (int)const_div((unsigned)wg, g.by_tm), tm = wg - tn * g.tilesM;
+
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.a_parts), 0, (int)g.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.B), 0, (int)g.b_bytes, 0x00020000);
+
+    // steps of this wavefront: a contiguous run
+    const int per_wave = (g.steps + WK - 1) / WK, first = wave * per_wave;
+    const int steps = g.steps - first < per_wave ? g.steps - first : per_wave;         // <= 0: none
+
+    const unsigned row_bytes = (unsigned)p.strideB_row * 4u;
+    unsigned b_base[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int col = (tn * TN + j) * 32 + ls;
+        const int img = (int)const_div((unsigned)col, g.by_l), rest = col - img * p.L;
+        b_base[j] = col < p.Ncols ? (unsigned)(img * (int)p.strideB_img + rest) * 4u : kOutsideBytes;
+    }
+    auto read_a = [&](int step, uintx4 (&a)[TM][3]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int mb = tm * TM + i;
+            const bool in = mb < g.blocks && step < g.steps;             // uniform
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                a[i][q] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
+                    rsA, in ? lane * 16 + q * 1024 : (int)kOutsideBytes, in ? (int)((unsigned)(mb * g.steps + step) * 3072u) : 0, 0));
+        }
+    };
+    auto read_b = [&](int step, float (&b)[TN][8]) __attribute__((always_inline)) {
+        const int r = step * 16 + lg * 8;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const unsigned o = r < p.R && b_base[j] != kOutsideBytes ? b_base[j] + (unsigned)r * row_bytes : kOutsideBytes;
+            // rows past the end may be the next image's, whose infinities and NaN a zero weight does not cancel
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                b[j][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsB, (int)(!RAGGED || r + e < p.R ? o : kOutsideBytes), (int)(e * row_bytes), 0));
+        }
+    };
+
+    floatx16 acc[TM][TN];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    };
+    clear();
+    unsigned lost = 0;
+    uintx4 av[TM][3];
+    float bv[TN][8];
+    if (steps > 0) {
+        read_b(first, bv);
+        read_a(first, av);
+    }
+#pragma unroll 1
+    for (int s = 0; s < steps; ++s) {
+        uintx4 a[TM][3];
+        bf16x8 v[TN][3];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) a[i][q] = av[i][q];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) split_octet<3>(bv[j], v[j], lost);
+        if (s + 1 < steps) {
+            read_b(first + s + 1, bv);
+            read_a(first + s + 1, av);
+        }
+        constexpr int pa[6] = {1, 1, 0, 2, 0, 0}, pb[6] = {1, 0, 1, 0, 2, 0};    // the product of the leading parts last
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][pa[t]]), v[j][pb[t]], acc[i][j], 0, 0, 0);
+    }
+
+    // as above, the wavefront's own steps
+    FiniteCheck check;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
+    if (check.failed() || parts_lost(lost)) {
+        clear();
+#pragma unroll 1
+        for (int q = 0; q < steps; ++q) {
+            read_a(first + q, av);
+            const int r0 = (first + q) * 16 + lg * 8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float x[TN];
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        rsB, (int)(r0 + e < p.R && b_base[j] != kOutsideBytes ? b_base[j] + (unsigned)(r0 + e) * row_bytes : kOutsideBytes), 0, 0));
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const float wv = weight_value(av[i], e);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x[j], acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    }
+
+    // ---- partial tiles added in wavefront order, then bias and store
+    constexpr int OUT = TM * TN * 1024, IT = OUT / THREADS;
+    auto out_row = [&](int o) -> int { const int r = (o >> 6) & 15, l = o & 63; return (tm * TM + (o >> 10) / TN) * 32 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3); };
+    float bias[IT];                           // on its way while the partial tiles cross LDS
+#pragma unroll
+    for (int t = 0; t < IT; ++t) {
+        const int m = out_row(tid + t * THREADS);
+        bias[t] = p.bias ? p.bias[m < p.M ? m : p.M - 1] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[((wave * TM * TN + i * TN + j) * 16 + r) * 64 + lane] = acc[i][j][r];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < IT; ++t) {
+        const int o = tid + t * THREADS;
+        float v = red[o];
+#pragma unroll
+        for (int w = 1; w < WK; ++w) v += red[w * OUT + o];
+        const int m = out_row(o), col = (tn * TN + (o >> 10) % TN) * 32 + (o & 31);
+        if (m < p.M && col < p.Ncols) {
+            const int img = (int)const_div((unsigned)col, g.by_l);
+            p.D[(long long)img * p.strideD_img + (long long)m * p.strideD_row + (col - img * p.L)] = v + bias[t];
+        }
+    }
+}
+
+bool prepared_args(const GemmProblem& p, int bm, int bn, int threads, PreparedArgs* g)
+{
+    unsigned plain = 0;
+    if (!p.a_parts || p.splitk > 1 || !gemm_prepared_covers(p) || !gemm_operand_extents(p, &plain, &g->b_bytes)) return false;
+    g->a_bytes = (unsigned)conv_patch_weight_bytes(p.M, p.R, 1);
+    g->blocks = (p.M + 31) / 32;
+    g->steps = (p.R + 15) / 16;
+    g->tilesM = (p.M + bm - 1) / bm;
+    g->tilesN = (p.Ncols + bn - 1) / bn;
+    const long long total = (long long)g->tilesM * g->tilesN;
+    if (!grid_fits(total, threads)) return false;
+    g->total = (int)total;
+    g->vecD = result_rows_vectorisable(p);
+    g->by_l = make_constdiv((unsigned)p.L);
+    g->by_tm = make_constdiv((unsigned)g->tilesM);
+    return true;
+}
+
+template <int TM, int TN, int WK>
+hipError_t launch_prepared_short_cfg(const GemmProblem& p, bool, hipStream_t s)
+{
+    PreparedArgs g{};
+    if (!prepared_args(p, 32 * TM, 32 * TN, WK * 64, &g)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)g.total), block(WK * 64);
+    if (p.R & 7) hipLaunchKernelGGL((gemm_prepared_short_kernel<TM, TN, WK, true>), grid, block, 0, s, p, g);
+    else hipLaunchKernelGGL((gemm_prepared_short_kernel<TM, TN, WK, false>), grid, block, 0, s, p, g);
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN>
+hipError_t launch_prepared_cfg(const GemmProblem& p, bool vec, hipStream_t s)
+{
+    PreparedArgs g{};
+    if (p.L % 2 != 0) return launch_prepared_short_cfg<2, 2, 8>(p, vec, s);          // a choice saved for another plane: a pair of columns may lie in two images
+    if (!prepared_args(p, BM, BN, WM * WN * 64, &g)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)g.total), block(WM * WN * 64);
+    if (p.R & 7) hipLaunchKernelGGL((gemm_prepared_kernel<BM, BN, WM, WN, true>), grid, block, 0, s, p, g);
+    else hipLaunchKernelGGL((gemm_prepared_kernel<BM, BN, WM, WN, false>), grid, block, 0, s, p, g);
+    return hipGetLastError();
+}
+
+const GemmVariant kPrepared[] = {
+    {"x6_prepared_128x128x32_w2x2", launch_prepared_cfg<128, 128, 2, 2>, 128, 128, 32},
+    {"x6_prepared_128x64x64_w2x2", launch_prepared_cfg<128, 64, 2, 2>, 128, 64, 64},
+    {"x6_prepared_64x128x32_w2x2", launch_prepared_cfg<64, 128, 2, 2>, 64, 128, 32},
+    {"x6_prepared_64x64x64_w2x2", launch_prepared_cfg<64, 64, 2, 2>, 64, 64, 64},
+    {"x6_prepared_32x32_k8", launch_prepared_short_cfg<1, 1, 8>, 32, 32, 128},
+    {"x6_prepared_64x64_k8", launch_prepared_short_cfg<2, 2, 8>, 64, 64, 128},
+};
+
+}  // namespace
+
+int gemm_prepared_variant_count() { return (int)(sizeof(kPrepared) / sizeof(kPrepared[0])); }
+const GemmVariant& gemm_prepared_variant(int i) { return kPrepared[i]; }
+
+// Results of 48 MB and more go to the plain tiles: they are bound by memory, and past the caches these lose 3 to 15 % (32 x 28 x 28 256 -> 1024 86 against
+// 93 us, 32 x 32 x 32 96 -> 1024 56 against 64; at 45 MB, 8 x 56 x 57 128 -> 442, 26.5 against 25.4).  Staged tiles where 64 x 64 tiles fill half the
+// chip (below, the divided ones always won: one of 56 x 56 405 -> 96, 98 tiles, 6.8 against 11.4), 128 x 128 where they fill it three times (16 x 14 x 14
+// 512 -> 512, 392 tiles, 26.5 against 16.6; 8 x 28 x 29 256 -> 1024, 1632 tiles, 25.4 against 27.1).  Divided ones up to two 64 x 64 tiles per CU, and
+// 64 x 64 among them from half the chip on and with two steps for each wavefront (32 x 14 x 15 1024 -> 256, 420 tiles, 28.4 against 29.5 staged; 2 x 28
+// x 28 1024 -> 128, 50 tiles, 14.3 against 8.2 in 32 x 32).  Planes of an odd size have the divided tiles alone.
+bool gemm_prepared_offered(const GemmProblem& p, int i)
+{
+    if (!gemm_prepared_covers(p) || (long long)p.M * p.Ncols > 12ll << 20) return false;
+    const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64);
+    switch (i) {
+        case 0: return p.L % 2 == 0 && tiles64 >= 768;
+        case 1: case 2: case 3: return p.L % 2 == 0 && tiles64 >= 128;
+        case 4: return tiles64 < 512;
+        default: return p.R >= 256 && tiles64 >= 128 && tiles64 < 512;
+    }
+}
+
+bool gemm_prepared_covers(const GemmProblem& p)
+{
+    unsigned a = 0, b = 0;
+    return p.prec == 0 && !p.gather && p.batch == 1 && p.M > 0 && p.R >= 16 && p.L > 0 && conv_patch_weight_bytes(p.M, p.R, 1) < ((size_t)1 << 31) &&
+           7ll * p.strideB_row * 4 < (1ll << 30) && gemm_operand_extents(p, &a, &b);
+}
+
+}  // namespace mnnconv

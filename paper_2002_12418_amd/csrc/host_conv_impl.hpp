@@ -27,8 +27,8 @@ struct Impl {
     int gemm_variant = 0;      // tile configuration of the GEMM stage (0 = shape heuristic)
     int gemm_splitk = 1;       // workgroups per tile along the reduction
     float* sk_partial = nullptr; size_t sk_partial_bytes = 0;
-    // sliding window: the kernels on staged patches (conv_patch.hip, conv_short.hip), whose weights have a form of their own, may be chosen
-    bool patch_offered = false, short_offered = false;
+    // kernels whose weights have a form of their own may be chosen: on staged patches (conv_patch.hip, conv_short.hip), pointwise (gemm_prepared.hip)
+    bool patch_offered = false, short_offered = false, prepared_offered = false;
     // V, M and the split-K partials hold nothing between two runs.  A plan on its own allocates them;
     // a chain of layers binds them to a region of its arena instead (bind_transient).
     bool transient_external = false;
@@ -207,23 +207,18 @@ struct Impl {
         if (s.kind == MNN_SCHEME_GEMM1X1) {
             if (!is_pointwise(L)) return fail(MNN_E_UNSUPPORTED, "GEMM scheme needs a 1x1 kernel, stride 1, no padding");
             if ((long long)sh.n * sh.h * sh.w >= (1ll << 31)) return fail(MNN_E_UNSUPPORTED, "too many pixels");
-            U_bytes = (size_t)sh.c_in * ldk * sizeof(float);
-            return alloc_persistent(&U, U_bytes, "hipMalloc Wt");
+            const GemmProblem p = pointwise_gemm_problem(nullptr, &kSomeBias, nullptr);
+            prepared_offered = !persistent_external && s.variant == 0 && gemm_prepared_covers(p);
+            return alloc_weights(p);
         }
         if (s.kind == MNN_SCHEME_DIRECT) {
             // implicit GEMM on the matrix cores: weights transposed to [C*kh*kw][ldk]
             if ((long long)sh.n * L.Ho * L.Wo >= (1ll << 31) || (long long)sh.n * sh.c_in * sh.h * sh.w >= (1ll << 31))
                 return fail(MNN_E_UNSUPPORTED, "tensor too large for the sliding-window kernel");
-            // (not where fixed scratch bounds U; U takes the form of a remembered choice, or is sized anew when the tuner takes the other)
             const GemmProblem p = direct_gemm_problem(nullptr, &kSomeBias, nullptr);
             patch_offered = !persistent_external && conv_patch_offered(p) && conv_patch_covers(p);
             short_offered = !persistent_external && conv_short_covers(p);
-            GemmChoice known{0, 1};
-            (void)cached_gemm_choice(p, &known);
-            U_bytes = weight_bytes(weight_form(known.variant));
-            int rcd = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
-            if (rcd) return rcd;
-            return MNN_OK;
+            return alloc_weights(p);
         }
         return fail(MNN_E_INVALID_ARG, "unknown scheme kind %d", s.kind);
     }
@@ -269,13 +264,14 @@ struct Impl {
         p.strideB_batch = 0; p.strideB_img = (long long)sh.c_in * HW; p.strideB_row = HW;
         p.strideD_batch = 0; p.strideD_img = (long long)sh.c_out * HW; p.strideD_row = HW;
         set_gemm_choice(&p);
+        p.a_parts = weight_form() == WeightForm::Parts ? U : nullptr;
         return p;
     }
 
-    // the form of the sliding window's prepared weights that a configuration reads
+    // the form of the sliding window's and the pointwise layer's prepared weights that a configuration reads
     WeightForm weight_form(int variant) const
     {
-        const bool offered = variant < gemm_named_variant_count(scheme.prec) ? patch_offered : short_offered;
+        const bool offered = variant < gemm_named_variant_count(scheme.prec) ? patch_offered : variant < gemm_first_prepared_variant() ? short_offered : prepared_offered;
         return offered ? gemm_variant_weights(scheme.prec, variant) : WeightForm::Rows;
     }
     WeightForm weight_form() const { return weight_form(gemm_variant); }
@@ -296,6 +292,15 @@ struct Impl {
             case WeightForm::Octets: return launch_octet_weights(w, to, L.s.c_out, L.s.c_in, taps, s);
             default: return launch_weight_transpose(w, (float*)to, L.s.c_out, L.s.c_in * taps, ldk, s);
         }
+    }
+
+    // U in the form of a remembered choice; it is sized anew when the tuner takes another
+    int alloc_weights(const GemmProblem& p)
+    {
+        GemmChoice known{0, 1};
+        (void)cached_gemm_choice(p, &known);
+        U_bytes = weight_bytes(weight_form(known.variant));
+        return alloc_persistent(&U, U_bytes, "hipMalloc Wt");
     }
 
     GemmProblem direct_gemm_problem(const float* x, const float* b, float* y) const
@@ -330,8 +335,8 @@ struct Impl {
         return alloc_transient(&sk_partial, sk_partial_bytes, "hipMalloc split-K partials");
     }
 
-    // the same for the sliding window, where U then takes the size of the form that the chosen kernel reads
-    int adopt_direct(const GemmProblem& p, const GemmChoice& c)
+    // the same for the sliding window and the pointwise layer, where U then takes the size of the form that the chosen kernel reads
+    int adopt_weights(const GemmProblem& p, const GemmChoice& c)
     {
         const bool elsewhere = gemm_variant_weights(p.prec, c.variant) != weight_form(c.variant);      // a saved choice that does not apply
         const int rc = adopt(p, elsewhere ? GemmChoice{0, 1} : c);
@@ -491,11 +496,10 @@ struct Impl {
             hipError_t e;
             int rc = MNN_OK;
             const bool direct = scheme.kind == MNN_SCHEME_DIRECT;
-            auto take = [&](const GemmProblem& p) { return direct ? adopt_direct(p, c) : adopt(p, c); };
             {
                 // a shape tuned before needs no scratch tensors (the key holds no addresses)
                 const GemmProblem q = direct ? direct_gemm_problem(nullptr, &kSomeBias, nullptr) : pointwise_gemm_problem(nullptr, &kSomeBias, nullptr);
-                if (cached_gemm_choice(q, &c)) return take(q);
+                if (cached_gemm_choice(q, &c)) return adopt_weights(q, c);
             }
             if ((e = hipMalloc((void**)&tx, xb)) != hipSuccess || (e = hipMalloc((void**)&ty, yb)) != hipSuccess ||
                 (e = hipMalloc((void**)&tb, (size_t)sh.c_out * sizeof(float))) != hipSuccess)
@@ -511,8 +515,8 @@ struct Impl {
                 if (hipMalloc((void**)t, weight_bytes(f)) != hipSuccess) { *t = nullptr; (void)hipGetLastError(); }
                 else if ((e = prepare_weights(f, U, *t, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
             };
-            if (!rc && direct && (patch_offered || short_offered)) other_form(WeightForm::Parts, &tp);
-            if (!rc && direct && short_offered) other_form(WeightForm::Octets, &to);
+            if (!rc && (patch_offered || short_offered || prepared_offered)) other_form(WeightForm::Parts, &tp);
+            if (!rc && short_offered) other_form(WeightForm::Octets, &to);
             p.a_parts = tp;
             p.a_octets = to;
             if (!rc) rc = tune_gemm(p, s, &c);
@@ -523,7 +527,7 @@ struct Impl {
             if (tb) (void)hipFree(tb);
             if (tp) (void)hipFree(tp);
             if (to) (void)hipFree(to);
-            return rc ? rc : take(p);
+            return rc ? rc : adopt_weights(p, c);
         }
         return MNN_OK;
     }
@@ -582,7 +586,7 @@ struct Impl {
         } else if (scheme.kind == MNN_SCHEME_GEMM1X1) {
             const int HW = sh.h * sh.w;
             if (st == MNN_STAGE_FILTER) {
-                e = launch_weight_transpose(w, U, sh.c_out, sh.c_in, ldk, s);
+                e = prepare_weights(weight_form(), w, U, s);
                 if (e == hipSuccess && strassen) {
                     int rc = strassen->set_left(U, s);
                     if (rc) return rc;

@@ -150,7 +150,7 @@ struct GemmArgs {
 };
 // What the product kernels do not read stays out of their arguments (gemm_split.hip says why it matters).
 struct GemmProblem : GemmArgs {
-    const void* a_parts;        // the patch kernels' weights (launch_patch_weights); At is then unused
+    const void* a_parts;        // weights of the patch kernels and of pointwise layers (launch_patch_weights); At is then unused
     const void* a_octets;       // the same for those of them that read fp32 (launch_octet_weights)
 };
 hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s);
@@ -188,7 +188,13 @@ bool conv_short_covers(const GemmProblem& p);
 bool conv_short_offered(const GemmProblem& p, int i);      // whether the planner times it
 size_t octet_weight_bytes(int K, int C, int taps);
 hipError_t launch_octet_weights(const float* w, void* Wq, int K, int C, int taps, hipStream_t s);
-// what a variant reads the weights of a sliding window from: At, a_parts or a_octets
+// pointwise layers with weights as parts, of the same form for one tap (gemm_prepared.hip); numbers after those
+int gemm_prepared_variant_count();
+const GemmVariant& gemm_prepared_variant(int i);
+bool gemm_prepared_covers(const GemmProblem& p);
+bool gemm_prepared_offered(const GemmProblem& p, int i);      // whether the planner times it
+int gemm_first_prepared_variant();
+// what a variant reads the weights of a planned layer from: At, a_parts or a_octets
 enum class WeightForm { Rows, Parts, Octets };
 WeightForm gemm_variant_weights(int prec, int variant);
 // bf16 / bf16x3 operands (gemm_split.hip; operands of 2 GiB and more: gemm_bf16.hip); launch_gemm_f32 forwards to them when prec != 0
