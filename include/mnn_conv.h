@@ -135,7 +135,8 @@ enum {
 /* Plan buffers that tests may look at (device memory owned by the plan). */
 enum {
     MNN_BUF_U = 0,            /* prepared weights.  Winograd, unfused: [alpha^2][C][ldk] (ldk = c_out rounded up to 4),
-                                 element (xi, c, k) = (G w[k][c] G^T)[xi / alpha][xi % alpha];
+                                 element (xi, c, k) = (G w[k][c] G^T)[xi / alpha][xi % alpha] (where the
+                                 chosen product kernel reads bf16 parts, the plan holds those besides);
                                  fused variants: [b][c/4][a][kg][c%4][k%16], xi = a*alpha + b (kg groups of 16
                                  output channels, channel groups padded to whole 16-channel chunks);
                                  FUSED_ALL: bf16 parts in matrix-operand order (no float layout); values that three parts

@@ -1049,7 +1049,7 @@ int chain_create_impl(const mnn_chain_layer* layers, int32_t n_layers, const mnn
         if ((rc = im.tune((hipStream_t)stream))) return rc;
         const size_t bb = (size_t)ch->layers[i].s.c_out * sizeof(float);
         if ((e = hipMalloc((void**)&ch->bias[i], bb)) != hipSuccess) return fail_hip(e, "hipMalloc bias");
-        ch->weight_bytes += im.U_bytes + bb;
+        ch->weight_bytes += im.U_bytes + im.U_parts_bytes + bb;
     }
     // the virtual walk: activation i lives over layers i and i+1, workspace i over layer i
     std::vector<ArenaBuffer> bufs;

@@ -531,20 +531,24 @@ const GemmVariant& x6_variant(int i)
 
 static int first_patch_variant() { return kNumVariants + gemm_split6_variant_count() + gemm_short_variant_count(); }
 
-int gemm_named_variant_count(int prec) { return prec == 0 ? first_patch_variant() + conv_patch_variant_count() : gemm_variant_count(prec); }
+int gemm_named_variant_count(int prec) { return prec == 0 ? first_patch_variant() + conv_patch_variant_count() : gemm_bf16_named_count(); }
 
 WeightForm gemm_variant_weights(int prec, int v)
 {
+    if (prec == 2 && v >= gemm_first_prepared_variant(2)) return WeightForm::Parts;
     if (prec != 0 || v < first_patch_variant() || v >= gemm_f32_variant_count()) return WeightForm::Rows;
     const int i = v - gemm_named_variant_count(0);
     return i >= 0 && i < conv_short_variant_count() && conv_short_takes_octets(i) ? WeightForm::Octets : WeightForm::Parts;
 }
 
-int gemm_product_variant_count(int prec) { return prec == 0 ? first_patch_variant() : gemm_variant_count(prec); }
+int gemm_product_variant_count(int prec) { return prec == 0 ? first_patch_variant() : gemm_bf16_named_count(); }
 
 // Variant ids: 0 = choose from the shape, 1 .. kNumVariants-1 = the tile configurations above.
-int gemm_first_prepared_variant() { return first_patch_variant() + conv_patch_variant_count() + conv_short_variant_count(); }
-int gemm_f32_variant_count() { return gemm_first_prepared_variant() + gemm_prepared_variant_count(); }
+int gemm_first_prepared_variant(int prec)
+{
+    return prec == 0 ? first_patch_variant() + conv_patch_variant_count() + conv_short_variant_count() : gemm_bf16_named_count();
+}
+int gemm_f32_variant_count() { return gemm_first_prepared_variant(0) + gemm_prepared_variant_count(); }
 const char* gemm_f32_variant_name(int v)
 {
     if (v < 0 || v >= gemm_f32_variant_count()) return nullptr;
@@ -574,7 +578,7 @@ bool gemm_f32_variant_tile(int v, int* bm, int* bn, int* bk)
 bool gemm_variant_tuned(const GemmProblem& p, int v)
 {
     if (v < 1 || v >= gemm_variant_count(p.prec)) return false;
-    if (p.prec == 0 && v >= gemm_first_prepared_variant()) return p.a_parts && gemm_prepared_offered(p, v - gemm_first_prepared_variant());
+    if (v >= gemm_first_prepared_variant(p.prec)) return p.a_parts && gemm_prepared_offered(p, v - gemm_first_prepared_variant(p.prec));
     if (p.prec == 0 && v >= gemm_named_variant_count(0)) return conv_short_offered(p, v - gemm_named_variant_count(0));
     if (p.prec == 0 && v >= first_patch_variant()) return p.a_parts && conv_patch_offered(p) && conv_patch_covers(p);
     if (p.prec != 0 || v >= kNumVariants) return true;

@@ -298,7 +298,7 @@ hipError_t (*const kConfigs[])(const GemmProblem&, bool, hipStream_t) = {
 hipError_t launch_gemm_bf16_wide(const GemmProblem& p, int config, bool vec, hipStream_t s)
 {
     constexpr int n = (int)(sizeof(kConfigs) / sizeof(kConfigs[0]));
-    if (config < 0 || config >= n || gemm_bf16_variant_count() != n + 1) return hipErrorInvalidValue;
+    if (config < 0 || config >= n || gemm_bf16_named_count() != n + 1) return hipErrorInvalidValue;
     return kConfigs[config](p, vec, s);
 }
 

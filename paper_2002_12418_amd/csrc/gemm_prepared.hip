@@ -1,4 +1,4 @@
-// Pointwise layers with weights prepared as bf16 parts in operand order (parts and terms as in gemm_split.hip).
+// Pointwise layers and Winograd products with weights prepared as bf16 parts in operand order (parts and terms as in gemm_split.hip).
 //
 // gemm_split.hip and gemm_short.hip cut both operands into parts anew for every tile, the weights among them, which never change: half of their vector
 // instructions, and in the staged tiles half of what goes through LDS.  Here the weights go from the L2 straight to the registers that the matrix instruction
@@ -27,20 +27,27 @@ struct PreparedArgs {
     unsigned a_bytes, b_bytes;
     int blocks, steps;           // 32-row blocks of the weights; steps of 16 reduction rows
     int vecD;
-    ConstDiv by_l, by_tm;
+    ConstDiv by_l, by_tm, by_tiles;
 };
+
+__device__ __forceinline__ void* parts_of(const GemmProblem& p, const PreparedArgs& g, int b) { return static_cast<char*>(const_cast<void*>(p.a_parts)) + (long long)b * g.a_bytes; }
+
+// Products of parts: six of three parts (fp32), three of two ("bf16x3", gemm_split.hip)
+template <int NP> struct Terms;
+template <> struct Terms<3> { static constexpr int end = 6, pa[6] = {1, 1, 0, 2, 0, 0}, pb[6] = {1, 0, 1, 0, 2, 0}; };
+template <> struct Terms<2> { static constexpr int end = 3, pa[3] = {1, 0, 0}, pb[3] = {0, 1, 0}; };
 
 // LDS slot of a column: a lane holds two of them and writes one at a time, a matrix operand is 32 in a row; both spread over all banks
 template <int BN>
 __device__ __forceinline__ int column_slot(int col) { return (col & 1) * (BN / 2) + ((col >> 1) ^ ((col & 1) << 3)); }
 
+// BATCH: Winograd products, one per position; a pointwise layer is spared the division.
 // Columns staged in LDS, two buffers, one barrier per chunk: planes of an even size (pairs of columns, aligned to 4 bytes).  RAGGED: a reduction that is no multiple of 8.
-template <int BM, int BN, int WM, int WN, bool RAGGED>
+template <int BM, int BN, int WM, int WN, bool RAGGED, bool BATCH, int NP>
 __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProblem p, PreparedArgs g)
 {
     constexpr int NW = WM * WN, THREADS = NW * 64;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int NP = 3;
     constexpr int KG = THREADS * 2 / BN, BK = KG * 8, KS = BK / 16;      // a lane stages eight rows of two columns
     constexpr int GROUP = BN * 16, BUF = NP * KG * GROUP;
     constexpr int EPI = NW * kStageFloats * 4;
@@ -55,11 +62,12 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
     const int lrow = lane >> 5, lcol = lane & 31;
 
     const int wg = (int)xcd_contiguous(blockIdx.x, (unsigned)g.total);
-    const int tn = (int)const_div((unsigned)wg, g.by_tm), tm = wg - tn * g.tilesM;
+    const int b = BATCH ? (int)const_div((unsigned)wg, g.by_tiles) : 0, tile = wg - b * (g.tilesM * g.tilesN);
+    const int tn = (int)const_div((unsigned)tile, g.by_tm), tm = tile - tn * g.tilesM;
     const int m0 = tm * BM, n0 = tn * BN;
 
-    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.a_parts), 0, (int)g.a_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.B), 0, (int)g.b_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(parts_of(p, g, b), 0, (int)g.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.B) + b * p.strideB_batch, 0, (int)g.b_bytes, 0x00020000);
 
     auto column = [&](int col) -> unsigned {             // byte offset in row 0, or kOutsideBytes
         const int img = (int)const_div((unsigned)col, g.by_l), rest = col - img * p.L;
@@ -137,14 +145,14 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
 #pragma unroll
             for (int j = 0; j < TN; ++j) bv[j][q] = *reinterpret_cast<const bf16x8*>(s0 + q * (KG * GROUP) + b_slot[j]);
         // the product of the leading parts last; every accumulator is touched once per round of tiles
-        constexpr int pa[6] = {1, 1, 0, 2, 0, 0}, pb[6] = {1, 0, 1, 0, 2, 0};
 #pragma unroll
-        for (int t = 0; t < 6; ++t) {
+        for (int t = 0; t < Terms<NP>::end; ++t) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    part[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][pa[t]]), bv[j][pb[t]], begin && t == 0 ? floatx16{} : part[i][j], 0, 0, 0);
+                    part[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][Terms<NP>::pa[t]]), bv[j][Terms<NP>::pb[t]],
+                                                                         begin && t == 0 ? floatx16{} : part[i][j], 0, 0, 0);
         }
     };
 
@@ -172,7 +180,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] += part[i][j];
     }
-    {
+    if constexpr (NP == 3) {
         const bool l = parts_lost(lost);
         if (lane == 0) wave_lost[wave] = l ? 1 : 0;
     }
@@ -180,50 +188,52 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
 
     // A wavefront with sums that are not finite, and every wavefront of a workgroup that staged a value its parts do not hold, repeats its
     // block on the fp32 matrix instructions, columns straight from memory (as in conv_patch.hip)
-    FiniteCheck check;
+    if constexpr (NP == 3) {
+        FiniteCheck check;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
-    int any_lost = 0;
+                for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
+        int any_lost = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) any_lost |= wave_lost[w];
-    if (check.failed() || __builtin_amdgcn_readfirstlane(any_lost) != 0) {
-        clear();
-        unsigned bc[TN];
+        for (int w = 0; w < NW; ++w) any_lost |= wave_lost[w];
+        if (check.failed() || __builtin_amdgcn_readfirstlane(any_lost) != 0) {
+            clear();
+            unsigned bc[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) bc[j] = column(n0 + wn * (BN / WN) + j * 32 + lcol);
+            for (int j = 0; j < TN; ++j) bc[j] = column(n0 + wn * (BN / WN) + j * 32 + lcol);
 #pragma unroll 1
-        for (int step = 0; step < g.steps; ++step) {
-            read_a(step, av[0]);
-            const int r0 = step * 16 + 8 * lrow;
+            for (int step = 0; step < g.steps; ++step) {
+                read_a(step, av[0]);
+                const int r0 = step * 16 + 8 * lrow;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float x[TN];
+                for (int e = 0; e < 8; ++e) {
+                    float x[TN];
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                        rsB, (int)(r0 + e < p.R && bc[j] != kOutsideBytes ? bc[j] + (unsigned)(r0 + e) * row_bytes : kOutsideBytes), 0, 0));
+                    for (int j = 0; j < TN; ++j)
+                        x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                            rsB, (int)(r0 + e < p.R && bc[j] != kOutsideBytes ? bc[j] + (unsigned)(r0 + e) * row_bytes : kOutsideBytes), 0, 0));
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const float wv = weight_value(av[0][i], e);
+                    for (int i = 0; i < TM; ++i) {
+                        const float wv = weight_value(av[0][i], e);
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x[j], acc[i][j], 0, 0, 0);
+                        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x[j], acc[i][j], 0, 0, 0);
+                    }
                 }
             }
         }
     }
 
-    const TileDest dest = tile_dest(p, 0, 0, 1, 0);
+    const TileDest dest = tile_dest(p, b, 0, 1, 0);
     store_tiles<TM, TN, true>(acc, dest, p.M, p.Ncols, m0 + wm * (BM / WM), n0 + wn * (BN / WN), lane,
                               reinterpret_cast<float*>(smem) + wave * kStageFloats, g.vecD);
 }
 
 // Few columns and a long reduction (as gemm_short.hip): the WK wavefronts divide the reduction, each loads its columns straight into registers, and
 // their sums are added through LDS in wavefront order.
-template <int TM, int TN, int WK, bool RAGGED>
+template <int TM, int TN, int WK, bool RAGGED, bool BATCH, int NP>
 __global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProblem p, PreparedArgs g)
 {
     constexpr int THREADS = WK * 64;
@@ -235,10 +245,11 @@ __global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProble
     const int ls = lane & 31, lg = lane >> 5;
 
     const int wg = (int)xcd_contiguous(blockIdx.x, (unsigned)g.total);
-    const int tn = (int)const_div((unsigned)wg, g.by_tm), tm = wg - tn * g.tilesM;
+    const int b = BATCH ? (int)const_div((unsigned)wg, g.by_tiles) : 0, tile = wg - b * (g.tilesM * g.tilesN);
+    const int tn = (int)const_div((unsigned)tile, g.by_tm), tm = tile - tn * g.tilesM;
 
-    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.a_parts), 0, (int)g.a_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.B), 0, (int)g.b_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(parts_of(p, g, b), 0, (int)g.a_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.B) + b * p.strideB_batch, 0, (int)g.b_bytes, 0x00020000);
 
     // steps of this wavefront: a contiguous run
     const int per_wave = (g.steps + WK - 1) / WK, first = wave * per_wave;
@@ -252,15 +263,15 @@ __global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProble
         const int img = (int)const_div((unsigned)col, g.by_l), rest = col - img * p.L;
         b_base[j] = col < p.Ncols ? (unsigned)(img * (int)p.strideB_img + rest) * 4u : kOutsideBytes;
     }
-    auto read_a = [&](int step, uintx4 (&a)[TM][3]) __attribute__((always_inline)) {
+    auto read_a = [&](int step, uintx4 (&a)[TM][NP]) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const int mb = tm * TM + i;
             const bool in = mb < g.blocks && step < g.steps;             // uniform
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
+            for (int q = 0; q < NP; ++q)
                 a[i][q] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(
-                    rsA, in ? lane * 16 + q * 1024 : (int)kOutsideBytes, in ? (int)((unsigned)(mb * g.steps + step) * 3072u) : 0, 0));
+                    rsA, in ? lane * 16 + q * 1024 : (int)kOutsideBytes, in ? (int)((unsigned)(mb * g.steps + step) * (NP * 1024u)) : 0, 0));
         }
     };
     auto read_b = [&](int step, float (&b)[TN][8]) __attribute__((always_inline)) {
@@ -286,7 +297,7 @@ __global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProble
     };
     clear();
     unsigned lost = 0;
-    uintx4 av[TM][3];
+    uintx4 av[TM][NP];
     float bv[TN][8];
     if (steps > 0) {
         read_b(first, bv);
@@ -294,54 +305,55 @@ __global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProble
     }
 #pragma unroll 1
     for (int s = 0; s < steps; ++s) {
-        uintx4 a[TM][3];
-        bf16x8 v[TN][3];
+        uintx4 a[TM][NP];
+        bf16x8 v[TN][NP];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int q = 0; q < 3; ++q) a[i][q] = av[i][q];
+            for (int q = 0; q < NP; ++q) a[i][q] = av[i][q];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) split_octet<3>(bv[j], v[j], lost);
+        for (int j = 0; j < TN; ++j) split_octet<NP>(bv[j], v[j], lost);
         if (s + 1 < steps) {
             read_b(first + s + 1, bv);
             read_a(first + s + 1, av);
         }
-        constexpr int pa[6] = {1, 1, 0, 2, 0, 0}, pb[6] = {1, 0, 1, 0, 2, 0};    // the product of the leading parts last
 #pragma unroll
-        for (int t = 0; t < 6; ++t)
+        for (int t = 0; t < Terms<NP>::end; ++t)              // the product of the leading parts last
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][pa[t]]), v[j][pb[t]], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][Terms<NP>::pa[t]]), v[j][Terms<NP>::pb[t]], acc[i][j], 0, 0, 0);
     }
 
     // as above, the wavefront's own steps
-    FiniteCheck check;
+    if constexpr (NP == 3) {
+        FiniteCheck check;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
-    if (check.failed() || parts_lost(lost)) {
-        clear();
+                for (int r = 0; r < 16; ++r) check.add(acc[i][j][r]);
+        if (check.failed() || parts_lost(lost)) {
+            clear();
 #pragma unroll 1
-        for (int q = 0; q < steps; ++q) {
-            read_a(first + q, av);
-            const int r0 = (first + q) * 16 + lg * 8;
+            for (int q = 0; q < steps; ++q) {
+                read_a(first + q, av);
+                const int r0 = (first + q) * 16 + lg * 8;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float x[TN];
+                for (int e = 0; e < 8; ++e) {
+                    float x[TN];
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                        rsB, (int)(r0 + e < p.R && b_base[j] != kOutsideBytes ? b_base[j] + (unsigned)(r0 + e) * row_bytes : kOutsideBytes), 0, 0));
+                    for (int j = 0; j < TN; ++j)
+                        x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                            rsB, (int)(r0 + e < p.R && b_base[j] != kOutsideBytes ? b_base[j] + (unsigned)(r0 + e) * row_bytes : kOutsideBytes), 0, 0));
 #pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const float wv = weight_value(av[i], e);
+                    for (int i = 0; i < TM; ++i) {
+                        const float wv = weight_value(av[i], e);
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x[j], acc[i][j], 0, 0, 0);
+                        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, x[j], acc[i][j], 0, 0, 0);
+                    }
                 }
             }
         }
@@ -372,7 +384,7 @@ __global__ __launch_bounds__(WK * 64) void gemm_prepared_short_kernel(GemmProble
         const int m = out_row(o), col = (tn * TN + (o >> 10) % TN) * 32 + (o & 31);
         if (m < p.M && col < p.Ncols) {
             const int img = (int)const_div((unsigned)col, g.by_l);
-            p.D[(long long)img * p.strideD_img + (long long)m * p.strideD_row + (col - img * p.L)] = v + bias[t];
+            p.D[b * p.strideD_batch + (long long)img * p.strideD_img + (long long)m * p.strideD_row + (col - img * p.L)] = v + bias[t];
         }
     }
 }
@@ -381,17 +393,18 @@ bool prepared_args(const GemmProblem& p, int bm, int bn, int threads, PreparedAr
 {
     unsigned plain = 0;
     if (!p.a_parts || p.splitk > 1 || !gemm_prepared_covers(p) || !gemm_operand_extents(p, &plain, &g->b_bytes)) return false;
-    g->a_bytes = (unsigned)conv_patch_weight_bytes(p.M, p.R, 1);
+    g->a_bytes = (unsigned)gemm_parts_bytes(p.prec, p.M, p.R);
     g->blocks = (p.M + 31) / 32;
     g->steps = (p.R + 15) / 16;
     g->tilesM = (p.M + bm - 1) / bm;
     g->tilesN = (p.Ncols + bn - 1) / bn;
-    const long long total = (long long)g->tilesM * g->tilesN;
+    const long long total = (long long)g->tilesM * g->tilesN * p.batch;
     if (!grid_fits(total, threads)) return false;
     g->total = (int)total;
     g->vecD = result_rows_vectorisable(p);
     g->by_l = make_constdiv((unsigned)p.L);
     g->by_tm = make_constdiv((unsigned)g->tilesM);
+    g->by_tiles = make_constdiv((unsigned)(g->tilesM * g->tilesN));
     return true;
 }
 
@@ -401,8 +414,15 @@ hipError_t launch_prepared_short_cfg(const GemmProblem& p, bool, hipStream_t s)
     PreparedArgs g{};
     if (!prepared_args(p, 32 * TM, 32 * TN, WK * 64, &g)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)g.total), block(WK * 64);
-    if (p.R & 7) hipLaunchKernelGGL((gemm_prepared_short_kernel<TM, TN, WK, true>), grid, block, 0, s, p, g);
-    else hipLaunchKernelGGL((gemm_prepared_short_kernel<TM, TN, WK, false>), grid, block, 0, s, p, g);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, p, g); };
+    if (p.prec == 2) {
+        if (p.R & 7) run(gemm_prepared_short_kernel<TM, TN, WK, true, true, 2>);
+        else run(gemm_prepared_short_kernel<TM, TN, WK, false, true, 2>);
+    } else if (p.batch > 1) {
+        if (p.R & 7) run(gemm_prepared_short_kernel<TM, TN, WK, true, true, 3>);
+        else run(gemm_prepared_short_kernel<TM, TN, WK, false, true, 3>);
+    } else if (p.R & 7) run(gemm_prepared_short_kernel<TM, TN, WK, true, false, 3>);
+    else run(gemm_prepared_short_kernel<TM, TN, WK, false, false, 3>);
     return hipGetLastError();
 }
 
@@ -413,9 +433,40 @@ hipError_t launch_prepared_cfg(const GemmProblem& p, bool vec, hipStream_t s)
     if (p.L % 2 != 0) return launch_prepared_short_cfg<2, 2, 8>(p, vec, s);          // a choice saved for another plane: a pair of columns may lie in two images
     if (!prepared_args(p, BM, BN, WM * WN * 64, &g)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)g.total), block(WM * WN * 64);
-    if (p.R & 7) hipLaunchKernelGGL((gemm_prepared_kernel<BM, BN, WM, WN, true>), grid, block, 0, s, p, g);
-    else hipLaunchKernelGGL((gemm_prepared_kernel<BM, BN, WM, WN, false>), grid, block, 0, s, p, g);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, p, g); };
+    if (p.prec == 2) {
+        if (p.R & 7) run(gemm_prepared_kernel<BM, BN, WM, WN, true, true, 2>);
+        else run(gemm_prepared_kernel<BM, BN, WM, WN, false, true, 2>);
+    } else if (p.batch > 1) {
+        if (p.R & 7) run(gemm_prepared_kernel<BM, BN, WM, WN, true, true, 3>);
+        else run(gemm_prepared_kernel<BM, BN, WM, WN, false, true, 3>);
+    } else if (p.R & 7) run(gemm_prepared_kernel<BM, BN, WM, WN, true, false, 3>);
+    else run(gemm_prepared_kernel<BM, BN, WM, WN, false, false, 3>);
     return hipGetLastError();
+}
+
+// One workgroup per 32 output channels x 64 channels of one position: rows of U, prepared as parts (as the preparation of the rows, bound by memory; it runs once).
+template <int NP>
+__global__ __launch_bounds__(256) void parts_of_rows_kernel(const float* __restrict__ U, uintx4* __restrict__ Up, int K, int C, int ldk, int blocks, int steps, int quads)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int q = blockIdx.x % quads, r1 = blockIdx.x / quads, kb = r1 % blocks, b = r1 / blocks;
+    const int step = q * 4 + wave, k = kb * 32 + (lane & 31), c = step * 16 + (lane >> 5) * 8;
+    if (step >= steps) return;
+    const float* u = U + ((long long)b * C + c) * ldk + k;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = k < K && c + e < C ? u[(long long)e * ldk] : 0.f;
+    unsigned part[4][NP];
+    if constexpr (NP == 3) weight_parts(v, part);
+    else {
+        unsigned lost = 0;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) split_pair<NP>(v[2 * h], v[2 * h + 1], part[h], lost);
+    }
+    uintx4* up = Up + (((long long)b * blocks + kb) * steps + step) * (NP * 64) + lane;
+#pragma unroll
+    for (int t = 0; t < NP; ++t) up[t * 64] = uintx4{part[0][t], part[1][t], part[2][t], part[3][t]};
 }
 
 const GemmVariant kPrepared[] = {
@@ -438,22 +489,48 @@ const GemmVariant& gemm_prepared_variant(int i) { return kPrepared[i]; }
 // 512 -> 512, 392 tiles, 26.5 against 16.6; 8 x 28 x 29 256 -> 1024, 1632 tiles, 25.4 against 27.1).  Divided ones up to two 64 x 64 tiles per CU, and
 // 64 x 64 among them from half the chip on and with two steps for each wavefront (32 x 14 x 15 1024 -> 256, 420 tiles, 28.4 against 29.5 staged; 2 x 28
 // x 28 1024 -> 128, 50 tiles, 14.3 against 8.2 in 32 x 32).  Planes of an odd size have the divided tiles alone.
+// Single products with a long reduction and few 32 x 32 tiles keep the plain divided ones: on operands that lie in no L2 the one step ahead is too
+// little there, and the weights' six bytes are more (one of 18 x 13 502 -> 641, 168 tiles, 6.1 against 5.9; 36 x 31 719 -> 110, 140 tiles, 6.6 against 6.4; 30 x 30
+// 700 -> 200, 203 tiles, 6.9 against 7.0; 14 x 14 x 2 300 -> 500, 208 tiles, 4.6 against 5.2).  Loads two steps ahead are slower everywhere (up to 0.4 us).
+// Winograd products take the same rules over all positions: 64 of 93 x 248 x 67 8.2 -> 7.6, 36 of 256 x 512 x 256 25.0 -> 22.3, 36 of 512 x 392 x 512 56.8 ->
+// 50.7, 64 of 256 x 124 x 256 12.7 -> 11.6, 16 of 256 x 1600 x 256 29.0 -> 27.7; 50 MB and more lose: 100 of 256 x 4096 x 256 304 against 337, 64 of
+// 128 x 4096 x 128 64 against 73, 64 of 256 x 1600 x 256 83 against 84.  Of few columns it is the weights that count, six bytes instead of four: more than
+// 12 MB of them for fewer than 64 columns stay as they are (whole calls, 100 of 115 x 36 x 254, 20 MB, 15.6 against 15.4; 16 of 512 x 52 x 512, 25 MB,
+// 13.1 against 13.0; 36 of 128 x 52 x 300, 8 MB, 12.0 against 12.6; 36 of 512 x 64 x 512, 57 MB, 21.0 against 21.2).  bf16x3: 36 of 256 x 512 x 256
+// 17.7 -> 16.5, 64 of 90 x 92 x 400 10.4 -> 7.3, 36 of 128 x 1600 x 128 14.9 -> 13.8.
 bool gemm_prepared_offered(const GemmProblem& p, int i)
 {
-    if (!gemm_prepared_covers(p) || (long long)p.M * p.Ncols > 12ll << 20) return false;
-    const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64);
+    if (!gemm_prepared_covers(p)) return false;
+    if ((long long)p.M * p.Ncols * p.batch > 12ll << 20) return false;
+    if (p.batch > 1 && p.Ncols < 64 && (long long)p.batch * gemm_parts_bytes(p.prec, p.M, p.R) > 12ll << 20) return false;
+    const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64) * p.batch;
+    const long long tiles32 = (long long)((p.M + 31) / 32) * ((p.Ncols + 31) / 32);
     switch (i) {
         case 0: return p.L % 2 == 0 && tiles64 >= 768;
         case 1: case 2: case 3: return p.L % 2 == 0 && tiles64 >= 128;
-        case 4: return tiles64 < 512;
+        case 4: return tiles64 < 512 && (p.batch > 1 || p.R <= 448 || tiles32 >= 192);
         default: return p.R >= 256 && tiles64 >= 128 && tiles64 < 512;
     }
+}
+
+size_t gemm_parts_bytes(int prec, int K, int C) { return conv_patch_weight_bytes(K, C, 1) / 3 * (prec == 2 ? 2 : 3); }
+
+hipError_t launch_parts_of_rows(int prec, const float* U, void* Up, int K, int C, int ldk, int batch, hipStream_t s)
+{
+    if (!U || !Up || K <= 0 || C <= 0 || ldk < K || batch <= 0 || (prec != 0 && prec != 2)) return hipErrorInvalidValue;
+    const int blocks = (K + 127) / 128 * 4, steps = (C + 15) / 16, quads = (steps + 3) / 4;        // whole blocks of 128 rows (conv_patch_weight_bytes)
+    const long long total = (long long)blocks * quads * batch;
+    if (!grid_fits(total, 256)) return hipErrorInvalidValue;
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)total), dim3(256), 0, s, U, static_cast<uintx4*>(Up), K, C, ldk, blocks, steps, quads); };
+    if (prec == 0) run(parts_of_rows_kernel<3>);
+    else run(parts_of_rows_kernel<2>);
+    return hipGetLastError();
 }
 
 bool gemm_prepared_covers(const GemmProblem& p)
 {
     unsigned a = 0, b = 0;
-    return p.prec == 0 && !p.gather && p.batch == 1 && p.M > 0 && p.R >= 16 && p.L > 0 && conv_patch_weight_bytes(p.M, p.R, 1) < ((size_t)1 << 31) &&
+    return (p.prec == 0 || (p.prec == 2 && p.batch > 1)) && !p.gather && p.batch > 0 && p.M > 0 && p.R >= 16 && p.L > 0 && conv_patch_weight_bytes(p.M, p.R, 1) < ((size_t)1 << 31) &&
            7ll * p.strideB_row * 4 < (1ll << 30) && gemm_operand_extents(p, &a, &b);
 }
 

@@ -23,6 +23,8 @@ struct Impl {
     float* U = nullptr; size_t U_bytes = 0;
     float* V = nullptr; size_t V_bytes = 0;
     float* M = nullptr; size_t M_bytes = 0;
+    // U of the separate Winograd kernels once more, as parts, where the product kernel reads them (gemm_prepared.hip)
+    float* U_parts = nullptr; size_t U_parts_bytes = 0;
     int ldk = 0;
     int gemm_variant = 0;      // tile configuration of the GEMM stage (0 = shape heuristic)
     int gemm_splitk = 1;       // workgroups per tile along the reduction
@@ -44,14 +46,15 @@ struct Impl {
     void release()
     {
         if (U && !persistent_external) (void)hipFree(U);
+        if (U_parts) (void)hipFree(U_parts);
         if (!transient_external) {
             if (V) (void)hipFree(V);
             if (M) (void)hipFree(M);
             if (sk_partial) (void)hipFree(sk_partial);
         }
-        U = V = M = nullptr;
+        U = V = M = U_parts = nullptr;
         sk_partial = nullptr;
-        U_bytes = V_bytes = M_bytes = sk_partial_bytes = 0;
+        U_bytes = V_bytes = M_bytes = U_parts_bytes = sk_partial_bytes = 0;
     }
 
     int alloc_zero(float** p, size_t bytes, const char* what)
@@ -202,6 +205,7 @@ struct Impl {
             if ((rc = alloc_persistent(&U, U_bytes, "hipMalloc U"))) return rc;
             if ((rc = alloc_transient(&V, V_bytes, "hipMalloc V"))) return rc;
             if ((rc = alloc_transient(&M, M_bytes, "hipMalloc M"))) return rc;
+            prepared_offered = !persistent_external && gemm_prepared_covers(wino_gemm_problem());
             return MNN_OK;
         }
         if (s.kind == MNN_SCHEME_GEMM1X1) {
@@ -241,7 +245,24 @@ struct Impl {
             p.strideD_batch = 64; p.strideD_img = a2 * 64; p.strideD_row = (long long)wg.pb * a2 * 64;
         }
         set_gemm_choice(&p);
+        p.a_parts = U_parts;
         return p;
+    }
+
+    size_t wino_parts_bytes() const { return (size_t)wg.alpha * wg.alpha_w * gemm_parts_bytes(scheme.prec, wg.K, wg.C); }
+    hipError_t prepare_wino_parts(void* to, hipStream_t s) const { return launch_parts_of_rows(scheme.prec, U, to, wg.K, wg.C, ldk, wg.alpha * wg.alpha_w, s); }
+    // the parts belong to the plan where the chosen kernel reads them
+    int adopt_parts(const GemmProblem& p, const GemmChoice& c)
+    {
+        const bool parts = c.variant >= gemm_first_prepared_variant(p.prec);
+        const int rc = adopt(p, parts && !prepared_offered ? GemmChoice{0, 1} : c);      // a saved choice that does not apply
+        if (rc || !parts || !prepared_offered || U_parts) return rc;
+        U_parts_bytes = wino_parts_bytes();
+        // written as a whole whenever weights are set
+        const hipError_t e = hipMalloc((void**)&U_parts, U_parts_bytes);
+        if (e == hipSuccess) return MNN_OK;
+        U_parts = nullptr;
+        return fail_hip(e, "hipMalloc U");
     }
 
     void set_gemm_choice(GemmProblem* p) const
@@ -271,7 +292,7 @@ struct Impl {
     // the form of the sliding window's and the pointwise layer's prepared weights that a configuration reads
     WeightForm weight_form(int variant) const
     {
-        const bool offered = variant < gemm_named_variant_count(scheme.prec) ? patch_offered : variant < gemm_first_prepared_variant() ? short_offered : prepared_offered;
+        const bool offered = variant < gemm_named_variant_count(scheme.prec) ? patch_offered : variant < gemm_first_prepared_variant(scheme.prec) ? short_offered : prepared_offered;
         return offered ? gemm_variant_weights(scheme.prec, variant) : WeightForm::Rows;
     }
     WeightForm weight_form() const { return weight_form(gemm_variant); }
@@ -390,7 +411,8 @@ struct Impl {
                 break;
             }
             if ((e = launch_fill_pattern(tx, xb / sizeof(float), 0x5fu, -1.f, 1.f, s)) != hipSuccess ||
-                (e = launch_fill_pattern(U, U_bytes / sizeof(float), 0x60u, -0.5f, 0.5f, s)) != hipSuccess) {
+                (e = launch_fill_pattern(U, U_bytes / sizeof(float), 0x60u, -0.5f, 0.5f, s)) != hipSuccess ||
+                (U_parts && (e = prepare_wino_parts(U_parts, s)) != hipSuccess)) {
                 rc = fail_hip(e, "input transform tuning set-up");
                 break;
             }
@@ -461,13 +483,13 @@ struct Impl {
     {
         GemmChoice c{0, 1};
         if (scheme.kind == MNN_SCHEME_WINOGRAD && scheme.variant == MNN_WINO_UNFUSED) {
-            const GemmProblem p = wino_gemm_problem();
+            GemmProblem p = wino_gemm_problem();
             if (transient_external) {
                 // V and M are not bound yet: take the remembered choice, else the shape heuristic
                 if (!cached_gemm_choice(p, &c)) c = GemmChoice{0, 1};
-                return adopt(p, c);
+                return adopt_parts(p, c);
             }
-            if (cached_gemm_choice(p, &c)) return adopt(p, c);
+            if (cached_gemm_choice(p, &c)) return adopt_parts(p, c);
             // the tile configurations are timed on operands with the spread of real U and V, not on the zeros the
             // buffers hold after allocation (matrix-core power, and with it the clock, depends on the operand bits);
             // afterwards the buffers, padding included, are zero again
@@ -475,11 +497,18 @@ struct Impl {
             if ((e = launch_fill_pattern(U, U_bytes / sizeof(float), 0x55u, -0.5f, 0.5f, s)) != hipSuccess ||
                 (e = launch_fill_pattern(V, V_bytes / sizeof(float), 0x56u, -2.f, 2.f, s)) != hipSuccess)
                 return fail_hip(e, "tuning operand fill");
-            int rc = tune_gemm(p, s, &c);
+            // without room for the weights as parts their kernels are not candidates
+            float* parts = nullptr;
+            if (prepared_offered && hipMalloc((void**)&parts, wino_parts_bytes()) != hipSuccess) { parts = nullptr; (void)hipGetLastError(); }
+            int rc = MNN_OK;
+            if (parts && (e = prepare_wino_parts(parts, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
+            p.a_parts = parts;
+            if (!rc) rc = tune_gemm(p, s, &c);
             if ((e = hipMemsetAsync(U, 0, U_bytes, s)) != hipSuccess || (e = hipMemsetAsync(V, 0, V_bytes, s)) != hipSuccess ||
                 (e = hipStreamSynchronize(s)) != hipSuccess)
-                return fail_hip(e, "tuning operand reset");
-            return rc ? rc : adopt(p, c);
+                rc = rc ? rc : fail_hip(e, "tuning operand reset");
+            if (parts) (void)hipFree(parts);
+            return rc ? rc : adopt_parts(p, c);
         }
         if (scheme.kind == MNN_SCHEME_GEMM1X1 && scheme.variant > 0) {
             if (scheme.prec != MNN_GEMM_FP32) return fail(MNN_E_UNSUPPORTED, "Strassen runs on the fp32 GEMM only");
@@ -561,6 +590,7 @@ struct Impl {
                     e = scheme.variant == MNN_WINO_FUSED_ALL ? launch_filter_full(wg, mats.G.data(), w, U, s)
                         : rect ? launch_filter_transform_rect(wg, mats.G.data(), mats_w.G.data(), w, U, s)
                                : launch_filter_transform(wg, mats.G.data(), w, U, s);
+                    if (e == hipSuccess && U_parts) e = prepare_wino_parts(U_parts, s);
                     break;
                 case MNN_STAGE_INPUT:
                     e = rect ? launch_input_transform_rect(wg, mats.BT.data(), mats_w.BT.data(), x, V, s)
@@ -611,7 +641,7 @@ struct Impl {
         return MNN_OK;
     }
 
-    size_t bytes() const { return U_bytes + V_bytes + M_bytes + sk_partial_bytes + (strassen ? strassen->bytes : 0); }
+    size_t bytes() const { return U_bytes + U_parts_bytes + V_bytes + M_bytes + sk_partial_bytes + (strassen ? strassen->bytes : 0); }
 };
 
 void describe_impl(const Impl& im, char* buf, size_t cap)

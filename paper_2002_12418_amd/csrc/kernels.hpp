@@ -150,7 +150,7 @@ struct GemmArgs {
 };
 // What the product kernels do not read stays out of their arguments (gemm_split.hip says why it matters).
 struct GemmProblem : GemmArgs {
-    const void* a_parts;        // weights of the patch kernels and of pointwise layers (launch_patch_weights); At is then unused
+    const void* a_parts;        // weights of the patch kernels and of pointwise layers (launch_patch_weights), U of Winograd (launch_parts_of_rows); At is then unused
     const void* a_octets;       // the same for those of them that read fp32 (launch_octet_weights)
 };
 hipError_t launch_gemm_f32(const GemmProblem& p, hipStream_t s);
@@ -193,12 +193,16 @@ int gemm_prepared_variant_count();
 const GemmVariant& gemm_prepared_variant(int i);
 bool gemm_prepared_covers(const GemmProblem& p);
 bool gemm_prepared_offered(const GemmProblem& p, int i);      // whether the planner times it
-int gemm_first_prepared_variant();
+int gemm_first_prepared_variant(int prec);
+// the same of Winograd-domain weights: rows of U of `batch` positions as three parts (prec 0) or two (prec 2), gemm_parts_bytes each
+size_t gemm_parts_bytes(int prec, int K, int C);
+hipError_t launch_parts_of_rows(int prec, const float* U, void* Up, int K, int C, int ldk, int batch, hipStream_t s);
 // what a variant reads the weights of a planned layer from: At, a_parts or a_octets
 enum class WeightForm { Rows, Parts, Octets };
 WeightForm gemm_variant_weights(int prec, int variant);
 // bf16 / bf16x3 operands (gemm_split.hip; operands of 2 GiB and more: gemm_bf16.hip); launch_gemm_f32 forwards to them when prec != 0
 int gemm_bf16_variant_count();
+int gemm_bf16_named_count();
 const char* gemm_bf16_variant_name(int variant);
 hipError_t launch_gemm_bf16(const GemmProblem& p, hipStream_t s);
 hipError_t launch_gemm_bf16_wide(const GemmProblem& p, int config, bool vec, hipStream_t s);     // config: gemm_bf16_variant - 1

@@ -130,3 +130,99 @@ def test_values_that_parts_do_not_hold(mnn, tmp_path):
                 assert torch.equal(out[1 - img], y[1 - img].float()), name
                 want = torch.nn.functional.conv2d(bad.cpu().double(), w.double(), b.double()).float()
                 assert torch.equal(torch.isnan(out[img]), torch.isnan(want[img])) and torch.equal(torch.isinf(out[img]), torch.isinf(want[img])), name
+
+
+# ---------------------------------------------------------------- Winograd products
+# n, c_in, h, w, c_out, kh, kw, tile
+PRODUCTS = [
+    (1, 16, 6, 6, 16, 3, 3, 4),            # one step, four columns
+    (3, 17, 14, 9, 33, 3, 3, 4),
+    (2, 130, 10, 11, 129, 3, 3, 2),        # one past the tiles and the chunks
+    (5, 24, 60, 62, 70, 3, 3, 4),          # runs of 64 columns, the last one ragged
+    (2, 300, 9, 8, 65, 5, 5, 2),
+    (2, 40, 17, 17, 100, 1, 7, 2),         # a kernel with one row
+]
+
+
+def wino_layer(shape):
+    n, c, h, w, k, kh, kw, tile = shape
+    return ConvLayer("x".join(map(str, shape)), n, c, h, w, k, kh, kw, 1, (kh // 2, kw // 2))
+
+
+def wino_planned(m, layer, tile, variant, path, prec, make=None):
+    opt = m.Options(force_kind=m.SCHEME_WINOGRAD, force_tile_n=tile, force_prec=prec, force_variant=m.WINO_UNFUSED)
+    m.cache_clear()
+    m.ConvPlan.for_layer(layer, options=opt).close()
+    m.cache_save(str(path))
+    lines = [l.split("|")[0] + f"| {variant} 1" if l.startswith("G ") and l.split("|")[0].split()[-1] == str(prec) else l
+             for l in path.read_text().splitlines()]
+    path.write_text("\n".join(lines) + "\n")
+    m.cache_clear()
+    m.cache_load(str(path))
+    return (make or (lambda o: m.ConvPlan.for_layer(layer, options=o)))(opt)
+
+
+def wino_variants(m, prec):
+    return prepared_variants(m) if prec == 0 else [(m.lib.mnn_gemm_variant_count(2) + i, name) for i, name in enumerate(NAMES)]
+
+
+@pytest.mark.parametrize("prec", [0, 2], ids=["fp32", "bf16x3"])
+@pytest.mark.parametrize("shape", PRODUCTS, ids=str)
+def test_winograd_products(mnn, shape, prec, tmp_path):
+    """M against the float64 product of the plan's own U and V: R sums, each rounded at 2^-24; two bf16 parts hold an operand to 2^-17, and the
+    product of the two second parts is left out."""
+    layer = wino_layer(shape)
+    x, w, b = inputs(layer, layer.c_in)
+    xd, wd, bd = x.cuda(), w.cuda(), b.cuda()
+    for v, name in wino_variants(mnn, prec):
+        with wino_planned(mnn, layer, shape[-1], v, tmp_path / "cache", prec) as plan:
+            assert name in plan.describe()
+            info = plan.info
+            for weights in (wd, wd * 3):                  # prepared again: another pointer
+                y = plan.run(xd, weights, bd)
+                torch.cuda.synchronize()
+                U, V, M = (torch.from_numpy(plan.buffer_to_numpy(i)) for i in (mnn.BUF_U, mnn.BUF_V, mnn.BUF_M))
+                a2, C, K = U.numel() // (layer.c_in * info["ldk"]), layer.c_in, layer.c_out
+                U = U.view(a2, C, info["ldk"])[:, :, :K].double()
+                if info["tiled"]:
+                    V, M = V.view(C, -1, a2, 64).permute(2, 0, 1, 3), M.view(K, -1, a2, 64).permute(2, 0, 1, 3)
+                V, M = V.reshape(a2, C, -1).double(), M.reshape(a2, K, -1).double()
+                Ut = U.transpose(1, 2).contiguous()
+                bound = ((C + 6) * 2.0 ** -24 + (3 * 2.0 ** -17 if prec else 0)) * torch.bmm(Ut.abs(), V.abs())
+                assert bool(((M - torch.bmm(Ut, V)).abs() <= bound).all()), name
+                assert torch.equal(y, plan.run(xd, weights, bd)), name       # the same bits every run
+
+
+def test_winograd_products_of_values_that_parts_do_not_hold(mnn, tmp_path):
+    layer = wino_layer((2, 40, 12, 12, 40, 3, 3, 4))
+    x, w, b = inputs(layer, 9)
+    x[0] *= 2.0 ** -115
+    w[3] *= 2.0 ** 60
+    w[5] *= 2.0 ** -118
+    bad = x.clone()
+    bad[1, 39, 5, 5], bad[1, 0, 0, 0] = float("nan"), float("inf")
+    bd = torch.zeros(layer.c_out).cuda()
+    runs = []
+    for v, name in [(next(i for i, n in enumerate(mnn.gemm_variants()) if n == "128x128x16_w2x2"), "128x128x16")] + prepared_variants(mnn):
+        with wino_planned(mnn, layer, 4, v, tmp_path / "cache", 0) as plan:
+            assert name in plan.describe()
+            runs.append((name, plan.run(x.cuda(), w.cuda(), bd).cpu().double(), plan.run(bad.cuda(), w.cuda(), bd).cpu()))
+    _, want, want_bad = runs[0]                           # the fp32 instructions
+    scale = want.abs().amax(dim=(2, 3), keepdim=True)     # per image and channel; sums of 40 products and a transform that amplifies 2^-24 some 30 times
+    for name, y, y_bad in runs[1:]:
+        assert bool(((y - want).abs() <= 1e-4 * scale + 2.0 ** -140).all()), name
+        assert torch.equal(torch.isfinite(y_bad), torch.isfinite(want_bad)), name
+        assert torch.equal(y_bad[0], y[0].float()), name
+
+
+def test_winograd_products_in_a_chain(mnn, tmp_path):
+    layer = wino_layer((2, 40, 12, 12, 40, 3, 3, 4))
+    x, w, b = inputs(layer, 4)
+    ref = conv64(layer, x, w, b)
+    for v, name in prepared_variants(mnn):
+        chain = wino_planned(mnn, layer, 4, v, tmp_path / "cache", 0, make=lambda o: mnn.ConvChain([layer], options=o))
+        assert name in chain.describe(0)
+        chain.set_weights(0, w.cuda(), b.cuda())
+        y = chain.run(x.cuda(), torch.empty(layer.out_shape, device="cuda"))
+        assert float((y.cpu().double() - ref).abs().max() / ref.abs().max()) < 1e-4, name
+        chain.close()
