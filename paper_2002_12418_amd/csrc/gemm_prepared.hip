@@ -496,7 +496,8 @@ const GemmVariant& gemm_prepared_variant(int i) { return kPrepared[i]; }
 // 50.7, 64 of 256 x 124 x 256 12.7 -> 11.6, 16 of 256 x 1600 x 256 29.0 -> 27.7; 50 MB and more lose: 100 of 256 x 4096 x 256 304 against 337, 64 of
 // 128 x 4096 x 128 64 against 73, 64 of 256 x 1600 x 256 83 against 84.  Of few columns it is the weights that count, six bytes instead of four: more than
 // 12 MB of them for fewer than 64 columns stay as they are (whole calls, 100 of 115 x 36 x 254, 20 MB, 15.6 against 15.4; 16 of 512 x 52 x 512, 25 MB,
-// 13.1 against 13.0; 36 of 128 x 52 x 300, 8 MB, 12.0 against 12.6; 36 of 512 x 64 x 512, 57 MB, 21.0 against 21.2).  bf16x3: 36 of 256 x 512 x 256
+// 13.1 against 13.0; 36 of 128 x 52 x 300, 8 MB, 12.0 against 12.6; 36 of 512 x 64 x 512, 57 MB, 21.0 against 21.2).  128 x 128 in fp32 is for reductions beyond four
+// chunks: at 128 the product ties (36 of 128 x 1600 x 128 18.6 against 18.9) and the whole call does not gain (37.9 against 37.0).  bf16x3: 36 of 256 x 512 x 256
 // 17.7 -> 16.5, 64 of 90 x 92 x 400 10.4 -> 7.3, 36 of 128 x 1600 x 128 14.9 -> 13.8.
 bool gemm_prepared_offered(const GemmProblem& p, int i)
 {
@@ -506,7 +507,7 @@ bool gemm_prepared_offered(const GemmProblem& p, int i)
     const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64) * p.batch;
     const long long tiles32 = (long long)((p.M + 31) / 32) * ((p.Ncols + 31) / 32);
     switch (i) {
-        case 0: return p.L % 2 == 0 && tiles64 >= 768;
+        case 0: return p.L % 2 == 0 && tiles64 >= 768 && (p.batch == 1 || p.prec != 0 || p.R > 128);
         case 1: case 2: case 3: return p.L % 2 == 0 && tiles64 >= 128;
         case 4: return tiles64 < 512 && (p.batch > 1 || p.R <= 448 || tiles32 >= 192);
         default: return p.R >= 256 && tiles64 >= 128 && tiles64 < 512;
