@@ -251,18 +251,20 @@ struct Impl {
 
     size_t wino_parts_bytes() const { return (size_t)wg.alpha * wg.alpha_w * gemm_parts_bytes(scheme.prec, wg.K, wg.C); }
     hipError_t prepare_wino_parts(void* to, hipStream_t s) const { return launch_parts_of_rows(scheme.prec, U, to, wg.K, wg.C, ldk, wg.alpha * wg.alpha_w, s); }
-    // the parts belong to the plan where the chosen kernel reads them
+    // the parts belong to the plan where the chosen kernel reads them; a saved choice that does not apply, or for whose parts there is no room, gives
+    // way to one that reads U
     int adopt_parts(const GemmProblem& p, const GemmChoice& c)
     {
         const bool parts = c.variant >= gemm_first_prepared_variant(p.prec);
-        const int rc = adopt(p, parts && !prepared_offered ? GemmChoice{0, 1} : c);      // a saved choice that does not apply
-        if (rc || !parts || !prepared_offered || U_parts) return rc;
-        U_parts_bytes = wino_parts_bytes();
-        // written as a whole whenever weights are set
-        const hipError_t e = hipMalloc((void**)&U_parts, U_parts_bytes);
-        if (e == hipSuccess) return MNN_OK;
-        U_parts = nullptr;
-        return fail_hip(e, "hipMalloc U");
+        if (parts && prepared_offered && !U_parts) {
+            // written as a whole whenever weights are set
+            const hipError_t e = hipMalloc((void**)&U_parts, wino_parts_bytes());
+            if (e != hipSuccess) U_parts = nullptr;
+            if (e != hipSuccess && e != hipErrorOutOfMemory) return fail_hip(e, "hipMalloc U");
+            if (U_parts) U_parts_bytes = wino_parts_bytes();
+            else (void)hipGetLastError();
+        }
+        return adopt(p, parts && !U_parts ? GemmChoice{0, 1} : c);
     }
 
     void set_gemm_choice(GemmProblem* p) const
@@ -320,8 +322,19 @@ struct Impl {
     {
         GemmChoice known{0, 1};
         (void)cached_gemm_choice(p, &known);
-        U_bytes = weight_bytes(weight_form(known.variant));
-        return alloc_persistent(&U, U_bytes, "hipMalloc Wt");
+        return alloc_form(weight_form(known.variant));
+    }
+
+    // U in this form, or as rows where there is no room for it
+    int alloc_form(WeightForm f)
+    {
+        U_bytes = weight_bytes(f);
+        int rc = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
+        if (rc == MNN_E_OOM && !U && U_bytes != weight_bytes(WeightForm::Rows)) {
+            U_bytes = weight_bytes(WeightForm::Rows);
+            rc = alloc_persistent(&U, U_bytes, "hipMalloc Wt");
+        }
+        return rc;
     }
 
     GemmProblem direct_gemm_problem(const float* x, const float* b, float* y) const
@@ -360,12 +373,13 @@ struct Impl {
     int adopt_weights(const GemmProblem& p, const GemmChoice& c)
     {
         const bool elsewhere = gemm_variant_weights(p.prec, c.variant) != weight_form(c.variant);      // a saved choice that does not apply
-        const int rc = adopt(p, elsewhere ? GemmChoice{0, 1} : c);
+        int rc = adopt(p, elsewhere ? GemmChoice{0, 1} : c);
         const size_t bytes = weight_bytes(weight_form());
         if (rc || persistent_external || U_bytes == bytes) return rc;
         (void)hipFree(U);
-        U_bytes = bytes;
-        return alloc_persistent(&U, U_bytes, "hipMalloc Wt");
+        U = nullptr;
+        rc = alloc_form(weight_form());
+        return rc || U_bytes == bytes ? rc : adopt(p, GemmChoice{0, 1});       // rows
     }
 
     // Resident wavefronts per CU of the input transform (WinoGeom::itx_waves), remembered per geometry.  What is timed is the
