@@ -911,6 +911,7 @@ int mnn_conv_cache_save(const char* path)
     {
         std::lock_guard<std::mutex> lk(g_gemm_mu);
         for (const auto& kv : g_gemm_choice) {
+            if (kv.second.partial) continue;
             const std::vector<long long>& v = std::get<1>(kv.first);
             std::fprintf(f, "G %d %zu", std::get<0>(kv.first), v.size());
             for (long long x : v) std::fprintf(f, " %lld", x);

@@ -503,7 +503,7 @@ struct Impl {
                 if (!cached_gemm_choice(p, &c)) c = GemmChoice{0, 1};
                 return adopt_parts(p, c);
             }
-            if (cached_gemm_choice(p, &c)) return adopt_parts(p, c);
+            if (cached_gemm_choice(p, &c) && !c.partial) return adopt_parts(p, c);
             // the tile configurations are timed on operands with the spread of real U and V, not on the zeros the
             // buffers hold after allocation (matrix-core power, and with it the clock, depends on the operand bits);
             // afterwards the buffers, padding included, are zero again
@@ -517,7 +517,7 @@ struct Impl {
             int rc = MNN_OK;
             if (parts && (e = prepare_wino_parts(parts, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
             p.a_parts = parts;
-            if (!rc) rc = tune_gemm(p, s, &c);
+            if (!rc) rc = tune_gemm(p, s, prepared_offered && !parts, &c);
             if ((e = hipMemsetAsync(U, 0, U_bytes, s)) != hipSuccess || (e = hipMemsetAsync(V, 0, V_bytes, s)) != hipSuccess ||
                 (e = hipStreamSynchronize(s)) != hipSuccess)
                 rc = rc ? rc : fail_hip(e, "tuning operand reset");
@@ -542,7 +542,7 @@ struct Impl {
             {
                 // a shape tuned before needs no scratch tensors (the key holds no addresses)
                 const GemmProblem q = direct ? direct_gemm_problem(nullptr, &kSomeBias, nullptr) : pointwise_gemm_problem(nullptr, &kSomeBias, nullptr);
-                if (cached_gemm_choice(q, &c)) return adopt_weights(q, c);
+                if (cached_gemm_choice(q, &c) && (!c.partial || transient_external)) return adopt_weights(q, c);
             }
             if ((e = hipMalloc((void**)&tx, xb)) != hipSuccess || (e = hipMalloc((void**)&ty, yb)) != hipSuccess ||
                 (e = hipMalloc((void**)&tb, (size_t)sh.c_out * sizeof(float))) != hipSuccess)
@@ -554,15 +554,16 @@ struct Impl {
                 rc = fail_hip(e, "tuning scratch fill");
             GemmProblem p = direct ? direct_gemm_problem(tx, tb, ty) : pointwise_gemm_problem(tx, tb, ty);
             // the weights once more in the other forms; without room for them their kernels are not candidates
+            bool partial = false;
             auto other_form = [&](WeightForm f, float** t) {
-                if (hipMalloc((void**)t, weight_bytes(f)) != hipSuccess) { *t = nullptr; (void)hipGetLastError(); }
+                if (hipMalloc((void**)t, weight_bytes(f)) != hipSuccess) { *t = nullptr; partial = true; (void)hipGetLastError(); }
                 else if ((e = prepare_weights(f, U, *t, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
             };
             if (!rc && (patch_offered || short_offered || prepared_offered)) other_form(WeightForm::Parts, &tp);
             if (!rc && short_offered) other_form(WeightForm::Octets, &to);
             p.a_parts = tp;
             p.a_octets = to;
-            if (!rc) rc = tune_gemm(p, s, &c);
+            if (!rc) rc = tune_gemm(p, s, partial, &c);
             if (!rc && ((e = hipMemsetAsync(U, 0, U_bytes, s)) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess))
                 rc = fail_hip(e, "tuning operand reset");
             if (tx) (void)hipFree(tx);

@@ -10,7 +10,9 @@ namespace {
 // itself it is chosen by measurement at pre-inference time and remembered per shape.
 using GemmKey = std::tuple<int, std::vector<long long>>;
 std::mutex g_gemm_mu;
-struct GemmChoice { int variant; int splitk; };
+// partial: timed without kernels whose weights have a form of their own, for which there was no room (or whose caller has none): a plan that can
+// time them does so again, and no file keeps it
+struct GemmChoice { int variant; int splitk; bool partial = false; };
 std::map<GemmKey, GemmChoice> g_gemm_choice;
 
 GemmKey gemm_key(int device, const GemmProblem& p)
@@ -50,8 +52,8 @@ bool cached_gemm_choice(const GemmProblem& p, GemmChoice* out)
 }
 
 // Times every usable tile configuration -- and, where the tiles do not fill the chip, every useful
-// split of the reduction -- on the given (valid, writable) buffers; returns the fastest.
-int tune_gemm(GemmProblem p, hipStream_t s, GemmChoice* out)
+// split of the reduction -- on the given (valid, writable) buffers; returns the fastest.  partial: as in GemmChoice.
+int tune_gemm(GemmProblem p, hipStream_t s, bool partial, GemmChoice* out)
 {
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -59,7 +61,10 @@ int tune_gemm(GemmProblem p, hipStream_t s, GemmChoice* out)
     {
         std::lock_guard<std::mutex> lk(g_gemm_mu);
         auto it = g_gemm_choice.find(key);
-        if (it != g_gemm_choice.end()) { *out = it->second; return MNN_OK; }
+        if (it != g_gemm_choice.end() && (partial || !it->second.partial)) {
+            const WeightForm f = gemm_variant_weights(p.prec, it->second.variant);
+            if (f == WeightForm::Rows || (f == WeightForm::Parts ? p.a_parts : p.a_octets)) { *out = it->second; return MNN_OK; }
+        }
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipError_t e;
@@ -152,9 +157,11 @@ int tune_gemm(GemmProblem p, hipStream_t s, GemmChoice* out)
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
+    best.partial = partial;
     *out = best;
     std::lock_guard<std::mutex> lk(g_gemm_mu);
-    g_gemm_choice[key] = best;
+    const auto it = g_gemm_choice.find(key);
+    if (!partial || it == g_gemm_choice.end() || it->second.partial) g_gemm_choice[key] = best;
     return MNN_OK;
 }
 

@@ -108,6 +108,30 @@ void check_layer(const char* what, const LayerSpec& l)
         const std::string chosen = plan_and_run(l).name;
         remembered(chosen);
     });
+    // timed while there was no room for the other form: good for a chain, which times nothing, but not for good, and not for a file
+    ok &= in_child([&] {
+        fake::refuse = scarce;
+        const Outcome poor = plan_and_run(l);
+        CHECK(poor.rc == MNN_OK && !poor.runs_kernel);
+        CHECK(mnn_conv_cache_save("poor.txt") == MNN_OK);
+        mnn_chain_layer cl{};
+        cl.shape = l.s; cl.geom = l.g;
+        mnn_chain_t ch = nullptr;
+        CHECK(mnn_chain_create(&cl, 1, &l.o, nullptr, &ch) == MNN_OK);
+        if (ch) {
+            char buf[256] = "";
+            mnn_chain_layer_describe(ch, 0, buf, sizeof buf);
+            CHECK(poor.name == buf);
+            mnn_chain_destroy(ch);
+        }
+        fake::refuse = plenty;
+        CHECK(plan_and_run(l).runs_kernel);
+        CHECK(fake::live.empty());
+    });
+    ok &= in_child([&] {
+        CHECK(mnn_conv_cache_load("poor.txt") == MNN_OK);
+        CHECK(plan_and_run(l).runs_kernel);
+    });
     std::printf("%s: %s\n", what, ok ? "ok" : "FAILED");
     failures += !ok;
 }
