@@ -139,10 +139,33 @@ void check_layer(const char* what, const LayerSpec& l)
 mnn_conv_shape shape(int n, int c, int h, int w, int k, int ks) { return mnn_conv_shape{n, c, h, w, k, ks, ks}; }
 mnn_conv_geom geom(int stride, int pad) { return mnn_conv_geom{stride, stride, pad, pad, 1, 1}; }
 
+// The products at the bottom of two Strassen levels have the shape of F(3,5)'s 49, but no weights as parts: they are timed on their own.
+void check_strassen_beside_winograd()
+{
+    const bool ok = in_child([] {
+        fake::takes = [](const std::string& k) { return k.find("gemm_prepared") != std::string::npos ? 0.1f : 1.f; };
+        const LayerSpec l{shape(8, 64, 21, 21, 96, 5), geom(1, 2), options(MNN_SCHEME_WINOGRAD, 3, MNN_GEMM_FP32), 0, 0, "gemm_prepared"};
+        CHECK(plan_and_run(l).runs_kernel);
+        mnn_gemm_desc d{};
+        d.M = 4 * 96; d.R = 4 * 64; d.ncols = d.L = 4 * 392; d.batch = 1; d.lda = d.M;
+        d.strideB_row = d.strideD_row = d.ncols;
+        mnn_strassen_t h = nullptr;
+        fake::launched.clear();
+        CHECK(mnn_strassen_create(&d, 2, nullptr, &h) == MNN_OK);
+        CHECK(fake::ran("gemm_split_kernel") && !fake::ran("gemm_prepared"));
+        mnn_strassen_destroy(h);
+        CHECK(plan_and_run(l).runs_kernel);
+        CHECK(fake::live.empty());
+    });
+    std::printf("Strassen beside Winograd: %s\n", ok ? "ok" : "FAILED");
+    failures += !ok;
+}
+
 }  // namespace
 
 int main()
 {
+    check_strassen_beside_winograd();
     // F(4,3) 64 -> 96 on 8 x 28 x 28: 392 tiles; U, V and M are kept besides the weights as parts
     const size_t p49 = 8 * 7 * 7, wino = (size_t)36 * 4 * (64 * 96 + 64 * p49 + 96 * p49);
     check_layer("Winograd, fp32", {shape(8, 64, 28, 28, 96, 3), geom(1, 1), options(MNN_SCHEME_WINOGRAD, 4, MNN_GEMM_FP32), 36 * parts(96, 64, 1, 3), wino, "gemm_prepared_kernel"});
