@@ -649,10 +649,12 @@ int mnn_gemm_f32(const mnn_gemm_desc* d, const float* At, const float* B, const 
     p.strideA_batch = d->strideA_batch;
     p.strideB_batch = d->strideB_batch; p.strideB_img = d->strideB_img; p.strideB_row = d->strideB_row;
     p.strideD_batch = d->strideD_batch; p.strideD_img = d->strideD_img; p.strideD_row = d->strideD_row;
-    hipError_t e = launch_gemm_f32(p, (hipStream_t)stream);
-    if (e == hipErrorInvalidValue) { (void)hipGetLastError(); return fail(MNN_E_INVALID_ARG, "GEMM descriptor rejected (sizes, lda, alignment or variant)"); }
-    if (e != hipSuccess) return fail_hip(e, "gemm launch");
-    return MNN_OK;
+    return no_throw([&]() -> int {
+        hipError_t e = launch_gemm_f32(p, (hipStream_t)stream);
+        if (e == hipErrorInvalidValue) { (void)hipGetLastError(); return fail(MNN_E_INVALID_ARG, "GEMM descriptor rejected (sizes, lda, alignment or variant)"); }
+        if (e != hipSuccess) return fail_hip(e, "gemm launch");
+        return MNN_OK;
+    });
 }
 
 struct mnn_strassen_s { Strassen impl; };
@@ -698,13 +700,13 @@ int mnn_strassen_set_left(mnn_strassen_t h, const float* At, void* stream)
 {
     if (!h) return fail(MNN_E_INVALID_ARG, "handle is NULL");
     if (At && (reinterpret_cast<uintptr_t>(At) & 15u)) return fail(MNN_E_INVALID_ARG, "At must be 16-byte aligned");
-    return h->impl.set_left(At, (hipStream_t)stream);
+    return no_throw([&] { return h->impl.set_left(At, (hipStream_t)stream); });
 }
 
 int mnn_strassen_run(mnn_strassen_t h, const float* B, const float* bias, float* D, void* stream)
 {
     if (!h) return fail(MNN_E_INVALID_ARG, "handle is NULL");
-    return h->impl.run(B, bias, D, (hipStream_t)stream);
+    return no_throw([&] { return h->impl.run(B, bias, D, (hipStream_t)stream); });
 }
 
 int mnn_strassen_info(mnn_strassen_t h, int32_t* levels, int32_t* launches, size_t* workspace_bytes)

@@ -589,7 +589,11 @@ struct Impl {
 
     int run_stage(int st, const float* x, const float* w, const float* b, float* y, hipStream_t s)
     {
-        if (!has_stage(st)) return MNN_OK;
+        return has_stage(st) ? no_throw([&] { return launch_stage(st, x, w, b, y, s); }) : (int)MNN_OK;
+    }
+
+    int launch_stage(int st, const float* x, const float* w, const float* b, float* y, hipStream_t s)
+    {
         hipError_t e = hipSuccess;
         const mnn_conv_shape& sh = L.s;
         if (scheme.kind == MNN_SCHEME_WINOGRAD && scheme.variant == MNN_WINO_BY_AXIS) {

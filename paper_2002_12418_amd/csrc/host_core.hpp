@@ -14,7 +14,11 @@ int fail(int code, const char* fmt, ...)
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    g_err = buf;
+    try {
+        g_err = buf;
+    } catch (...) {
+        g_err.clear();
+    }
     return code;
 }
 
@@ -24,6 +28,19 @@ int fail_hip(hipError_t e, const char* what)
     (void)hipGetLastError();
     if (e == hipErrorOutOfMemory) return fail(MNN_E_OOM, "%s: %s", what, hipGetErrorString(e));
     return fail(MNN_E_HIP, "%s: %s", what, hipGetErrorString(e));
+}
+
+// For what an entry point does beyond checking its arguments: no exception leaves the C interface
+template <class F>
+int no_throw(F f)
+{
+    try {
+        return f();
+    } catch (const std::bad_alloc&) {
+        return fail(MNN_E_OOM, "host allocation failed");
+    } catch (...) {
+        return fail(MNN_E_HIP, "unexpected exception");
+    }
 }
 
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }

@@ -161,10 +161,57 @@ void check_strassen_beside_winograd()
     failures += !ok;
 }
 
+// Launching runs out of host memory: every entry point that launches says so, none lets the exception out, and the next call works.
+void check_exceptions()
+{
+    const bool ok = in_child([] {
+        fake::takes = [](const std::string&) { return 1.f; };
+        const LayerSpec layers[] = {{shape(2, 64, 28, 28, 96, 3), geom(1, 1), options(MNN_SCHEME_WINOGRAD, 4, MNN_GEMM_FP32), 0, 0, ""},
+                                    {shape(2, 64, 28, 28, 96, 1), geom(1, 0), options(MNN_SCHEME_GEMM1X1, 0, MNN_GEMM_FP32), 0, 0, ""},
+                                    {shape(2, 64, 28, 28, 96, 3), geom(2, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), 0, 0, ""}};
+        for (const LayerSpec& l : layers) {
+            mnn_conv_plan_t p = nullptr;
+            CHECK(mnn_conv_plan(&l.s, &l.g, &l.o, nullptr, &p) == MNN_OK);
+            mnn_chain_layer cl{};
+            cl.shape = l.s; cl.geom = l.g;
+            mnn_chain_t ch = nullptr;
+            CHECK(mnn_chain_create(&cl, 1, &l.o, nullptr, &ch) == MNN_OK && mnn_chain_set_weights(ch, 0, some(1), nullptr, nullptr) == MNN_OK);
+            float ms[MNN_STAGE_COUNT];
+            fake::launch_throws = true;
+            CHECK(mnn_conv_run(p, some(0), some(1), some(2), some(3), nullptr) == MNN_E_OOM);
+            CHECK(mnn_conv_run_stage(p, MNN_STAGE_GEMM, some(0), some(1), some(2), some(3), nullptr) == MNN_E_OOM);
+            CHECK(mnn_conv_run_timed(p, some(0), some(1), some(2), some(3), nullptr, 1, ms) == MNN_E_OOM);
+            CHECK(mnn_conv_set_weights(p, some(1), nullptr) == MNN_E_OOM);
+            CHECK(mnn_chain_run(ch, some(0), some(3), nullptr) == MNN_E_OOM);
+            CHECK(mnn_chain_set_weights(ch, 0, some(1), nullptr, nullptr) == MNN_E_OOM);
+            CHECK(mnn_conv_run_static(&l.s, &l.g, l.o.force_tile_n, some(0), some(1), some(2), some(3), nullptr) == MNN_E_OOM);
+            fake::launch_throws = false;
+            fake::pushed.clear();
+            CHECK(mnn_conv_run(p, some(0), some(1), some(2), some(3), nullptr) == MNN_OK && mnn_chain_run(ch, some(0), some(3), nullptr) == MNN_OK);
+            mnn_conv_plan_destroy(p);
+            mnn_chain_destroy(ch);
+        }
+        mnn_gemm_desc d{};
+        d.M = d.R = d.ncols = d.L = d.lda = 256; d.batch = 1;
+        d.strideB_row = d.strideD_row = 256;
+        mnn_strassen_t h = nullptr;
+        CHECK(mnn_strassen_create(&d, 1, nullptr, &h) == MNN_OK && mnn_strassen_set_left(h, some(1), nullptr) == MNN_OK);
+        fake::launch_throws = true;
+        CHECK(mnn_gemm_f32(&d, some(0), some(1), nullptr, some(2), nullptr) == MNN_E_OOM);
+        CHECK(mnn_strassen_set_left(h, some(1), nullptr) == MNN_E_OOM && mnn_strassen_run(h, some(0), nullptr, some(2), nullptr) == MNN_E_OOM);
+        fake::launch_throws = false;
+        mnn_strassen_destroy(h);
+        CHECK(fake::live.empty());
+    });
+    std::printf("exceptions: %s\n", ok ? "ok" : "FAILED");
+    failures += !ok;
+}
+
 }  // namespace
 
 int main()
 {
+    check_exceptions();
     check_strassen_beside_winograd();
     // F(4,3) 64 -> 96 on 8 x 28 x 28: 392 tiles; U, V and M are kept besides the weights as parts
     const size_t p49 = 8 * 7 * 7, wino = (size_t)36 * 4 * (64 * 96 + 64 * p49 + 96 * p49);
