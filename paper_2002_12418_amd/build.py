@@ -47,15 +47,19 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build_fast_call() -> None:
-    """The short way from Python into the library (fast_call.cpp), against the headers of the torch that is installed."""
+def fast_call_command(out: str, *flags: str) -> list:
+    """Compiles fast_call.cpp against the headers of the torch that is installed."""
     torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", *flags, "-I", INCLUDE,
+            "-I", sysconfig.get_paths()["include"], "-I", os.path.join(torch_dir, "include"), "-I", "/opt/rocm/include",
+            os.path.join(CSRC, "fast_call.cpp"), "-o", out, "-L", os.path.join(torch_dir, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
+def build_fast_call() -> None:
+    """The short way from Python into the library (fast_call.cpp)."""
     tmp = FAST_CALL_PATH + ".tmp"
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", INCLUDE,
-           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(torch_dir, "include"), "-I", "/opt/rocm/include",
-           os.path.join(CSRC, "fast_call.cpp"), "-o", tmp, "-L", os.path.join(torch_dir, "lib"),
-           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
+    r = subprocess.run(fast_call_command(tmp), capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed on fast_call.cpp:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, FAST_CALL_PATH)

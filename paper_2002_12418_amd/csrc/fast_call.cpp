@@ -15,20 +15,41 @@ namespace {
 typedef int (*run_fn)(mnn_conv_plan_t, const float*, const float*, const float*, float*, void*);
 typedef int (*static_fn)(const mnn_conv_shape*, const mnn_conv_geom*, int32_t, const float*, const float*, const float*, float*, void*);
 
+#ifndef FAST_CALL_ON_CPU
+bool on_device(const at::Tensor& t) { return t.is_cuda(); }
+// The stream that torch works on, of the current device
+void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+#else       // for tests without a GPU, which call functions of their own
+bool on_device(const at::Tensor& t) { return t.is_cpu(); }
+void* current_stream() { return nullptr; }
+#endif
+
 // Address of a tensor of these sizes as the kernels take it, or null
 float* plain(PyObject* o, const std::vector<int64_t>* sizes)
 {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.defined() || !t.is_cuda() || t.layout() != c10::kStrided || t.scalar_type() != c10::kFloat || t.unsafeGetTensorImpl()->is_python_dispatch() ||
+    if (!t.defined() || !on_device(t) || t.layout() != c10::kStrided || t.scalar_type() != c10::kFloat || t.unsafeGetTensorImpl()->is_python_dispatch() ||
         !t.has_storage())
         return nullptr;
     if (sizes && (!t.sizes().equals(*sizes) || !t.is_contiguous())) return nullptr;
     return static_cast<float*>(t.mutable_data_ptr());
 }
 
-// The stream that torch works on, of the current device
-void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+// The call, without the GIL and with it again whatever happens.  False if an exception came out.
+template <class F>
+bool without_gil(F call, int* rc)
+{
+    bool ok = true;
+    PyThreadState* const state = PyEval_SaveThread();
+    try {
+        *rc = call();
+    } catch (...) {
+        ok = false;
+    }
+    PyEval_RestoreThread(state);
+    return ok;
+}
 
 struct Runner {
     PyObject_HEAD
@@ -56,9 +77,7 @@ PyObject* runner_call(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
         const at::Tensor& wt = THPVariable_Unpack(args[1]);
         if (wt.is_inference() || w != r->weight_ptr || (int64_t)wt._version() != r->weight_version) Py_RETURN_NONE;
         void* s = current_stream();
-        Py_BEGIN_ALLOW_THREADS
-        rc = r->fn(r->plan, x, w, b, y, s);
-        Py_END_ALLOW_THREADS
+        if (!without_gil([&] { return r->fn(r->plan, x, w, b, y, s); }, &rc)) Py_RETURN_NONE;
     } catch (...) {
         Py_RETURN_NONE;
     }
@@ -175,9 +194,7 @@ PyObject* run_static(PyObject*, PyObject* const* args, Py_ssize_t nargs)
         float* y = plain(args[6], nullptr);
         if (!x || !w || !y || (!b && args[5] != Py_None)) Py_RETURN_NONE;
         void* s = current_stream();
-        Py_BEGIN_ALLOW_THREADS
-        rc = fn(&shape, &geom, tile, x, w, b, y, s);
-        Py_END_ALLOW_THREADS
+        if (!without_gil([&] { return fn(&shape, &geom, tile, x, w, b, y, s); }, &rc)) Py_RETURN_NONE;
     } catch (...) {
         Py_RETURN_NONE;
     }

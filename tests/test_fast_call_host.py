@@ -1,0 +1,76 @@
+"""The short way from Python into the library, built for CPU tensors and calling functions of the test instead of the library's."""
+import ctypes
+import importlib.util
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+FUNCTIONS = r"""
+#include <new>
+#include <vector>
+static std::vector<const void*> seen;
+extern "C" int record(void* plan, const float* x, const float* w, const float* b, float* y, void* s) { seen = {plan, x, w, b, y, s}; y[0] = x[0] + w[0]; return 0; }
+extern "C" int refuse(void*, const float*, const float*, const float*, float*, void*) { return -3; }
+extern "C" int throws(void*, const float*, const float*, const float*, float*, void*) { throw std::bad_alloc(); }
+extern "C" int throws_static(const void*, const void*, int, const float*, const float*, const float*, float*, void*) { throw std::bad_alloc(); }
+extern "C" int record_static(const int* shape, const int* geom, int tile, const float* x, const float*, const float*, float* y, void*)
+{
+    for (int i = 0; i < 7; ++i) y[i] = (float)shape[i];
+    for (int i = 0; i < 6; ++i) y[7 + i] = (float)geom[i];
+    y[13] = (float)tile;
+    return 0;
+}
+"""
+SHAPES = ((1, 2, 3, 3), (2, 2, 1, 1), (2,), (1, 2, 3, 3))
+
+
+@pytest.fixture(scope="module")
+def fast(tmp_path_factory):
+    """(the module, address of a named function)"""
+    pytest.importorskip("torch")
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    from paper_2002_12418_amd.build import fast_call_command
+    d = tmp_path_factory.mktemp("fast_call")
+    subprocess.run(fast_call_command(str(d / "_fast_call.so"), "-DFAST_CALL_ON_CPU", "-O0"), check=True, timeout=300)
+    (d / "functions.cpp").write_text(FUNCTIONS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", str(d / "functions.cpp"), "-o", str(d / "functions.so")], check=True, timeout=120)
+    spec = importlib.util.spec_from_file_location("_fast_call", str(d / "_fast_call.so"))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    functions = ctypes.CDLL(str(d / "functions.so"))
+    yield module, lambda name: ctypes.cast(getattr(functions, name), ctypes.c_void_p).value
+
+
+def tensors():
+    import torch
+    return [torch.rand(s) for s in SHAPES]
+
+
+def test_an_exception_leaves_the_interpreter_whole(fast):
+    """In a process of its own: without the GIL the interpreter ends where it next looks for it."""
+    module, _ = fast
+    d = module.__file__.rsplit("/", 1)[0]
+    code = f"""
+import ctypes, importlib.util, threading, torch
+spec = importlib.util.spec_from_file_location("_fast_call", {module.__file__!r})
+m = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(m)
+f = ctypes.CDLL({d + "/functions.so"!r})
+address = lambda n: ctypes.cast(getattr(f, n), ctypes.c_void_p).value
+x, w, b, y = [torch.rand(s) for s in {SHAPES!r}]
+r = m.Runner(address("throws"), 1, *{SHAPES!r})
+r.remember(w)
+class L: n = c_in = h = w = c_out = kh = kw = stride = pad = dil = 1
+for _ in range(3):
+    assert r(x, w, b, y) is None
+    assert m.run_static(address("throws_static"), L, 2, x, w, b, y) is None
+    t = threading.Thread(target=lambda: [list(range(10)) for _ in range(1000)])
+    t.start()
+    t.join()
+print("whole")
+"""
+    p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0 and "whole" in p.stdout, p.stderr[-2000:]
