@@ -84,21 +84,31 @@ PyObject* runner_call(PyObject* self, PyObject* const* args, size_t nargsf, PyOb
     return PyLong_FromLong(rc);
 }
 
+// Holds another weight tensor, or none.  Letting go of the one before may run Python code: last.
+void hold(Runner* r, PyObject* w)
+{
+    PyObject* const before = r->weight;
+    Py_XINCREF(w);
+    r->weight = w;
+    Py_XDECREF(before);
+}
+
 // remember(weight): the general path has just run with this tensor; remember(None): forget it
 PyObject* runner_remember(PyObject* self, PyObject* w)
 {
     Runner* r = reinterpret_cast<Runner*>(self);
-    Py_CLEAR(r->weight);
     try {
         const float* p = plain(w, &r->sizes[1]);
         if (p && !THPVariable_Unpack(w).is_inference()) {
+            const int64_t version = (int64_t)THPVariable_Unpack(w)._version();
             r->weight_ptr = p;
-            r->weight_version = (int64_t)THPVariable_Unpack(w)._version();
-            Py_INCREF(w);
-            r->weight = w;
+            r->weight_version = version;
+            hold(r, w);
+            Py_RETURN_NONE;
         }
     } catch (...) {
     }
+    hold(r, nullptr);
     Py_RETURN_NONE;
 }
 
@@ -107,14 +117,28 @@ PyObject* runner_close(PyObject* self, PyObject*)
 {
     Runner* r = reinterpret_cast<Runner*>(self);
     r->plan = nullptr;
-    Py_CLEAR(r->weight);
+    hold(r, nullptr);
     Py_RETURN_NONE;
+}
+
+// A weight tensor can hold the plan that holds the runner
+int runner_traverse(PyObject* self, visitproc visit, void* arg)
+{
+    Py_VISIT(reinterpret_cast<Runner*>(self)->weight);
+    return 0;
+}
+
+int runner_clear(PyObject* self)
+{
+    hold(reinterpret_cast<Runner*>(self), nullptr);
+    return 0;
 }
 
 void runner_dealloc(PyObject* self)
 {
     Runner* r = reinterpret_cast<Runner*>(self);
-    Py_CLEAR(r->weight);
+    PyObject_GC_UnTrack(self);
+    hold(r, nullptr);
     delete[] r->sizes;
     Py_TYPE(self)->tp_free(self);
 }
@@ -213,7 +237,10 @@ PyMODINIT_FUNC PyInit__fast_call()
         if (!(names[i] = PyUnicode_InternFromString(attr[i]))) return nullptr;
     RunnerType.tp_name = "_fast_call.Runner";
     RunnerType.tp_basicsize = sizeof(Runner);
-    RunnerType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
+    RunnerType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL | Py_TPFLAGS_HAVE_GC;
+    RunnerType.tp_traverse = runner_traverse;
+    RunnerType.tp_clear = runner_clear;
+    RunnerType.tp_free = PyObject_GC_Del;
     RunnerType.tp_new = runner_new;
     RunnerType.tp_dealloc = runner_dealloc;
     RunnerType.tp_methods = runner_methods;

@@ -74,3 +74,47 @@ print("whole")
 """
     p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert p.returncode == 0 and "whole" in p.stdout, p.stderr[-2000:]
+
+
+def test_a_plan_that_its_weights_hold_is_collected(fast):
+    """weight -> plan -> runner -> weight, as where a module keeps the plan with its parameter."""
+    import gc
+    import weakref
+    module, address = fast
+
+    class Plan:
+        pass
+
+    x, w, b, y = tensors()
+    plan = Plan()
+    plan.fast = module.Runner(address("record"), 1, *SHAPES)
+    plan.fast.remember(w)
+    assert plan.fast(x, w, b, y) == 0
+    w.plan = plan
+    gone = weakref.ref(plan)
+    assert gc.is_tracked(plan.fast)
+    del plan, w
+    gc.collect()
+    assert gone() is None
+
+
+def test_the_last_reference_to_a_remembered_tensor(fast):
+    """Forgetting a tensor may run Python code, which may use the runner again."""
+    module, address = fast
+    x, w, b, y = tensors()
+    other, third = w * 2, w * 3
+    r = module.Runner(address("record"), 1, *SHAPES)
+
+    class Last:
+        def __del__(self):
+            r.remember(other)
+
+    w.last = Last()
+    r.remember(w)
+    del w
+    r.remember(third)                       # w's last reference goes here, and the runner is told of another
+    assert r(x, other, b, y) == 0 and r(x, third, b, y) is None
+    assert float(y.view(-1)[0]) == float(x.view(-1)[0] + other.view(-1)[0])
+    r.close()
+    assert r(x, other, b, y) is None
+    assert sys.getrefcount(other) == 2 and sys.getrefcount(third) == 2       # the name and the argument
