@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes
 import importlib
 import os
+import warnings
 from ctypes import POINTER, byref, c_char_p, c_double, c_float, c_int32, c_size_t, c_void_p
 from dataclasses import dataclass
 from typing import List, Optional, Sequence, Tuple
@@ -392,8 +393,33 @@ def cache_load(path: str) -> None:
 
 _current_stream = None   # () -> handle of the current stream, once a GPU was seen: asking for one costs more than the rest of a small call
 _float32 = None
-_fast_call = None        # the short way into mnn_conv_run and mnn_conv_run_static, once a GPU was seen
+_fast_call = None        # the short way into mnn_conv_run and mnn_conv_run_static, once a GPU was seen and if it is built
 _address = {}            # of the library's functions that it calls
+
+
+class _NoFastCall:
+    """A plan's short way where there is none: every call goes the general way."""
+
+    def __call__(self, x, w, b, y):
+        return None
+
+    def remember(self, w):
+        pass
+
+    def close(self):
+        pass
+
+
+def _load_fast_call():
+    """The native module of fast_call.cpp, or None where it is not built: everything works without it, small layers take longer on the host."""
+    try:
+        fast = importlib.import_module("._fast_call", __package__)
+    except ImportError as e:
+        warnings.warn(f"the short call path is not built ({e}); calls take the general one.  python -m {__package__}.build builds it", RuntimeWarning)
+        return None
+    for f in ("mnn_conv_run", "mnn_conv_run_static"):
+        _address[f] = ctypes.cast(getattr(lib, f), c_void_p).value
+    return fast
 
 
 def _find_current_stream():
@@ -404,16 +430,7 @@ def _find_current_stream():
         return None
     torch.cuda.init()
     _float32 = torch.float32
-    if _fast_call is None:
-        try:
-            fast = importlib.import_module("._fast_call", __package__)
-        except ImportError:
-            from .build import build_fast_call
-            build_fast_call()
-            fast = importlib.import_module("._fast_call", __package__)
-        for f in ("mnn_conv_run", "mnn_conv_run_static"):
-            _address[f] = ctypes.cast(getattr(lib, f), c_void_p).value
-        _fast_call = fast
+    _fast_call = _load_fast_call()
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is not None and device is not None:
         _current_stream = lambda: raw(device())          # 0.2 us; through torch.cuda.current_stream 1.4
@@ -449,7 +466,8 @@ class ConvPlan:
             _find_current_stream()   # a plan made with a stream of the caller's has not asked for one
         self._w_seen = None          # (address, torch version counter) of the weight tensor last handed to the library
         # takes the usual call: the weight tensor that _w_seen names, nothing out of the ordinary
-        self._fast = _fast_call.Runner(_address["mnn_conv_run"], self._h.value, self._in_shape, self._w_shape, self._b_shape, self.out_shape)
+        self._fast = (_fast_call.Runner(_address["mnn_conv_run"], self._h.value, self._in_shape, self._w_shape, self._b_shape, self.out_shape)
+                      if _fast_call else _NoFastCall())
 
     @classmethod
     def for_layer(cls, layer, options: Optional[Options] = None, stream=None) -> "ConvPlan":
@@ -587,7 +605,9 @@ def static_scratch_bytes() -> int:
 
 def conv_run_static(layer, tile_n: int, x, w, b, y, stream=None):
     """mnn_conv_run_static: one convolution with no device allocation (scratch in the library's fixed array)."""
-    if stream is None and (_fast_call or (_find_current_stream() and _fast_call)):
+    if stream is None and _float32 is None:
+        _find_current_stream()
+    if stream is None and _fast_call:
         rc = _fast_call.run_static(_address["mnn_conv_run_static"], layer, tile_n, x, w, b, y)
         if rc == 0:
             return y
