@@ -7,7 +7,7 @@ There is no CPU fallback: if libmnnconv.so is missing the import fails loudly.
 from __future__ import annotations
 
 import ctypes
-import importlib
+import importlib.util
 import os
 import warnings
 from ctypes import POINTER, byref, c_char_p, c_double, c_float, c_int32, c_size_t, c_void_p
@@ -15,6 +15,8 @@ from dataclasses import dataclass
 from typing import List, Optional, Sequence, Tuple
 
 import numpy as np
+
+from . import build
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libmnnconv.so")
@@ -412,8 +414,13 @@ class _NoFastCall:
 
 def _load_fast_call():
     """The native module of fast_call.cpp, or None where it is not built: everything works without it, small layers take longer on the host."""
+    path = build.fast_call_path()
     try:
-        fast = importlib.import_module("._fast_call", __package__)
+        if path is None or not os.path.exists(path):
+            raise ImportError(f"no {os.path.basename(path) if path else 'source'}")
+        spec = importlib.util.spec_from_file_location(f"{__package__}._fast_call", path)
+        fast = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(fast)
     except ImportError as e:
         warnings.warn(f"the short call path is not built ({e}); calls take the general one.  python -m {__package__}.build builds it", RuntimeWarning)
         return None

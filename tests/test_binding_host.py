@@ -10,9 +10,6 @@ def binding(monkeypatch):
     import paper_2002_12418_amd.binding as b
     import paper_2002_12418_amd.build as build
 
-    def no_module(*args, **kw):
-        raise ImportError("no module")
-
     def no_compiler(*args, **kw):
         raise RuntimeError("g++ failed")
 
@@ -21,10 +18,8 @@ def binding(monkeypatch):
     monkeypatch.setattr(b, "_current_stream", None)
     monkeypatch.setattr(b, "_float32", None)
     monkeypatch.setattr(b, "_fast_call", None)
-    monkeypatch.setattr(b.importlib, "import_module", no_module)
     monkeypatch.setattr(build, "build_fast_call", no_compiler)
-    if hasattr(build, "fast_call_path"):
-        monkeypatch.setattr(build, "fast_call_path", lambda: None)
+    monkeypatch.setattr(build, "fast_call_path", lambda: None)
     return b
 
 

@@ -118,3 +118,81 @@ def test_the_last_reference_to_a_remembered_tensor(fast):
     r.close()
     assert r(x, other, b, y) is None
     assert sys.getrefcount(other) == 2 and sys.getrefcount(third) == 2       # the name and the argument
+
+
+def test_the_built_file_is_for_this_torch_and_source(monkeypatch, tmp_path):
+    """A module built against other headers reads tensors at other places: it is not the file that the binding looks for."""
+    import paper_2002_12418_amd.build as build
+    path = build.fast_call_path()
+    assert path.startswith(build.PKG) and path.endswith(".so") and path == build.fast_call_path()
+    # the binding loads that file and no other
+    import paper_2002_12418_amd.binding as binding
+    monkeypatch.setattr(build, "fast_call_path", lambda: str(tmp_path / "other.so"))
+    with pytest.warns(RuntimeWarning):
+        assert binding._load_fast_call() is None
+    monkeypatch.undo()
+    # another torch, another Python, another source, another interface
+    root = tmp_path / "torch"
+    root.mkdir()
+    (root / "version.py").write_text("__version__ = '0.0'\n")
+    monkeypatch.setattr(build, "_torch_dir", lambda: str(root))
+    other = {path, build.fast_call_path()}
+    monkeypatch.undo()
+    monkeypatch.setattr(build.sys, "version", "9.9")
+    other.add(build.fast_call_path())
+    monkeypatch.undo()
+    for name in ("CSRC", "INCLUDE"):
+        changed = tmp_path / name
+        shutil.copytree(getattr(build, name), changed)
+        for f in ("fast_call.cpp", "mnn_conv.h"):
+            if (changed / f).exists():
+                (changed / f).write_text((changed / f).read_text() + "\n")
+        monkeypatch.setattr(build, name, str(changed))
+        other.add(build.fast_call_path())
+        monkeypatch.undo()
+    assert len(other) == 5
+    monkeypatch.setattr(build, "CSRC", str(tmp_path / "nowhere"))
+    assert build.fast_call_path() is None
+
+
+def test_without_torch_or_a_compiler_the_library_is_built(monkeypatch, tmp_path, capsys):
+    import paper_2002_12418_amd.build as build
+    monkeypatch.setattr(build, "OBJ_DIR", str(tmp_path))
+    monkeypatch.setattr(build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "_compile", lambda src: src)
+    monkeypatch.setattr(build, "_hipcc", lambda: "true")
+    real = subprocess.run
+
+    def run(cmd, *args, **kw):
+        if cmd[0] == "true":
+            open(cmd[cmd.index("-o") + 1], "w").close()
+        if cmd[0] == "g++":
+            raise FileNotFoundError("g++")
+        return real(cmd, *args, **kw)
+
+    monkeypatch.setattr(build.subprocess, "run", run)
+    assert build.build_library(verbose=False) == str(tmp_path / "lib.so")
+    assert "g++" in capsys.readouterr().err
+    find = importlib.util.find_spec
+    monkeypatch.setattr(build.importlib.util, "find_spec", lambda name, *a: None if name == "torch" else find(name, *a))
+    assert build.build_library(verbose=False) == str(tmp_path / "lib.so")
+
+
+def test_builds_at_the_same_time_write_files_of_their_own(monkeypatch, tmp_path):
+    import os
+
+    import paper_2002_12418_amd.build as build
+    written = []
+
+    def run(cmd, *args, **kw):
+        written.append(cmd[cmd.index("-o") + 1])
+        open(written[-1], "w").close()
+        return subprocess.CompletedProcess(cmd, 0, "", "")
+
+    monkeypatch.setattr(build.subprocess, "run", run)
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    for pid in (11, 12):
+        monkeypatch.setattr(build.os, "getpid", lambda: pid)
+        build.build_fast_call()
+    assert len(set(written)) == 2 and all(os.path.dirname(f) == str(tmp_path) for f in written)
+    assert os.listdir(tmp_path) == [os.path.basename(build.fast_call_path())]
