@@ -35,12 +35,29 @@ def layer_of(shape):
     return ConvLayer("x".join(map(str, shape)), n, c, h, w, k, 1, 1, 1, 0)
 
 
-def prepared_variants(m):
-    """(number, name): they follow the last configuration with a public name and the four of the sliding window on short grids."""
-    v = len(m.gemm_variants())
-    while m.gemm_variant_name(v):
+def numbers(m, plan_of):
+    """(number, name) of NAMES, as plans describe them that were made by plan_of(number): these have no public names."""
+    found, v = {}, len(m.gemm_variants())
+    while len(found) < len(NAMES):
+        with plan_of(v) as plan:                          # a number beyond the last is refused, and ends the search with an error
+            found.update({n: v for n in NAMES if f"gemm={n}" in plan.describe()})
         v += 1
-    return [(v + 4 + i, name) for i, name in enumerate(NAMES)]
+    return [(found[n], n) for n in NAMES]
+
+
+@pytest.fixture(scope="module")
+def prepared_variants(tmp_path_factory):
+    import paper_2002_12418_amd as m
+    path = tmp_path_factory.mktemp("numbers") / "cache"
+    return numbers(m, lambda v: planned(m, layer_of((2, 40, 8, 16, 64)), v, path, m.SCHEME_GEMM1X1))
+
+
+@pytest.fixture(scope="module")
+def wino_variants(tmp_path_factory, prepared_variants):
+    """By precision; in fp32 they are those of pointwise layers."""
+    import paper_2002_12418_amd as m
+    path, shape = tmp_path_factory.mktemp("numbers") / "cache", (2, 40, 12, 12, 40, 3, 3, 4)
+    return {0: prepared_variants, 2: numbers(m, lambda v: wino_planned(m, wino_layer(shape), 4, v - len(m.gemm_variants()) + 1, path, 2))}
 
 
 def planned(m, layer, variant, path, kind):
@@ -75,11 +92,11 @@ def check(plan, name, x, w, b, ref):
 
 
 @pytest.mark.parametrize("shape", LAYERS, ids=str)
-def test_every_configuration_against_float64(mnn, shape, tmp_path):
+def test_every_configuration_against_float64(mnn, prepared_variants, shape, tmp_path):
     layer = layer_of(shape)
     x, w, b = inputs(layer, layer.c_in)
     ref = conv64(layer, x, w, b)
-    for v, name in prepared_variants(mnn):
+    for v, name in prepared_variants:
         with planned(mnn, layer, v, tmp_path / "cache", mnn.SCHEME_GEMM1X1) as plan:
             assert name in plan.describe()
             assert plan.workspace_bytes == (layer.c_out + 127) // 128 * 128 * ((layer.c_in + 15) // 16 * 16) * 6
@@ -92,19 +109,21 @@ def test_every_configuration_against_float64(mnn, shape, tmp_path):
     (ConvLayer("fifteen_channels", 2, 15, 8, 8, 40, 1, 1, 1, 0), "SCHEME_GEMM1X1"),
     (ConvLayer("sliding", 2, 24, 9, 9, 40, 3, 3, 1, 1), "SCHEME_DIRECT"),
     (ConvLayer("strided", 2, 24, 9, 9, 40, 1, 1, 2, 0), "SCHEME_DIRECT"),
-    (ConvLayer("products", 2, 24, 9, 9, 40, 3, 3, 1, 1), "SCHEME_WINOGRAD"),
+    (ConvLayer("products", 2, 12, 9, 9, 40, 3, 3, 1, 1), "SCHEME_WINOGRAD"),             # a reduction below one step
 ], ids=lambda v: getattr(v, "name", v))
-def test_remembered_where_it_does_not_apply(mnn, layer, kind, tmp_path):
+def test_remembered_where_it_does_not_apply(mnn, prepared_variants, layer, kind, tmp_path):
     x, w, b = inputs(layer, 3)
     ref = conv64(layer, x, w, b)
-    for v, name in prepared_variants(mnn):
-        with planned(mnn, layer, v, tmp_path / "cache", getattr(mnn, kind)) as plan:
+    for v, name in prepared_variants:
+        make = wino_planned(mnn, layer, 4, v, tmp_path / "cache", 0) if kind == "SCHEME_WINOGRAD" else planned(mnn, layer, v, tmp_path / "cache", getattr(mnn, kind))
+        with make as plan:
+            assert name not in plan.describe()
             y = plan.run(x.cuda(), w.cuda(), b.cuda()).cpu().double()
-            # a transform may be chosen: its error is bounded by the largest tile's, 1e-4 of the largest result
+            # F(4,3): its error is bounded by 1e-4 of the largest result
             assert float((y - ref).abs().max() / ref.abs().max()) < (1e-4 if kind == "SCHEME_WINOGRAD" else 2e-6), name
 
 
-def test_values_that_parts_do_not_hold(mnn, tmp_path):
+def test_values_that_parts_do_not_hold(mnn, prepared_variants, tmp_path):
     """Tiny and non-finite inputs and weights: what fp32 gives, and only where they reach, past the last channel and image included."""
     layer = ConvLayer("edge", 2, 180, 6, 6, 40, 1, 1, 1, 0)
     x, w, b = inputs(layer, 5)
@@ -117,7 +136,7 @@ def test_values_that_parts_do_not_hold(mnn, tmp_path):
     ref = conv64(layer, x, w, b)
     scale = conv64(layer, x.abs(), w.abs(), b)            # sum of magnitudes
     xd, wd, bd = x.cuda(), w.cuda(), b.cuda()
-    for v, name in prepared_variants(mnn):
+    for v, name in prepared_variants:
         with planned(mnn, layer, v, tmp_path / "cache", mnn.SCHEME_GEMM1X1) as plan:
             y = plan.run(xd, wd, bd).cpu().double()
             finite = scale < 3.0e38
@@ -162,19 +181,15 @@ def wino_planned(m, layer, tile, variant, path, prec, make=None):
     return (make or (lambda o: m.ConvPlan.for_layer(layer, options=o)))(opt)
 
 
-def wino_variants(m, prec):
-    return prepared_variants(m) if prec == 0 else [(m.lib.mnn_gemm_variant_count(2) + i, name) for i, name in enumerate(NAMES)]
-
-
 @pytest.mark.parametrize("prec", [0, 2], ids=["fp32", "bf16x3"])
 @pytest.mark.parametrize("shape", PRODUCTS, ids=str)
-def test_winograd_products(mnn, shape, prec, tmp_path):
+def test_winograd_products(mnn, wino_variants, shape, prec, tmp_path):
     """M against the float64 product of the plan's own U and V: R sums, each rounded at 2^-24; two bf16 parts hold an operand to 2^-17, and the
     product of the two second parts is left out."""
     layer = wino_layer(shape)
     x, w, b = inputs(layer, layer.c_in)
     xd, wd, bd = x.cuda(), w.cuda(), b.cuda()
-    for v, name in wino_variants(mnn, prec):
+    for v, name in wino_variants[prec]:
         with wino_planned(mnn, layer, shape[-1], v, tmp_path / "cache", prec) as plan:
             assert name in plan.describe()
             info = plan.info
@@ -193,7 +208,7 @@ def test_winograd_products(mnn, shape, prec, tmp_path):
                 assert torch.equal(y, plan.run(xd, weights, bd)), name       # the same bits every run
 
 
-def test_winograd_products_of_values_that_parts_do_not_hold(mnn, tmp_path):
+def test_winograd_products_of_values_that_parts_do_not_hold(mnn, prepared_variants, tmp_path):
     layer = wino_layer((2, 40, 12, 12, 40, 3, 3, 4))
     x, w, b = inputs(layer, 9)
     x[0] *= 2.0 ** -115
@@ -203,7 +218,7 @@ def test_winograd_products_of_values_that_parts_do_not_hold(mnn, tmp_path):
     bad[1, 39, 5, 5], bad[1, 0, 0, 0] = float("nan"), float("inf")
     bd = torch.zeros(layer.c_out).cuda()
     runs = []
-    for v, name in [(next(i for i, n in enumerate(mnn.gemm_variants()) if n == "128x128x16_w2x2"), "128x128x16")] + prepared_variants(mnn):
+    for v, name in [(next(i for i, n in enumerate(mnn.gemm_variants()) if n == "128x128x16_w2x2"), "128x128x16")] + prepared_variants:
         with wino_planned(mnn, layer, 4, v, tmp_path / "cache", 0) as plan:
             assert name in plan.describe()
             runs.append((name, plan.run(x.cuda(), w.cuda(), bd).cpu().double(), plan.run(bad.cuda(), w.cuda(), bd).cpu()))
@@ -215,11 +230,11 @@ def test_winograd_products_of_values_that_parts_do_not_hold(mnn, tmp_path):
         assert torch.equal(y_bad[0], y[0].float()), name
 
 
-def test_winograd_products_in_a_chain(mnn, tmp_path):
+def test_winograd_products_in_a_chain(mnn, prepared_variants, tmp_path):
     layer = wino_layer((2, 40, 12, 12, 40, 3, 3, 4))
     x, w, b = inputs(layer, 4)
     ref = conv64(layer, x, w, b)
-    for v, name in prepared_variants(mnn):
+    for v, name in prepared_variants:
         chain = wino_planned(mnn, layer, 4, v, tmp_path / "cache", 0, make=lambda o: mnn.ConvChain([layer], options=o))
         assert name in chain.describe(0)
         chain.set_weights(0, w.cuda(), b.cuda())
