@@ -317,6 +317,16 @@ struct Impl {
         }
     }
 
+    // whether the tuner would time a configuration that reads the weights in this form
+    static bool form_timed(GemmProblem p, WeightForm f, const float* some)
+    {
+        p.splitk = 1; p.splitk_partial = nullptr;
+        p.a_parts = p.a_octets = some;
+        for (int v = 1; v < gemm_variant_count(p.prec); ++v)
+            if (gemm_variant_weights(p.prec, v) == f && gemm_variant_tuned(p, v)) return true;
+        return false;
+    }
+
     // U in the form of a remembered choice; it is sized anew when the tuner takes another
     int alloc_weights(const GemmProblem& p)
     {
@@ -513,11 +523,12 @@ struct Impl {
                 return fail_hip(e, "tuning operand fill");
             // without room for the weights as parts their kernels are not candidates
             float* parts = nullptr;
-            if (prepared_offered && hipMalloc((void**)&parts, wino_parts_bytes()) != hipSuccess) { parts = nullptr; (void)hipGetLastError(); }
+            const bool want_parts = prepared_offered && form_timed(p, WeightForm::Parts, U);
+            if (want_parts && hipMalloc((void**)&parts, wino_parts_bytes()) != hipSuccess) { parts = nullptr; (void)hipGetLastError(); }
             int rc = MNN_OK;
             if (parts && (e = prepare_wino_parts(parts, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
             p.a_parts = parts;
-            if (!rc) rc = tune_gemm(p, s, prepared_offered && !parts, &c);
+            if (!rc) rc = tune_gemm(p, s, want_parts && !parts, &c);
             if ((e = hipMemsetAsync(U, 0, U_bytes, s)) != hipSuccess || (e = hipMemsetAsync(V, 0, V_bytes, s)) != hipSuccess ||
                 (e = hipStreamSynchronize(s)) != hipSuccess)
                 rc = rc ? rc : fail_hip(e, "tuning operand reset");
@@ -559,8 +570,8 @@ struct Impl {
                 if (hipMalloc((void**)t, weight_bytes(f)) != hipSuccess) { *t = nullptr; partial = true; (void)hipGetLastError(); }
                 else if ((e = prepare_weights(f, U, *t, s)) != hipSuccess) rc = fail_hip(e, "tuning operand fill");
             };
-            if (!rc && (patch_offered || short_offered || prepared_offered)) other_form(WeightForm::Parts, &tp);
-            if (!rc && short_offered) other_form(WeightForm::Octets, &to);
+            if (!rc && (patch_offered || short_offered || prepared_offered) && form_timed(p, WeightForm::Parts, U)) other_form(WeightForm::Parts, &tp);
+            if (!rc && short_offered && form_timed(p, WeightForm::Octets, U)) other_form(WeightForm::Octets, &to);
             p.a_parts = tp;
             p.a_octets = to;
             if (!rc) rc = tune_gemm(p, s, partial, &c);

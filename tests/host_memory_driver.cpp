@@ -61,6 +61,7 @@ bool in_child(const std::function<void()>& f)
     std::fflush(stdout);
     const pid_t pid = fork();
     if (pid == 0) {
+        failures = 0;
         f();
         std::fflush(stdout);
         _exit(failures ? 1 : 0);
@@ -207,10 +208,38 @@ void check_exceptions()
     failures += !ok;
 }
 
+// A form of the weights that no configuration worth timing reads is not made for timing either.
+void check_forms_made()
+{
+    struct Case { const char* what; LayerSpec l; bool made; };
+    const Case cases[] = {
+        {"pointwise, result of 103 MB", {shape(32, 256, 28, 28, 1024, 1), geom(1, 0), options(MNN_SCHEME_GEMM1X1, 0, MNN_GEMM_FP32), parts(1024, 256, 1, 3), 0, ""}, false},
+        {"pointwise, result of 6 MB", {shape(8, 256, 28, 28, 256, 1), geom(1, 0), options(MNN_SCHEME_GEMM1X1, 0, MNN_GEMM_FP32), parts(256, 256, 1, 3), 0, ""}, true},
+        {"Winograd, result of 460 MB", {shape(16, 128, 128, 128, 128, 3), geom(1, 1), options(MNN_SCHEME_WINOGRAD, 4, MNN_GEMM_FP32), 36 * parts(128, 128, 1, 3), 0, ""}, false},
+        {"Winograd, result of 7 MB", {shape(8, 128, 28, 28, 128, 3), geom(1, 1), options(MNN_SCHEME_WINOGRAD, 4, MNN_GEMM_FP32), 36 * parts(128, 128, 1, 3), 0, ""}, true},
+        {"sliding window, operand order, 1568 tiles of 32 channels", {shape(32, 64, 56, 56, 32, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)2 * 2 * 9 * 2048, 0, ""}, true},
+        {"sliding window, operand order, 49 tiles", {shape(1, 64, 56, 56, 64, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)4 * 2 * 9 * 2048, 0, ""}, true},
+    };
+    for (const Case& c : cases) {
+        const bool ok = in_child([&] {
+            fake::takes = [](const std::string&) { return 1.f; };
+            mnn_conv_plan_t p = nullptr;
+            CHECK(mnn_conv_plan(&c.l.s, &c.l.g, &c.l.o, nullptr, &p) == MNN_OK);
+            mnn_conv_plan_destroy(p);
+            bool made = false;
+            for (size_t b : fake::asked) made |= b == c.l.other_form;
+            CHECK(made == c.made);
+        });
+        std::printf("forms made, %s: %s\n", c.what, ok ? "ok" : "FAILED");
+        failures += !ok;
+    }
+}
+
 }  // namespace
 
 int main()
 {
+    check_forms_made();
     check_exceptions();
     check_strassen_beside_winograd();
     // F(4,3) 64 -> 96 on 8 x 28 x 28: 392 tiles; U, V and M are kept besides the weights as parts
