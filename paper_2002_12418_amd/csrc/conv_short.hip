@@ -490,7 +490,14 @@ size_t octet_weight_bytes(int K, int C, int taps)
     return (size_t)((K + kOctetRows - 1) / kOctetRows) * ((C + kOctetChannels - 1) / kOctetChannels) * taps * 2048;
 }
 
-bool conv_short_offered(const GemmProblem& p, int i) { return (conv_short_takes_octets(i) ? p.a_octets : p.a_parts) && conv_short_covers(p); }
+// Not where 64 x 64 tiles fill the chip one and a half times: of 33 such layers none was fastest here, the best of these took 1.04 to 2.3 times as long as the
+// best of the others (16 x 16 tiles up to 3.9 times), and timing them costs every plan (64 -> 64 on 16 x 56 x 56, 784 tiles).  But for few output channels,
+// which leave a larger tile half empty: 453 -> 13 7 x 7 on 34 x 26 x 26 313 -> 216 us, 280 -> 15 3 x 3 on 34 x 45 x 45, 1076 tiles, 102 -> 83.
+bool conv_short_offered(const GemmProblem& p, int i)
+{
+    const long long tiles64 = (long long)((p.M + 63) / 64) * ((p.Ncols + 63) / 64);
+    return (conv_short_takes_octets(i) ? p.a_octets : p.a_parts) && (p.M <= 32 || tiles64 < 384) && conv_short_covers(p);
+}
 
 bool conv_short_covers(const GemmProblem& p)
 {

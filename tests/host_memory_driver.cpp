@@ -217,8 +217,10 @@ void check_forms_made()
         {"pointwise, result of 6 MB", {shape(8, 256, 28, 28, 256, 1), geom(1, 0), options(MNN_SCHEME_GEMM1X1, 0, MNN_GEMM_FP32), parts(256, 256, 1, 3), 0, ""}, true},
         {"Winograd, result of 460 MB", {shape(16, 128, 128, 128, 128, 3), geom(1, 1), options(MNN_SCHEME_WINOGRAD, 4, MNN_GEMM_FP32), 36 * parts(128, 128, 1, 3), 0, ""}, false},
         {"Winograd, result of 7 MB", {shape(8, 128, 28, 28, 128, 3), geom(1, 1), options(MNN_SCHEME_WINOGRAD, 4, MNN_GEMM_FP32), 36 * parts(128, 128, 1, 3), 0, ""}, true},
-        {"sliding window, operand order, 1568 tiles of 32 channels", {shape(32, 64, 56, 56, 32, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)2 * 2 * 9 * 2048, 0, ""}, true},
-        {"sliding window, operand order, 49 tiles", {shape(1, 64, 56, 56, 64, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)4 * 2 * 9 * 2048, 0, ""}, true},
+        {"sliding window, operand order, 1568 tiles", {shape(32, 66, 56, 56, 64, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)4 * 3 * 9 * 2048, 0, ""}, false},
+        {"sliding window, operand order, 1568 tiles of 32 channels", {shape(32, 66, 56, 56, 32, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)2 * 3 * 9 * 2048, 0, ""}, true},
+        {"sliding window, operand order, 49 tiles", {shape(1, 66, 56, 56, 64, 3), geom(1, 1), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), (size_t)4 * 3 * 9 * 2048, 0, ""}, true},
+        {"one tap, parts, 1568 tiles", {shape(32, 64, 112, 112, 64, 1), geom(2, 0), options(MNN_SCHEME_DIRECT, 0, MNN_GEMM_FP32), parts(64, 64, 1, 3), 0, ""}, false},
     };
     for (const Case& c : cases) {
         const bool ok = in_child([&] {
