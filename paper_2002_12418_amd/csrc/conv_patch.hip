@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "kernels.hpp"
+#include "lds_barrier.hpp"
 #include "xcd_remap.hpp"
 #include "gemm_epilogue.hpp"
 #include "bf16_parts.hpp"
@@ -142,13 +143,6 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, 2) void conv_patch_kernel(Gemm
             }
         }
     };
-    // LDS writes of this wavefront done, then all wavefronts: loads from global memory stay in flight
-    auto barrier = [&]() {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-
     auto flag_lost = [&]() {                            // read behind a barrier
         const bool l = parts_lost(lost);
         if (lane == 0) wave_lost[wave - S0] = l ? 1 : 0;
@@ -159,16 +153,16 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, 2) void conv_patch_kernel(Gemm
         load_b(0);
         store_b(0);
         if (g.nch > 1) load_b(1);
-        barrier();
+        lds_barrier();
 #pragma unroll 1
         for (int ch = 0; ch < g.nch; ++ch) {
-            if (g.nbuf == 1) barrier();                  // the taps of this chunk have been read
+            if (g.nbuf == 1) lds_barrier();                  // the taps of this chunk have been read
             if (ch + 1 < g.nch) {
                 store_b(g.nbuf == 2 ? (ch + 1) & 1 : 0);
                 load_b(ch + 2 < g.nch ? ch + 2 : ch + 1);
             }
             if (ch + 1 == g.nch) flag_lost();
-            barrier();
+            lds_barrier();
         }
         return;
     }
@@ -253,7 +247,7 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, 2) void conv_patch_kernel(Gemm
     for (int ch = 0; ch < g.nch; ++ch) {
         const char* patch = smem + (g.nbuf == 2 ? (ch & 1) * PBUF : 0);
         const bool more = NS == 0 && ch + 1 < g.nch;
-        barrier();
+        lds_barrier();
         if (more) load_b(ch + 1);
         read_b(patch, bv[0]);
         auto tap = [&](auto slot) __attribute__((always_inline)) {
@@ -297,14 +291,14 @@ __global__ __launch_bounds__((WM * WN + NS) * 64, 2) void conv_patch_kernel(Gemm
             if (rest == 2) { tap(I0{}); tap(I1{}); rotate(I2{}); }
             if (rest == 3) { tap(I0{}); tap(I1{}); tap(I2{}); rotate(I3{}); }
         }
-        if (NS > 0 && g.nbuf == 1) barrier();
+        if (NS > 0 && g.nbuf == 1) lds_barrier();
         if (more) {
-            if (g.nbuf == 1) barrier();
+            if (g.nbuf == 1) lds_barrier();
             store_b(g.nbuf == 2 ? (ch + 1) & 1 : 0);
         }
     }
     if (NS == 0) flag_lost();
-    barrier();
+    lds_barrier();
 
     // A wavefront with sums that are not finite, and every wavefront of a workgroup that staged a value its parts do not hold, repeats its
     // block on the fp32 matrix instructions, inputs straight from memory (as in gemm_split.hip; the weights come out of their stored form with

@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "kernels.hpp"
+#include "lds_barrier.hpp"
 #include "xcd_remap.hpp"
 #include "fast_div.hpp"
 #include "patch_rect.hpp"
@@ -169,13 +170,6 @@ __global__ __launch_bounds__(WK * 64, PARTS || BATCH > 2 ? 2 : 4) void conv_shor
             }
         }
     };
-    // LDS writes of this wavefront done, then all wavefronts: loads from global memory stay in flight
-    auto barrier = [&]() {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-
     const int all_taps = g.nch * g.taps;
     // weights of step u of the whole reduction
     auto read_a = [&](int u, uintx4 (&a)[TM][NP]) __attribute__((always_inline)) {
@@ -262,7 +256,7 @@ __global__ __launch_bounds__(WK * 64, PARTS || BATCH > 2 ? 2 : 4) void conv_shor
 #pragma unroll 1
     for (;;) {
         const int groups = chunks * GPS, ubase = ch0 * g.taps + u0;
-        if (ch0 > 0) barrier();                          // the patch before has been read
+        if (ch0 > 0) lds_barrier();                          // the patch before has been read
         store_batch(early, 0, groups);
 #pragma unroll 1
         for (int first = BATCH * gstep; first < groups; first += BATCH * gstep) {
@@ -270,7 +264,7 @@ __global__ __launch_bounds__(WK * 64, PARTS || BATCH > 2 ? 2 : 4) void conv_shor
             load_batch(st, first, ch0 * CHANNELS);
             store_batch(st, first, groups);
         }
-        barrier();
+        lds_barrier();
         int chunk = (int)const_div((unsigned)u0, g.by_taps), tap = u0 - chunk * g.taps;
         // LDS bytes of the step; behind the last one some other's
         auto offset = [&]() -> int { return (chunk < chunks ? chunk : 0) * GPS * NP * 16 * g.pp + __builtin_amdgcn_readlane(tap_offset, tap); };
@@ -323,7 +317,7 @@ __global__ __launch_bounds__(WK * 64, PARTS || BATCH > 2 ? 2 : 4) void conv_shor
         const bool l = parts_lost(lost);
         if (lane == 0) wave_lost[wave] = l ? 1 : 0;
     }
-    barrier();                                           // the patch has been read
+    lds_barrier();                                           // the patch has been read
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -390,7 +384,7 @@ __global__ __launch_bounds__(WK * 64, PARTS || BATCH > 2 ? 2 : 4) void conv_shor
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < REGS; ++r) red[(((wave * TM + i) * TN + j) * REGS + r) * 64 + lane] = acc[i][j][0][r];
-    barrier();
+    lds_barrier();
 #pragma unroll
     for (int t = 0; t < IT; ++t) {
         const int o = tid + t * THREADS;

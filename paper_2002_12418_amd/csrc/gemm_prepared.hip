@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "kernels.hpp"
+#include "lds_barrier.hpp"
 #include "xcd_remap.hpp"
 #include "gemm_epilogue.hpp"
 #include "bf16_parts.hpp"
@@ -102,13 +103,6 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
                 *reinterpret_cast<uintx4*>(d0 + q * (KG * GROUP) + slot * 16) = uintx4{part[0][q], part[1][q], part[2][q], part[3][q]};
         }
     };
-    // LDS writes of this wavefront done, then all wavefronts: loads from global memory stay in flight
-    auto barrier = [&]() {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-
     floatx16 acc[TM][TN];
     auto clear = [&]() {
 #pragma unroll
@@ -164,7 +158,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
 #pragma unroll 1
     for (int c = 0; c < nchunks; ++c) {
         const char* s0 = smem + (c & 1) * BUF;
-        barrier();
+        lds_barrier();
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             read_a(c * KS + ks + 1, av[(ks + 1) & 1]);
@@ -184,7 +178,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_prepared_kernel(GemmProb
         const bool l = parts_lost(lost);
         if (lane == 0) wave_lost[wave] = l ? 1 : 0;
     }
-    barrier();
+    lds_barrier();
 
     // A wavefront with sums that are not finite, and every wavefront of a workgroup that staged a value its parts do not hold, repeats its
     // block on the fp32 matrix instructions, columns straight from memory (as in conv_patch.hip)

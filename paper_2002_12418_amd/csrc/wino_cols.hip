@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include "kernels.hpp"
+#include "lds_barrier.hpp"
 #include "xcd_remap.hpp"
 #include "wino_paired.hpp"
 #include "row_shares.hpp"
@@ -222,12 +223,6 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
             for (int q = 0; q < 3; ++q) *reinterpret_cast<unsigned*>(d0 + a * POS + q * 2048) = part[q];
         }
     };
-    auto barrier = [&]() __attribute__((always_inline)) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    };
-
     floatx16 acc[A0][2];
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -293,14 +288,14 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
     auto ahead = [&](int c) { return c + 2 < last ? c + 2 : last; };
     stage(0);
     load_t(last < 1 ? last : 1);
-    barrier();
+    lds_barrier();
     if (wave < NW / 2) {
 #pragma unroll 1
         for (int c = 0; c < last; ++c) {
             multiply(c, c & 1);
             stage((c + 1) & 1);
             load_t(ahead(c));
-            barrier();
+            lds_barrier();
         }
     } else {
 #pragma unroll 1
@@ -308,7 +303,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
             stage((c + 1) & 1);
             load_t(ahead(c));
             multiply(c, c & 1);
-            barrier();
+            lds_barrier();
         }
     }
     multiply(last, last & 1);
@@ -316,7 +311,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
     // A workgroup with sums that are not finite, or with a transformed input that its parts do not hold, repeats the channels on the fp32 matrix
     // instructions (as in gemm_split.hip; the weights come out of their stored form with all their bits)
     if (tid == 0) redo = 0;
-    barrier();
+    lds_barrier();
     FiniteCheck check;
 #pragma unroll
     for (int q = 0; q < A0; ++q)
@@ -325,7 +320,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
 #pragma unroll
             for (int r = 0; r < 16; ++r) check.add(acc[q][j][r]);
     if ((check.failed() || parts_lost(lost)) && lane == 0) redo = 1;
-    barrier();
+    lds_barrier();
     if (__builtin_amdgcn_readfirstlane(redo) != 0) {
         clear();
 #pragma unroll 1
@@ -381,7 +376,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
         };
 #pragma unroll
         for (int i0 = 0; i0 < NT; i0 += RI * MERGE) {
-            barrier();                                    // V, or what the round before left, has been read
+            lds_barrier();                                    // V, or what the round before left, has been read
 #pragma unroll
             for (int m = 0; m < MERGE; ++m)
 #pragma unroll
@@ -393,7 +388,7 @@ __global__ __launch_bounds__(512, 2) void cols_kernel(ColsArgs g, MatArg<A, A> b
                         *reinterpret_cast<float4*>(smem + ((m * NW + wave) * (Q - 1) + o - (o > H ? 1 : 0)) * 4096 + r4 * 1024 + lane * 16) =
                             make_float4(sum(i, o % 2, 4 * r4), sum(i, o % 2, 4 * r4 + 1), sum(i, o % 2, 4 * r4 + 2), sum(i, o % 2, 4 * r4 + 3));
                 }
-            barrier();
+            lds_barrier();
 #pragma unroll
             for (int m = 0; m < MERGE; ++m) {
                 const int i = i0 + m * RI + H / 2;
