@@ -64,6 +64,10 @@ __global__ __launch_bounds__(256) void patch_weights_kernel(const float* __restr
 // of one wavefront return in order, and weights that follow pixels wait for those, a trip to memory in every chunk: it pays where chunks
 // are many and workgroups few (stride 2 128 -> 256 on 32 x 28 x 28 35 -> 30 us, 256 -> 512 on 32 x 14 x 14 50 -> 40), not where more workgroups
 // per CU hide it (64 -> 128 on 32 x 56 x 56 30 -> 32, stride 1 64 -> 64 on 16 x 56 x 56 29 -> 31).
+//
+// Two workgroups of four wavefronts per CU also in registers: left to itself the compiler takes so many for the 64 x 128 tile that one fits (whole calls,
+// us: stride 2 32 -> 64 on 16 x 112 x 112 27.7 -> 19.4, 64 -> 64 on 16 x 56 x 56 36.2 -> 27.9, although ten scalar registers spill), and the others are 1 to 4 % slower
+// (128 x 64, stride 2 64 -> 128 on 32 x 56 x 56 31.5 -> 30.8; 64 x 64, 48 -> 96 on 24 x 40 x 40 27.4 -> 26.5; 5 x 5 128 -> 128 on 8 x 28 x 28 41.1 -> 40.9).
 template <int BM, int BN, int WM, int WN, int ITEMS, int NS>
 __global__ __launch_bounds__((WM * WN + NS) * 64, 2) void conv_patch_kernel(GemmProblem p, PatchArgs g)
 {

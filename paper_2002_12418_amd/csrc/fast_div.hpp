@@ -21,8 +21,8 @@ inline FastDiv make_fastdiv(unsigned d)
 __device__ __forceinline__ unsigned fast_div(unsigned n, const FastDiv& f) { return f.d <= 1 ? n : (__umulhi(n, f.m) >> f.sh); }
 
 // The same, for the same n < 2^31 (n + n has to fit), without a branch for d = 1: q = n * m >> (31 + L) with m = ceil(2^(31+L) / d), from 2^31 to 2^32 - 1.  For kernels whose time before the first load
-// counts (sliding window on staged patches, stride 2 64 -> 128 on 32 x 56 x 56: places worked out in 0.8 us instead of 1.1, a call 32.2 -> 31.2).  Not
-// everywhere: it takes registers, of which gemm_split.hip's gather and some transforms have none to spare (a wavefront per SIMD).
+// counts (sliding window on staged patches: places worked out in 0.8 us instead of 1.1; whole calls 5 x 5 128 -> 128 on 8 x 28 x 28 44.0 -> 41.1 us, 3 x 3 48 -> 96 on
+// 24 x 40 x 40 28.1 -> 27.1, stride 2 64 -> 128 on 32 x 56 x 56 31.4 both).  Not everywhere: it takes registers, of which gemm_split.hip's gather and some transforms have none to spare (a wavefront per SIMD).
 struct ConstDiv { unsigned m, L, d; };
 inline ConstDiv make_constdiv(unsigned d)
 {

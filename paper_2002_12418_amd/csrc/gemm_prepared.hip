@@ -483,15 +483,18 @@ const GemmVariant& gemm_prepared_variant(int i) { return kPrepared[i]; }
 // 512 -> 512, 392 tiles, 26.5 against 16.6; 8 x 28 x 29 256 -> 1024, 1632 tiles, 25.4 against 27.1).  Divided ones up to two 64 x 64 tiles per CU, and
 // 64 x 64 among them from half the chip on and with two steps for each wavefront (32 x 14 x 15 1024 -> 256, 420 tiles, 28.4 against 29.5 staged; 2 x 28
 // x 28 1024 -> 128, 50 tiles, 14.3 against 8.2 in 32 x 32).  Planes of an odd size have the divided tiles alone.
-// Single products with a long reduction and few 32 x 32 tiles keep the plain divided ones: on operands that lie in no L2 the one step ahead is too
-// little there, and the weights' six bytes are more (one of 18 x 13 502 -> 641, 168 tiles, 6.1 against 5.9; 36 x 31 719 -> 110, 140 tiles, 6.6 against 6.4; 30 x 30
-// 700 -> 200, 203 tiles, 6.9 against 7.0; 14 x 14 x 2 300 -> 500, 208 tiles, 4.6 against 5.2).  Loads two steps ahead are slower everywhere (up to 0.4 us).
+// Single products with a long reduction and few 32 x 32 tiles keep the plain divided ones: the weights' six bytes count more there, and timing, on operands
+// that are in the L2, does not show it.  Of 30 such layers (454 to 1211 channels, three plans in turn, whole calls) these take 0.99 to 1.42 times as long as
+// the plain ones below 130 tiles, and a planner that may take them does so wrongly for 1199 -> 956 on 10 x 10 (120 tiles, 9.9 against 10.3 us) and 896 -> 546
+// on 14 x 14 (126, 7.7 against 8.1); from 140 to 190 tiles it is 0.96 to 1.01 (502 -> 641 on 18 x 13 6.4 both).  From 192 tiles on (17 layers) and with
+// up to 448 channels the planner's choice is the better one within 3 %.  Loads two steps ahead are slower everywhere (up to 0.4 us).
 // Winograd products take the same rules over all positions: 64 of 93 x 248 x 67 8.2 -> 7.6, 36 of 256 x 512 x 256 25.0 -> 22.3, 36 of 512 x 392 x 512 56.8 ->
 // 50.7, 64 of 256 x 124 x 256 12.7 -> 11.6, 16 of 256 x 1600 x 256 29.0 -> 27.7; 50 MB and more lose: 100 of 256 x 4096 x 256 304 against 337, 64 of
 // 128 x 4096 x 128 64 against 73, 64 of 256 x 1600 x 256 83 against 84.  Of few columns it is the weights that count, six bytes instead of four: more than
 // 12 MB of them for fewer than 64 columns stay as they are (whole calls, 100 of 115 x 36 x 254, 20 MB, 15.6 against 15.4; 16 of 512 x 52 x 512, 25 MB,
 // 13.1 against 13.0; 36 of 128 x 52 x 300, 8 MB, 12.0 against 12.6; 36 of 512 x 64 x 512, 57 MB, 21.0 against 21.2).  128 x 128 in fp32 is for reductions beyond four
-// chunks: at 128 the product ties (36 of 128 x 1600 x 128 18.6 against 18.9) and the whole call does not gain (37.9 against 37.0).  bf16x3: 36 of 256 x 512 x 256
+// chunks: of 24 layers with 35 to 128 channels a planner that may take it did so in none (three processes each), and with it the whole call takes 0.97 to 1.25
+// times as long, 1.08 on average (F(4,3) 128 -> 128 on 32 x 28 x 28 38.7 against 39.1 us, 128 -> 135 F(4,5) on 3 x 42 x 42 26.3 against 24.3).  bf16x3: 36 of 256 x 512 x 256
 // 17.7 -> 16.5, 64 of 90 x 92 x 400 10.4 -> 7.3, 36 of 128 x 1600 x 128 14.9 -> 13.8.
 bool gemm_prepared_offered(const GemmProblem& p, int i)
 {
