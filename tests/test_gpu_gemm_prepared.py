@@ -35,9 +35,9 @@ def layer_of(shape):
     return ConvLayer("x".join(map(str, shape)), n, c, h, w, k, 1, 1, 1, 0)
 
 
-def numbers(m, plan_of):
+def numbers(first, plan_of):
     """(number, name) of NAMES, as plans describe them that were made by plan_of(number): these have no public names."""
-    found, v = {}, len(m.gemm_variants())
+    found, v = {}, first
     while len(found) < len(NAMES):
         with plan_of(v) as plan:                          # a number beyond the last is refused, and ends the search with an error
             found.update({n: v for n in NAMES if f"gemm={n}" in plan.describe()})
@@ -49,7 +49,7 @@ def numbers(m, plan_of):
 def prepared_variants(tmp_path_factory):
     import paper_2002_12418_amd as m
     path = tmp_path_factory.mktemp("numbers") / "cache"
-    return numbers(m, lambda v: planned(m, layer_of((2, 40, 8, 16, 64)), v, path, m.SCHEME_GEMM1X1))
+    return numbers(len(m.gemm_variants()), lambda v: planned(m, layer_of((2, 40, 8, 16, 64)), v, path, m.SCHEME_GEMM1X1))
 
 
 @pytest.fixture(scope="module")
@@ -57,7 +57,7 @@ def wino_variants(tmp_path_factory, prepared_variants):
     """By precision; in fp32 they are those of pointwise layers."""
     import paper_2002_12418_amd as m
     path, shape = tmp_path_factory.mktemp("numbers") / "cache", (2, 40, 12, 12, 40, 3, 3, 4)
-    return {0: prepared_variants, 2: numbers(m, lambda v: wino_planned(m, wino_layer(shape), 4, v - len(m.gemm_variants()) + 1, path, 2))}
+    return {0: prepared_variants, 2: numbers(1, lambda v: wino_planned(m, wino_layer(shape), 4, v, path, 2))}
 
 
 def planned(m, layer, variant, path, kind):
