@@ -452,7 +452,8 @@ int mnn_conv_cache_size(void);
 void mnn_conv_cache_clear(void);
 
 /* Pre-inference results outlive the process: mnn_conv_cache_save writes every cached choice (scheme per
- * layer shape, GEMM tile configuration per matrix shape) to a text file, mnn_conv_cache_load merges such a
+ * layer shape, GEMM tile configuration per matrix shape; not configurations timed while there was no memory
+ * for another form of the weights, which a plan times again) to a text file, mnn_conv_cache_load merges such a
  * file into the cache, so that a later mnn_conv_plan for a known shape launches no timing kernels.
  * path: host, NUL-terminated.  Entries are keyed by the HIP device ordinal they were measured on. */
 int mnn_conv_cache_save(const char* path);

@@ -10,8 +10,8 @@ namespace {
 // itself it is chosen by measurement at pre-inference time and remembered per shape.
 using GemmKey = std::tuple<int, std::vector<long long>>;
 std::mutex g_gemm_mu;
-// partial: timed without kernels whose weights have a form of their own, for which there was no room (or whose caller has none): a plan that can
-// time them does so again, and no file keeps it
+// partial: timed without kernels whose weights have a form of their own, for which there was no room: a plan that can time them does so again, and no file
+// keeps it
 struct GemmChoice { int variant; int splitk; bool partial = false; };
 std::map<GemmKey, GemmChoice> g_gemm_choice;
 
@@ -58,12 +58,14 @@ int tune_gemm(GemmProblem p, hipStream_t s, bool partial, GemmChoice* out)
     int dev = 0;
     (void)hipGetDevice(&dev);
     const GemmKey key = gemm_key(dev, p);
+    bool keep = false;           // the remembered choice of a layer, whose weights have a form that this product's left operand has not
     {
         std::lock_guard<std::mutex> lk(g_gemm_mu);
         auto it = g_gemm_choice.find(key);
         if (it != g_gemm_choice.end() && (partial || !it->second.partial)) {
             const WeightForm f = gemm_variant_weights(p.prec, it->second.variant);
             if (f == WeightForm::Rows || (f == WeightForm::Parts ? p.a_parts : p.a_octets)) { *out = it->second; return MNN_OK; }
+            keep = true;
         }
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -161,7 +163,7 @@ int tune_gemm(GemmProblem p, hipStream_t s, bool partial, GemmChoice* out)
     *out = best;
     std::lock_guard<std::mutex> lk(g_gemm_mu);
     const auto it = g_gemm_choice.find(key);
-    if (!partial || it == g_gemm_choice.end() || it->second.partial) g_gemm_choice[key] = best;
+    if (it == g_gemm_choice.end() || (!keep && (!partial || it->second.partial))) g_gemm_choice[key] = best;
     return MNN_OK;
 }
 

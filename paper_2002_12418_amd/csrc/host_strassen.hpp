@@ -85,7 +85,7 @@ struct Strassen {
             if (!rc) {
                 GemmProblem p = top;
                 p.At = ta; p.B = tb; p.D = td; p.bias = nullptr; p.variant = 0; p.splitk = 1; p.splitk_partial = nullptr;
-                rc = tune_gemm(p, s, true, &choice);
+                rc = tune_gemm(p, s, false, &choice);
                 if (!rc && choice.splitk > 1) {
                     const size_t pb = (size_t)gemm_splitk_workspace(p, choice.splitk) * sizeof(float);
                     if ((e = hipMalloc((void**)&sk_partial, pb)) != hipSuccess) rc = fail_hip(e, "hipMalloc split-K partials");
@@ -108,7 +108,7 @@ struct Strassen {
             if ((e = launch_fill_pattern(Ax[levels], nb * Rl(levels) * Ml(levels), 0x5du, -0.5f, 0.5f, s)) != hipSuccess ||
                 (e = launch_fill_pattern(Bx[levels], nb * Rl(levels) * Nl(levels), 0x5eu, -1.f, 1.f, s)) != hipSuccess)
                 return fail_hip(e, "Strassen tuning operand fill");
-            int rc = tune_gemm(p, s, true, &choice);
+            int rc = tune_gemm(p, s, false, &choice);
             if (rc) return rc;
             if (choice.splitk > 1) {
                 const size_t pb = (size_t)gemm_splitk_workspace(p, choice.splitk) * sizeof(float);

@@ -143,7 +143,7 @@ mnn_conv_geom geom(int stride, int pad) { return mnn_conv_geom{stride, stride, p
 // The products at the bottom of two Strassen levels have the shape of F(3,5)'s 49, but no weights as parts: they are timed on their own.
 void check_strassen_beside_winograd()
 {
-    const bool ok = in_child([] {
+    bool ok = in_child([] {
         fake::takes = [](const std::string& k) { return k.find("gemm_prepared") != std::string::npos ? 0.1f : 1.f; };
         const LayerSpec l{shape(8, 64, 21, 21, 96, 5), geom(1, 2), options(MNN_SCHEME_WINOGRAD, 3, MNN_GEMM_FP32), 0, 0, "gemm_prepared"};
         CHECK(plan_and_run(l).runs_kernel);
@@ -157,6 +157,26 @@ void check_strassen_beside_winograd()
         mnn_strassen_destroy(h);
         CHECK(plan_and_run(l).runs_kernel);
         CHECK(fake::live.empty());
+    });
+    // on its own it is remembered and saved like any other
+    mnn_gemm_desc d{};
+    d.M = d.R = d.ncols = d.L = d.lda = 512; d.batch = 1;
+    d.strideB_row = d.strideD_row = d.ncols;
+    auto create = [&](int levels) {
+        mnn_strassen_t h = nullptr;
+        fake::launched.clear();
+        CHECK(mnn_strassen_create(&d, levels, nullptr, &h) == MNN_OK);
+        mnn_strassen_destroy(h);
+        return fake::ran("gemm_");
+    };
+    ok &= in_child([&] {
+        CHECK(create(0) && create(1));
+        CHECK(!create(0) && !create(1));
+        CHECK(mnn_conv_cache_save("strassen.txt") == MNN_OK);
+    });
+    ok &= in_child([&] {
+        CHECK(mnn_conv_cache_load("strassen.txt") == MNN_OK);
+        CHECK(!create(0) && !create(1));
     });
     std::printf("Strassen beside Winograd: %s\n", ok ? "ok" : "FAILED");
     failures += !ok;
