@@ -436,8 +436,8 @@ def _find_current_stream():
     if not torch.cuda.is_available():
         return None
     torch.cuda.init()
-    _float32 = torch.float32
     _fast_call = _load_fast_call()
+    _float32 = torch.float32             # what others ask whether this has been done
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
     if raw is not None and device is not None:
         _current_stream = lambda: raw(device())          # 0.2 us; through torch.cuda.current_stream 1.4
